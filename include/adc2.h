@@ -57,7 +57,11 @@ typedef enum {
 } adc2_status;
 
 typedef enum {
-  ADC2_FP64 = 0,               /* complex FP64 contractions on the FP64 MFMA     */
+  ADC2_FP64 = 0,               /* complex FP64 contractions: on the FP64 MFMA, and
+                                  where the work spaces exceed the reach of
+                                  adc2_sigma_noalloc as exact integer products on
+                                  the INT8 MFMA (operands rounded at 2^-57 of
+                                  their row norm; errors below the FP64 MFMA's)   */
   ADC2_C64 = 1                 /* precision form: the two heavy sigma
                                   contractions on complex64 operands with the
                                   FP32 MFMA and FP32 accumulation; setup,

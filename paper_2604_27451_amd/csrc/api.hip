@@ -47,6 +47,7 @@ static void free_handle(adc2_handle h) {
   dfree(h, h->part);
   dfree(h, h->Zb);
   dfree(h, h->Tp);
+  rns_release(h);
   dfree(h, h->Vpp);
   dfree(h, h->Hh);
   dfree(h, h->WvT);
@@ -160,7 +161,7 @@ using namespace adc2;
 
 namespace adc2 {
 
-hipError_t dmalloc_raw(adc2_handle h, void** p, size_t bytes) {
+static hipError_t dmalloc_once(adc2_handle h, void** p, size_t bytes) {
   if (!h || !h->alloc.alloc) return hipMalloc(p, bytes);
   if (bytes == 0) {          // as hipMalloc: success, no memory
     *p = nullptr;
@@ -168,6 +169,19 @@ hipError_t dmalloc_raw(adc2_handle h, void** p, size_t bytes) {
   }
   *p = h->alloc.alloc(bytes, h->alloc.ctx);
   return *p ? hipSuccess : hipErrorOutOfMemory;
+}
+
+// A request that fails while the handle holds residue-engine memory is tried
+// again without it (that engine is an option, the request is not).
+hipError_t dmalloc_raw(adc2_handle h, void** p, size_t bytes) {
+  hipError_t e = dmalloc_once(h, p, bytes);
+  if (e == hipErrorOutOfMemory && h && (h->rns_lvo || h->rns_lvt || h->rns_ws)) {
+    (void)hipGetLastError();
+    rns_release(h);
+    h->rns_off = true;
+    e = dmalloc_once(h, p, bytes);
+  }
+  return e;
 }
 
 void dfree(adc2_handle h, void* p) {
@@ -225,11 +239,13 @@ adc2_status adc2_setup(const void* L, const double* eps, int nc, int no, int nv,
     }
     h->alloc = *alloc;
   }
-  if (const char* v = getenv("ADC2_ZGEMM"))
+  if (const char* v = getenv("ADC2_ZGEMM")) {
     h->zgemm = strcmp(v, "3m") == 0    ? ZGEMM_3M
                : strcmp(v, "big") == 0 ? ZGEMM_BIG
                : strcmp(v, "mid") == 0 ? ZGEMM_MID
                                        : ZGEMM_WIDE;
+    h->rns_mode = strcmp(v, "rns") == 0 ? RNS_ALWAYS : RNS_NEVER;
+  }
 #define SETUP_TRY(call)                                                           \
   do {                                                                            \
     hipError_t e_ = (call);                                                       \

@@ -95,13 +95,16 @@ struct Rendezvous {
 // addresses and capacities (a work space re-sized to fewer vectors can come
 // back at the same address), precision form, method and split counts.
 struct SigState {
-  int prec, method, zgemm, ysplit, nsplit, ws_m, wsb_m;
-  const void* buf[18];
+  int prec, method, zgemm, ysplit, nsplit, ws_m, wsb_m, zb_m;
+  bool rns_off;
+  size_t rns_ws_bytes;
+  const void* buf[21];
   bool operator==(const SigState& o) const {
     if (prec != o.prec || method != o.method || zgemm != o.zgemm || ysplit != o.ysplit || nsplit != o.nsplit ||
-        ws_m != o.ws_m || wsb_m != o.wsb_m)
+        ws_m != o.ws_m || wsb_m != o.wsb_m || zb_m != o.zb_m || rns_off != o.rns_off ||
+        rns_ws_bytes != o.rns_ws_bytes)
       return false;
-    for (int i = 0; i < 18; ++i)
+    for (int i = 0; i < 21; ++i)
       if (buf[i] != o.buf[i]) return false;
     return true;
   }
@@ -116,9 +119,12 @@ SigState sig_state(adc2_handle h) {
   s.nsplit = h->nsplit;
   s.ws_m = h->ws_m;
   s.wsb_m = h->wsb_m;
-  const void* b[18] = {h->X,    h->Y,     h->Zb,  h->Tp,  h->part, h->XB,  h->RB, h->Lv32, h->LvT32,
-                       h->LvB,  h->LvTB,  h->LvT, h->Lvo, h->Lvv,  h->Vt,  h->eps, h->M11, nullptr};
-  for (int i = 0; i < 18; ++i) s.buf[i] = b[i];
+  s.zb_m = h->zb_m;
+  s.rns_off = h->rns_off;
+  s.rns_ws_bytes = h->rns_ws_bytes;
+  const void* b[21] = {h->X,   h->Y,   h->Zb,  h->Tp, h->part, h->XB,  h->RB,      h->Lv32,    h->LvT32, h->LvB, h->LvTB,
+                       h->LvT, h->Lvo, h->Lvv, h->Vt, h->eps,  h->M11, h->rns_lvo, h->rns_lvt, h->rns_ws, nullptr};
+  for (int i = 0; i < 21; ++i) s.buf[i] = b[i];
   return s;
 }
 

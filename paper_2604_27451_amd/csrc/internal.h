@@ -40,6 +40,10 @@ inline hipError_t dmalloc(adc2_handle h, T** p, size_t bytes) {
 // default).  Chosen per handle at setup (environment ADC2_ZGEMM = big, 3m,
 // mid or wide) or by adc2_autotune.
 constexpr int ZGEMM_BIG = 0, ZGEMM_3M = 1, ZGEMM_MID = 2, ZGEMM_WIDE = 3;
+// Whether the FP64 products may run on the residue engine (rns.h): by the size
+// rule, always, or never (ADC2_ZGEMM = rns forces it at every size, any other
+// value of ADC2_ZGEMM keeps the FP64 MFMA engines).
+enum RnsMode { RNS_AUTO = 0, RNS_ALWAYS = 1, RNS_NEVER = 2 };
 
 struct Dims {
   int nc, no, nv, naux;
@@ -91,7 +95,16 @@ struct adc2_handle_s {
   int nsplit = 0;
   int ysplit = 1;           // K-splits of the Y-build GEMM
   int ysplit_tuned = 0;     // K-split fixed by adc2_autotune (0: the size heuristic)
+  int zb_m = 0;             // vectors that Zb holds
   int zgemm = adc2::ZGEMM_WIDE;  // engine of the FP64 heavy GEMMs (ZGEMM_*)
+  // residue engine of the FP64 form (rns.h): the two static operands, built on
+  // first use, and the work space of one chunk of (vector, core) rows
+  adc2::RnsMode rns_mode = adc2::RNS_AUTO;
+  bool rns_off = false;     // its memory was not to be had: the FP64 MFMA engines serve this handle
+  char* rns_lvo = nullptr;  // residues of the valence rows of Lvo (rows (j,b), K = P), then their exponents
+  char* rns_lvt = nullptr;  // residues of LvT (rows P, K = (j,d)), then their exponents
+  char* rns_ws = nullptr;
+  size_t rns_ws_bytes = 0;
   // method: ADC2_METHOD_ADC2 or ADC2_METHOD_ADC2X (first-order doubles block, adc2x.hip)
   int method = 0;
   double2* Vpp = nullptr;   // ADC(2)-x: [(a<b)][(c<d)] <ab||cd>
@@ -137,14 +150,18 @@ struct SigReq {
   double2* sout;
   int parts;
 };
-adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st);
+// allow_rns: large FP64 requests may run on the residue engine (rns.h)
+adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_rns = true);
 // A solver's sigma: through h->sigma_hook when set, else sigma_parts.
 adc2_status sigma_call(adc2_handle h, int m, const double2* X, double2* S, int parts, hipStream_t st);
 adc2_status build_lvt(adc2_handle h, hipStream_t st);
 adc2_status build_c64(adc2_handle h, hipStream_t st);
 adc2_status build_b3(adc2_handle h, hipStream_t st);
 adc2_status ensure_ws_b3(adc2_handle h, int m);
-adc2_status ensure_ws(adc2_handle h, int m);
+// work spaces of m vectors; zb: also the unpacked doubles / sigma2 products of all of them
+adc2_status ensure_ws(adc2_handle h, int m, bool zb = true);
+// gives back what the residue engine holds on h
+void rns_release(adc2_handle h);
 // K-split count of the Y-build by the size rule for h's form and engine at block size m
 int ysplit_rule(adc2_handle h, int m);
 adc2_status unpack_weighted(adc2_handle h, int m, const double2* xin, const double* wts, hipStream_t st);

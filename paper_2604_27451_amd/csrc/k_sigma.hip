@@ -23,6 +23,7 @@
 #include <mutex>
 
 #include "internal.h"
+#include "rns.h"
 #include "tile.h"
 #include "zgemm.h"
 #include "zgemm32.h"
@@ -709,20 +710,22 @@ __device__ __forceinline__ long pair_offset(int a, int b, int nv) {
   return (long)a * nv - (long)a * (a + 1) / 2 + (b - a - 1);
 }
 
-// Unpack the doubles of all m vectors into the k-major Y-build operand
-//   Rt[(j, d)][(mI, c)] = R_{mI j}[c][d]   (c<d packed, c>d negated, 0 on c=d)
-// with row (j,d) = j*nv + d of length m*nc*nv.  One workgroup per
+// Unpack the doubles of the nrow (vector, core) pairs mI0 <= mI into the
+// k-major Y-build operand
+//   Rt[(j, d)][(mI - mI0, c)] = R_{mI j}[c][d]   (c<d packed, c>d negated, 0 on c=d)
+// with row (j,d) = j*nv + d of length nrow*nv.  One workgroup per
 // (mI, j, 32x32 tile pair cb <= db): the packed upper tile is read along d
 // (contiguous) and written both straight and, through LDS, transposed; every
 // global access is coalesced.
 constexpr int UT = 32;
 template <class TO, bool WTS>
-__global__ __launch_bounds__(256) void k_unpack(const double2* __restrict__ xin, long dim, int m, int nc, int no,
-                                                 int nv, TO* __restrict__ Rt, const double* __restrict__ wts) {
+__global__ __launch_bounds__(256) void k_unpack(const double2* __restrict__ xin, long dim, int mI0, int nrow, int nc,
+                                                 int no, int nv, TO* __restrict__ Rt,
+                                                 const double* __restrict__ wts) {
   __shared__ double2 t[UT][UT + 1];
   const int nb = (nv + UT - 1) / UT;
   const int ntp = nb * (nb + 1) / 2;
-  const long g = blockIdx.x / ntp;           // g = mI*no + j
+  const long g = blockIdx.x / ntp;           // g = (mI - mI0)*no + j
   int tt = blockIdx.x % ntp, cbk = 0;
   while (tt >= nb - cbk) {
     tt -= nb - cbk;
@@ -732,11 +735,12 @@ __global__ __launch_bounds__(256) void k_unpack(const double2* __restrict__ xin,
   const int c0 = cbk * UT, d0 = dbk * UT;
   const long ns = (long)nc * nv;
   const long npair = (long)nv * (nv - 1) / 2;
-  const int mI = (int)(g / no), j = (int)(g % no);
+  const int ml = (int)(g / no), j = (int)(g % no);
+  const int mI = mI0 + ml;
   const int mv = mI / nc, I = mI - mv * nc;
   const double2* r2 = xin + (long)mv * dim + ns + ((long)I * no + j) * npair;
-  const long ld = (long)m * nc * nv;
-  TO* R = Rt + (long)j * nv * ld + (long)mI * nv;   // R[d*ld + c] = R_{mIj}[c][d]
+  const long ld = (long)nrow * nv;
+  TO* R = Rt + (long)j * nv * ld + (long)ml * nv;   // R[d*ld + c] = R_{mIj}[c][d]
   const int tid = threadIdx.x;
   for (int e = tid; e < UT * UT; e += 256) {
     const int rc = e / UT, cd = e % UT;
@@ -799,25 +803,25 @@ constexpr int LJG = 4;
 //   Tp[mI][jg][K][c] = sum_{j in group} sum_d conj(<Kd||Ij>) R_{mIj}[c][d]
 //                    = sum_j sum_d conj(Vt[I][j][K][d]) Rt[(j,d)][(mI,c)]
 template <class TI>
-__global__ __launch_bounds__(256) void k_light1(const TI* __restrict__ Rt, const double2* __restrict__ Vt,
-                                                 int rows, int nc, int no, int nv, double2* __restrict__ Tp) {
+__global__ __launch_bounds__(256) void k_light1(const TI* __restrict__ Rt, const double2* __restrict__ Vt, int mI0,
+                                                 int nrow, int nc, int no, int nv, double2* __restrict__ Tp) {
   __shared__ double2 vs[8][256];
   const int ncb = (nv + 255) / 256;
   const int njg = (no + LJG - 1) / LJG;
   const int cb = blockIdx.x % ncb;
   const int jg = (blockIdx.x / ncb) % njg;
-  const int mI = blockIdx.x / (ncb * njg);
+  const int ml = blockIdx.x / (ncb * njg), mI = mI0 + ml;
   const int I = mI % nc;
   const int c = cb * 256 + threadIdx.x;
   const bool cok = c < nv;
   const int cs = cok ? c : 0;
-  const long ld = (long)rows * nv;
+  const long ld = (long)nrow * nv;
   for (int K0 = 0; K0 < nc; K0 += 8) {
     double2 acc[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) acc[q] = czero();
     for (int j = jg * LJG; j < min(no, (jg + 1) * LJG); ++j) {
-      const TI* R = Rt + (long)j * nv * ld + (long)mI * nv;   // R[d*ld + c]
+      const TI* R = Rt + (long)j * nv * ld + (long)ml * nv;   // R[d*ld + c]
       const double2* V = Vt + ((long)I * no + j) * nc * nv;
       for (int dd0 = 0; dd0 < nv; dd0 += 256) {
         __syncthreads();
@@ -859,14 +863,14 @@ __global__ __launch_bounds__(256) void k_light1(const TI* __restrict__ Rt, const
 }
 
 // sigma2 = Z_ab - Z_ba + D r2 + sum_K (<Ka||Ij> r1_Kb - r1_Ka <Kb||Ij>), a < b, packed.
-// One workgroup per (g = (m,I,j), 32x32 tile pair ab <= bb); the mirror tile
+// One workgroup per (g = (mI - mI0, j), 32x32 tile pair ab <= bb); the mirror tile
 // is staged in LDS so that both reads of Z are coalesced.
 constexpr int PT = 32;
 constexpr int PK = 8;    // core spinors staged in LDS by the pack kernel (more read from global memory)
 template <class TZ>
 __global__ __launch_bounds__(256) void k_pack2(const TZ* __restrict__ Z, const double2* __restrict__ xin,
                                                 double2* __restrict__ sout, long dim, const double2* __restrict__ Vt,
-                                                const double* __restrict__ eps, int m, int nc, int no, int nv,
+                                                const double* __restrict__ eps, int mI0, int nc, int no, int nv,
                                                 int with_d) {
   __shared__ double2 zt[PT][PT + 1];
   __shared__ double2 va[PK][PT], vb[PK][PT], ra[PK][PT], rb[PK][PT];
@@ -881,8 +885,8 @@ __global__ __launch_bounds__(256) void k_pack2(const TZ* __restrict__ Z, const d
   }
   const int bbk = abk + t;
   const int a0 = abk * PT, b0 = bbk * PT;
-  const int mv = (int)(g / ((long)nc * no));
-  const int I = (int)((g / no) % nc), j = (int)(g % no);
+  const int mI = mI0 + (int)(g / no), j = (int)(g % no);
+  const int mv = mI / nc, I = mI - mv * nc;
   const int o = nc + no;
   const TZ* Zg = Z + g * (long)nv * nv;
   const double2* r1 = xin + (long)mv * dim;
@@ -1148,27 +1152,261 @@ static WsPlan ws_plan(adc2_handle h, int m, int ys = 0, int ns = 0) {
   return p;
 }
 
-adc2_status ensure_ws(adc2_handle h, int m) {
-  if (h->ws_m >= m) return ADC2_OK;
-  dfree(h, h->X);
-  dfree(h, h->Y);
-  dfree(h, h->part);
-  dfree(h, h->Zb);
-  dfree(h, h->Tp);
-  h->X = h->Y = h->part = h->Zb = h->Tp = nullptr;
-  h->ws_m = 0;
-  const WsPlan p = ws_plan(h, m);
-  h->ysplit = p.ysplit;
-  h->nsplit = p.nsplit;
-  ADC2_HIP(dmalloc(h, &h->X, p.x));
-  ADC2_HIP(dmalloc(h, &h->Y, p.y));
-  ADC2_HIP(dmalloc(h, &h->Zb, p.zb));
-  ADC2_HIP(dmalloc(h, &h->Tp, p.tp));
-  ADC2_HIP(dmalloc(h, &h->part, p.part));
-  h->ws_m = m;
+adc2_status ensure_ws(adc2_handle h, int m, bool zb) {
+  if (h->ws_m < m) {
+    dfree(h, h->X);
+    dfree(h, h->Y);
+    dfree(h, h->part);
+    dfree(h, h->Tp);
+    h->X = h->Y = h->part = h->Tp = nullptr;
+    h->ws_m = 0;
+    const WsPlan p = ws_plan(h, m);
+    h->ysplit = p.ysplit;
+    h->nsplit = p.nsplit;
+    ADC2_HIP(dmalloc(h, &h->X, p.x));
+    ADC2_HIP(dmalloc(h, &h->Y, p.y));
+    ADC2_HIP(dmalloc(h, &h->Tp, p.tp));
+    ADC2_HIP(dmalloc(h, &h->part, p.part));
+    h->ws_m = m;
+  }
+  if (zb && h->zb_m < m) {
+    dfree(h, h->Zb);
+    h->Zb = nullptr;
+    h->zb_m = 0;
+    ADC2_HIP(dmalloc(h, &h->Zb, ws_plan(h, m).zb));
+    h->zb_m = m;
+  }
   return ADC2_OK;
 }
 
+// ---------------------------------------------------------------------------
+// The FP64 form on the residue engine (rns.h).  The doubles are unpacked,
+// multiplied and packed again in chunks of (vector, core) rows, so that its
+// work space is that of one chunk whatever m: the unpacked doubles or the
+// sigma2 product of the chunk in FP64 (16 B an entry), the residues of the one
+// operand or product (32 B), and the other, smaller, in residues.
+// ---------------------------------------------------------------------------
+constexpr size_t NOALLOC_SCRATCH_BYTES = size_t(128) << 20;   // adc2_sigma_noalloc's work space
+constexpr size_t RNS_CHUNK_BYTES = size_t(3) << 30;           // target of a chunk's work space
+
+// Which requests take it: those whose work spaces are past the reach of
+// adc2_sigma_noalloc (which runs the MFMA engines, and gives adc2_sigma's
+// results bit for bit), with enough terms per entry in both products to pay
+// for the conversions (32 B written and read per entry of operand and product
+// besides the FP64 image).
+static bool rns_wanted(adc2_handle h, int m) {
+  const Dims& d = h->d;
+  const long kx = d.naux, ky = (long)d.no * d.nv;
+  if (h->prec != ADC2_FP64 || h->rns_off || h->rns_mode == RNS_NEVER || kx > RNS_KMAX || ky > RNS_KMAX) return false;
+  if (h->rns_mode == RNS_ALWAYS) return true;
+  const double rows = (double)m * d.nc;
+  return kx >= 192 && ky >= 512 && 16.0 * rows * (2.0 * d.naux * d.nv + (double)d.no * d.nv * d.nv) > NOALLOC_SCRATCH_BYTES;
+}
+
+// Work space of a chunk of c (vector, core) rows, as offsets.
+struct RnsPlan {
+  int c;
+  size_t f64, opnd, out, ex, norm, bytes;
+};
+static RnsPlan rns_plan(adc2_handle h, int rows) {
+  const Dims& d = h->d;
+  const long ky = (long)d.no * d.nv;
+  auto at = [&](int c) {
+    RnsPlan p;
+    p.c = c;
+    const long r = (long)c * d.nv;
+    size_t q = 0;
+    auto take = [&](size_t b) {
+      const size_t o = q;
+      q += (b + 255) & ~size_t(255);
+      return o;
+    };
+    p.f64 = take(sizeof(double2) * r * ky);
+    p.opnd = take(std::max(rns_op_bytes(r, ky), rns_op_bytes(r, d.naux)));
+    p.out = take(std::max(rns_out_bytes(d.naux, r), rns_out_bytes(r, ky)));
+    p.ex = take(rns_exp_bytes(r));
+    p.norm = take(rns_norm_bytes(r));
+    p.bytes = q;
+    return p;
+  };
+  const double one = (double)at(1).bytes;
+  const int most = (int)std::max(1.0, std::min((double)rows, std::floor((double)RNS_CHUNK_BYTES / one)));
+  return at(cdiv(rows, cdiv(rows, most)));   // equal chunks
+}
+
+void rns_release(adc2_handle h) {
+  char *a = h->rns_lvo, *b = h->rns_lvt, *c = h->rns_ws;
+  h->rns_lvo = h->rns_lvt = h->rns_ws = nullptr;
+  h->rns_ws_bytes = 0;
+  dfree(h, a);
+  dfree(h, b);
+  dfree(h, c);
+}
+
+// The residue engine's buffers for m vectors; false (and the MFMA engines from
+// then on) where the memory is not to be had.
+static adc2_status rns_ready(adc2_handle h, int m, hipStream_t st, bool* ok) {
+  const Dims& d = h->d;
+  const long ky = (long)d.no * d.nv;
+  *ok = false;
+  const RnsPlan p = rns_plan(h, m * d.nc);
+  const bool fresh = !h->rns_lvo || !h->rns_lvt;
+  const size_t wneed = std::max(p.bytes, fresh ? std::max(rns_norm_bytes(ky), rns_norm_bytes(d.naux)) : size_t(0));
+  hipError_t e = hipSuccess;
+  if (h->rns_ws_bytes < wneed) {
+    dfree(h, h->rns_ws);
+    h->rns_ws = nullptr;
+    h->rns_ws_bytes = 0;
+    e = dmalloc(h, &h->rns_ws, wneed);
+    if (e == hipSuccess) h->rns_ws_bytes = wneed;
+  }
+  if (e == hipSuccess && fresh && !h->rns_off) {
+    e = dmalloc(h, &h->rns_lvo, rns_op_bytes(ky, d.naux) + rns_exp_bytes(ky));
+    if (e == hipSuccess && !h->rns_off) e = dmalloc(h, &h->rns_lvt, rns_op_bytes(d.naux, ky) + rns_exp_bytes(d.naux));
+  }
+  if (e != hipSuccess || h->rns_off) {
+    (void)hipGetLastError();
+    rns_release(h);
+    h->rns_off = true;
+    return ADC2_OK;
+  }
+  if (fresh) {
+    RnsMat t;
+    double* norm = (double*)h->rns_ws;
+    adc2_status rc = rns_pack(h->Lvo + (long)d.nc * d.naux * d.nv, (long)d.naux * d.nv, d.nv, d.nv, (int)ky, d.naux,
+                              false, (int8_t*)h->rns_lvo, (int*)(h->rns_lvo + rns_op_bytes(ky, d.naux)), norm, &t, st);
+    if (rc == ADC2_OK)
+      rc = rns_pack(h->LvT, 0, d.naux, d.naux, d.naux, (int)ky, false, (int8_t*)h->rns_lvt,
+                    (int*)(h->rns_lvt + rns_op_bytes(d.naux, ky)), norm, &t, st);
+    if (rc != ADC2_OK) {
+      rns_release(h);
+      return rc;
+    }
+    ADC2_HIP(hipStreamSynchronize(st));   // later calls may use other streams
+  }
+  *ok = true;
+  return ADC2_OK;
+}
+
+static RnsMat rns_static(char* mem, long rows, long K) {
+  RnsMat a;
+  a.p = (int8_t*)mem;
+  a.e = (int*)(mem + rns_op_bytes(rows, K));
+  a.rows = (int)rows;
+  a.K = (int)K;
+  a.nrt = cdiv(rows, RNS_RT);
+  a.nkc = cdiv(K, RNS_KC);
+  return a;
+}
+
+// Event pairs around the launches of a kernel class, summed at the end.
+struct RnsProf {
+  bool on;
+  hipStream_t st;
+  struct Seg {
+    int slot;
+    hipEvent_t a, b;
+  };
+  std::vector<Seg> segs;
+  template <class F>
+  adc2_status run(int slot, F&& f) {
+    if (!on) return f();
+    Seg s{slot, nullptr, nullptr};
+    ADC2_HIP(hipEventCreate(&s.a));
+    ADC2_HIP(hipEventCreate(&s.b));
+    segs.push_back(s);
+    ADC2_HIP(hipEventRecord(s.a, st));
+    const adc2_status rc = f();
+    ADC2_HIP(hipEventRecord(s.b, st));
+    return rc;
+  }
+  // ms of a slot (the stream has been waited for)
+  double ms(int slot) const {
+    double t = 0.0;
+    for (const Seg& s : segs) {
+      float x = 0.f;
+      if (s.slot == slot && hipEventElapsedTime(&x, s.a, s.b) == hipSuccess) t += x;
+    }
+    return t;
+  }
+  ~RnsProf() {
+    for (const Seg& s : segs) {
+      if (s.a) (void)hipEventDestroy(s.a);
+      if (s.b) (void)hipEventDestroy(s.b);
+    }
+  }
+};
+
+// Y of the doubles input (and the light partials Tp), chunk by chunk.
+static adc2_status rns_doubles_in(adc2_handle h, const SigReq& rq, RnsProf& pf, hipStream_t st) {
+  const Dims& d = h->d;
+  const int rows = rq.m * d.nc, K = d.no * d.nv;
+  const RnsPlan p = rns_plan(h, rows);
+  double2* R = (double2*)(h->rns_ws + p.f64);
+  int8_t* out = (int8_t*)(h->rns_ws + p.out);
+  const RnsMat L = rns_static(h->rns_lvt, d.naux, K);
+  const int nb = cdiv(d.nv, UT), njg = (d.no + LJG - 1) / LJG;
+  for (int r0 = 0; r0 < rows; r0 += p.c) {
+    const int c = std::min(p.c, rows - r0);
+    adc2_status rc = pf.run(0, [&]() -> adc2_status {
+      k_unpack<double2, false><<<(unsigned)((long)c * d.no * (nb * (nb + 1) / 2)), 256, 0, st>>>(
+          rq.xin, d.dim, r0, c, d.nc, d.no, d.nv, R, nullptr);
+      ADC2_CHECK_LAUNCH();
+      return ADC2_OK;
+    });
+    if (rc != ADC2_OK) return rc;
+    rc = pf.run(2, [&]() -> adc2_status {
+      k_light1<double2><<<(unsigned)(c * njg * ((d.nv + 255) / 256)), 256, 0, st>>>(R, h->Vt, r0, c, d.nc, d.no, d.nv,
+                                                                                    h->Tp);
+      ADC2_CHECK_LAUNCH();
+      return ADC2_OK;
+    });
+    if (rc != ADC2_OK) return rc;
+    rc = pf.run(1, [&]() -> adc2_status {
+      RnsMat B;
+      const int ncol = c * d.nv;
+      adc2_status r = rns_pack(R, 0, ncol, ncol, ncol, K, false, (int8_t*)(h->rns_ws + p.opnd), (int*)(h->rns_ws + p.ex),
+                               (double*)(h->rns_ws + p.norm), &B, st);
+      if (r == ADC2_OK) r = rns_gemm(L, B, 0, ncol, out, st);
+      if (r == ADC2_OK) r = rns_to_y(L, B, out, d.naux, d.nv, h->Y + (long)r0 * d.naux * d.nv, st);
+      return r;
+    });
+    if (rc != ADC2_OK) return rc;
+  }
+  return ADC2_OK;
+}
+
+// sigma2 of the singles input (X built), chunk by chunk.
+static adc2_status rns_singles_in(adc2_handle h, const SigReq& rq, int with_d, RnsProf& pf, hipStream_t st) {
+  const Dims& d = h->d;
+  const int rows = rq.m * d.nc, N = d.no * d.nv;
+  const RnsPlan p = rns_plan(h, rows);
+  double2* Z = (double2*)(h->rns_ws + p.f64);
+  int8_t* out = (int8_t*)(h->rns_ws + p.out);
+  const RnsMat L = rns_static(h->rns_lvo, N, d.naux);
+  const int nb = cdiv(d.nv, PT);
+  for (int r0 = 0; r0 < rows; r0 += p.c) {
+    const int c = std::min(p.c, rows - r0);
+    adc2_status rc = pf.run(4, [&]() -> adc2_status {
+      RnsMat A;
+      adc2_status r = rns_pack(h->X + (long)r0 * d.naux * d.nv, (long)d.naux * d.nv, d.nv, d.nv, c * d.nv, d.naux, false,
+                               (int8_t*)(h->rns_ws + p.opnd), (int*)(h->rns_ws + p.ex), (double*)(h->rns_ws + p.norm), &A,
+                               st);
+      if (r == ADC2_OK) r = rns_gemm(A, L, 0, N, out, st);
+      if (r == ADC2_OK) r = rns_to_z(A, L, out, d.no, d.nv, Z, st);
+      return r;
+    });
+    if (rc != ADC2_OK) return rc;
+    rc = pf.run(5, [&]() -> adc2_status {
+      k_pack2<double2><<<(unsigned)((long)c * d.no * (nb * (nb + 1) / 2)), 256, 0, st>>>(
+          Z, rq.xin, rq.sout, d.dim, h->Vt, h->eps, r0, d.nc, d.no, d.nv, with_d);
+      ADC2_CHECK_LAUNCH();
+      return ADC2_OK;
+    });
+    if (rc != ADC2_OK) return rc;
+  }
+  return ADC2_OK;
+}
 
 // Weighted unpack Rt[(j,d)][(mI,c)] = w_m R_{mIj}[c][d] into h->Zb, and the
 // FP64 Y-build on it into h->Y (split partials summed); used by the adjoint.
@@ -1176,7 +1414,7 @@ adc2_status unpack_weighted(adc2_handle h, int m, const double2* xin, const doub
   const Dims& d = h->d;
   const int nb = cdiv(d.nv, UT);
   const long nblk = (long)m * d.nc * d.no * (nb * (nb + 1) / 2);
-  k_unpack<double2, true><<<(unsigned)nblk, 256, 0, st>>>(xin, d.dim, m, d.nc, d.no, d.nv, h->Zb, wts);
+  k_unpack<double2, true><<<(unsigned)nblk, 256, 0, st>>>(xin, d.dim, 0, m * d.nc, d.nc, d.no, d.nv, h->Zb, wts);
   ADC2_CHECK_LAUNCH();
   return ADC2_OK;
 }
@@ -1334,11 +1572,17 @@ static adc2_status grouped_gemm(int nreq, const SigReq* rq, const std::vector<ch
 // request the two heavy GEMMs of the requests in the complex64 and split-BF16
 // forms are one grouped launch per form.  Per-kernel profiling (adc2_profile)
 // is recorded for single requests only.
-adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st) {
+adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_rns) {
   adc2_status rc;
+  std::vector<char> rns(nreq, 0);   // requests on the residue engine
   for (int q = 0; q < nreq; ++q) {
     adc2_handle h = rq[q].h;
-    if ((rc = ensure_ws(h, rq[q].m)) != ADC2_OK) return rc;
+    if (allow_rns && rns_wanted(h, rq[q].m)) {
+      bool ok = false;
+      if ((rc = ensure_ws(h, rq[q].m, false)) != ADC2_OK || (rc = rns_ready(h, rq[q].m, st, &ok)) != ADC2_OK) return rc;
+      rns[q] = ok;
+    }
+    if ((rc = ensure_ws(h, rq[q].m, !rns[q])) != ADC2_OK) return rc;
     const bool b3 = h->prec == ADC2_BF16X3;
     const bool c64 = h->prec == ADC2_C64 || b3;   // complex64 operand copies
     if (c64 && (rc = build_c64(h, st)) != ADC2_OK) return rc;
@@ -1346,6 +1590,7 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st) {
   }
   adc2_handle h0 = rq[0].h;
   const bool prof = nreq == 1 && h0->profiling != 0;
+  RnsProf rp{prof && rns[0], st, {}};
   auto mark = [&](int i) -> adc2_status {
     if (prof) ADC2_HIP(hipEventRecord(h0->kev[i], st));
     return ADC2_OK;
@@ -1365,20 +1610,22 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st) {
   auto is_grouped = [&](int q) { return nreq > 1 && rq[q].h->prec != ADC2_FP64; };
 
   // kernel order (profiling slots): unpack, ygemm, light1, xbuild, zsig2, pack2, backc, m11mv+finish
+  for (int q = 0; q < nreq; ++q)
+    if (rns[q] && dbl[q] && (rc = rns_doubles_in(rq[q].h, rq[q], rp, st)) != ADC2_OK) return rc;
   if ((rc = mark(0)) != ADC2_OK) return rc;
   for (int q = 0; q < nreq; ++q) {
-    if (!dbl[q]) continue;
+    if (!dbl[q] || rns[q]) continue;
     adc2_handle h = rq[q].h;
     const Dims& d = h->d;
     const bool c64 = h->prec != ADC2_FP64;
     const int nb = cdiv(d.nv, UT);
     const long nblk = (long)rq[q].m * d.nc * d.no * (nb * (nb + 1) / 2);
     if (c64)
-      k_unpack<float2, false><<<(unsigned)nblk, 256, 0, st>>>(rq[q].xin, d.dim, rq[q].m, d.nc, d.no, d.nv,
-                                                               (float2*)h->Zb, nullptr);
+      k_unpack<float2, false><<<(unsigned)nblk, 256, 0, st>>>(rq[q].xin, d.dim, 0, rq[q].m * d.nc, d.nc, d.no,
+                                                               d.nv, (float2*)h->Zb, nullptr);
     else
-      k_unpack<double2, false><<<(unsigned)nblk, 256, 0, st>>>(rq[q].xin, d.dim, rq[q].m, d.nc, d.no, d.nv, h->Zb,
-                                                                nullptr);
+      k_unpack<double2, false><<<(unsigned)nblk, 256, 0, st>>>(rq[q].xin, d.dim, 0, rq[q].m * d.nc, d.nc, d.no,
+                                                                d.nv, h->Zb, nullptr);
     ADC2_CHECK_LAUNCH();
   }
   for (int q = 0; q < nreq; ++q) {   // split-BF16: the unpacked doubles into the blocked split layout
@@ -1394,23 +1641,23 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st) {
   for (int prec : {ADC2_C64, ADC2_BF16X3})
     if (grouped(dbl, prec) && (rc = grouped_gemm(nreq, rq, dbl, prec, true, st)) != ADC2_OK) return rc;
   for (int q = 0; q < nreq; ++q) {
-    if (!dbl[q]) continue;
+    if (!dbl[q] || rns[q]) continue;
     adc2_handle h = rq[q].h;
     if (!is_grouped(q) && (rc = ybuild_launch(h, rq[q].m, st)) != ADC2_OK) return rc;
     if ((rc = ybuild_sum(h, rq[q].m, st)) != ADC2_OK) return rc;
   }
   if ((rc = mark(2)) != ADC2_OK) return rc;
   for (int q = 0; q < nreq; ++q) {
-    if (!dbl[q]) continue;
+    if (!dbl[q] || rns[q]) continue;
     adc2_handle h = rq[q].h;
     const Dims& d = h->d;
     const int rows = rq[q].m * d.nc;
     const int njg = (d.no + LJG - 1) / LJG;
     const unsigned g = (unsigned)(rows * njg * ((d.nv + 255) / 256));
     if (h->prec != ADC2_FP64)
-      k_light1<float2><<<g, 256, 0, st>>>((const float2*)h->Zb, h->Vt, rows, d.nc, d.no, d.nv, h->Tp);
+      k_light1<float2><<<g, 256, 0, st>>>((const float2*)h->Zb, h->Vt, 0, rows, d.nc, d.no, d.nv, h->Tp);
     else
-      k_light1<double2><<<g, 256, 0, st>>>(h->Zb, h->Vt, rows, d.nc, d.no, d.nv, h->Tp);
+      k_light1<double2><<<g, 256, 0, st>>>(h->Zb, h->Vt, 0, rows, d.nc, d.no, d.nv, h->Tp);
     ADC2_CHECK_LAUNCH();
   }
   if ((rc = mark(3)) != ADC2_OK) return rc;
@@ -1443,6 +1690,10 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st) {
     adc2_handle h = rq[q].h;
     const Dims& d = h->d;
     const int rows = rq[q].m * d.nc;
+    if (rns[q]) {
+      if ((rc = rns_singles_in(h, rq[q], dbl[q] ? 1 : 0, rp, st)) != ADC2_OK) return rc;
+      continue;
+    }
     if (h->prec != ADC2_FP64) {
       const long nblk = (long)cdiv((long)rows * d.nv, BT) * cdiv((long)d.no * d.nv, BT);
       if (h->prec == ADC2_BF16X3)
@@ -1468,7 +1719,7 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st) {
   }
   if ((rc = mark(5)) != ADC2_OK) return rc;
   for (int q = 0; q < nreq; ++q) {
-    if (!sgl[q]) continue;
+    if (!sgl[q] || rns[q]) continue;
     adc2_handle h = rq[q].h;
     const Dims& d = h->d;
     const int m = rq[q].m;
@@ -1477,9 +1728,9 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st) {
     const long nblk = (long)m * d.nc * d.no * (nb * (nb + 1) / 2);
     if (h->prec != ADC2_FP64)
       k_pack2<float2><<<(unsigned)nblk, 256, 0, st>>>((const float2*)h->Zb, rq[q].xin, rq[q].sout, d.dim, h->Vt,
-                                                      h->eps, m, d.nc, d.no, d.nv, with_d);
+                                                      h->eps, 0, d.nc, d.no, d.nv, with_d);
     else
-      k_pack2<double2><<<(unsigned)nblk, 256, 0, st>>>(h->Zb, rq[q].xin, rq[q].sout, d.dim, h->Vt, h->eps, m, d.nc,
+      k_pack2<double2><<<(unsigned)nblk, 256, 0, st>>>(h->Zb, rq[q].xin, rq[q].sout, d.dim, h->Vt, h->eps, 0, d.nc,
                                                        d.no, d.nv, with_d);
     ADC2_CHECK_LAUNCH();
   }
@@ -1546,6 +1797,7 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st) {
       if (!ran[i]) continue;
       float ms = 0.f;
       ADC2_HIP(hipEventElapsedTime(&ms, h->kev[i], h->kev[i + 1]));
+      if (rns[0] && i != 3 && i < 6) ms = (float)rp.ms(i);   // its chunks' launches
       h->k_ms[i] += ms;
       h->k_launches[i] += 1;
       h->k_flops[i] += fl[i];
@@ -1567,7 +1819,6 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st) {
 // ---------------------------------------------------------------------------
 namespace adc2 {
 namespace {
-constexpr size_t NOALLOC_SCRATCH_BYTES = size_t(128) << 20;
 constexpr int NOALLOC_MAX_DEVICES = 64;
 }  // namespace
 }  // namespace adc2
@@ -1650,7 +1901,7 @@ extern "C" adc2_status adc2_sigma_noalloc(adc2_handle h, int m, const void* X, v
   // point the handle's work spaces into the scratch for this call only; the
   // kernels take these addresses as arguments at launch
   double2 *sX = h->X, *sY = h->Y, *sZb = h->Zb, *sTp = h->Tp, *spart = h->part;
-  const int sws = h->ws_m, sys = h->ysplit, sns = h->nsplit;
+  const int sws = h->ws_m, szb = h->zb_m, sys = h->ysplit, sns = h->nsplit;
   unsigned char* q = static_cast<unsigned char*>(base);
   auto take = [&](size_t b) {
     double2* r = reinterpret_cast<double2*>(q);
@@ -1662,17 +1913,18 @@ extern "C" adc2_status adc2_sigma_noalloc(adc2_handle h, int m, const void* X, v
   h->Zb = take(p.zb);
   h->Tp = take(p.tp);
   h->part = take(p.part);
-  h->ws_m = m;
+  h->ws_m = h->zb_m = m;
   h->ysplit = p.ysplit;
   h->nsplit = p.nsplit;
-  rc = sigma_parts(h, m, static_cast<const double2*>(X), static_cast<double2*>(S),
-                   SIGMA_SINGLES_IN | SIGMA_DOUBLES_IN, static_cast<hipStream_t>(stream));
+  const SigReq rq{h, m, static_cast<const double2*>(X), static_cast<double2*>(S), SIGMA_SINGLES_IN | SIGMA_DOUBLES_IN};
+  rc = sigma_multi(1, &rq, static_cast<hipStream_t>(stream), false);   // the residue engine has work spaces of its own
   h->X = sX;
   h->Y = sY;
   h->Zb = sZb;
   h->Tp = sTp;
   h->part = spart;
   h->ws_m = sws;
+  h->zb_m = szb;
   h->ysplit = sys;
   h->nsplit = sns;
   return rc;

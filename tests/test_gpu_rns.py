@@ -1,0 +1,139 @@
+"""The residue engine of the large FP64 products (csrc/rns.h), forced at small
+sizes with ADC2_ZGEMM=rns.
+
+Tolerance against the oracle.  An entry's integers are rounded at 2^-58 of its
+row's norm, so a product of K terms is off by at most sqrt(2K) 2^-57 of
+||a|| ||b|| (3e-16 at K = 1000), below the K-term FP64 sums around it; with
+the FP64 sums of the oracle and of the other terms, 1e-12 of the largest entry
+of sigma is a bound with a margin of two decades at these sizes.
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2604_27451_amd as A
+from oracle import adc2 as O
+from synth import make_system, random_vectors
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+def handle(s, **kw):
+    return A.adc2_setup(dev(s.L), dev(s.eps), s.nc, s.no, s.nv, s.naux, **kw)
+
+
+# rows m nc nv and columns no nv around the 128-row blocks and the 256 x 128
+# tiles, K = naux and no nv around the 64-k chunks; the last has K above the
+# 4096 terms up to which one reduction step is enough
+@pytest.mark.parametrize("nc,no,nv,naux,m", [
+    (1, 1, 2, 3, 1), (2, 3, 9, 20, 2), (2, 4, 16, 64, 4), (3, 5, 33, 65, 2), (2, 2, 64, 63, 1), (3, 7, 37, 129, 3),
+    (1, 52, 80, 40, 1)])
+def test_sigma_against_oracle(monkeypatch, nc, no, nv, naux, m):
+    s = make_system(nc, no, nv, naux, seed=900 + naux)
+    print(f"[case] rns sigma {(nc, no, nv, naux)} m={m}", flush=True)
+    monkeypatch.setenv("ADC2_ZGEMM", "rns")
+    h = handle(s)
+    x = random_vectors(9, m, h.dim)
+    S = A.adc2_sigma(h, dev(x)).cpu()
+    h.close()
+    ref = O.Adc2(s.L, s.eps, nc, no, nv).sigma(torch.from_numpy(x))
+    err = float((S - ref).abs().max() / ref.abs().max())
+    print(f"  rel err {err:.2e}", flush=True)
+    assert err < 1e-12
+
+
+@pytest.mark.parametrize("p", [600, -600])
+def test_scales_exactly(monkeypatch, p):
+    """Rows whose squares overflow or underflow: sigma(2^p x) = 2^p sigma(x)."""
+    monkeypatch.setenv("ADC2_ZGEMM", "rns")
+    s = make_system(2, 3, 20, 30, seed=911)
+    h = handle(s)
+    x = dev(random_vectors(3, 2, h.dim))
+    f = 2.0 ** p
+    print(f"[case] rns scale 2^{p}", flush=True)
+    S, T = A.adc2_sigma(h, x), A.adc2_sigma(h, x * f)
+    assert torch.equal(S * f, T)
+    h.close()
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_non_finite_vector_stays_alone(monkeypatch, bad):
+    """A NaN or Inf in one vector shows in that vector's sigma and no other's;
+    zero vectors give exact zeros."""
+    monkeypatch.setenv("ADC2_ZGEMM", "rns")
+    s = make_system(2, 3, 20, 30, seed=912)
+    h = handle(s)
+    x = dev(random_vectors(4, 3, h.dim))
+    x[2] = 0.0
+    S = A.adc2_sigma(h, x)
+    y = x.clone()
+    y[1, h.ns + 5] = bad
+    y[1, 3] = bad
+    print(f"[case] rns non-finite {bad}", flush=True)
+    T = A.adc2_sigma(h, y)
+    assert torch.equal(S[0], T[0]) and torch.equal(S[2], T[2])
+    assert float(T[2].abs().max()) == 0.0
+    # every doubles entry of core 0 that the bad singles entry reaches, and every singles entry
+    assert not torch.isfinite(torch.view_as_real(T[1, :h.ns])).any()
+    no, npair = 3, 20 * 19 // 2
+    d0 = torch.view_as_real(T[1, h.ns:h.ns + no * npair]).reshape(no * npair, 2)
+    assert not torch.isfinite(d0).any()
+    h.close()
+
+
+def test_batch_and_graph_replays_equal_separate(monkeypatch):
+    monkeypatch.setenv("ADC2_ZGEMM", "rns")
+    systems = [make_system(2, 3, 21, 40, seed=921), make_system(1, 5, 34, 70, seed=922)]
+    hs = [handle(s) for s in systems]
+    xs = [dev(random_vectors(5 + q, 2 + q, h.dim)) for q, h in enumerate(hs)]
+    ref = [A.adc2_sigma(h, x) for h, x in zip(hs, xs)]
+    print("[case] rns batch and graph", flush=True)
+    for a, b in zip(ref, A.adc2_sigma_batch(hs, xs)):
+        assert torch.equal(a, b)
+    g = A.adc2_graph_sigma_batch(hs, xs)
+    for k in range(3):
+        for q, x in enumerate(xs):
+            x.copy_(dev(random_vectors(50 + 10 * k + q, x.shape[0], x.shape[1])))
+        want = [A.adc2_sigma(h, x) for h, x in zip(hs, xs)]
+        got = g.launch()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(want, got))
+    g.close()
+    for h in hs:
+        h.close()
+
+
+def test_without_its_memory_the_mfma_engine_serves(monkeypatch):
+    """An allocator that refuses the engine's own buffers: the result is that
+    of the FP64 MFMA engine, and a later call does not ask again."""
+    s = make_system(2, 3, 21, 40, seed=931)
+    monkeypatch.setenv("ADC2_ZGEMM", "wide")
+    hw = handle(s)
+    x = dev(random_vectors(6, 2, hw.dim))
+    want = A.adc2_sigma(hw, x)
+    hw.close()
+    monkeypatch.setenv("ADC2_ZGEMM", "rns")
+    base = A.torch_allocator()
+    state = {"count": None, "refused": 0}
+
+    def _alloc(nbytes, ctx):
+        if state["count"] is not None:
+            state["count"] += 1
+            if state["count"] == 5:      # after X, Y, Tp and the back-contraction partials
+                state["refused"] += 1
+                return None
+        return base.alloc(nbytes, ctx)
+
+    al = A.Alloc(A._ALLOC_FN(_alloc), base.release, None)
+    h = handle(s, alloc=al)
+    state["count"] = 0
+    print("[case] rns without its memory", flush=True)
+    got = A.adc2_sigma(h, x)
+    assert state["refused"] == 1 and torch.equal(got, want)
+    n = state["count"]
+    assert torch.equal(A.adc2_sigma(h, x), want) and state["count"] == n
+    h.close()

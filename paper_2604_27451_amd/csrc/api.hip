@@ -246,6 +246,7 @@ adc2_status adc2_setup(const void* L, const double* eps, int nc, int no, int nv,
                                        : ZGEMM_WIDE;
     h->rns_mode = strcmp(v, "rns") == 0 ? RNS_ALWAYS : RNS_NEVER;
   }
+  if (const char* v = getenv("ADC2_RNS_MB")) h->rns_target = (size_t)std::max(1, atoi(v)) << 20;
 #define SETUP_TRY(call)                                                           \
   do {                                                                            \
     hipError_t e_ = (call);                                                       \

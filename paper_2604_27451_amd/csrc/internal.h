@@ -105,6 +105,7 @@ struct adc2_handle_s {
   char* rns_lvt = nullptr;  // residues of LvT (rows P, K = (j,d)), then their exponents
   char* rns_ws = nullptr;
   size_t rns_ws_bytes = 0;
+  size_t rns_target = size_t(3) << 30;   // bytes a chunk's work space aims at (environment ADC2_RNS_MB)
   // method: ADC2_METHOD_ADC2 or ADC2_METHOD_ADC2X (first-order doubles block, adc2x.hip)
   int method = 0;
   double2* Vpp = nullptr;   // ADC(2)-x: [(a<b)][(c<d)] <ab||cd>

@@ -37,6 +37,7 @@
 #include <vector>
 
 #include "internal.h"
+#include "rns.h"
 #include "tile.h"
 #include "zgemm.h"
 
@@ -798,37 +799,45 @@ __global__ __launch_bounds__(256) void k_rho(const double2* __restrict__ xin, lo
   if (tid == 0) Sv[(long)g * (nv + 1) + nv] = red4[0] + red4[1] + red4[2] + red4[3];
 }
 
-// d eps, one thread per spinor.
-__global__ void k_eps_final(const double2* __restrict__ gam, const double* __restrict__ Sv,
-                            const double* __restrict__ hr, int nc, int no, int nv, double* __restrict__ deps) {
-  const int o = nc + no, n = o + nv;
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= n) return;
+// d eps, one workgroup per spinor (one thread each read 0.8 MB serially: 1.7 ms
+// at nc=6 no=35 nv=250).
+__global__ __launch_bounds__(256) void k_eps_final(const double2* __restrict__ gam, const double* __restrict__ Sv,
+                                                    const double* __restrict__ hr, int nc, int no, int nv,
+                                                    double* __restrict__ deps) {
+  __shared__ double red[256];
+  const int o = nc + no;
+  const int q = blockIdx.x, tid = threadIdx.x;
   const long ns = (long)nc * nv;
   double v = 0.0;
   if (q >= o) {
     const int a = q - o;
-    for (int I = 0; I < nc; ++I) v += gam[((long)I * nv + a) * ns + (long)I * nv + a].x;
-    for (int g = 0; g < nc * no; ++g) v += Sv[(long)g * (nv + 1) + a];
+    for (int I = tid; I < nc; I += 256) v += gam[((long)I * nv + a) * ns + (long)I * nv + a].x;
+    for (int g = tid; g < nc * no; g += 256) v += Sv[(long)g * (nv + 1) + a];
     const long npairs = (long)o * (o - 1) / 2;
-    for (long p = 0; p < npairs; ++p) v += hr[p * nv + a];
+    for (long p = tid; p < npairs; p += 256) v += hr[p * nv + a];
   } else {
     if (q < nc) {
-      for (int a = 0; a < nv; ++a) v -= gam[((long)q * nv + a) * ns + (long)q * nv + a].x;
-      for (int j = 0; j < no; ++j) v -= Sv[((long)q * no + j) * (nv + 1) + nv];
+      for (int a = tid; a < nv; a += 256) v -= gam[((long)q * nv + a) * ns + (long)q * nv + a].x;
+      for (int j = tid; j < no; j += 256) v -= Sv[((long)q * no + j) * (nv + 1) + nv];
     } else {
       const int j = q - nc;
-      for (int I = 0; I < nc; ++I) v -= Sv[((long)I * no + j) * (nv + 1) + nv];
+      for (int I = tid; I < nc; I += 256) v -= Sv[((long)I * no + j) * (nv + 1) + nv];
     }
     double hp = 0.0;
     for (int l = 0; l < o; ++l) {
       if (l == q) continue;
       const long p = q < l ? pair_id(q, l, o) : pair_id(l, q, o);
-      for (int a = 0; a < nv; ++a) hp += hr[p * nv + a];
+      for (int a = tid; a < nv; a += 256) hp += hr[p * nv + a];
     }
     v -= 0.5 * hp;
   }
-  deps[q] = v;
+  red[tid] = v;
+  __syncthreads();
+  for (int s = 128; s > 0; s >>= 1) {
+    if (tid < s) red[tid] += red[tid + s];
+    __syncthreads();
+  }
+  if (tid == 0) deps[q] = red[0];
 }
 
 // dL[P][p][q] = 1/2 (g[p][q] + conj(g[q][p])) with g assembled from the blocks
@@ -871,19 +880,22 @@ __global__ __launch_bounds__(256) void k_dl_assemble(const double2* __restrict__
   }
 }
 
-// per-vector norms |x_k|^2 (one workgroup per vector)
-__global__ __launch_bounds__(256) void k_vnorm2(const double2* __restrict__ x, long dim, double* __restrict__ out) {
+// per-vector norms |x_k|^2, VN slices a vector (HBM-bound; one workgroup a
+// vector read at 28 GB/s: 11.2 ms for six vectors of 6.5 M entries)
+constexpr int VN = 256;
+__global__ __launch_bounds__(256) void k_vnorm2(const double2* __restrict__ x, long dim, double* __restrict__ part) {
   __shared__ double red[256];
-  const double2* v = x + (long)blockIdx.x * dim;
+  const double2* v = x + (long)blockIdx.y * dim;
+  const long per = (dim + VN - 1) / VN, e0 = blockIdx.x * per, e1 = min(dim, e0 + per);
   double s = 0.0;
-  for (long e = threadIdx.x; e < dim; e += 256) s += v[e].x * v[e].x + v[e].y * v[e].y;
+  for (long e = e0 + threadIdx.x; e < e1; e += 256) s += v[e].x * v[e].x + v[e].y * v[e].y;
   red[threadIdx.x] = s;
   __syncthreads();
   for (int st = 128; st > 0; st >>= 1) {
     if (threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[blockIdx.x] = red[0];
+  if (threadIdx.x == 0) part[(long)blockIdx.y * VN + blockIdx.x] = red[0];
 }
 
 // ---------------------------------------------------------------------------
@@ -940,13 +952,14 @@ adc2_status omega_backward(adc2_handle h, int m, const double2* X, const double*
   // weights w_k = g_k / |x_k|^2
   double *wts = nullptr, *nrm = nullptr;
   BW_TRY(alloc((void**)&wts, sizeof(double) * m));
-  BW_TRY(alloc((void**)&nrm, sizeof(double) * m));
-  k_vnorm2<<<m, 256, 0, st>>>(X, dim, nrm);
+  BW_TRY(alloc((void**)&nrm, sizeof(double) * m * VN));
+  k_vnorm2<<<dim3(VN, m), 256, 0, st>>>(X, dim, nrm);
   BW_HIP(hipGetLastError());
-  std::vector<double> hn(m), hw(m);
-  BW_HIP(hipMemcpyAsync(hn.data(), nrm, sizeof(double) * m, hipMemcpyDeviceToHost, st));
+  std::vector<double> hn(m, 0.0), hw(m), hp((size_t)m * VN);
+  BW_HIP(hipMemcpyAsync(hp.data(), nrm, sizeof(double) * m * VN, hipMemcpyDeviceToHost, st));
   BW_HIP(hipStreamSynchronize(st));
   for (int k = 0; k < m; ++k) {
+    for (int q = 0; q < VN; ++q) hn[k] += hp[(size_t)k * VN + q];
     if (!(hn[k] > 0.0) || !std::isfinite(hn[k])) {
       release();
       set_error("adc2_omega_backward: a vector has zero or non-finite norm");
@@ -991,7 +1004,10 @@ adc2_status omega_backward(adc2_handle h, int m, const double2* X, const double*
   // ---- coupling ----
   // weighted unpacks, Y-build
   BW_TRY(unpack_weighted(h, m, X, wts, st));
-  BW_TRY(ybuild_fp64(h, m, st));
+  bool done = false;
+  BW_TRY(rns_product(h, rns_kmajor(h->LvT, naux, no * nv), naux, rns_kmajor(h->Zb, (long)m * nc * nv, no * nv), m * nc * nv,
+                     no * nv, RnsDst{h->Y, 1 << 30, 0, nv, nv, (long)naux * nv, 1, 1.0, false}, RNS_VS_BIG, &done, st));
+  if (!done) BW_TRY(ybuild_fp64(h, m, st));
   const long ldrt = (long)m * nc * nv;
   // T[I][j][K][a]
   BW_TRY(fgemm(nv, nc, m * nv, nc * no, SrcRtc{h->Zb, ldrt, nc, nv, no}, SrcR1kb{X, dim, nv}, EpT{T, nc, nv}, S,
@@ -1021,21 +1037,25 @@ adc2_status omega_backward(adc2_handle h, int m, const double2* X, const double*
     k_unpack_rows<<<(unsigned)((long)m * nc * no * (nb * (nb + 1) / 2)), 256, 0, st>>>(X, dim, nc, no, nv, wts, Rn);
     BW_HIP(hipGetLastError());
     const int M = naux, N = no * nv;
-    const long tiles = (long)cdv(M, BT) * cdv(N, BT);
-    const int nsplit = (int)std::max<long>(1, std::min<long>(8, (512 + tiles - 1) / tiles));
-    BW_TRY(alloc((void**)&C, sizeof(double2) * nsplit * (long)M * N));
-    SrcGroupedK<8> A{XT, 0, naux, naux, naux, (int)K};
-    SrcGroupedK<8> B{Rn, 0, (long)N, N, N, (int)K};
-    k_bgemm<<<dim3((unsigned)tiles, nsplit), 256, 0, st>>>(A, B, M, N, (int)K, C);
-    BW_HIP(hipGetLastError());
-    k_scatter_add<<<grid1((long)M * N), 256, 0, st>>>(C, nsplit, M, N, nv, (long)naux * nv, nv, 2.0,
-                                                      hvo + (long)nc * naux * nv);
-    BW_HIP(hipGetLastError());
+    BW_TRY(rns_product(h, rns_kmajor(XT, naux, (int)K), M, rns_kmajor(Rn, N, (int)K), N, (int)K,
+                       RnsDst{hvo + (long)nc * naux * nv, 1 << 30, 0, nv, nv, (long)naux * nv, 1, 2.0, true}, RNS_VS_BIG, &done, st));
+    if (!done) {
+      const long tiles = (long)cdv(M, BT) * cdv(N, BT);
+      const int nsplit = (int)std::max<long>(1, std::min<long>(8, (512 + tiles - 1) / tiles));
+      BW_TRY(alloc((void**)&C, sizeof(double2) * nsplit * (long)M * N));
+      SrcGroupedK<8> A{XT, 0, naux, naux, naux, (int)K};
+      SrcGroupedK<8> B{Rn, 0, (long)N, N, N, (int)K};
+      k_bgemm<<<dim3((unsigned)tiles, nsplit), 256, 0, st>>>(A, B, M, N, (int)K, C);
+      BW_HIP(hipGetLastError());
+      k_scatter_add<<<grid1((long)M * N), 256, 0, st>>>(C, nsplit, M, N, nv, (long)naux * nv, nv, 2.0,
+                                                        hvo + (long)nc * naux * nv);
+      BW_HIP(hipGetLastError());
+    }
     BW_HIP(hipStreamSynchronize(st));
     dfree(h, Rn);
     dfree(h, C);
     owned.erase(std::remove(owned.begin(), owned.end(), (void*)Rn), owned.end());
-    owned.erase(std::remove(owned.begin(), owned.end(), (void*)C), owned.end());
+    if (C) owned.erase(std::remove(owned.begin(), owned.end(), (void*)C), owned.end());
   }
 
   // ---- second order (W) ----
@@ -1065,19 +1085,23 @@ adc2_status omega_backward(adc2_handle h, int m, const double2* X, const double*
     owned.erase(std::remove(owned.begin(), owned.end(), (void*)PQ), owned.end());
     // hvo[k][P][a] += 8 sum_{(l,c)} LoT[(l,c)][P] Ef[k][l][c][a]
     const int M = naux, N = o * nv, K = o * nv;
-    const long tiles = (long)cdv(M, BT) * cdv(N, BT);
-    const int nsplit = (int)std::max<long>(1, std::min<long>(8, (512 + tiles - 1) / tiles));
-    BW_TRY(alloc((void**)&C, sizeof(double2) * nsplit * (long)M * N));
-    SrcGroupedK<8> A{h->LoT, 0, naux, naux, naux, K};
-    SrcGroupedK<8> B{Ef, (long)o * nv2, nv, nv, N, K};
-    k_bgemm<<<dim3((unsigned)tiles, nsplit), 256, 0, st>>>(A, B, M, N, K, C);
-    BW_HIP(hipGetLastError());
-    k_scatter_add<<<grid1((long)M * N), 256, 0, st>>>(C, nsplit, M, N, nv, (long)naux * nv, nv, 8.0, hvo);
-    BW_HIP(hipGetLastError());
+    BW_TRY(rns_product(h, rns_kmajor(h->LoT, naux, K), M, RnsSrc{Ef, nv, (long)o * nv2, 1, 1 << 30, 0, nv, false}, N, K,
+                       RnsDst{hvo, 1 << 30, 0, nv, nv, (long)naux * nv, 1, 8.0, true}, RNS_VS_BIG, &done, st));
+    if (!done) {
+      const long tiles = (long)cdv(M, BT) * cdv(N, BT);
+      const int nsplit = (int)std::max<long>(1, std::min<long>(8, (512 + tiles - 1) / tiles));
+      BW_TRY(alloc((void**)&C, sizeof(double2) * nsplit * (long)M * N));
+      SrcGroupedK<8> A{h->LoT, 0, naux, naux, naux, K};
+      SrcGroupedK<8> B{Ef, (long)o * nv2, nv, nv, N, K};
+      k_bgemm<<<dim3((unsigned)tiles, nsplit), 256, 0, st>>>(A, B, M, N, K, C);
+      BW_HIP(hipGetLastError());
+      k_scatter_add<<<grid1((long)M * N), 256, 0, st>>>(C, nsplit, M, N, nv, (long)naux * nv, nv, 8.0, hvo);
+      BW_HIP(hipGetLastError());
+    }
     // eps
     k_rho<<<nc * no, 256, sizeof(double) * 5 * nv, st>>>(X, dim, m, nc, no, nv, wts, Sv);
     BW_HIP(hipGetLastError());
-    k_eps_final<<<cdv(d.n, 128), 128, 0, st>>>(gam, Sv, hr, nc, no, nv, deps);
+    k_eps_final<<<d.n, 256, 0, st>>>(gam, Sv, hr, nc, no, nv, deps);
     BW_HIP(hipGetLastError());
   }
 

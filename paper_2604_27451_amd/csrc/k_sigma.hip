@@ -1187,7 +1187,6 @@ adc2_status ensure_ws(adc2_handle h, int m, bool zb) {
 // operand or product (32 B), and the other, smaller, in residues.
 // ---------------------------------------------------------------------------
 constexpr size_t NOALLOC_SCRATCH_BYTES = size_t(128) << 20;   // adc2_sigma_noalloc's work space
-constexpr size_t RNS_CHUNK_BYTES = size_t(3) << 30;           // target of a chunk's work space
 
 // Which requests take it: those whose work spaces are past the reach of
 // adc2_sigma_noalloc (which runs the MFMA engines, and gives adc2_sigma's
@@ -1230,17 +1229,14 @@ static RnsPlan rns_plan(adc2_handle h, int rows) {
     return p;
   };
   const double one = (double)at(1).bytes;
-  const int most = (int)std::max(1.0, std::min((double)rows, std::floor((double)RNS_CHUNK_BYTES / one)));
+  const int most = (int)std::max(1.0, std::min((double)rows, std::floor((double)h->rns_target / one)));
   return at(cdiv(rows, cdiv(rows, most)));   // equal chunks
 }
 
-void rns_release(adc2_handle h) {
-  char *a = h->rns_lvo, *b = h->rns_lvt, *c = h->rns_ws;
-  h->rns_lvo = h->rns_lvt = h->rns_ws = nullptr;
-  h->rns_ws_bytes = 0;
-  dfree(h, a);
-  dfree(h, b);
-  dfree(h, c);
+// Valence rows of Lvo as an operand: rows (j, b), K = P.
+static RnsSrc rns_lvo_rows(adc2_handle h) {
+  const Dims& d = h->d;
+  return RnsSrc{h->Lvo + (long)d.nc * d.naux * d.nv, d.nv, (long)d.naux * d.nv, 1, 1 << 30, 0, d.nv, false};
 }
 
 // The residue engine's buffers for m vectors; false (and the MFMA engines from
@@ -1252,15 +1248,9 @@ static adc2_status rns_ready(adc2_handle h, int m, hipStream_t st, bool* ok) {
   const RnsPlan p = rns_plan(h, m * d.nc);
   const bool fresh = !h->rns_lvo || !h->rns_lvt;
   const size_t wneed = std::max(p.bytes, fresh ? std::max(rns_norm_bytes(ky), rns_norm_bytes(d.naux)) : size_t(0));
+  if (!rns_reserve(h, wneed)) return ADC2_OK;
   hipError_t e = hipSuccess;
-  if (h->rns_ws_bytes < wneed) {
-    dfree(h, h->rns_ws);
-    h->rns_ws = nullptr;
-    h->rns_ws_bytes = 0;
-    e = dmalloc(h, &h->rns_ws, wneed);
-    if (e == hipSuccess) h->rns_ws_bytes = wneed;
-  }
-  if (e == hipSuccess && fresh && !h->rns_off) {
+  if (fresh) {
     e = dmalloc(h, &h->rns_lvo, rns_op_bytes(ky, d.naux) + rns_exp_bytes(ky));
     if (e == hipSuccess && !h->rns_off) e = dmalloc(h, &h->rns_lvt, rns_op_bytes(d.naux, ky) + rns_exp_bytes(d.naux));
   }
@@ -1273,11 +1263,9 @@ static adc2_status rns_ready(adc2_handle h, int m, hipStream_t st, bool* ok) {
   if (fresh) {
     RnsMat t;
     double* norm = (double*)h->rns_ws;
-    adc2_status rc = rns_pack(h->Lvo + (long)d.nc * d.naux * d.nv, (long)d.naux * d.nv, d.nv, d.nv, (int)ky, d.naux,
-                              false, (int8_t*)h->rns_lvo, (int*)(h->rns_lvo + rns_op_bytes(ky, d.naux)), norm, &t, st);
+    adc2_status rc = rns_pack(rns_lvo_rows(h), (int)ky, d.naux, (int8_t*)h->rns_lvo, (int*)(h->rns_lvo + rns_op_bytes(ky, d.naux)), norm, &t, st);
     if (rc == ADC2_OK)
-      rc = rns_pack(h->LvT, 0, d.naux, d.naux, d.naux, (int)ky, false, (int8_t*)h->rns_lvt,
-                    (int*)(h->rns_lvt + rns_op_bytes(d.naux, ky)), norm, &t, st);
+      rc = rns_pack(rns_kmajor(h->LvT, d.naux, (int)ky), d.naux, (int)ky, (int8_t*)h->rns_lvt, (int*)(h->rns_lvt + rns_op_bytes(d.naux, ky)), norm, &t, st);
     if (rc != ADC2_OK) {
       rns_release(h);
       return rc;
@@ -1365,10 +1353,12 @@ static adc2_status rns_doubles_in(adc2_handle h, const SigReq& rq, RnsProf& pf, 
     rc = pf.run(1, [&]() -> adc2_status {
       RnsMat B;
       const int ncol = c * d.nv;
-      adc2_status r = rns_pack(R, 0, ncol, ncol, ncol, K, false, (int8_t*)(h->rns_ws + p.opnd), (int*)(h->rns_ws + p.ex),
+      adc2_status r = rns_pack(rns_kmajor(R, ncol, K), ncol, K, (int8_t*)(h->rns_ws + p.opnd), (int*)(h->rns_ws + p.ex),
                                (double*)(h->rns_ws + p.norm), &B, st);
-      if (r == ADC2_OK) r = rns_gemm(L, B, 0, ncol, out, st);
-      if (r == ADC2_OK) r = rns_to_y(L, B, out, d.naux, d.nv, h->Y + (long)r0 * d.naux * d.nv, st);
+      if (r == ADC2_OK) r = rns_gemm(L, B, 0, ncol, 1, out, st);
+      // Y[mI][P][c], columns (mI, c)
+      const RnsDst y{h->Y + (long)r0 * d.naux * d.nv, 1 << 30, 0, d.nv, d.nv, (long)d.naux * d.nv, 1, 1.0, false};
+      if (r == ADC2_OK) r = rns_join(L, B, 0, ncol, 1, out, y, st);
       return r;
     });
     if (rc != ADC2_OK) return rc;
@@ -1389,11 +1379,13 @@ static adc2_status rns_singles_in(adc2_handle h, const SigReq& rq, int with_d, R
     const int c = std::min(p.c, rows - r0);
     adc2_status rc = pf.run(4, [&]() -> adc2_status {
       RnsMat A;
-      adc2_status r = rns_pack(h->X + (long)r0 * d.naux * d.nv, (long)d.naux * d.nv, d.nv, d.nv, c * d.nv, d.naux, false,
-                               (int8_t*)(h->rns_ws + p.opnd), (int*)(h->rns_ws + p.ex), (double*)(h->rns_ws + p.norm), &A,
-                               st);
-      if (r == ADC2_OK) r = rns_gemm(A, L, 0, N, out, st);
-      if (r == ADC2_OK) r = rns_to_z(A, L, out, d.no, d.nv, Z, st);
+      const RnsSrc x{h->X + (long)r0 * d.naux * d.nv, d.nv, (long)d.naux * d.nv, 1, 1 << 30, 0, d.nv, false};
+      adc2_status r = rns_pack(x, c * d.nv, d.naux, (int8_t*)(h->rns_ws + p.opnd), (int*)(h->rns_ws + p.ex),
+                               (double*)(h->rns_ws + p.norm), &A, st);
+      if (r == ADC2_OK) r = rns_gemm(A, L, 0, N, 1, out, st);
+      // Z[mI][j][a][b], rows (mI, a), columns (j, b)
+      const RnsDst z{Z, d.nv, (long)d.no * d.nv * d.nv, d.nv, d.nv, (long)d.nv * d.nv, 1, 1.0, false};
+      if (r == ADC2_OK) r = rns_join(A, L, 0, N, 1, out, z, st);
       return r;
     });
     if (rc != ADC2_OK) return rc;

@@ -57,30 +57,79 @@ struct RnsMat {
 };
 constexpr int RNS_NAN = 1 << 20;
 
+constexpr int RNS_SPLITS = 32;          // most K-splits of a product
+
 size_t rns_op_bytes(long rows, long K);                 // planes of an operand
 size_t rns_exp_bytes(long rows);                        // its exponents
 size_t rns_norm_bytes(long rows);                       // work space of rns_pack
-size_t rns_out_bytes(long rows, long cols);             // planes of a product
+size_t rns_out_bytes(long rows, long cols);             // planes of a product (one K-split)
 
-// Residues of the K-major operand with element (k, row) at
-// src[(row / inner) * gstride + (row % inner) + k * ld]; conj negates the
-// imaginary parts.  buf, ebuf and nbuf hold the sizes above.
-adc2_status rns_pack(const double2* src, long gstride, long ld, int inner, int rows, int K, bool conj,
-                     int8_t* buf, int* ebuf, double* nbuf, RnsMat* out, hipStream_t st);
+// Element (row, k) of a strided complex128 operand, conjugated if conj:
+//   p[(r / ri) * rg + (r % ri) * rx + (k / ki) * kg + (k % ki) * kx],  r = r0 + row
+struct RnsSrc {
+  const double2* p;
+  int ri;
+  long rg, rx;
+  int ki;
+  long kg, kx;
+  bool conj;
+  int r0 = 0;
+};
+// rows x K with unit stride along the rows, k stride ld
+inline RnsSrc rns_kmajor(const double2* p, long ld, int K, bool conj = false) {
+  return RnsSrc{p, 1 << 30, 0, 1, 1 << 30, 0, ld, conj};
+}
+// rows x K with unit stride along k, row stride ld
+inline RnsSrc rns_rmajor(const double2* p, long ld, bool conj = false) {
+  return RnsSrc{p, 1 << 30, 0, ld, 1 << 30, 0, 1, conj};
+}
+// Where entry (i, j) of a product goes:
+//   C[(i' / ii) * ig + (i' % ii) * ix + (j' / ji) * jg + (j' % ji) * jx] = (or +=) alpha v,
+// i' = i0 + i, j' = j0 + j
+struct RnsDst {
+  double2* C;
+  int ii;
+  long ig, ix;
+  int ji;
+  long jg, jx;
+  double alpha;
+  bool add;
+  int i0 = 0, j0 = 0;
+};
+inline RnsDst rns_rows(double2* C, long ldc, double alpha = 1.0, bool add = false) {
+  return RnsDst{C, 1 << 30, 0, ldc, 1 << 30, 0, 1, alpha, add};
+}
 
-// out = residues of A^T B for the rows [col0, col0 + ncols) of B (col0 a
-// multiple of 128): plane q, 32 x 32 block (rb, cb) as a 1 KB run at
-// ((q * nrb + rb) * ncb + cb) * 1024, in MFMA register order.
-adc2_status rns_gemm(const RnsMat& A, const RnsMat& B, int col0, int ncols, int8_t* out, hipStream_t st);
-
-// The sigma build's two products out of those residues, rows x cols of out
-//   Z: rows (g, a), a < nv, columns (j, b), b < nv:  Z[((g * no + j) * nv + a) * nv + b]
-//   Y: rows P, columns (g, c):                        Y[(g * naux + P) * nv + c]
-adc2_status rns_to_z(const RnsMat& A, const RnsMat& B, const int8_t* out, int no, int nv, double2* Z, hipStream_t st);
-adc2_status rns_to_y(const RnsMat& A, const RnsMat& B, const int8_t* out, int naux, int nv, double2* Y,
+// Residues of an operand; buf, ebuf and nbuf hold the sizes above.
+adc2_status rns_pack(const RnsSrc& src, int rows, int K, int8_t* buf, int* ebuf, double* nbuf, RnsMat* out,
                      hipStream_t st);
-// Row-major C[i * ldc + j]
-adc2_status rns_to_rows(const RnsMat& A, const RnsMat& B, int col0, int ncols, const int8_t* out, double2* C, long ldc,
-                        hipStream_t st);
+
+// out = residues of the products of the rows of A with the rows [col0,
+// col0 + ncols) of B (col0 a multiple of 128) over nsplit runs of K: split s, plane
+// q, 32 x 32 block (rb, cb) as a 1 KB run at
+// (((s * RNS_PL + q) * nrb + rb) * ncb + cb) * 1024, in MFMA register order.
+adc2_status rns_gemm(const RnsMat& A, const RnsMat& B, int col0, int ncols, int nsplit, int8_t* out, hipStream_t st);
+// The products themselves out of those residues.
+adc2_status rns_join(const RnsMat& A, const RnsMat& B, int col0, int ncols, int nsplit, const int8_t* out,
+                     const RnsDst& dst, hipStream_t st);
+
+// dst(i, j) = sum_k A(i, k) B(j, k), i < M, j < N, in chunks of rows whose work
+// space is at most 2 h->rns_target (or that of one 256 x 128 tile).  *done = false (nothing written, no error)
+// where the caller's own FP64 MFMA kernel, of `rate` flop/s at such sizes, is the
+// faster one or the memory is not to be had: the caller then uses that.
+constexpr double RNS_VS_BIG = 60e12;    // 128 x 128 tiles (k_bgemm)
+// 64 x 64 tiles (gemm_rr): 25 TFLOP/s from two tiles a CU on, in proportion
+// below (0.32 measured on 4 tiles)
+inline double rns_vs_tile(long M, long N) {
+  const double tiles = (double)((M + 63) / 64) * ((N + 63) / 64);
+  return 25e12 * (tiles < 512.0 ? tiles / 512.0 : 1.0);
+}
+adc2_status rns_product(adc2_handle h, const RnsSrc& A, int M, const RnsSrc& B, int N, int K, const RnsDst& dst,
+                        double rate, bool* done, hipStream_t st);
+// The size rule of rns_product
+bool rns_pays(adc2_handle h, long M, long N, long K, double rate);
+// At least `bytes` of the handle's work space, contents undefined; false where
+// it is not to be had.
+bool rns_reserve(adc2_handle h, size_t bytes);
 
 }  // namespace adc2

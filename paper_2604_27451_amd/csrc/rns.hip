@@ -46,7 +46,7 @@ struct RnsSplit {
 //   re / M = sum (u_1 kre1 + u_2 kre2) / (p1 p2) mod 1,  im / M the same with w, kim.
 struct RnsJoin {
   int kre1, kre2, kim1, kim2;
-  double hi, lo;       // 1 / (p1 p2) = hi + lo, hi a multiple of 2^-38
+  double hi, lo;       // 1 / (p1 p2) = hi + lo, hi a multiple of 2^-34
 };
 struct RnsConst {
   RnsSplit split[RNS_NM];
@@ -83,7 +83,7 @@ constexpr RnsConst make_const() {
       kim[h] = balanced(ti * inverse(2 * s, p), p);
     }
     const int p1 = RNS_P[2 * t], p2 = RNS_P[2 * t + 1];
-    const long pp = (long)p1 * p2, one = 1L << 38;
+    const long pp = (long)p1 * p2, one = 1L << 34;
     const long n = (one + pp / 2) / pp;
     c.join[t].kre1 = kre[0] * p2;
     c.join[t].kre2 = kre[1] * p1;
@@ -118,51 +118,83 @@ size_t rns_out_bytes(long rows, long cols) { return (size_t)RNS_PL * rcdiv(rows,
 // ---------------------------------------------------------------------------
 // row exponents
 // ---------------------------------------------------------------------------
-// Partial sums of squares of the rows, lane = row (coalesced), K split over
-// blockIdx.y.  Three sums, of x, 2^-540 x and 2^540 x, so that no row of
-// finite entries overflows or underflows.  HBM-bound (one read of the operand).
-__global__ __launch_bounds__(256) void k_rns_norm(const double2* __restrict__ src, long gstride, long ld, int inner,
-                                                   int rows, int K, double* __restrict__ part) {
+__device__ __forceinline__ long rns_row(const RnsSrc& s, int row) {
+  row += s.r0;
+  const int g = row / s.ri;
+  return (long)g * s.rg + (long)(row - g * s.ri) * s.rx;
+}
+__device__ __forceinline__ long rns_k(const RnsSrc& s, int k) {
+  const int g = k / s.ki;
+  return (long)g * s.kg + (long)(k - g * s.ki) * s.kx;
+}
+
+// Three sums of squares, of x, 2^-540 x and 2^540 x, so that no row of finite
+// entries overflows or underflows.
+struct RnsSums {
+  double s[3];
+  __device__ __forceinline__ void add(double x) {
+    const double b = x * 0x1p-540, t = x * 0x1p540;
+    s[0] = fma(x, x, s[0]);
+    s[1] = fma(b, b, s[1]);
+    s[2] = fma(t, t, s[2]);
+  }
+};
+
+// Partial sums of squares of the rows, K split over blockIdx.y.  HBM-bound (one
+// read of the operand): lane = row where rows are contiguous, a wave per row
+// where k is.
+__global__ __launch_bounds__(256) void k_rns_norm(const RnsSrc src, int rows, int K, double* __restrict__ part) {
   __shared__ double red[4][3][64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int row = blockIdx.x * 64 + lane;
   const bool ok = row < rows;
-  const int rr = ok ? row : 0;
-  const int g = rr / inner;
-  const double2* p = src + (long)g * gstride + (rr - g * inner);
+  const double2* p = src.p + rns_row(src, ok ? row : 0);
   const int per = (K + gridDim.y - 1) / gridDim.y;
   const int k0 = blockIdx.y * per, k1 = min(K, k0 + per);
-  const double big = 0x1p-540, small = 0x1p540;
-  double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-  auto add = [&](double x) {
-    s0 = fma(x, x, s0);
-    const double b = x * big, t = x * small;
-    s1 = fma(b, b, s1);
-    s2 = fma(t, t, s2);
-  };
+  RnsSums t{{0.0, 0.0, 0.0}};
   int k = k0 + w;
   for (; k + 12 < k1; k += 16) {
     double2 v[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = p[(long)(k + 4 * u) * ld];
+    for (int u = 0; u < 4; ++u) v[u] = p[rns_k(src, k + 4 * u)];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      add(v[u].x);
-      add(v[u].y);
+      t.add(v[u].x);
+      t.add(v[u].y);
     }
   }
   for (; k < k1; k += 4) {
-    const double2 v = p[(long)k * ld];
-    add(v.x);
-    add(v.y);
+    const double2 v = p[rns_k(src, k)];
+    t.add(v.x);
+    t.add(v.y);
   }
-  red[w][0][lane] = s0;
-  red[w][1][lane] = s1;
-  red[w][2][lane] = s2;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) red[w][q][lane] = t.s[q];
   __syncthreads();
   if (w < 3 && ok) {
-    const double t = (red[0][w][lane] + red[1][w][lane]) + (red[2][w][lane] + red[3][w][lane]);
-    part[((long)blockIdx.y * 3 + w) * rows + row] = t;
+    const double v = (red[0][w][lane] + red[1][w][lane]) + (red[2][w][lane] + red[3][w][lane]);
+    part[((long)blockIdx.y * 3 + w) * rows + row] = v;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_rns_norm_k(const RnsSrc src, int rows, int K, double* __restrict__ part) {
+  const int lane = threadIdx.x & 63;
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= rows) return;
+  const double2* p = src.p + rns_row(src, row);
+  const int per = (K + gridDim.y - 1) / gridDim.y;
+  const int k0 = blockIdx.y * per, k1 = min(K, k0 + per);
+  RnsSums t{{0.0, 0.0, 0.0}};
+  for (int k = k0 + lane; k < k1; k += 64) {
+    const double2 v = p[rns_k(src, k)];
+    t.add(v.x);
+    t.add(v.y);
+  }
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    double v = t.s[q];
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    if (lane == 0) part[((long)blockIdx.y * 3 + q) * rows + row] = v;
   }
 }
 
@@ -193,10 +225,13 @@ __global__ void k_rns_expo(const double* __restrict__ part, int nsplit, int rows
 // integers, splits these into signed bytes once, and forms both residues for
 // each modulus from four 4-byte dot products and a float reduction; the 16
 // bytes of a plane are one store, so a wave writes 1 KB runs.  Bound by its
-// vector instructions (about 250 per entry) and its 32-byte writes per entry.
+// vector instructions (about 250 per entry) and its 32-byte writes per entry:
+// 0.29 ms for the 27 M entries of a 18000 x 1500 operand, 4 TB/s.  Operands
+// contiguous along k go through LDS, so that both their reads and the writes
+// are whole lines.
 constexpr int RNS_MAGIC = 0x4B400000;   // 1.5 * 2^23 as a float: float(MAGIC + x) = 1.5 * 2^23 + x
-__global__ __launch_bounds__(256) void k_rns_pack(const double2* __restrict__ src, long gstride, long ld, int inner,
-                                                   int rows, int K, double cs, const int* __restrict__ e, int nrt,
+template <bool KLANE>
+__global__ __launch_bounds__(256) void k_rns_pack(const RnsSrc src, int rows, int K, const int* __restrict__ e, int nrt,
                                                    int nkc, int8_t* __restrict__ dst) {
   const int lane = threadIdx.x & 63, kg = threadIdx.x >> 6;
   const int rb = blockIdx.x % (2 * nrt), kc = blockIdx.x / (2 * nrt);
@@ -204,20 +239,44 @@ __global__ __launch_bounds__(256) void k_rns_pack(const double2* __restrict__ sr
   const int k0 = kc * RNS_KC + kg * 16;
   i4v d[16];   // re lo, re hi, im lo, im hi
   const bool ok = row < rows;
-  const int rr = ok ? row : 0;
-  const int g = rr / inner;
-  const double2* p = src + (long)g * gstride + (rr - g * inner);
-  int ex = e[rr];
-  if (ex == RNS_NAN) ex = 0;
+  if constexpr (KLANE) {
+    __shared__ double2 t[64][65];
+    const int k = kc * RNS_KC + lane;
+    const double2* p = src.p + (k < K ? rns_k(src, k) : 0);
+#pragma unroll 4
+    for (int r = 0; r < 16; ++r) {
+      const int rr = rb * 64 + kg * 16 + r;
+      t[kg * 16 + r][lane] = (rr < rows && k < K) ? p[rns_row(src, rr)] : make_double2(0.0, 0.0);
+    }
+    __syncthreads();
 #pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    double2 v = make_double2(0.0, 0.0);
-    if (ok && k0 + u < K) v = p[(long)(k0 + u) * ld];
-    d[u].x = __double2loint(v.x);
-    d[u].y = __double2hiint(v.x);
-    d[u].z = __double2loint(v.y);
-    d[u].w = __double2hiint(v.y);
+    for (int u = 0; u < 16; ++u) {
+      const double2 v = t[lane][kg * 16 + u];
+      d[u].x = __double2loint(v.x);
+      d[u].y = __double2hiint(v.x);
+      d[u].z = __double2loint(v.y);
+      d[u].w = __double2hiint(v.y);
+    }
+  } else {
+    const double2* p = src.p + rns_row(src, ok ? row : 0);
+    int q = k0 / src.ki, r = k0 - q * src.ki;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      double2 v = make_double2(0.0, 0.0);
+      if (ok && k0 + u < K) v = p[(long)q * src.kg + (long)r * src.kx];
+      if (++r == src.ki) {
+        r = 0;
+        ++q;
+      }
+      d[u].x = __double2loint(v.x);
+      d[u].y = __double2hiint(v.x);
+      d[u].z = __double2loint(v.y);
+      d[u].w = __double2hiint(v.y);
+    }
   }
+  const double cs = src.conj ? -1.0 : 1.0;
+  int ex = e[ok ? row : 0];
+  if (ex == RNS_NAN) ex = 0;
   auto digits = [&](double x, int& lo, int& hi) {
     x = rint(ldexp(x, ex));
     // x = h 2^32 + l, |x| < 2^59: exact
@@ -268,24 +327,27 @@ __global__ __launch_bounds__(256) void k_rns_pack(const double2* __restrict__ sr
   }
 }
 
-adc2_status rns_pack(const double2* src, long gstride, long ld, int inner, int rows, int K, bool conj, int8_t* buf,
-                     int* ebuf, double* nbuf, RnsMat* out, hipStream_t st) {
+adc2_status rns_pack(const RnsSrc& src, int rows, int K, int8_t* buf, int* ebuf, double* nbuf, RnsMat* out,
+                     hipStream_t st) {
   out->p = buf;
   out->e = ebuf;
   out->rows = rows;
   out->K = K;
   out->nrt = rcdiv(rows, RNS_RT);
   out->nkc = rcdiv(K, RNS_KC);
-  const int nrow64 = rcdiv(rows, 64);
-  // enough blocks to fill the chip, at least 16 k a block
-  const int ns = std::max(1, std::min({NORM_SPLIT, rcdiv(4096, nrow64), rcdiv(K, 16)}));
-  k_rns_norm<<<dim3((unsigned)nrow64, (unsigned)ns), 256, 0, st>>>(src, gstride, ld, inner, rows, K, nbuf);
+  const bool klane = src.rx != 1 && src.kx == 1;
+  // enough blocks to fill the chip, at least 16 (64) k a block
+  const int nrow = rcdiv(rows, klane ? 4 : 64);
+  const int ns = std::max(1, std::min({NORM_SPLIT, rcdiv(4096, nrow), rcdiv(K, klane ? 64 : 16)}));
+  if (klane) k_rns_norm_k<<<dim3((unsigned)nrow, (unsigned)ns), 256, 0, st>>>(src, rows, K, nbuf);
+  else k_rns_norm<<<dim3((unsigned)nrow, (unsigned)ns), 256, 0, st>>>(src, rows, K, nbuf);
   ADC2_CHECK_LAUNCH();
   const int padded = out->nrt * RNS_RT;
   k_rns_expo<<<rcdiv(padded, 256), 256, 0, st>>>(nbuf, ns, rows, padded, ebuf);
   ADC2_CHECK_LAUNCH();
-  k_rns_pack<<<(unsigned)((long)2 * out->nrt * out->nkc), 256, 0, st>>>(src, gstride, ld, inner, rows, K,
-                                                                       conj ? -1.0 : 1.0, ebuf, out->nrt, out->nkc, buf);
+  const unsigned nblk = (unsigned)((long)2 * out->nrt * out->nkc);
+  if (klane) k_rns_pack<true><<<nblk, 256, 0, st>>>(src, rows, K, ebuf, out->nrt, out->nkc, buf);
+  else k_rns_pack<false><<<nblk, 256, 0, st>>>(src, rows, K, ebuf, out->nrt, out->nkc, buf);
   ADC2_CHECK_LAUNCH();
   return ADC2_OK;
 }
@@ -299,8 +361,8 @@ adc2_status rns_pack(const double2* src, long gstride, long ld, int inner, int r
 // LDS image), NB - 1 chunks ahead; one barrier a chunk.
 template <int WM, int WN, int NB>
 __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm(
-    const int8_t* __restrict__ A, const int8_t* __restrict__ B, int nrtA, int nrtB, int brt0, int nkc, int nbm, int nbn,
-    int nrb, int ncb, int8_t* __restrict__ C) {
+    const int8_t* __restrict__ A, const int8_t* __restrict__ B, int nrtA, int nrtB, int brt0, int nkca, int nkcs, int nbm,
+    int nbn, int nrb, int ncb, int8_t* __restrict__ C) {
   constexpr int BM = 128 * WM, BN = 64 * WN, T = 64 * WM * WN;
   constexpr int SB = (BM + BN) * RNS_KC, NL = SB / (T * 16), NLA = BM * RNS_KC / (T * 16);
   __shared__ __align__(16) int8_t s[NB][SB];
@@ -308,8 +370,10 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm
   // planes in order, so that each XCD works on the tiles of few planes; tiles
   // in groups of 8 row panels
   const long lid = xcd_remap(blockIdx.x, gridDim.x);
-  const int pl = (int)(lid / nt);
-  const int t0 = (int)(lid - (long)pl * nt);
+  const int sp = (int)(lid / nt);                     // K-split * RNS_PL + plane
+  const int t0 = (int)(lid - (long)sp * nt);
+  const int pl = sp % RNS_PL, kc0 = sp / RNS_PL * nkcs;
+  const int nkc = min(nkcs, nkca - kc0);              // chunks of this split
   const int per = 8 * nbn, grp = t0 / per, gm = min(8, nbm - grp * 8), r = t0 - grp * per;
   const int bm = grp * 8 + r % gm, bn = r / gm;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -320,11 +384,11 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm
     const int off = (q * T + tid) * 16;
     if (q < NLA) {
       const int rt = min(bm * (BM / RNS_RT) + (off >> 13), nrtA - 1);   // past the end: discarded rows
-      src[q] = A + ((long)pl * nrtA + rt) * nkc * RNS_BLK + (off & (RNS_BLK - 1));
+      src[q] = A + (((long)pl * nrtA + rt) * nkca + kc0) * RNS_BLK + (off & (RNS_BLK - 1));
     } else {
       const int ob = off - BM * RNS_KC;
       const int rt = min(brt0 + bn * (BN / RNS_RT) + (ob >> 13), nrtB - 1);
-      src[q] = B + ((long)pl * nrtB + rt) * nkc * RNS_BLK + (ob & (RNS_BLK - 1));
+      src[q] = B + (((long)pl * nrtB + rt) * nkca + kc0) * RNS_BLK + (ob & (RNS_BLK - 1));
     }
   }
   auto load = [&](int t) {
@@ -404,15 +468,15 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm
                                           __builtin_amdgcn_perm(rr[1], rr[0], 0x0c0c0400), 0x05040100);
       }
       const int rb = (bm * BM + wm * 128) / 32 + i, cb = (bn * BN + wn * 64) / 32 + j;
-      if (rb < nrb && cb < ncb) *(i4v*)(C + (((long)pl * nrb + rb) * ncb + cb) * 1024 + lane * 16) = o;
+      if (rb < nrb && cb < ncb) *(i4v*)(C + (((long)sp * nrb + rb) * ncb + cb) * 1024 + lane * 16) = o;
     }
 }
 
-adc2_status rns_gemm(const RnsMat& A, const RnsMat& B, int col0, int ncols, int8_t* out, hipStream_t st) {
+adc2_status rns_gemm(const RnsMat& A, const RnsMat& B, int col0, int ncols, int nsplit, int8_t* out, hipStream_t st) {
   const int nrb = rcdiv(A.rows, 32), ncb = rcdiv(ncols, 32);
   const int nbm = rcdiv(A.rows, 256), nbn = rcdiv(ncols, 128);
-  k_rns_gemm<2, 2, 3><<<(unsigned)((long)RNS_PL * nbm * nbn), 256, 0, st>>>(
-      A.p, B.p, A.nrt, B.nrt, col0 / RNS_RT, A.nkc, nbm, nbn, nrb, ncb, out);
+  k_rns_gemm<2, 2, 3><<<(unsigned)((long)nsplit * RNS_PL * nbm * nbn), 256, 0, st>>>(
+      A.p, B.p, A.nrt, B.nrt, col0 / RNS_RT, A.nkc, rcdiv(A.nkc, nsplit), nbm, nbn, nrb, ncb, out);
   ADC2_CHECK_LAUNCH();
   return ADC2_OK;
 }
@@ -422,12 +486,14 @@ adc2_status rns_gemm(const RnsMat& A, const RnsMat& B, int col0, int ncols, int8
 // ---------------------------------------------------------------------------
 // A thread recombines 8 entries of one column (two runs of 4 rows): 32 loads
 // of 8 bytes, each a 512-byte run of the wave.  Per entry and pair of moduli
-// the two weighted residue sums are exact 24-bit integers; their multiples of
-// hi are summed exactly in FP64 and reduced modulo 1, those of lo added after.
-// Bound by the 32 bytes read and 16 written per entry.
-template <class ST>
+// the two weighted residue sums (over the K-splits, at most RNS_SPLITS) are
+// exact integers; their multiples of hi are summed exactly in FP64 and reduced
+// modulo 1, those of lo added after.  Bound by the 32 bytes read and 16 written
+// per entry.
+template <bool SPLIT>
 __global__ __launch_bounds__(256) void k_rns_join(const int8_t* __restrict__ R, int nrb, int ncb, int rows, int cols,
-                                                   const int* __restrict__ ea, const int* __restrict__ eb, ST store) {
+                                                   int nsplit, const int* __restrict__ ea, const int* __restrict__ eb,
+                                                   const RnsDst dst) {
   const int ncp = (ncb + 1) >> 1;
   const int rb = blockIdx.x / ncp;
   const int cb = 2 * (blockIdx.x % ncp) + (threadIdx.x >> 7);
@@ -442,17 +508,32 @@ __global__ __launch_bounds__(256) void k_rns_join(const int8_t* __restrict__ R, 
   for (int x = 0; x < 8; ++x) fr[x] = fi[x] = gr[x] = gi[x] = 0.0;
 #pragma unroll 2
   for (int t = 0; t < RNS_NM / 2; ++t) {
-    int2 v[4];
+    int u[4][8];   // residues c+, c- of the two moduli, summed over the splits
+    {
+      int2 v[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = *(const int2*)(src + (4 * t + q) * ps);
+      for (int q = 0; q < 4; ++q) v[q] = *(const int2*)(src + (4 * t + q) * ps);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int x = 0; x < 8; ++x) u[q][x] = (int)(int8_t)((x < 4 ? v[q].x : v[q].y) >> (8 * (x & 3)));
+    }
+    if constexpr (SPLIT) {
+      for (int s = 1; s < nsplit; ++s) {
+        int2 v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = *(const int2*)(src + ((long)s * RNS_PL + 4 * t + q) * ps);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int x = 0; x < 8; ++x) u[q][x] += (int)(int8_t)((x < 4 ? v[q].x : v[q].y) >> (8 * (x & 3)));
+      }
+    }
     const RnsJoin c = RNS_C.join[t];
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
-      int b[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) b[q] = (int)(int8_t)((x < 4 ? v[q].x : v[q].y) >> (8 * (x & 3)));
-      const int yr = __mul24(b[0] + b[1], c.kre1) + __mul24(b[2] + b[3], c.kre2);
-      const int yi = __mul24(b[0] - b[1], c.kim1) + __mul24(b[2] - b[3], c.kim2);
+      const int yr = __mul24(u[0][x] + u[1][x], c.kre1) + __mul24(u[2][x] + u[3][x], c.kre2);
+      const int yi = __mul24(u[0][x] - u[1][x], c.kim1) + __mul24(u[2][x] - u[3][x], c.kim2);
       const double dr = (double)yr, di = (double)yi;
       fr[x] = fma(dr, c.hi, fr[x]);
       gr[x] = fma(dr, c.lo, gr[x]);
@@ -463,7 +544,8 @@ __global__ __launch_bounds__(256) void k_rns_join(const int8_t* __restrict__ R, 
   if (col >= cols) return;
   const int ec = eb[col];
   constexpr double M = rns_m();
-  store.column(col);
+  const int jj = dst.j0 + col, cg = jj / dst.ji;
+  double2* pc = dst.C + (long)cg * dst.jg + (long)(jj - cg * dst.ji) * dst.jx;
 #pragma unroll
   for (int x = 0; x < 8; ++x) {
     const int row = row0 + (x >> 2) * 8 + (x & 3);
@@ -476,63 +558,119 @@ __global__ __launch_bounds__(256) void k_rns_join(const int8_t* __restrict__ R, 
       re = ldexp(re, -(er + ec));
       im = ldexp(im, -(er + ec));
     }
-    store.put(row, make_double2(re, im));
+    const int i = dst.i0 + row, rg = i / dst.ii;
+    double2* o = pc + (long)rg * dst.ig + (long)(i - rg * dst.ii) * dst.ix;
+    double2 v = make_double2(dst.alpha * re, dst.alpha * im);
+    if (dst.add) v = cadd(*o, v);
+    *o = v;
   }
 }
 
-struct StoreZ {
-  double2* Z;
-  int no, nv;
-  double2* p;
-  int b;
-  __device__ __forceinline__ void column(int col) {
-    const int j = col / nv;
-    b = col - j * nv;
-    p = Z + (long)j * nv * nv;
-  }
-  __device__ __forceinline__ void put(int row, double2 v) const {
-    const int g = row / nv, a = row - g * nv;
-    p[(long)g * no * nv * nv + (long)a * nv + b] = v;
-  }
-};
-
-struct StoreY {
-  double2* Y;
-  int naux, nv;
-  double2* p;
-  __device__ __forceinline__ void column(int col) {
-    const int g = col / nv;
-    p = Y + (long)g * naux * nv + (col - g * nv);
-  }
-  __device__ __forceinline__ void put(int row, double2 v) const { p[(long)row * nv] = v; }
-};
-
-struct StoreRows {
-  double2* C;
-  long ldc;
-  int c;
-  __device__ __forceinline__ void column(int col) { c = col; }
-  __device__ __forceinline__ void put(int row, double2 v) const { C[(long)row * ldc + c] = v; }
-};
-
-template <class ST>
-static adc2_status join(const RnsMat& A, const int* eb, int ncols, const int8_t* out, const ST& s, hipStream_t st) {
+adc2_status rns_join(const RnsMat& A, const RnsMat& B, int col0, int ncols, int nsplit, const int8_t* out,
+                     const RnsDst& dst, hipStream_t st) {
   const int nrb = rcdiv(A.rows, 32), ncb = rcdiv(ncols, 32);
-  k_rns_join<ST><<<(unsigned)((long)nrb * ((ncb + 1) / 2)), 256, 0, st>>>(out, nrb, ncb, A.rows, ncols, A.e, eb, s);
+  const unsigned nblk = (unsigned)((long)nrb * ((ncb + 1) / 2));
+  if (nsplit > 1) k_rns_join<true><<<nblk, 256, 0, st>>>(out, nrb, ncb, A.rows, ncols, nsplit, A.e, B.e + col0, dst);
+  else k_rns_join<false><<<nblk, 256, 0, st>>>(out, nrb, ncb, A.rows, ncols, 1, A.e, B.e + col0, dst);
   ADC2_CHECK_LAUNCH();
   return ADC2_OK;
 }
 
-adc2_status rns_to_z(const RnsMat& A, const RnsMat& B, const int8_t* out, int no, int nv, double2* Z, hipStream_t st) {
-  return join(A, B.e, no * nv, out, StoreZ{Z, no, nv, nullptr, 0}, st);
+// ---------------------------------------------------------------------------
+// general products
+// ---------------------------------------------------------------------------
+// Where the conversions pay: per term of the product 8 / 225e12 s against 8 / rate
+// on the FP64 MFMA kernel, per operand entry about 1.6e-11 s (norm, residues and
+// their reads in the product), per output entry 1.8e-11 s; about 60 us of
+// launches and part-filled rounds.
+bool rns_pays(adc2_handle h, long M, long N, long K, double rate) {
+  if (h->rns_mode == RNS_ALWAYS) return K <= RNS_KMAX * RNS_SPLITS;
+  if (h->rns_off || h->rns_mode == RNS_NEVER || K > RNS_KMAX * RNS_SPLITS) return false;
+  const double terms = (double)M * N * K;
+  const double padded = 256.0 * rcdiv(M, 256) * 128.0 * rcdiv(N, 128) * K;
+  const double rns = 6e-5 + padded * 8 / 225e12 + 1.6e-11 * ((double)M * K + (double)N * K) + 1.8e-11 * (double)M * N;
+  return rns < 0.8 * terms * 8 / rate;
 }
-adc2_status rns_to_y(const RnsMat& A, const RnsMat& B, const int8_t* out, int naux, int nv, double2* Y,
-                     hipStream_t st) {
-  return join(A, B.e, B.rows, out, StoreY{Y, naux, nv, nullptr}, st);
+
+bool rns_reserve(adc2_handle h, size_t bytes) {
+  if (h->rns_off) return false;
+  if (h->rns_ws_bytes >= bytes) return true;
+  dfree(h, h->rns_ws);
+  h->rns_ws = nullptr;
+  h->rns_ws_bytes = 0;
+  const hipError_t e = dmalloc(h, &h->rns_ws, bytes);
+  if (e == hipSuccess && !h->rns_off) {
+    h->rns_ws_bytes = bytes;
+    return true;
+  }
+  (void)hipGetLastError();
+  rns_release(h);
+  h->rns_off = true;
+  return false;
 }
-adc2_status rns_to_rows(const RnsMat& A, const RnsMat& B, int col0, int ncols, const int8_t* out, double2* C, long ldc,
-                        hipStream_t st) {
-  return join(A, B.e + col0, ncols, out, StoreRows{C, ldc, 0}, st);
+
+void rns_release(adc2_handle h) {
+  char *a = h->rns_lvo, *b = h->rns_lvt, *c = h->rns_ws;
+  h->rns_lvo = h->rns_lvt = h->rns_ws = nullptr;
+  h->rns_ws_bytes = 0;
+  dfree(h, a);
+  dfree(h, b);
+  dfree(h, c);
+}
+
+adc2_status rns_product(adc2_handle h, const RnsSrc& A, int M, const RnsSrc& B, int N, int K, const RnsDst& dst,
+                        double rate, bool* done, hipStream_t st) {
+  *done = false;
+  if (M <= 0 || N <= 0 || K <= 0 || !rns_pays(h, M, N, K, rate)) return ADC2_OK;
+  // K-splits: within the INT32 range, and enough tiles for two a CU
+  const long tiles = (long)RNS_PL * rcdiv(M, 256) * rcdiv(N, 128);
+  const int nkc = rcdiv(K, RNS_KC);
+  int ns = std::max(rcdiv(K, RNS_KMAX), (int)std::min<long>({(long)RNS_SPLITS, (1024 + tiles - 1) / tiles, std::max(1, nkc / 8)}));
+  ns = rcdiv(nkc, rcdiv(nkc, ns));   // no empty split
+  auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
+  auto need = [&](long m, long n) {
+    return al(rns_op_bytes(m, K)) + al(rns_op_bytes(n, K)) + al(rns_out_bytes(m, n) * ns) + al(rns_exp_bytes(m)) +
+           al(rns_exp_bytes(n)) + al(rns_norm_bytes(std::max(m, n)));
+  };
+  long mc = M, nc = N;
+  while (need(mc, nc) > 2 * h->rns_target && (mc > 256 || nc > 128)) {
+    if (mc > 256 && (mc >= nc || nc <= 128)) mc = (mc / 2 + 255) / 256 * 256;
+    else nc = (nc / 2 + 127) / 128 * 128;
+  }
+  if (!rns_reserve(h, need(mc, nc))) return ADC2_OK;
+  char* q = h->rns_ws;
+  auto take = [&](size_t b) {
+    char* r = q;
+    q += al(b);
+    return r;
+  };
+  int8_t* ap = (int8_t*)take(rns_op_bytes(mc, K));
+  int8_t* bp = (int8_t*)take(rns_op_bytes(nc, K));
+  int8_t* out = (int8_t*)take(rns_out_bytes(mc, nc) * ns);
+  int* ae = (int*)take(rns_exp_bytes(mc));
+  int* be = (int*)take(rns_exp_bytes(nc));
+  double* nrm = (double*)take(rns_norm_bytes(std::max(mc, nc)));
+  auto rows_from = [](RnsSrc s, long r0) {   // the operand from row r0 on
+    s.r0 += (int)r0;
+    return s;
+  };
+  *done = true;
+  RnsMat am, bm;
+  adc2_status rc;
+  for (long n0 = 0; n0 < N; n0 += nc) {
+    const int n = (int)std::min<long>(nc, N - n0);
+    if ((rc = rns_pack(rows_from(B, n0), n, K, bp, be, nrm, &bm, st)) != ADC2_OK) return rc;
+    for (long m0 = 0; m0 < M; m0 += mc) {
+      const int m = (int)std::min<long>(mc, M - m0);
+      if ((n0 == 0 || mc < M) && (rc = rns_pack(rows_from(A, m0), m, K, ap, ae, nrm, &am, st)) != ADC2_OK) return rc;
+      RnsDst o = dst;
+      o.i0 += (int)m0;
+      o.j0 += (int)n0;
+      if ((rc = rns_gemm(am, bm, 0, n, ns, out, st)) != ADC2_OK) return rc;
+      if ((rc = rns_join(am, bm, 0, n, ns, out, o, st)) != ADC2_OK) return rc;
+    }
+  }
+  return ADC2_OK;
 }
 
 }  // namespace adc2

@@ -33,6 +33,7 @@
 #include <vector>
 
 #include "internal.h"
+#include "rns.h"
 #include "tile.h"
 
 namespace adc2 {
@@ -324,6 +325,19 @@ __global__ __launch_bounds__(256) void k_sigma_part(const double2* __restrict__ 
   }
 }
 
+// N[g][a][b] = -N[g][b][a] for a > b
+__global__ void k_mirror_neg(double2* __restrict__ N, int ng, int nv) {
+  const long nv2 = (long)nv * nv, total = nv2 * ng;
+  for (long e = blockIdx.x * 256L + threadIdx.x; e < total; e += (long)gridDim.x * 256) {
+    const long g = e / nv2;
+    const int r = (int)(e - g * nv2), a = r / nv, b = r - a * nv;
+    if (a > b) {
+      const double2 v = N[g * nv2 + (long)b * nv + a];
+      N[e] = make_double2(-v.x, -v.y);
+    }
+  }
+}
+
 // dst[e] = conj(src[e])
 __global__ void k_conj(const double2* __restrict__ src, long n, double2* __restrict__ dst) {
   for (long e = blockIdx.x * 256L + threadIdx.x; e < n; e += (long)gridDim.x * 256) {
@@ -398,12 +412,18 @@ adc2_status tm_second_order(adc2_handle h, const double2* tau, const int2* dpair
   k_build_tph<<<grid_for(onv * onv), 256, 0, st>>>(tau, o, nv, Tph);
   T2_TRY(launched("k_build_tph"));
   // Z^P_ib at ZT[i][b][P] = sum_{(j,c)} Tph[i][b][(j,c)] L^P_jc, L^P_jc = conj(Lvo[j][P][c]) at LovP[P][(j,c)]
-  T2_TRY(alloc(&LovP, (long)naux * onv));
   T2_TRY(alloc(&ZT, onv * naux));
-  k_swap12<true><<<grid_for((long)naux * onv), 256, 0, st>>>(h->Lvo, o, naux, nv, LovP);
-  T2_TRY(launched("k_swap12"));
-  T2_TRY(gemm_rr((int)onv, naux, (int)onv, Tph, onv, false, LovP, onv, false, ZT, naux, 1.0, false, st));
-  drop(LovP);
+  bool done = false;
+  T2_TRY(rns_product(h, rns_rmajor(Tph, onv), (int)onv,
+                     RnsSrc{h->Lvo, 1 << 30, 0, nv, nv, (long)naux * nv, 1, true}, naux, (int)onv, rns_rows(ZT, naux),
+                     rns_vs_tile(onv, naux), &done, st));
+  if (!done) {
+    T2_TRY(alloc(&LovP, (long)naux * onv));
+    k_swap12<true><<<grid_for((long)naux * onv), 256, 0, st>>>(h->Lvo, o, naux, nv, LovP);
+    T2_TRY(launched("k_swap12"));
+    T2_TRY(gemm_rr((int)onv, naux, (int)onv, Tph, onv, false, LovP, onv, false, ZT, naux, 1.0, false, st));
+    drop(LovP);
+  }
   // second-order singles amplitudes
   double2 *LvvT, *N1, *ZA, *LooK, *N2T, *sa;
   T2_TRY(alloc(&LvvT, nv2 * naux));      // [a][b][P] = L^P_ab
@@ -418,12 +438,15 @@ adc2_status tm_second_order(adc2_handle h, const double2* tau, const int2* dpair
   const long loo_tiles = ((naux + 31) / 32) * (((long)o * o + 31) / 32);
   k_transpose<<<(unsigned)loo_tiles, 256, 0, st>>>(h->Loo, naux, (long)o * o, LooK);
   T2_TRY(launched("k_transpose"));
-  T2_TRY(gemm_rr(o, nv, (int)(nv * (long)naux), ZT, nv * (long)naux, false, LvvT, nv * (long)naux, false, N1, nv,
-                 1.0, false, st));
+  const long nvx = nv * (long)naux, ox = (long)o * naux;
+  T2_TRY(rns_product(h, rns_rmajor(ZT, nvx), o, rns_rmajor(LvvT, nvx), nv, (int)nvx, rns_rows(N1, nv), rns_vs_tile(o, nv),
+                     &done, st));
+  if (!done) T2_TRY(gemm_rr(o, nv, (int)nvx, ZT, nvx, false, LvvT, nvx, false, N1, nv, 1.0, false, st));
   k_swap12<false><<<grid_for(onv * naux), 256, 0, st>>>(ZT, o, nv, naux, ZA);
   T2_TRY(launched("k_swap12"));
-  T2_TRY(gemm_rr(nv, o, (int)((long)o * naux), ZA, (long)o * naux, false, LooK, (long)o * naux, true, N2T, o, 1.0,
-                 false, st));
+  T2_TRY(rns_product(h, rns_rmajor(ZA, ox), nv, rns_rmajor(LooK, ox, true), o, (int)ox, rns_rows(N2T, o),
+                     rns_vs_tile(nv, o), &done, st));
+  if (!done) T2_TRY(gemm_rr(nv, o, (int)ox, ZA, ox, false, LooK, ox, true, N2T, o, 1.0, false, st));
   k_singles_amp<<<grid_for(onv), 256, 0, st>>>(N1, N2T, h->eps, o, nv, sa);
   T2_TRY(launched("k_singles_amp"));
   drop(ZA);
@@ -431,37 +454,67 @@ adc2_status tm_second_order(adc2_handle h, const double2* tau, const int2* dpair
   drop(N2T);
   // (kj|bc) at P1[(j,b)][(k,c)]
   double2 *Koovv, *P1;
-  T2_TRY(alloc(&Koovv, (long)o * o * nv2));
-  T2_TRY(gemm_rr(o * o, (int)nv2, naux, LooK, naux, false, LvvT, naux, false, Koovv, nv2, 1.0, false, st));
+  T2_TRY(alloc(&P1, (long)o * o * nv2));
+  // rows (k, j), columns (b, c), straight into place
+  T2_TRY(rns_product(h, rns_kmajor(h->Loo, (long)o * o, naux), o * o, rns_kmajor(h->Lvv, nv2, naux), (int)nv2, naux,
+                     RnsDst{P1, o, nv, nv * onv, nv, onv, 1, 1.0, false}, rns_vs_tile((long)o * o, nv2), &done, st));
+  if (!done) {
+    T2_TRY(alloc(&Koovv, (long)o * o * nv2));
+    T2_TRY(gemm_rr(o * o, (int)nv2, naux, LooK, naux, false, LvvT, naux, false, Koovv, nv2, 1.0, false, st));
+    k_swap12<false><<<grid_for((long)o * o * nv2), 256, 0, st>>>(Koovv, o, onv, nv, P1);
+    T2_TRY(launched("k_swap12"));
+    drop(Koovv);
+  }
   drop(LvvT);
   drop(LooK);
-  T2_TRY(alloc(&P1, (long)o * o * nv2));
-  k_swap12<false><<<grid_for((long)o * o * nv2), 256, 0, st>>>(Koovv, o, onv, nv, P1);
-  T2_TRY(launched("k_swap12"));
-  drop(Koovv);
   // numerators of u for the pairs (I, j): hole ladder first (it writes Nt)
   double2 *Nt, *G;
   T2_TRY(alloc(&Nt, (long)nc * o * nv2));
   T2_TRY(alloc(&G, (long)npairs * nc * o));
   k_oooo<<<grid_for((long)npairs * nc * o), 256, 0, st>>>(h->Loo, naux, o, nc, dpairs, npairs, G);
   T2_TRY(launched("k_oooo"));
-  T2_TRY(bgemm_kmajor(G, 0, (long)nc * o, nc * o, tau, 0, nv2, (int)nv2, nc * o, (int)nv2, npairs, 1, Nt, st));
+  T2_TRY(rns_product(h, rns_kmajor(G, (long)nc * o, npairs), nc * o, rns_kmajor(tau, nv2, npairs), (int)nv2, npairs,
+                     rns_rows(Nt, nv2), RNS_VS_BIG, &done, st));
+  if (!done)
+    T2_TRY(bgemm_kmajor(G, 0, (long)nc * o, nc * o, tau, 0, nv2, (int)nv2, nc * o, (int)nv2, npairs, 1, Nt, st));
   drop(G);
-  // ring terms, one core I at a time
+  // ring terms: R[I][a][(j,b)] and Rp[I][(j,b)][a], for every core I at once on
+  // the residue engine, one core at a time on the MFMA tiles
   double2 *R, *Rp;
-  T2_TRY(alloc(&R, nv * onv));
-  T2_TRY(alloc(&Rp, onv * nv));
-  for (int I = 0; I < nc; ++I) {
-    T2_TRY(gemm_rr(nv, (int)onv, naux, ZT + (long)I * nv * naux, naux, false, h->LoT, naux, true, R, onv, 1.0, false,
-                   st));
-    T2_TRY(gemm_rr(nv, (int)onv, (int)onv, Tph + (long)I * nv * onv, onv, false, P1, onv, false, R, onv, -1.0, true,
-                   st));
-    T2_TRY(gemm_rr((int)onv, nv, naux, ZT, naux, false, h->LoT + (long)I * nv * naux, naux, true, Rp, nv, 1.0, false,
-                   st));
-    T2_TRY(gemm_rr((int)onv, nv, (int)onv, Tph, onv, false, P1 + (long)I * nv * onv, onv, false, Rp, nv, -1.0, true,
-                   st));
-    k_ring_add<<<grid_for((long)o * nv2), 256, 0, st>>>(R, Rp, o, nv, Nt + (long)I * o * nv2);
-    T2_TRY(launched("k_ring_add"));
+  const int nI = rns_pays(h, nc * nv, onv, onv, rns_vs_tile(nv, onv)) ? nc : 1;
+  T2_TRY(alloc(&R, nI * nv * onv));
+  T2_TRY(alloc(&Rp, nI * onv * nv));
+  for (int I = 0; I < nc; I += nI) {
+    const int M = nI * nv;
+    const double2 *Zi = ZT + (long)I * nv * naux, *Ti = Tph + (long)I * nv * onv;
+    const double2 *Li = h->LoT + (long)I * nv * naux, *Pi = P1 + (long)I * nv * onv;
+    const RnsDst dp{Rp, 1 << 30, 0, nv, nv, onv * nv, 1, 1.0, false};
+    RnsDst dpa = dp;
+    dpa.alpha = -1.0;
+    dpa.add = true;
+    T2_TRY(rns_product(h, rns_rmajor(Zi, naux), M, rns_rmajor(h->LoT, naux, true), (int)onv, naux, rns_rows(R, onv),
+                       rns_vs_tile(nv, onv), &done, st));
+    for (int q = 0; q < nI && !done; ++q)
+      T2_TRY(gemm_rr(nv, (int)onv, naux, Zi + q * nv * (long)naux, naux, false, h->LoT, naux, true, R + q * nv * onv,
+                     onv, 1.0, false, st));
+    T2_TRY(rns_product(h, rns_rmajor(Ti, onv), M, rns_rmajor(P1, onv), (int)onv, (int)onv,
+                       rns_rows(R, onv, -1.0, true), rns_vs_tile(nv, onv), &done, st));
+    for (int q = 0; q < nI && !done; ++q)
+      T2_TRY(gemm_rr(nv, (int)onv, (int)onv, Ti + q * nv * onv, onv, false, P1, onv, false, R + q * nv * onv, onv, -1.0,
+                     true, st));
+    T2_TRY(rns_product(h, rns_rmajor(ZT, naux), (int)onv, rns_rmajor(Li, naux, true), M, naux, dp, rns_vs_tile(nv, onv), &done, st));
+    for (int q = 0; q < nI && !done; ++q)
+      T2_TRY(gemm_rr((int)onv, nv, naux, ZT, naux, false, Li + q * nv * (long)naux, naux, true, Rp + q * onv * nv, nv,
+                     1.0, false, st));
+    T2_TRY(rns_product(h, rns_rmajor(Tph, onv), (int)onv, rns_rmajor(Pi, onv), M, (int)onv, dpa, rns_vs_tile(nv, onv), &done, st));
+    for (int q = 0; q < nI && !done; ++q)
+      T2_TRY(gemm_rr((int)onv, nv, (int)onv, Tph, onv, false, Pi + q * nv * onv, onv, false, Rp + q * onv * nv, nv,
+                     -1.0, true, st));
+    for (int q = 0; q < nI; ++q) {
+      k_ring_add<<<grid_for((long)o * nv2), 256, 0, st>>>(R + q * nv * onv, Rp + q * onv * nv, o, nv,
+                                                          Nt + (long)(I + q) * o * nv2);
+      T2_TRY(launched("k_ring_add"));
+    }
   }
   drop(R);
   drop(Rp);
@@ -484,8 +537,39 @@ adc2_status tm_second_order(adc2_handle h, const double2* tau, const int2* dpair
       T2_TRY(launched("k_swap12"));
     }
     T2_TRY(alloc(&V, (long)ab * nv * nv2));
-    T2_TRY(alloc(&W, (long)ab * nv * nv2));
-    for (int a0 = 0; a0 < nv; a0 += ab) {
+    // On the residue engine the first product is written as V[a][b][(c,d)] at
+    // once, and only for b >= a0: u is antisymmetric in (a, b), so the rest is
+    // mirrored.
+    bool half = rns_pays(h, (long)ab * nv, nv2, naux, RNS_VS_BIG);
+    for (int a0 = 0; a0 < nv && half; a0 += ab) {
+      const int na = std::min(ab, nv - a0), nbv = nv - a0;
+      const double2* La = h->Lvv + (long)a0 * nv;
+      T2_TRY(rns_product(h, rns_kmajor(La, nv2, naux), na * nv, rns_kmajor(La, nv2, naux), nbv * nv, naux,
+                         RnsDst{V, nv, nbv * nv2, nv, nv, nv2, 1, 1.0, false}, RNS_VS_BIG, &done, st));
+      if (!done) {   // K-major products of the MFMA tiles, rows (a,c) and columns (b,d), into place row by row
+        T2_TRY(alloc(&W, (long)ab * nv * nv2));
+        T2_TRY(bgemm_kmajor(La, 0, nv2, na * nv, La, 0, nv2, nbv * nv, na * nv, nbv * nv, naux, 1, W, st));
+        for (int q = 0; q < na; ++q) {   // [c][b][d] -> [b][c][d]
+          k_swap12<false><<<grid_for(nbv * nv2), 256, 0, st>>>(W + (long)q * nbv * nv2, nv, nbv, nv,
+                                                               V + (long)q * nbv * nv2);
+          T2_TRY(launched("k_swap12"));
+        }
+        drop(W);
+      }
+      const RnsDst dn{Nt + (long)a0 * nv + a0, 1 << 30, 0, nv2, nbv, nv, 1, 1.0, true};
+      T2_TRY(rns_product(h, rns_rmajor(TIj, nv2), nc * o, rns_rmajor(V, nv2), na * nbv, (int)nv2, dn,
+                         rns_vs_tile(nc * o, nbv), &done, st));
+      for (int q = 0; q < na && !done; ++q)
+        T2_TRY(gemm_rr(nc * o, nbv, (int)nv2, TIj, nv2, false, V + (long)q * nbv * nv2, nv2, false,
+                       Nt + (long)(a0 + q) * nv + a0, nv2, 1.0, true, st));
+    }
+    if (half) {
+      k_mirror_neg<<<grid_for((long)nc * o * nv2), 256, 0, st>>>(Nt, nc * o, nv);
+      T2_TRY(launched("k_mirror_neg"));
+    } else {
+      T2_TRY(alloc(&W, (long)ab * nv * nv2));
+    }
+    for (int a0 = 0; a0 < nv && !half; a0 += ab) {
       const int na = std::min(ab, nv - a0);
       T2_TRY(bgemm_kmajor(h->Lvv + (long)a0 * nv, 0, nv2, na * nv, h->Lvv, 0, nv2, (int)nv2, na * nv, (int)nv2, naux,
                           1, V, st));
@@ -499,7 +583,7 @@ adc2_status tm_second_order(adc2_handle h, const double2* tau, const int2* dpair
     }
     drop(TIj);
     drop(V);
-    drop(W);
+    if (!half) drop(W);
   }
   k_u_divide<<<grid_for((long)nc * o * nv2), 256, 0, st>>>(Nt, h->eps, nc, o, nv);
   T2_TRY(launched("k_u_divide"));
@@ -517,6 +601,9 @@ adc2_status tm_second_order(adc2_handle h, const double2* tau, const int2* dpair
     const long Kr = (long)npairs * nv;
     const int nsr = (int)std::max<long>(1, std::min<long>(std::max(1, 1024 / (((nv + 127) / 128) * ((nv + 127) / 128))),
                                                           Kr / 256));
+    T2_TRY(rns_product(h, rns_kmajor(tau, nv, (int)Kr), nv, rns_kmajor(tau, nv, (int)Kr, true), nv, (int)Kr,
+                       rns_rows(rho, nv, 2.0), RNS_VS_BIG, &done, st));
+    if (!done) {
     T2_TRY(alloc(&tc, (long)npairs * nv2));
     T2_TRY(alloc(&rpart, (long)nsr * nv2));
     k_conj<<<grid_for((long)npairs * nv2), 256, 0, st>>>(tau, (long)npairs * nv2, tc);
@@ -527,6 +614,7 @@ adc2_status tm_second_order(adc2_handle h, const double2* tau, const int2* dpair
     T2_TRY(launched("k_sum_parts"));
     drop(tc);
     drop(rpart);
+    }
     // sigma_Ik over slices of the rows of Tph
     double2* spart;
     const long Ks = nv * onv;

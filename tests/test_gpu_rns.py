@@ -13,7 +13,7 @@ import torch
 
 import paper_2604_27451_amd as A
 from oracle import adc2 as O
-from synth import make_system, random_vectors
+from synth import dipole_integrals, make_system, random_vectors
 
 pytestmark = pytest.mark.gpu
 
@@ -44,6 +44,53 @@ def test_sigma_against_oracle(monkeypatch, nc, no, nv, naux, m):
     err = float((S - ref).abs().max() / ref.abs().max())
     print(f"  rel err {err:.2e}", flush=True)
     assert err < 1e-12
+
+
+@pytest.mark.parametrize("mb", [1, 4])
+def test_chunks_equal_whole(monkeypatch, mb):
+    """Exact integer products: work spaces of 1 and 4 MiB (one, several
+    (vector, core) rows a chunk) give the same bits as one chunk."""
+    monkeypatch.setenv("ADC2_ZGEMM", "rns")
+    s = make_system(2, 6, 40, 70, seed=905)
+    h = handle(s)
+    x = dev(random_vectors(8, 3, h.dim))
+    want = A.adc2_sigma(h, x)
+    h.close()
+    monkeypatch.setenv("ADC2_RNS_MB", str(mb))
+    h = handle(s)
+    print(f"[case] rns chunks of {mb} MiB", flush=True)
+    assert torch.equal(A.adc2_sigma(h, x), want)
+    h.close()
+
+
+@pytest.mark.parametrize("nc,no,nv,naux,mb", [(1, 2, 7, 12, 0), (2, 6, 40, 70, 0), (2, 6, 40, 70, 1)])
+def test_setup_transition_and_adjoint_against_oracle(monkeypatch, nc, no, nv, naux, mb):
+    """The general products: whole and (mb = 1) in chunks of 256 x 128."""
+    monkeypatch.setenv("ADC2_ZGEMM", "rns")
+    if mb:
+        monkeypatch.setenv("ADC2_RNS_MB", str(mb))
+    s = make_system(nc, no, nv, naux, seed=950 + naux)
+    print(f"[case] rns setup, transition, adjoint {(nc, no, nv, naux)} chunk {mb}", flush=True)
+    o = O.Adc2(s.L, s.eps, nc, no, nv)
+    h = handle(s)
+    m11 = A.adc2_get_m11(h).cpu()
+    ref = o.m11().reshape(nc * nv, nc * nv)
+    assert float((m11 - ref).abs().max() / ref.abs().max()) < 1e-12
+    assert abs(A.adc2_mp2_energy(h) / float(o.mp2_energy()) - 1.0) < 1e-12
+    k = 2
+    x = random_vectors(7, k, h.dim)
+    dip = dipole_integrals(3, nc + no + nv)
+    T, f = A.adc2_transition(h, dev(dip), dev(x), [9.0, 9.5], order=2)
+    Tr, fr = O.oscillator_strengths(torch.from_numpy(s.L), torch.from_numpy(s.eps), o.sp, torch.from_numpy(dip),
+                                    torch.from_numpy(x), [9.0, 9.5], order=2)
+    assert np.abs(T - Tr.numpy()).max() < 1e-12 * np.abs(Tr.numpy()).max()
+    g = [1.0, -0.5]
+    dL, de = A.adc2_omega_backward(h, dev(x), g)
+    w = np.array(g) / (np.abs(x) ** 2).sum(1)
+    Lr, er = O.omega_gradient(s.L, s.eps, o.sp, torch.from_numpy(x), w)
+    assert float((dL.cpu() - Lr).abs().max() / Lr.abs().max()) < 1e-12
+    assert float((de.cpu() - er).abs().max() / er.abs().max()) < 1e-12
+    h.close()
 
 
 @pytest.mark.parametrize("p", [600, -600])

@@ -9,6 +9,8 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <map>
+#include <mutex>
 #include <numeric>
 #include <string>
 #include <vector>
@@ -25,6 +27,8 @@ static adc2_status fail(adc2_status st, const std::string& msg) {
   set_error(msg);
   return st;
 }
+
+static void pool_leave();
 
 static void free_handle(adc2_handle h) {
   if (!h) return;
@@ -58,7 +62,9 @@ static void free_handle(adc2_handle h) {
   if (h->ev1) hipEventDestroy(h->ev1);
   for (int i = 0; i <= adc2_handle_s::NK; ++i)
     if (h->kev[i]) hipEventDestroy(h->kev[i]);
+  const bool pooled = !h->alloc.alloc;
   delete h;
+  if (pooled) pool_leave();
 }
 
 static double sigma_flops_per_vector(const Dims& d) {
@@ -161,8 +167,119 @@ using namespace adc2;
 
 namespace adc2 {
 
+// ---------------------------------------------------------------------------
+// Device blocks of the hipMalloc path.  The entry points take work spaces of
+// up to several GB and give them back before they return; with a few handles
+// alive the driver then spent 0.1 to 1.8 s in single hipMalloc / hipFree calls
+// (a second-order transition of 0.1 s took up to 1.8 s).  Freed blocks are kept
+// for the next request of about their size: per device at most POOL_BYTES, all
+// of them returned to the driver when a request cannot be served and when the
+// last handle is destroyed.  A block enters the pool only after the device
+// was idle (as hipFree waits), so any stream and thread may take it.
+// ---------------------------------------------------------------------------
+namespace {
+constexpr size_t POOL_BYTES = size_t(16) << 30;
+struct Pool {
+  std::mutex mu;
+  int handles = 0;
+  struct Blk {
+    void* p;
+    size_t bytes;
+    int dev;
+  };
+  std::map<void*, std::pair<size_t, int>> live;   // size and device of the blocks handed out
+  std::vector<Blk> idle;
+  size_t idle_bytes(int dev) const {
+    size_t n = 0;
+    for (const Blk& b : idle)
+      if (b.dev == dev) n += b.bytes;
+    return n;
+  }
+  void flush() {
+    for (const Blk& b : idle) (void)hipFree(b.p);
+    idle.clear();
+  }
+};
+Pool& pool() {
+  static Pool* p = new Pool;   // outlives every static destructor
+  return *p;
+}
+}  // namespace
+
+static void pool_enter() {
+  std::lock_guard<std::mutex> lk(pool().mu);
+  ++pool().handles;
+}
+
+static void pool_leave() {
+  std::lock_guard<std::mutex> lk(pool().mu);
+  if (--pool().handles == 0) pool().flush();
+}
+
+static hipError_t pool_alloc(void** p, size_t bytes) {
+  if (bytes == 0) return hipMalloc(p, bytes);
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const size_t unit = bytes > (size_t(8) << 20) ? size_t(2) << 20 : 4096;
+  const size_t want = (bytes + unit - 1) / unit * unit;
+  Pool& P = pool();
+  std::lock_guard<std::mutex> lk(P.mu);
+  int best = -1;   // smallest idle block of at least the size and at most a quarter more
+  for (int i = 0; i < (int)P.idle.size(); ++i) {
+    const Pool::Blk& b = P.idle[i];
+    if (b.dev == dev && b.bytes >= want && b.bytes <= want + want / 4 && (best < 0 || b.bytes < P.idle[best].bytes))
+      best = i;
+  }
+  if (best >= 0) {
+    *p = P.idle[best].p;
+    P.live[*p] = {P.idle[best].bytes, dev};
+    P.idle.erase(P.idle.begin() + best);
+    return hipSuccess;
+  }
+  e = hipMalloc(p, want);
+  if (e == hipErrorOutOfMemory && !P.idle.empty()) {
+    (void)hipGetLastError();
+    P.flush();
+    e = hipMalloc(p, want);
+  }
+  if (e == hipSuccess) P.live[*p] = {want, dev};
+  return e;
+}
+
+static void pool_free(void* p) {
+  Pool& P = pool();
+  Pool::Blk b{p, 0, 0};
+  {
+    std::lock_guard<std::mutex> lk(P.mu);
+    const auto it = P.live.find(p);
+    if (it != P.live.end()) {
+      b.bytes = it->second.first;
+      b.dev = it->second.second;
+      P.live.erase(it);
+    }
+  }
+  if (b.bytes == 0 || b.bytes > POOL_BYTES / 2) {
+    (void)hipFree(p);
+    return;
+  }
+  int cur = b.dev;   // wait for the block's own device
+  (void)hipGetDevice(&cur);
+  if (cur != b.dev) (void)hipSetDevice(b.dev);
+  (void)hipDeviceSynchronize();
+  if (cur != b.dev) (void)hipSetDevice(cur);
+  std::lock_guard<std::mutex> lk(P.mu);
+  while (P.idle_bytes(b.dev) + b.bytes > POOL_BYTES) {   // the oldest go first
+    int i = 0;
+    while (P.idle[i].dev != b.dev) ++i;
+    (void)hipFree(P.idle[i].p);
+    P.idle.erase(P.idle.begin() + i);
+  }
+  P.idle.push_back(b);
+}
+
 static hipError_t dmalloc_once(adc2_handle h, void** p, size_t bytes) {
-  if (!h || !h->alloc.alloc) return hipMalloc(p, bytes);
+  if (!h || !h->alloc.alloc) return pool_alloc(p, bytes);
   if (bytes == 0) {          // as hipMalloc: success, no memory
     *p = nullptr;
     return hipSuccess;
@@ -187,7 +304,7 @@ hipError_t dmalloc_raw(adc2_handle h, void** p, size_t bytes) {
 void dfree(adc2_handle h, void* p) {
   if (!p) return;
   if (!h || !h->alloc.alloc) {
-    hipFree(p);
+    pool_free(p);
     return;
   }
   hipDeviceSynchronize();
@@ -239,6 +356,7 @@ adc2_status adc2_setup(const void* L, const double* eps, int nc, int no, int nv,
     }
     h->alloc = *alloc;
   }
+  if (!h->alloc.alloc) pool_enter();
   if (const char* v = getenv("ADC2_ZGEMM")) {
     h->zgemm = strcmp(v, "3m") == 0    ? ZGEMM_3M
                : strcmp(v, "big") == 0 ? ZGEMM_BIG

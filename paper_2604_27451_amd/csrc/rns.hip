@@ -595,6 +595,7 @@ bool rns_pays(adc2_handle h, long M, long N, long K, double rate) {
 bool rns_reserve(adc2_handle h, size_t bytes) {
   if (h->rns_off) return false;
   if (h->rns_ws_bytes >= bytes) return true;
+  if (bytes > (size_t(256) << 20)) bytes = (bytes + (size_t(512) << 20) - 1) >> 29 << 29;   // few sizes: blocks are reused
   dfree(h, h->rns_ws);
   h->rns_ws = nullptr;
   h->rns_ws_bytes = 0;

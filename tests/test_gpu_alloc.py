@@ -126,3 +126,51 @@ def test_torch_allocator_precision_forms_and_two_stage():
     assert np.abs(np.array(wa) - np.array(wt)).max() < 1e-12
     ha.close()
     ht.close()
+
+
+def test_pooled_memory_is_bounded_and_given_back():
+    """hipMalloc handles: blocks freed by calls are reused while a handle
+    lives, at most 16 GiB of them are held, and the last handle's destruction
+    returns everything (in a process of its own: no other handles)."""
+    import os
+    import subprocess
+    import sys
+    code = """
+import torch, gc
+import paper_2604_27451_amd as A
+from synth import make_system, random_vectors, dipole_integrals
+s = make_system(2, 6, 40, 70, seed=75)
+L, e = torch.from_numpy(s.L).cuda(), torch.from_numpy(s.eps).cuda()
+d = torch.from_numpy(dipole_integrals(3, 48)).cuda()
+torch.cuda.synchronize()
+free = lambda: torch.cuda.mem_get_info()[0]
+a, b = (A.adc2_setup(L, e, s.nc, s.no, s.nv, s.naux) for _ in range(2))
+x = torch.from_numpy(random_vectors(5, 2, a.dim)).cuda()
+w = A.adc2_sigma(a, x)
+g = A.adc2_omega_backward(a, x, [1.0, 0.5])
+T = A.adc2_transition(a, d, x, [9.0, 9.5])
+first = free()
+for h in (b, a):
+    assert torch.equal(A.adc2_omega_backward(h, x, [1.0, 0.5])[0], g[0])
+    assert (A.adc2_transition(h, d, x, [9.0, 9.5])[0] == T[0]).all()
+for _ in range(3):
+    A.adc2_transition(a, d, x, [9.0, 9.5])
+assert first - free() < 16 << 30
+steady = free()
+A.adc2_transition(a, d, x, [9.0, 9.5])
+assert free() == steady
+a.close()
+b.close()
+c = A.adc2_setup(L, e, s.nc, s.no, s.nv, s.naux)
+assert torch.equal(A.adc2_sigma(c, x), w)
+held = free()
+c.close()
+torch.cuda.synchronize()
+assert free() > held
+print("pool ok", flush=True)
+"""
+    env = dict(os.environ, ADC2_ZGEMM="rns")
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=110, env=env,
+                       cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    print(r.stdout[-300:], r.stderr[-1500:], flush=True)
+    assert r.returncode == 0 and "pool ok" in r.stdout

@@ -18,6 +18,7 @@
 #include <algorithm>
 
 #include "internal.h"
+#include "rns.h"
 #include "tile.h"
 
 namespace adc2 {
@@ -191,6 +192,190 @@ __global__ __launch_bounds__(256) void k_wbuild(const double2* __restrict__ Lvo,
   if (tid == 0) epart[lid] = red[0];
 }
 
+// W of the pairs (k < l), k0 <= k < k1, from V[k - k0][l - k0][a][c] = (ak|cl):
+// W[a][c] = V[a][c] - V[c][a].  One workgroup per (pair, 64 x 64 tile a-blk <= c-blk);
+// the mirror blocks pass through LDS, so every access is coalesced (HBM-bound:
+// 16 B read, 16 B written per entry).
+constexpr int WS = 32;
+__global__ __launch_bounds__(256) void k_w_from_v(const double2* __restrict__ V, const double* __restrict__ eps,
+                                                   const int2* __restrict__ pairs, int p0, int k0, int nl, int nv, int o,
+                                                   double2* __restrict__ W, double* __restrict__ epart) {
+  __shared__ double2 t[WS][WS + 1], u[WS][WS + 1];
+  __shared__ double red[256];
+  const int nb = (nv + TM - 1) / TM, ntp = nb * (nb + 1) / 2;
+  const int p = p0 + blockIdx.x / ntp;
+  int ab, cb;
+  tile_pair(blockIdx.x % ntp, nb, ab, cb);
+  const int2 kl = pairs[p];
+  const double2* Vp = V + ((long)(kl.x - k0) * nl + (kl.y - k0)) * nv * nv;
+  double2* Wp = W + (long)p * nv * nv;
+  const double ekl = eps[kl.x] + eps[kl.y];
+  const int tid = threadIdx.x;
+  double e = 0.0;
+  for (int q = 0; q < 4; ++q) {
+    const int a0 = ab * TM + (q >> 1) * WS, c0 = cb * TM + (q & 1) * WS;
+    if (c0 < a0 || a0 >= nv || c0 >= nv) continue;   // below the diagonal: the mirror of another block
+    __syncthreads();
+    for (int x = tid; x < WS * WS; x += 256) {
+      const int r = x / WS, c = x % WS;
+      t[r][c] = (a0 + r < nv && c0 + c < nv) ? Vp[(long)(a0 + r) * nv + c0 + c] : make_double2(0.0, 0.0);
+      u[r][c] = (c0 + r < nv && a0 + c < nv) ? Vp[(long)(c0 + r) * nv + a0 + c] : make_double2(0.0, 0.0);
+    }
+    __syncthreads();
+    for (int x = tid; x < WS * WS; x += 256) {
+      const int r = x / WS, c = x % WS;
+      if (a0 + r < nv && c0 + c < nv) {
+        const double2 w = csub(t[r][c], u[c][r]);
+        Wp[(long)(a0 + r) * nv + c0 + c] = w;
+        if (a0 + r < c0 + c) e -= (w.x * w.x + w.y * w.y) / (eps[o + a0 + r] + eps[o + c0 + c] - ekl);
+      }
+      if (a0 != c0 && c0 + r < nv && a0 + c < nv) Wp[(long)(c0 + r) * nv + a0 + c] = csub(u[r][c], t[c][r]);
+    }
+  }
+  red[tid] = e;
+  __syncthreads();
+  for (int st = 128; st > 0; st >>= 1) {
+    if (tid < st) red[tid] += red[tid + st];
+    __syncthreads();
+  }
+  if (tid == 0) epart[(long)p * ntp + blockIdx.x % ntp] = red[0];
+}
+
+// W and the energy partials of every pair on the residue engine: (ak|cl) for
+// groups of k against all l >= k as one product over the Cholesky index, then
+// antisymmetrised.  The same terms as k_wbuild (each pair once); nc=6 no=60
+// nv=300 naux=1500: 71 ms -> 16 ms.
+static adc2_status wbuild_rns(adc2_handle h, const int2* dpairs, double2* W, double* epart, bool* done,
+                              hipStream_t st) {
+  const Dims& d = h->d;
+  const int o = d.o, nv = d.nv;
+  const long nv2 = (long)nv * nv, lds = (long)d.naux * nv;
+  *done = false;
+  if (!rns_pays(h, (long)o * nv, (long)o * nv / 2, d.naux, RNS_VS_BIG)) return ADC2_OK;
+  const int g = (int)std::max<long>(1, std::min<long>(o, (long)(h->rns_target / 2) / (16 * o * nv2)));   // k per group
+  double2* V = nullptr;
+  if (dmalloc(h, &V, sizeof(double2) * g * o * nv2) != hipSuccess) {
+    (void)hipGetLastError();
+    return ADC2_OK;
+  }
+  const int nb = (nv + TM - 1) / TM, ntp = nb * (nb + 1) / 2;
+  int p0 = 0;
+  adc2_status rc = ADC2_OK;
+  for (int k0 = 0; k0 < o - 1 && rc == ADC2_OK; k0 += g) {
+    const int k1 = std::min(k0 + g, o), nl = o - k0;
+    const RnsSrc rows{h->Lvo + k0 * lds, nv, lds, 1, 1 << 30, 0, nv, false};
+    bool ok = false;
+    rc = rns_product(h, rows, (k1 - k0) * nv, rows, nl * nv, d.naux, RnsDst{V, nv, nl * nv2, nv, nv, nv2, 1, 1.0, false},
+                     0.0, &ok, st);
+    if (rc != ADC2_OK || !ok) break;   // (without its memory: the MFMA kernel does every pair)
+    int np = 0;
+    for (int k = k0; k < k1; ++k) np += o - 1 - k;
+    k_w_from_v<<<(unsigned)((long)np * ntp), 256, 0, st>>>(V, h->eps, dpairs, p0, k0, nl, nv, o, W, epart);
+    if (hipGetLastError() != hipSuccess) {
+      set_error("k_w_from_v launch failed");
+      rc = ADC2_ERR_HIP;
+    }
+    p0 += np;
+    *done = k1 >= o - 1;
+  }
+  if (hipStreamSynchronize(st) != hipSuccess && rc == ADC2_OK) {
+    set_error("wbuild: stream synchronisation failed");
+    rc = ADC2_ERR_HIP;
+  }
+  dfree(h, V);
+  return rc;
+}
+
+// T[t][c][a] = W_p[c][a] / D for the pairs p = p0 + t (antisymmetric like W).
+__global__ void k_tau_chunk(const double2* __restrict__ W, const double* __restrict__ eps, const int2* __restrict__ pairs,
+                            int p0, int o, int nv, double2* __restrict__ T) {
+  const int2 kl = pairs[p0 + blockIdx.y];
+  const double ekl = eps[kl.x] + eps[kl.y];
+  const double2* w = W + (long)(p0 + blockIdx.y) * nv * nv;
+  double2* t = T + (long)blockIdx.y * nv * nv;
+  for (int e = blockIdx.x * 256 + threadIdx.x; e < nv * nv; e += gridDim.x * 256) {
+    const int c = e / nv, a = e - c * nv;
+    t[e] = (a == c) ? czero() : cscale(w[e], 1.0 / (eps[o + a] + eps[o + c] - ekl));
+  }
+}
+
+// Wc[I][k][c][a] = <ca||Ik> and Tc the same over its denominator, every core I
+// and occupied k (zero at k = I).
+__global__ void k_core_rows(const double2* __restrict__ W, const double* __restrict__ eps, const int* __restrict__ pidx,
+                            int o, int nv, double2* __restrict__ Wc, double2* __restrict__ Tc) {
+  const int k = blockIdx.y % o, I = blockIdx.y / o;
+  const long base = (long)blockIdx.y * nv * nv;
+  const double s = I < k ? 1.0 : -1.0, eIk = eps[I] + eps[k];
+  const double2* w = W + (k == I ? 0L : (long)pidx[I * o + k] * nv * nv);
+  for (int e = blockIdx.x * 256 + threadIdx.x; e < nv * nv; e += gridDim.x * 256) {
+    const int c = e / nv, a = e - c * nv;
+    const double2 v = k == I ? czero() : cscale(w[e], s);
+    Wc[base + e] = v;
+    Tc[base + e] = (k == I || a == c) ? czero() : cscale(v, 1.0 / (eps[o + a] + eps[o + c] - eIk));
+  }
+}
+
+// Terms (i) and (iii) on the residue engine.  W is antisymmetric in its two
+// virtuals, so both operands of sum_c tau_ac conj(W_bc) are read as
+// (p, c) x a, contiguous in a (the two signs cancel).
+//   Bm[a][b] = sum_{p,c} T_p[c][a] conj(W_p[c][b]), tau formed for a chunk of pairs at a time
+//   E[I][J][a][b] = sum_{k,c} Tc[I][k][c][a] conj(Wc[J][k][c][b])
+static adc2_status pair_terms_rns(adc2_handle h, const double2* W, const int2* dpairs, int npairs, const int* dpidx,
+                                  double2* Bm, double2* E, bool* done_i, bool* done_iii, hipStream_t st) {
+  const Dims& d = h->d;
+  const int o = d.o, nv = d.nv, nc = d.nc;
+  const long nv2 = (long)nv * nv;
+  const unsigned gx = (unsigned)std::min<long>(64, (nv2 + 255) / 256);
+  adc2_status rc = ADC2_OK;
+  *done_i = *done_iii = false;
+  // pairs per chunk: K of about 10^5 terms (1.5 MB of tau per virtual), whatever
+  // the work-space target, so that the FP64 sum of the chunks does not depend on it
+  const long per = std::max<long>(1, std::min<long>({(long)npairs, 98304L / nv, 65535L}));
+  if (npairs > 0 && rns_pays(h, nv, nv, per * nv, rns_vs_tile(nv * 8L, nv * 8L))) {
+    double2* T = nullptr;
+    bool ok = dmalloc(h, &T, sizeof(double2) * per * nv2) == hipSuccess;
+    if (!ok) (void)hipGetLastError();
+    for (long p0 = 0; p0 < npairs && ok && rc == ADC2_OK; p0 += per) {
+      const int np = (int)std::min<long>(per, npairs - p0);
+      k_tau_chunk<<<dim3(gx, np), 256, 0, st>>>(W, h->eps, dpairs, (int)p0, o, nv, T);
+      if (hipGetLastError() != hipSuccess) {
+        set_error("k_tau_chunk launch failed");
+        rc = ADC2_ERR_HIP;
+        break;
+      }
+      rc = rns_product(h, rns_kmajor(T, nv, np * nv), nv, rns_kmajor(W + p0 * nv2, nv, np * nv, true), nv, np * nv,
+                       rns_rows(Bm, nv, 1.0, p0 > 0), 0.0, &ok, st);
+    }
+    *done_i = ok && rc == ADC2_OK;
+    (void)hipStreamSynchronize(st);
+    dfree(h, T);
+    if (rc != ADC2_OK) return rc;
+  }
+  if (rns_pays(h, (long)nc * nv, (long)nc * nv, (long)o * nv, rns_vs_tile((long)nc * nv, (long)nc * nv)) &&
+      (long)nc * o <= 65535) {
+    double2 *Wc = nullptr, *Tc = nullptr;
+    bool ok = dmalloc(h, &Wc, sizeof(double2) * nc * o * nv2) == hipSuccess &&
+              dmalloc(h, &Tc, sizeof(double2) * nc * o * nv2) == hipSuccess;
+    if (!ok) (void)hipGetLastError();
+    if (ok) {
+      k_core_rows<<<dim3(gx, nc * o), 256, 0, st>>>(W, h->eps, dpidx, o, nv, Wc, Tc);
+      if (hipGetLastError() != hipSuccess) {
+        set_error("k_core_rows launch failed");
+        rc = ADC2_ERR_HIP;
+      } else {
+        RnsSrc A{Tc, nv, o * nv2, 1, 1 << 30, 0, nv, false}, B{Wc, nv, o * nv2, 1, 1 << 30, 0, nv, true};
+        rc = rns_product(h, A, nc * nv, B, nc * nv, o * nv, RnsDst{E, nv, nc * nv2, nv, nv, nv2, 1, 1.0, false}, 0.0, &ok,
+                         st);
+      }
+    }
+    *done_iii = ok && rc == ADC2_OK;
+    (void)hipStreamSynchronize(st);
+    dfree(h, Wc);
+    dfree(h, Tc);
+  }
+  return rc;
+}
+
 // ---------------------------------------------------------------------------
 // Pair contraction  C_b[a][x] = sum_t s_t sum_c W[pA_t][a][c] / D(a,c;kA_t,lA_t)
 //                                          * conj(W[pB_t][x][c])
@@ -317,24 +502,78 @@ __global__ __launch_bounds__(256) void k_qterm(const double2* __restrict__ W, co
 // ---------------------------------------------------------------------------
 // <Ka||Ij> = (KI|aj) - (Kj|aI)  stored as Vt[I][j][K][a]
 // ---------------------------------------------------------------------------
-__global__ void k_vint(const double2* __restrict__ Lvo, const double2* __restrict__ Loo, int nc, int no,
-                       int nv, int naux, int o, double2* __restrict__ Vt) {
-  const long total = (long)nc * no * nc * nv;
-  for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < total; e += (long)gridDim.x * blockDim.x) {
-    const int a = (int)(e % nv);
-    const int K = (int)((e / nv) % nc);
-    const int j = (int)((e / ((long)nv * nc)) % no);
-    const int I = (int)(e / ((long)nv * nc * no));
-    const int jo = nc + j;
-    double2 acc = make_double2(0, 0);
-    for (int P = 0; P < naux; ++P) {
-      const double2 lKI = Loo[((long)P * o + K) * o + I];
-      const double2 laj = Lvo[((long)jo * naux + P) * nv + a];
-      const double2 lKj = Loo[((long)P * o + K) * o + jo];
-      const double2 laI = Lvo[((long)I * naux + P) * nv + a];
-      acc = cadd(acc, csub(cmul(lKI, laj), cmul(lKj, laI)));
+// Two products over the Cholesky index with few rows: coefficients Loo[P][K][x]
+// of one x-range times rows Lvo[l][P][a] of one l.  One workgroup per (l,
+// x-group of VX, 64 values of a); its four waves split P, a lane holds nc VX
+// sums of its a (the coefficients are broadcast from LDS), and the waves' sums
+// are added in order.  Each row of Lvo is read once per x-group.
+//   DIRECT:    l = nc + j, x = I (all nc of them):  Vt[I][j][K][a]  = (KI|aj)
+//   otherwise: l = I,      x = nc + j:              Vt[I][j][K][a] -= (Kj|aI)
+constexpr int VX = 6, VK = 6, VP = 32;
+template <bool DIRECT>
+__global__ __launch_bounds__(256) void k_vint(const double2* __restrict__ Lvo, const double2* __restrict__ Loo, int nc,
+                                               int no, int nv, int naux, int o, double2* __restrict__ Vt) {
+  __shared__ double2 co[4][VP][VK * VX];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int nx = DIRECT ? nc : no, x0 = DIRECT ? 0 : nc;
+  const int nxg = (nx + VX - 1) / VX, nkg = (nc + VK - 1) / VK, nat = (nv + 63) / 64;
+  int b = blockIdx.x;
+  const int a = (b % nat) * 64 + lane;
+  b /= nat;
+  const int K0 = (b % nkg) * VK;
+  b /= nkg;
+  const int X0 = (b % nxg) * VX;
+  const int l = (DIRECT ? nc : 0) + b / nxg;
+  const double2* row = Lvo + (long)l * naux * nv + min(a, nv - 1);
+  double2 acc[VK * VX];
+#pragma unroll
+  for (int q = 0; q < VK * VX; ++q) acc[q] = czero();
+  const int per = (naux + 3) / 4, p0 = w * per, p1 = min(naux, p0 + per);
+  for (int pb = p0; pb < p0 + per; pb += VP) {   // the same trips in every wave (barriers below)
+    __syncthreads();
+    for (int e = lane; e < VP * VK * VX; e += 64) {
+      const int p = pb + e / (VK * VX), q = e % (VK * VX), K = K0 + q / VX, x = X0 + q % VX;
+      co[w][e / (VK * VX)][q] = (p < p1 && K < nc && x < nx) ? Loo[((long)p * o + K) * o + x0 + x] : czero();
     }
-    Vt[e] = acc;
+    __syncthreads();
+    const int n = min(VP, p1 - pb);
+    for (int u = 0; u < n; u += 4) {
+      double2 v[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[t] = row[(long)min(pb + u + t, naux - 1) * nv];   // past the end: zero coefficients
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int q = 0; q < VK * VX; ++q) acc[q] = cadd(acc[q], cmul(co[w][u + t][q], v[t]));
+    }
+  }
+  // waves 1..3 hand their sums over through LDS, six at a time
+  double2* red = &co[0][0][0];   // 3 x 64 x VX
+  for (int g = 0; g < VK; ++g) {
+    __syncthreads();
+    if (w > 0)
+#pragma unroll
+      for (int q = 0; q < VX; ++q) {
+        double2 t = czero();
+#pragma unroll
+        for (int gg = 0; gg < VK; ++gg)
+          if (gg == g) t = acc[gg * VX + q];
+        red[((w - 1) * VX + q) * 64 + lane] = t;
+      }
+    __syncthreads();
+    if (w == 0 && a < nv && K0 + g < nc)
+#pragma unroll
+      for (int q = 0; q < VX; ++q) {
+        if (X0 + q >= nx) break;
+        double2 t = czero();
+#pragma unroll
+        for (int gg = 0; gg < VK; ++gg)
+          if (gg == g) t = acc[gg * VX + q];
+        for (int s = 0; s < 3; ++s) t = cadd(t, red[(s * VX + q) * 64 + lane]);
+        const int I = DIRECT ? X0 + q : l, j = DIRECT ? l - nc : X0 + q;
+        double2* out = Vt + (((long)I * no + j) * nc + K0 + g) * nv + a;
+        *out = DIRECT ? t : csub(*out, t);
+      }
   }
 }
 
@@ -485,13 +724,17 @@ adc2_status wbuild(adc2_handle h, double2* W, hipStream_t st) {
   hipError_t e = dmalloc(h, &dpairs, sizeof(int2) * npairs);
   if (e == hipSuccess) e = dmalloc(h, &epart, sizeof(double) * nwblk);
   if (e == hipSuccess) e = hipMemcpyAsync(dpairs, pairs.data(), sizeof(int2) * npairs, hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) {
+  adc2_status rc = ADC2_OK;
+  bool done = false;
+  if (e == hipSuccess) rc = wbuild_rns(h, dpairs, W, epart, &done, st);
+  if (e == hipSuccess && rc == ADC2_OK && !done) {
     k_wbuild<<<(unsigned)nwblk, 256, 0, st>>>(h->Lvo, h->eps, dpairs, npairs, d.naux, nv, o, W, epart);
     e = hipGetLastError();
   }
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   dfree(h, dpairs);
   dfree(h, epart);
+  if (rc != ADC2_OK) return rc;
   if (e != hipSuccess) {
     set_error(std::string("wbuild: ") + hipGetErrorString(e));
     return e == hipErrorOutOfMemory ? ADC2_ERR_OOM : ADC2_ERR_HIP;
@@ -572,7 +815,6 @@ adc2_status build_m11(adc2_handle h, hipStream_t st) {
   SETUP_HIP(dmalloc(h, &dsgn, sizeof(double) * std::max<size_t>(1, sgn.size())));
   SETUP_HIP(dmalloc(h, &doff, sizeof(int) * off.size()));
   SETUP_HIP(dmalloc(h, &W, sizeof(double2) * std::max<long>(1, (long)npairs * nv2)));
-  SETUP_HIP(dmalloc(h, &part, sizeof(double2) * part_len));
   SETUP_HIP(dmalloc(h, &Bm, sizeof(double2) * nv2));
   SETUP_HIP(dmalloc(h, &E, sizeof(double2) * nc * nc * nv2));
   SETUP_HIP(dmalloc(h, &G2, sizeof(double2) * nc * nc * nv2));
@@ -585,22 +827,33 @@ adc2_status build_m11(adc2_handle h, hipStream_t st) {
   SETUP_HIP(hipMemcpyAsync(doff, off.data(), sizeof(int) * off.size(), hipMemcpyHostToDevice, st));
 
   // MP2 amplitudes / W for every occupied pair
+  bool done_w = false, done_i = false, done_iii = false;
   if (npairs > 0) {
-    k_wbuild<<<(unsigned)nwblk, 256, 0, st>>>(h->Lvo, h->eps, dpairs, npairs, naux, nv, o, W, epart);
-    SETUP_HIP(hipGetLastError());
+    adc2_status rc = wbuild_rns(h, dpairs, W, epart, &done_w, st);
+    if (rc == ADC2_OK && !done_w) {
+      k_wbuild<<<(unsigned)nwblk, 256, 0, st>>>(h->Lvo, h->eps, dpairs, npairs, naux, nv, o, W, epart);
+      SETUP_HIP(hipGetLastError());
+    }
+    if (rc == ADC2_OK) rc = pair_terms_rns(h, W, dpairs, npairs, dpidx, Bm, E, &done_i, &done_iii, st);
+    if (rc != ADC2_OK) {
+      hipStreamSynchronize(st);
+      cleanup();
+      return rc;
+    }
   }
+  if (!done_i || !done_iii) SETUP_HIP(dmalloc(h, &part, sizeof(double2) * part_len));
   // term (i): B = sum_{k<l} tau^{kl} W^{kl H}
-  if (npairs > 0) {
+  if (npairs > 0 && !done_i) {
     dim3 g(nb * nb * nsplit_i, 1);
     k_pairc<<<g, 256, 0, st>>>(W, h->eps, dent, dsgn, doff, o, nv, nsplit_i, part);
     SETUP_HIP(hipGetLastError());
     k_sum_splits<<<grid_for(nv2), 256, 0, st>>>(part, nsplit_i, nv2, 1, Bm);
     SETUP_HIP(hipGetLastError());
-  } else {
+  } else if (npairs == 0) {
     SETUP_HIP(hipMemsetAsync(Bm, 0, sizeof(double2) * nv2, st));
   }
   // term (iii): E^{IJ} = sum_k tau^{Ik} W^{Jk H}
-  {
+  if (!done_iii) {
     dim3 g(nb * nb * nsplit_iii, nc * nc);
     k_pairc<<<g, 256, 0, st>>>(W, h->eps, dent, dsgn, doff + 1, o, nv, nsplit_iii, part);
     SETUP_HIP(hipGetLastError());
@@ -611,16 +864,36 @@ adc2_status build_m11(adc2_handle h, hipStream_t st) {
   k_qterm<<<nc * nc * o, 256, 0, st>>>(W, h->eps, dpidx, nc, o, nv, qpart);
   SETUP_HIP(hipGetLastError());
   // first order
-  k_first_aIJb<<<nc * nc * nb * nb, 256, 0, st>>>(h->Lvo, nc, nv, naux, h->M11);
-  SETUP_HIP(hipGetLastError());
+  {
+    const long lds = (long)naux * nv;
+    const RnsSrc A{h->Lvo, nv, lds, 1, 1 << 30, 0, nv, false}, B{h->Lvo, nv, lds, 1, 1 << 30, 0, nv, true};
+    bool done = false;
+    const adc2_status rc = rns_product(h, A, (int)ns, B, (int)ns, naux, rns_rows(h->M11, ns), rns_vs_tile(ns, ns), &done, st);
+    if (rc != ADC2_OK) {
+      hipStreamSynchronize(st);
+      cleanup();
+      return rc;
+    }
+    if (!done) {
+      k_first_aIJb<<<nc * nc * nb * nb, 256, 0, st>>>(h->Lvo, nc, nv, naux, h->M11);
+      SETUP_HIP(hipGetLastError());
+    }
+  }
   {
     const int nbi = (int)((nv2 + TM - 1) / TM);
     const int nbj = (nc * nc + TN - 1) / TN;
     k_first_abJI<<<nbi * nbj, 256, 0, st>>>(h->Lvv, h->Loo, nc, nv, naux, o, G2);
     SETUP_HIP(hipGetLastError());
   }
-  k_vint<<<grid_for((long)nc * d.no * nc * nv), 256, 0, st>>>(h->Lvo, h->Loo, nc, d.no, nv, naux, o, h->Vt);
-  SETUP_HIP(hipGetLastError());
+  {
+    const long nat = (nv + 63) / 64, nkg = (nc + VK - 1) / VK;
+    k_vint<true><<<(unsigned)(d.no * nat * nkg * ((nc + VX - 1) / VX)), 256, 0, st>>>(h->Lvo, h->Loo, nc, d.no, nv, naux,
+                                                                                     o, h->Vt);
+    SETUP_HIP(hipGetLastError());
+    k_vint<false><<<(unsigned)(nc * nat * nkg * ((d.no + VX - 1) / VX)), 256, 0, st>>>(h->Lvo, h->Loo, nc, d.no, nv, naux,
+                                                                                      o, h->Vt);
+    SETUP_HIP(hipGetLastError());
+  }
 
   // Q and E_MP2 reductions on the host (small)
   std::vector<double2> hq(nc * nc * o);

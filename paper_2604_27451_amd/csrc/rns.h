@@ -116,7 +116,8 @@ adc2_status rns_join(const RnsMat& A, const RnsMat& B, int col0, int ncols, int 
 // dst(i, j) = sum_k A(i, k) B(j, k), i < M, j < N, in chunks of rows whose work
 // space is at most 2 h->rns_target (or that of one 256 x 128 tile).  *done = false (nothing written, no error)
 // where the caller's own FP64 MFMA kernel, of `rate` flop/s at such sizes, is the
-// faster one or the memory is not to be had: the caller then uses that.
+// faster one (rate 0: the caller has asked rns_pays itself) or the memory is
+// not to be had: the caller then uses that.
 constexpr double RNS_VS_BIG = 60e12;    // 128 x 128 tiles (k_bgemm)
 // 64 x 64 tiles (gemm_rr): 25 TFLOP/s from two tiles a CU on, in proportion
 // below (0.32 measured on 4 tiles)

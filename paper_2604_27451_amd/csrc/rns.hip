@@ -622,7 +622,7 @@ void rns_release(adc2_handle h) {
 adc2_status rns_product(adc2_handle h, const RnsSrc& A, int M, const RnsSrc& B, int N, int K, const RnsDst& dst,
                         double rate, bool* done, hipStream_t st) {
   *done = false;
-  if (M <= 0 || N <= 0 || K <= 0 || !rns_pays(h, M, N, K, rate)) return ADC2_OK;
+  if (M <= 0 || N <= 0 || K <= 0 || h->rns_off || (rate > 0.0 && !rns_pays(h, M, N, K, rate))) return ADC2_OK;
   // K-splits: within the INT32 range, and enough tiles for two a CU
   const long tiles = (long)RNS_PL * rcdiv(M, 256) * rcdiv(N, 128);
   const int nkc = rcdiv(K, RNS_KC);

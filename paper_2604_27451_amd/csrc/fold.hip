@@ -864,7 +864,7 @@ adc2_status fold_davidson(adc2_handle h, int k, const adc2_dav_opts* opt, const 
   for (it = 1; it <= max_iter; ++it) {
     // ---- projected nonlinear problem: one workgroup per root, lowest eigenvalue of H11 first ----
     const auto tp0 = now();
-    FD_TRY(dav_heevj(Hd, s, JMAX, hw, Gw, JMAX, st));
+    FD_TRY(dav_heevj(Hd, s, JMAX, hw, nullptr, JMAX, st));
     // a pole at |x| >= 1.05 has r = |x| - sqrt(x^2 - 1) < 0.73 and r^126 < 1e-17,
     // so at most 126 Chebyshev terms: with the shifted inverse, roots closer
     // to min D than about 0.025 (min D - w0) are out of reach of this solver

@@ -95,7 +95,34 @@ __device__ int fold_coeffs(const FoldMap& r, double omega, int mmax, double* b, 
 // expansion at omega, 3 more moments needed (need), 4 below the shifted
 // map's range, 5 eigensolve did not converge, 6 branch beyond the space.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_fold_solve(const double2* __restrict__ H, const double2* __restrict__ K,
+// Hermitian part of the s x s matrix in S.ar / S.ai (ends with a barrier)
+__device__ __forceinline__ void fold_hermitian(JacobiSmem& S, int s) {
+  for (int e = threadIdx.x; e < JMAX * JMAX; e += JTHR) {
+    const int i = e >> 6, l = e & 63;
+    if (i >= s || l >= s) continue;
+    if (i < l) {
+      const double xr = 0.5 * (S.ar[i][l] + S.ar[l][i]), xi = 0.5 * (S.ai[i][l] - S.ai[l][i]);
+      S.ar[i][l] = xr;
+      S.ai[i][l] = xi;
+      S.ar[l][i] = xr;
+      S.ai[l][i] = -xi;
+    } else if (i == l) {
+      S.ai[i][i] = 0.0;
+    }
+  }
+  __syncthreads();
+}
+
+// S.zt[c][r] = Zp[r][c], the stored warm x warm eigenvectors padded with the identity to s
+__device__ __forceinline__ void fold_load_z(JacobiSmem& S, const double2* Zg, int warm, int s) {
+  for (int e = threadIdx.x; e < JMAX * JMAX; e += JTHR) {
+    const int r = e >> 6, c = e & 63;
+    if (r >= s || c >= s) continue;
+    S.zt[c][r] = (r < warm && c < warm) ? Zg[(long)r * JMAX + c] : make_double2(r == c ? 1.0 : 0.0, 0.0);
+  }
+}
+
+__global__ __launch_bounds__(JTHR) void k_fold_solve(const double2* __restrict__ H, const double2* __restrict__ K,
                                                      int s, int Mmax, FoldMap map, double Dmin, double hi0,
                                                      double tol, const double* __restrict__ hw,
                                                      const FoldEntry* __restrict__ ent,
@@ -105,7 +132,6 @@ __global__ __launch_bounds__(256) void k_fold_solve(const double2* __restrict__ 
   __shared__ double cb[FOLD_MM], ce[FOLD_MM], cg[FOLD_MM], chh[FOLD_MM];
   __shared__ double2 ys[JMAX];
   __shared__ double wsh[JMAX];
-  __shared__ double red2[256];
   __shared__ int sM, sflag, sdone;
   __shared__ double swv, slo, shi, swlo, slo0;
   const int tid = threadIdx.x;
@@ -159,122 +185,134 @@ __global__ __launch_bounds__(256) void k_fold_solve(const double2* __restrict__ 
       break;
     }
     const int M = sM;
-    // G = H11 + sum_m g_m K_m into S.ar / S.ai
-    for (int e = tid; e < s * s; e += 256) {
-      const int i = e / s, l = e % s;
+    // G = H11 + sum_m g_m K_m into S.ar / S.ai, its Hermitian part
+    for (int e = tid; e < JMAX * JMAX; e += JTHR) {
+      const int i = e >> 6, l = e & 63;
+      if (i >= s || l >= s) continue;
       double2 a = H[(long)i * JMAX + l];
+      const double2* k = K + (long)i * JMAX + l;
+#pragma unroll 8
       for (int m = 0; m < M; ++m) {
-        const double2 k = K[((long)m * JMAX + i) * JMAX + l];
-        a.x += cg[m] * k.x;
-        a.y += cg[m] * k.y;
+        const double2 v = k[(long)m * JMAX * JMAX];
+        a.x += cg[m] * v.x;
+        a.y += cg[m] * v.y;
       }
       S.ar[i][l] = a.x;
       S.ai[i][l] = a.y;
     }
     __syncthreads();
-    // Hermitian part
-    for (int e = tid; e < s * s; e += 256) {
-      const int i = e / s, l = e % s;
-      if (i < l) {
-        const double xr = 0.5 * (S.ar[i][l] + S.ar[l][i]), xi = 0.5 * (S.ai[i][l] - S.ai[l][i]);
-        S.ar[i][l] = xr;
-        S.ai[i][l] = xi;
-        S.ar[l][i] = xr;
-        S.ai[l][i] = -xi;
-      } else if (i == l) {
-        S.ai[i][i] = 0.0;
-      }
-    }
-    __syncthreads();
+    fold_hermitian(S, s);
     if (warm > 0) {
       // G <- Zp^H G Zp, Zp = the stored eigenvectors padded with the identity
-      for (int e = tid; e < s * s; e += 256) {
-        const int i = e / s, c = e % s;
-        double2 a = make_double2(0.0, 0.0);
-        for (int l = 0; l < s; ++l) {
-          const double2 z = (l < warm && c < warm) ? Zg[(long)l * JMAX + c] : make_double2(l == c ? 1.0 : 0.0, 0.0);
-          a = cadd(a, cmul(make_double2(S.ar[i][l], S.ai[i][l]), z));
-        }
-        S.zs[i][c] = a;
+      // (column c of Zp into S.zt[c], then G Zp, then the product from the left)
+      fold_load_z(S, Zg, warm, s);
+      __syncthreads();
+      double2 t[4];   // this thread's entries of G Zp
+  #pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int e = tid + u * JTHR, i = e & 63, c = e >> 6;
+        double2 a = czero();
+        if (i < s && c < s)
+          for (int l = 0; l < s; ++l) a = cadd(a, cmul(make_double2(S.ar[i][l], S.ai[i][l]), S.zt[c][l]));
+        t[u] = a;
       }
       __syncthreads();
-      for (int e = tid; e < s * s; e += 256) {
-        const int r = e / s, c = e % s;
-        double2 a = make_double2(0.0, 0.0);
-        for (int i = 0; i < s; ++i) {
-          const double2 z = (i < warm && r < warm) ? Zg[(long)i * JMAX + r] : make_double2(i == r ? 1.0 : 0.0, 0.0);
-          a = cadd(a, cmul(cconj(z), S.zs[i][c]));
-        }
-        S.ar[r][c] = a.x;
-        S.ai[r][c] = a.y;
-      }
-      __syncthreads();
-      for (int e = tid; e < s * s; e += 256) {
-        const int i = e / s, l = e % s;
-        if (i < l) {
-          const double xr = 0.5 * (S.ar[i][l] + S.ar[l][i]), xi = 0.5 * (S.ai[i][l] - S.ai[l][i]);
-          S.ar[i][l] = xr;
-          S.ai[i][l] = xi;
-          S.ar[l][i] = xr;
-          S.ai[l][i] = -xi;
-        } else if (i == l) {
-          S.ai[i][i] = 0.0;
+  #pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int e = tid + u * JTHR, i = e & 63, c = e >> 6;
+        if (i < s && c < s) {
+          S.ar[i][c] = t[u].x;
+          S.ai[i][c] = t[u].y;
         }
       }
       __syncthreads();
+  #pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int e = tid + u * JTHR, c = e & 63, r = e >> 6;
+        double2 a = czero();
+        if (r < s && c < s)
+          for (int i = 0; i < s; ++i) a = cadd(a, cmul(cconj(S.zt[r][i]), make_double2(S.ar[i][c], S.ai[i][c])));
+        t[u] = a;
+      }
+      __syncthreads();
+  #pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int e = tid + u * JTHR, c = e & 63, r = e >> 6;
+        if (r < s && c < s) {
+          S.ar[r][c] = t[u].x;
+          S.ai[r][c] = t[u].y;
+        }
+      }
+      __syncthreads();
+      fold_hermitian(S, s);
     }
-    jacobi_lds(S, s);
+    jacobi_lds<true>(S, s);
     if (!S.done) {
       status = 5;
       if (tid == 0) R.status = 5;
       break;
     }
-    for (int i = tid; i < s; i += 256) wsh[i] = S.ar[S.perm[i]][S.perm[i]];
+    if (tid < s) wsh[tid] = S.ar[S.perm[tid]][S.perm[tid]];
     __syncthreads();
-    // eigenvectors of G in ascending order: Z = Zp Z' (into S.ar / S.ai), then to the slot
-    for (int e = tid; e < s * s; e += 256) {
-      const int r = e / s, c = e % s;
-      double2 a;
-      if (warm > 0) {
-        a = make_double2(0.0, 0.0);
-        for (int i = 0; i < s; ++i) {
-          const double2 z = (r < warm && i < warm) ? Zg[(long)r * JMAX + i] : make_double2(r == i ? 1.0 : 0.0, 0.0);
-          a = cadd(a, cmul(z, S.zs[i][S.perm[c]]));
-        }
-      } else {
-        a = S.zs[r][S.perm[c]];
+    // eigenvectors of G in ascending order: Z = Zp Z' (Zp through S.ar / S.ai, then
+    // Z in its place), then to the slot
+    for (int e = tid; e < JMAX * JMAX; e += JTHR) {
+      const int r = e >> 6, c = e & 63;
+      if (r >= s || c >= s) continue;
+      const double2 z = (r < warm && c < warm) ? Zg[(long)r * JMAX + c] : make_double2(r == c ? 1.0 : 0.0, 0.0);
+      S.ar[r][c] = z.x;
+      S.ai[r][c] = z.y;
+    }
+    __syncthreads();
+    double2 zn[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int e = tid + u * JTHR, r = e & 63, c = e >> 6;
+      double2 a = czero();
+      if (r < s && c < s) {
+        const double2* z = S.zt[S.perm[c]];
+        if (r < warm)
+          for (int i = 0; i < warm; ++i) a = cadd(a, cmul(make_double2(S.ar[r][i], S.ai[r][i]), z[i]));
+        else
+          a = z[r];
       }
-      S.ar[r][c] = a.x;
-      S.ai[r][c] = a.y;
+      zn[u] = a;
     }
     __syncthreads();
-    for (int e = tid; e < s * s; e += 256) {
-      const int r = e / s, c = e % s;
-      Zg[(long)r * JMAX + c] = make_double2(S.ar[r][c], S.ai[r][c]);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int e = tid + u * JTHR, r = e & 63, c = e >> 6;
+      if (r < s && c < s) {
+        S.ar[r][c] = zn[u].x;
+        S.ai[r][c] = zn[u].y;
+      }
     }
-    for (int i = tid; i < s; i += 256) ys[i] = make_double2(S.ar[i][j], S.ai[i][j]);
+    __syncthreads();
+    for (int e = tid; e < JMAX * JMAX; e += JTHR) {
+      const int r = e >> 6, c = e & 63;
+      if (r < s && c < s) Zg[(long)r * JMAX + c] = make_double2(S.ar[r][c], S.ai[r][c]);
+    }
+    if (tid < s) ys[tid] = make_double2(S.ar[tid][j], S.ai[tid][j]);
     warm = s;
     __syncthreads();
     // |x2|^2 = y^H (sum_m h_m K_m) y
-    double acc = 0.0;
-    for (int e = tid; e < s * s; e += 256) {
-      const int i = e / s, l = e % s;
+    double acc = 0.0, zero = 0.0;
+    for (int e = tid; e < JMAX * JMAX; e += JTHR) {
+      const int i = e >> 6, l = e & 63;
+      if (i >= s || l >= s) continue;
       double2 kk = make_double2(0.0, 0.0);
+      const double2* k = K + (long)i * JMAX + l;
+#pragma unroll 8
       for (int m = 0; m < M; ++m) {
-        const double2 k = K[((long)m * JMAX + i) * JMAX + l];
-        kk.x += chh[m] * k.x;
-        kk.y += chh[m] * k.y;
+        const double2 v = k[(long)m * JMAX * JMAX];
+        kk.x += chh[m] * v.x;
+        kk.y += chh[m] * v.y;
       }
       acc += cmul(cconj(ys[i]), cmul(kk, ys[l])).x;
     }
-    red2[tid] = acc;
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-      if (tid < st) red2[tid] += red2[tid + st];
-      __syncthreads();
-    }
+    jacobi_sum2(S, acc, zero);
     if (tid == 0) {
-      const double n2 = red2[0];
+      const double n2 = acc;
       const double wv = swv;
       const double f = wsh[j] - wv;
       if (f > 0.0) slo = fmax(slo, wv);
@@ -294,7 +332,7 @@ __global__ __launch_bounds__(256) void k_fold_solve(const double2* __restrict__ 
       if (!sdone) swv = wn;
     }
     wrote = true;
-    for (int i = tid; i < s; i += 256) Ybr[(long)E.slot * JMAX + i] = ys[i];
+    if (tid < s) Ybr[(long)E.slot * JMAX + tid] = ys[tid];
     __syncthreads();
     if (sdone) break;
   }
@@ -599,7 +637,7 @@ adc2_status fold_solve_launch(const double2* H, const double2* K, int s, int Mma
     set_error("adc2_davidson (folded): projected problem size out of range");
     return ADC2_ERR_ARG;
   }
-  k_fold_solve<<<n, 256, 0, st>>>(H, K, s, Mmax, map, Dmin, hi0, tol, hw, ent, res, Ybr, Zbr, bnd);
+  k_fold_solve<<<n, JTHR, 0, st>>>(H, K, s, Mmax, map, Dmin, hi0, tol, hw, ent, res, Ybr, Zbr, bnd);
   ADC2_CHECK_LAUNCH();
   return ADC2_OK;
 }

@@ -282,12 +282,15 @@ adc2_status dav_unit_guess(double2* V, int g, long dim, const int* idx, hipStrea
 // the parallel cyclic Jacobi of jacobi.h; ascending eigenvalues w[n] and
 // eigenvectors as columns of Z (row-major, ldz).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_heevj(const double2* __restrict__ G, int n, int ldg,
-                                                double* __restrict__ w, double2* __restrict__ Z, int ldz) {
+// Z may be NULL: eigenvalues only.
+template <bool VEC>
+__global__ __launch_bounds__(JTHR) void k_heevj(const double2* __restrict__ G, int n, int ldg, double* __restrict__ w,
+                                                double2* __restrict__ Z, int ldz) {
   __shared__ JacobiSmem S;
   const int tid = threadIdx.x;
-  for (int e = tid; e < n * n; e += 256) {
-    const int i = e / n, j = e % n;
+  for (int e = tid; e < JMAX * JMAX; e += JTHR) {
+    const int i = e >> 6, j = e & 63;
+    if (i >= n || j >= n) continue;
     double x, y;
     if (i <= j) {
       const double2 g = G[(long)i * ldg + j];
@@ -302,12 +305,13 @@ __global__ __launch_bounds__(256) void k_heevj(const double2* __restrict__ G, in
     S.ai[i][j] = y;
   }
   __syncthreads();
-  jacobi_lds(S, n);
-  for (int i = tid; i < n; i += 256) w[i] = S.ar[S.perm[i]][S.perm[i]];
-  for (int e = tid; e < n * n; e += 256) {
-    const int r = e / n, c = e % n;
-    Z[(long)r * ldz + c] = S.zs[r][S.perm[c]];
-  }
+  jacobi_lds<VEC>(S, n);
+  if (tid < n) w[tid] = S.ar[S.perm[tid]][S.perm[tid]];
+  if (VEC)
+    for (int e = tid; e < JMAX * JMAX; e += JTHR) {
+      const int r = e >> 6, c = e & 63;
+      if (r < n && c < n) Z[(long)r * ldz + c] = S.zt[S.perm[c]][r];
+    }
 }
 
 adc2_status dav_heevj(const double2* G, int n, int ldg, double* w, double2* Z, int ldz, hipStream_t st) {
@@ -315,7 +319,8 @@ adc2_status dav_heevj(const double2* G, int n, int ldg, double* w, double2* Z, i
     set_error("dav_heevj: subspace dimension out of range");
     return ADC2_ERR_ARG;
   }
-  k_heevj<<<1, 256, 0, st>>>(G, n, ldg, w, Z, ldz);
+  if (Z) k_heevj<true><<<1, JTHR, 0, st>>>(G, n, ldg, w, Z, ldz);
+  else k_heevj<false><<<1, JTHR, 0, st>>>(G, n, ldg, w, Z, ldz);
   ADC2_CHECK_LAUNCH();
   return ADC2_OK;
 }

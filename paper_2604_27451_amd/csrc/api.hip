@@ -292,7 +292,7 @@ static hipError_t dmalloc_once(adc2_handle h, void** p, size_t bytes) {
 // again without it (that engine is an option, the request is not).
 hipError_t dmalloc_raw(adc2_handle h, void** p, size_t bytes) {
   hipError_t e = dmalloc_once(h, p, bytes);
-  if (e == hipErrorOutOfMemory && h && (h->rns_lvo || h->rns_lvt || h->rns_ws)) {
+  if (e == hipErrorOutOfMemory && h && (h->rns_lvo || h->rns_lvt || h->rns_ws || h->rns_tmp)) {
     (void)hipGetLastError();
     rns_release(h);
     h->rns_off = true;
@@ -412,11 +412,13 @@ adc2_status adc2_setup(const void* L, const double* eps, int nc, int no, int nv,
   }
   rc = build_m11(h, st);
   if (rc == ADC2_OK) rc = build_lvt(h, st);
+  if (rc == ADC2_OK) rc = rns_build_static(h, true, st);
   if (rc == ADC2_OK && hipStreamSynchronize(st) != hipSuccess) rc = fail(ADC2_ERR_HIP, "adc2_setup: sync failed");
   if (rc != ADC2_OK) {
     free_handle(h);
     return rc;
   }
+  rns_tmp_release(h);
   *out = h;
   return ADC2_OK;
 #undef SETUP_TRY

@@ -105,6 +105,9 @@ struct adc2_handle_s {
   char* rns_lvt = nullptr;  // residues of LvT (rows P, K = (j,d)), then their exponents
   char* rns_ws = nullptr;
   size_t rns_ws_bytes = 0;
+  bool rns_setup = false;   // the static operands were built by adc2_setup
+  char* rns_tmp = nullptr;  // work space of the general products, held during an entry point
+  size_t rns_tmp_bytes = 0;
   size_t rns_target = size_t(3) << 30;   // bytes a chunk's work space aims at (environment ADC2_RNS_MB)
   // method: ADC2_METHOD_ADC2 or ADC2_METHOD_ADC2X (first-order doubles block, adc2x.hip)
   int method = 0;
@@ -163,6 +166,9 @@ adc2_status ensure_ws_b3(adc2_handle h, int m);
 adc2_status ensure_ws(adc2_handle h, int m, bool zb = true);
 // gives back what the residue engine holds on h
 void rns_release(adc2_handle h);
+void rns_tmp_release(adc2_handle h);
+// the residue engine's static operands of the sigma, where the size rule may use them
+adc2_status rns_build_static(adc2_handle h, bool at_setup, hipStream_t st);
 // K-split count of the Y-build by the size rule for h's form and engine at block size m
 int ysplit_rule(adc2_handle h, int m);
 adc2_status unpack_weighted(adc2_handle h, int m, const double2* xin, const double* wts, hipStream_t st);

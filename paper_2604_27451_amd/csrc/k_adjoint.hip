@@ -918,6 +918,7 @@ adc2_status omega_backward(adc2_handle h, int m, const double2* X, const double*
   auto release = [&]() {
     for (void* p : owned) dfree(h, p);
     owned.clear();
+    rns_tmp_release(h);
   };
   auto alloc = [&](void** p, size_t bytes) -> adc2_status {
     *p = nullptr;

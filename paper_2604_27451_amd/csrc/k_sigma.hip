@@ -124,6 +124,167 @@ __global__ __launch_bounds__(256) void k_xbuild(const double2* __restrict__ x, l
   });
 }
 
+// ---------------------------------------------------------------------------
+// X-build and back-contraction of at most 32 rows (mI)
+// ---------------------------------------------------------------------------
+// Both read Lvv once and are bound by that where rows are few; 64-row tiles do
+// the matrix work of 64 rows whatever their number (nc=6 no=120 nv=600
+// naux=3000, two vectors: 8.9 and 9.0 ms).  Here a wave multiplies RT tiles of 16
+// rows with 64 columns of Lvv on the 16x16x4 FP64 MFMA, operands straight from
+// global memory: a lane's element of a column tile is Lvv[column][k] with four
+// k of a column in one 64-byte piece and four steps of k unrolled, so whole lines are
+// used; the row operand stays in cache.
+//
+// acc[t][c] += A(rows 16 t + .., k) B(k, columns 16 c + ..) over k < K; a(t, k) and
+// b(c, k) give this lane's elements, zero past the ends.
+template <int RT, class FA, class FB>
+__device__ __forceinline__ void thin_mma(int K, d4 (&re)[RT][4], d4 (&im)[RT][4], FA&& fa, FB&& fb) {
+  const int lk = (threadIdx.x & 63) >> 4;
+  for (int k0 = 0; k0 < K; k0 += 16) {
+    double2 a[4][RT], b[4][4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+#pragma unroll
+      for (int t = 0; t < RT; ++t) a[u][t] = fa(t, k0 + 4 * u + lk);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) b[u][c] = fb(c, k0 + 4 * u + lk);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          re[t][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][t].x, b[u][c].x, re[t][c], 0, 0, 0);
+          re[t][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[u][t].y, b[u][c].y, re[t][c], 0, 0, 0);
+          im[t][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][t].x, b[u][c].y, im[t][c], 0, 0, 0);
+          im[t][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][t].y, b[u][c].x, im[t][c], 0, 0, 0);
+        }
+  }
+}
+
+// Where the thin kernels are the faster ones: Lvv of at least 2^23 entries (few
+// workgroups below: nc=6 no=10 nv=40 naux=150, one vector, 14 and 16 us against 13
+// and 13 on 64-row tiles) for up to 16 rows, 2^25 for up to 32 (nc=6 no=12 nv=100
+// naux=300, four vectors: back-contraction 78 us against 45).
+static bool thin_rows(const Dims& d, int rows) {
+  const double lvv = (double)d.naux * d.nv * d.nv;
+  return rows <= 16 ? lvv >= 8388608.0 : rows <= 32 && lvv >= 33554432.0;
+}
+
+template <class TO, int RT>
+__global__ __launch_bounds__(256) void k_xbuild_thin(const double2* __restrict__ x, long dim, int nc, int nv, int naux,
+                                                     int nrows, const double2* __restrict__ Lvv, TO* __restrict__ X) {
+  const int lane = threadIdx.x & 63, li = lane & 15;
+  const long ncol = (long)naux * nv;
+  const long j0 = (xcd_remap(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6)) * 64;
+  if (j0 >= ncol) return;
+  const double2* pa[RT];
+  bool oka[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    const int mi = 16 * t + li;
+    oka[t] = mi < nrows;
+    const int mm = oka[t] ? mi : 0, m = mm / nc;
+    pa[t] = x + (long)m * dim + (long)(mm - m * nc) * nv;
+  }
+  const double2* pb[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) pb[c] = Lvv + min(j0 + 16 * c + li, ncol - 1) * nv;   // past the end: never stored
+  d4 re[RT][4], im[RT][4];
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) re[t][c] = im[t][c] = d4{0.0, 0.0, 0.0, 0.0};
+  thin_mma<RT>(
+      nv, re, im, [&](int t, int k) { return oka[t] && k < nv ? pa[t][k] : czero(); },
+      [&](int c, int k) { return k < nv ? pb[c][k] : czero(); });
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int mi = 16 * t + (lane >> 4) + 4 * r;
+        const long j = j0 + 16 * c + li;
+        if (mi < nrows && j < ncol) X[(long)mi * ncol + j] = from_d2<TO>(make_double2(re[t][c][r], im[t][c][r]));
+      }
+}
+
+// part[split][mI][a] = sum_{P in split} sum_c Y[mI][P][c] Lvv[P][a][c]: a workgroup
+// owns a split and 64 values of a, its waves share the split's P.
+template <int RT>
+__global__ __launch_bounds__(256) void k_backc_thin(const double2* __restrict__ Y, const double2* __restrict__ Lvv,
+                                                    int nrows, int nv, int naux, int nsplit, double2* __restrict__ part) {
+  __shared__ double2 red[3][64][17];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15;
+  const int nba = (nv + 63) / 64;
+  const int split = blockIdx.x / nba, a0 = (blockIdx.x % nba) * 64;
+  const int per = (naux + nsplit - 1) / nsplit;
+  const int P0 = split * per, P1 = min(naux, P0 + per);
+  d4 re[RT][4], im[RT][4];
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) re[t][c] = im[t][c] = d4{0.0, 0.0, 0.0, 0.0};
+  for (int P = P0 + w; P < P1; P += 4) {
+    const double2* pb[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) pb[c] = Lvv + ((long)P * nv + min(a0 + 16 * c + li, nv - 1)) * nv;
+    const double2* pa[RT];
+    bool oka[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      oka[t] = 16 * t + li < nrows;
+      pa[t] = Y + ((long)(oka[t] ? 16 * t + li : 0) * naux + P) * nv;
+    }
+    thin_mma<RT>(
+        nv, re, im, [&](int t, int k) { return oka[t] && k < nv ? pa[t][k] : czero(); },
+        [&](int c, int k) { return k < nv ? pb[c][k] : czero(); });
+  }
+  double2* out = part + (long)split * nrows * nv;
+  for (int t = 0; t < RT; ++t) {   // the four waves' sums, in order, one row tile at a time
+    __syncthreads();
+    if (w > 0)
+#pragma unroll
+      for (int tt = 0; tt < RT; ++tt)
+        if (tt == t)
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) red[w - 1][lane][4 * c + r] = make_double2(re[tt][c][r], im[tt][c][r]);
+    __syncthreads();
+    if (w == 0)
+#pragma unroll
+      for (int tt = 0; tt < RT; ++tt)
+        if (tt == t)
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              double2 v = make_double2(re[tt][c][r], im[tt][c][r]);
+#pragma unroll
+              for (int q = 0; q < 3; ++q) v = cadd(v, red[q][lane][4 * c + r]);
+              const int mi = 16 * t + (lane >> 4) + 4 * r, a = a0 + 16 * c + li;
+              if (mi < nrows && a < nv) out[(long)mi * nv + a] = v;
+            }
+  }
+}
+
+template <class TO>
+static adc2_status xbuild_launch(const double2* x, const Dims& d, int rows, const double2* Lvv, TO* X, hipStream_t st) {
+  if (thin_rows(d, rows)) {
+    const unsigned nblk = (unsigned)cdiv((long)d.naux * d.nv, 256);
+    if (rows <= 16) k_xbuild_thin<TO, 1><<<nblk, 256, 0, st>>>(x, d.dim, d.nc, d.nv, d.naux, rows, Lvv, X);
+    else k_xbuild_thin<TO, 2><<<nblk, 256, 0, st>>>(x, d.dim, d.nc, d.nv, d.naux, rows, Lvv, X);
+  } else {
+    const long nblk = (long)cdiv(rows, TM) * cdiv((long)d.naux * d.nv, TN);
+    k_xbuild<TO><<<(unsigned)nblk, 256, 0, st>>>(x, d.dim, d.nc, d.nv, d.naux, rows, Lvv, X);
+  }
+  ADC2_CHECK_LAUNCH();
+  return ADC2_OK;
+}
+
 // Y-build A: element (k = (j, d), i = P) = conj(L^P_{d j}) = conj(Lvo[nc+j][P][d]);
 // k runs over j-blocks of cpe chunks (d padded to a multiple of BK).
 template <int NS>
@@ -798,67 +959,75 @@ __global__ __launch_bounds__(256) void k_lvo_transpose(const double2* __restrict
 
 // light sigma1 term, partial over a group of 4 valence j:
 //   Tp[mI][jg][K][c] = sum_{j in group} sum_d conj(<Kd||Ij>) R_{mIj}[c][d]
-//                    = -sum_j sum_d conj(Vt[I][j][K][d]) Rf[mI][j][d][c]
-constexpr int LJG = 4;
-//   Tp[mI][jg][K][c] = sum_{j in group} sum_d conj(<Kd||Ij>) R_{mIj}[c][d]
 //                    = sum_j sum_d conj(Vt[I][j][K][d]) Rt[(j,d)][(mI,c)]
+// One workgroup per (mI, group, 64 values of c): wave w takes the group's j = w,
+// lanes run over c (coalesced), the coefficients are broadcast from LDS, and
+// the four waves' sums are added in order.  Bound by the one read of Rt; small
+// tiles and one j a wave keep short systems and short chunks from running on a
+// few workgroups (nc=6 no=10 nv=40, one vector: 59 us before on 18 workgroups
+// that each walked four j; a chunk of eight rows at nv=300: 0.55 ms).
+constexpr int LJG = 4;
+constexpr int LC = 64;   // columns a workgroup
+constexpr int LD = 64;   // d per staged run of coefficients
 template <class TI>
 __global__ __launch_bounds__(256) void k_light1(const TI* __restrict__ Rt, const double2* __restrict__ Vt, int mI0,
                                                  int nrow, int nc, int no, int nv, double2* __restrict__ Tp) {
-  __shared__ double2 vs[8][256];
-  const int ncb = (nv + 255) / 256;
+  __shared__ double2 vs[LJG][LD][8];
+  const int ncb = (nv + LC - 1) / LC;
   const int njg = (no + LJG - 1) / LJG;
   const int cb = blockIdx.x % ncb;
   const int jg = (blockIdx.x / ncb) % njg;
   const int ml = blockIdx.x / (ncb * njg), mI = mI0 + ml;
   const int I = mI % nc;
-  const int c = cb * 256 + threadIdx.x;
-  const bool cok = c < nv;
-  const int cs = cok ? c : 0;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int c = cb * LC + lane;
+  const int cs = c < nv ? c : 0;
+  const int j = jg * LJG + w;
+  const bool jok = j < no;
   const long ld = (long)nrow * nv;
+  const TI* R = Rt + (long)(jok ? j : 0) * nv * ld + (long)ml * nv + cs;   // R[d*ld]
+  const double2* V = Vt + ((long)I * no + (jok ? j : 0)) * nc * nv;
   for (int K0 = 0; K0 < nc; K0 += 8) {
     double2 acc[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) acc[q] = czero();
-    for (int j = jg * LJG; j < min(no, (jg + 1) * LJG); ++j) {
-      const TI* R = Rt + (long)j * nv * ld + (long)ml * nv;   // R[d*ld + c]
-      const double2* V = Vt + ((long)I * no + j) * nc * nv;
-      for (int dd0 = 0; dd0 < nv; dd0 += 256) {
-        __syncthreads();
-        for (int e = threadIdx.x; e < 8 * 256; e += 256) {
-          const int q = e / 256, dd = e % 256;
-          const int K = K0 + q, d = dd0 + dd;
-          vs[q][dd] = (K < nc && d < nv) ? cconj(V[(long)K * nv + d]) : czero();
-        }
-        __syncthreads();
-        const int dend = min(256, nv - dd0);
-        int dd = 0;
-        // DU loads in flight per thread (16 for complex64 operands, where more loads
-        // in flight paid; 4 for complex128, where the registers would cost occupancy); a lane
-        // past the last column reads column 0 and its sums are never stored
-        constexpr int DU = sizeof(TI) == 8 ? 16 : 4;
-        for (; dd + DU <= dend; dd += DU) {
-          TI r[DU];
+    for (int d0 = 0; d0 < nv; d0 += LD) {
+      __syncthreads();
+      for (int e = lane; e < 8 * LD; e += 64) {
+        const int q = e / LD, dd = e % LD;
+        const int K = K0 + q, d = d0 + dd;
+        vs[w][dd][q] = (jok && K < nc && d < nv) ? cconj(V[(long)K * nv + d]) : czero();
+      }
+      __syncthreads();
+      const int dend = min(LD, nv - d0);
+      // eight loads in flight a lane; past the end of the run the last row is read again and its
+      // coefficients are zero; a lane past the last column reads column 0, its sums are never stored
+      for (int dd = 0; dd < dend; dd += 8) {
+        TI r[8];
 #pragma unroll
-          for (int u = 0; u < DU; ++u) r[u] = R[(long)(dd0 + dd + u) * ld + cs];
+        for (int u = 0; u < 8; ++u) r[u] = R[(long)min(d0 + dd + u, nv - 1) * ld];
 #pragma unroll
-          for (int u = 0; u < DU; ++u) {
-            const double2 x = to_d2(r[u]);
+        for (int u = 0; u < 8; ++u) {
+          const double2 x = to_d2(r[u]);
 #pragma unroll
-            for (int q = 0; q < 8; ++q) acc[q] = cadd(acc[q], cmul(vs[q][dd + u], x));
-          }
-        }
-        for (; dd < dend; ++dd) {
-          const double2 x = to_d2(R[(long)(dd0 + dd) * ld + cs]);
-#pragma unroll
-          for (int q = 0; q < 8; ++q) acc[q] = cadd(acc[q], cmul(vs[q][dd], x));
+          for (int q = 0; q < 8; ++q) acc[q] = cadd(acc[q], cmul(vs[w][dd + u][q], x));
         }
       }
     }
-    if (cok)
+    __syncthreads();
+    double2* red = &vs[0][0][0];   // 3 x 8 x 64
+    if (w > 0)
 #pragma unroll
-      for (int q = 0; q < 8; ++q)
-        if (K0 + q < nc) Tp[(((long)mI * njg + jg) * nc + K0 + q) * nv + c] = acc[q];
+      for (int q = 0; q < 8; ++q) red[((w - 1) * 8 + q) * 64 + lane] = acc[q];
+    __syncthreads();
+    if (w == 0 && c < nv)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        if (K0 + q >= nc) break;
+        double2 t = acc[q];
+        for (int v = 0; v < 3; ++v) t = cadd(t, red[(v * 8 + q) * 64 + lane]);
+        Tp[(((long)mI * njg + jg) * nc + K0 + q) * nv + c] = t;
+      }
   }
 }
 
@@ -997,23 +1166,81 @@ __global__ __launch_bounds__(256) void k_backc(const double2* __restrict__ Y, co
   });
 }
 
-// s1[m][K][a] += sum_split part[split][mK][a] + sum_{I,jg} Tp[mI][jg][K][a]
-__global__ void k_sigma1_finish(const double2* __restrict__ part, int nsplit, const double2* __restrict__ Tp,
-                                int m, int nc, int no, int nv, long dim, double2* __restrict__ sout) {
+// s1[m][K][a] += sum_split part[split][mK][a] - sum_{I,jg} Tp[mI][jg][K][a].
+// One workgroup per 64 entries; its 16 waves share the two lists of partials
+// (a thread per entry walked up to 256 + nc no/4 dependent loads: 72 us at
+// nc=6 no=12 nv=100, four vectors), and their sums are added in order.
+constexpr int FW = 16;
+__global__ __launch_bounds__(64 * FW) void k_sigma1_finish(const double2* __restrict__ part, int nsplit,
+                                                           const double2* __restrict__ Tp, int m, int nc, int no, int nv,
+                                                           long dim, double2* __restrict__ sout) {
+  __shared__ double2 red[FW][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const long total = (long)m * nc * nv;
+  const long e = (long)blockIdx.x * 64 + lane;
+  const bool ok = e < total;
+  const long ec = ok ? e : 0;
   const int njg = (no + LJG - 1) / LJG;
-  for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < total; e += (long)gridDim.x * blockDim.x) {
-    const int a = (int)(e % nv);
-    const int mK = (int)(e / nv);
-    const int mv = mK / nc, K = mK - mv * nc;
-    double2 acc = make_double2(0, 0);
-    for (int sp = 0; sp < nsplit; ++sp) acc = cadd(acc, part[((long)sp * m * nc + mK) * nv + a]);
-    for (int I = 0; I < nc; ++I)
-      for (int jg = 0; jg < njg; ++jg)
-        acc = csub(acc, Tp[((((long)(mv * nc + I)) * njg + jg) * nc + K) * nv + a]);
+  const int a = (int)(ec % nv);
+  const int mK = (int)(ec / nv);
+  const int mv = mK / nc, K = mK - mv * nc;
+  double2 acc = czero();
+#pragma unroll 4
+  for (int sp = w; sp < nsplit; sp += FW) acc = cadd(acc, part[((long)sp * m * nc + mK) * nv + a]);
+  const double2* T = Tp + ((long)mv * nc * njg * nc + K) * nv + a;   // (I, jg) at stride nc nv
+#pragma unroll 4
+  for (int q = w; q < nc * njg; q += FW) acc = csub(acc, T[(long)q * nc * nv]);
+  red[w][lane] = acc;
+  __syncthreads();
+  if (w == 0 && ok) {
+    for (int t = 1; t < FW; ++t) acc = cadd(acc, red[t][lane]);
     double2* p = sout + (long)mv * dim + (long)K * nv + a;
     *p = cadd(*p, acc);
   }
+}
+
+// y[m][row] = sum_k M11[row][k] x[m][k] for the rows of the singles block: a wave
+// owns MVR rows and MVM vectors, lanes along k.  Bound by the read of M11 (64 x 64
+// MFMA tiles put ns/64 workgroups on it: 287 us at ns=1800, ten vectors).
+constexpr int MVR = 4, MVM = 4;
+__global__ __launch_bounds__(256) void k_m11_mv(const double2* __restrict__ M11, int ns, const double2* __restrict__ x,
+                                                long dim, int m, double2* __restrict__ y) {
+  const int lane = threadIdx.x & 63;
+  const int row0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * MVR, m0 = blockIdx.y * MVM;
+  if (row0 >= ns) return;
+  double2 acc[MVR][MVM];
+#pragma unroll
+  for (int r = 0; r < MVR; ++r)
+#pragma unroll
+    for (int q = 0; q < MVM; ++q) acc[r][q] = czero();
+  const double2 *pr[MVR], *px[MVM];   // rows and vectors past the end: the last one again, never stored
+#pragma unroll
+  for (int r = 0; r < MVR; ++r) pr[r] = M11 + (long)min(row0 + r, ns - 1) * ns;
+#pragma unroll
+  for (int q = 0; q < MVM; ++q) px[q] = x + (long)min(m0 + q, m - 1) * dim;
+#pragma unroll 2
+  for (int k = lane; k < ns; k += 64) {
+    double2 a[MVR], b[MVM];
+#pragma unroll
+    for (int r = 0; r < MVR; ++r) a[r] = pr[r][k];
+#pragma unroll
+    for (int q = 0; q < MVM; ++q) b[q] = px[q][k];
+#pragma unroll
+    for (int r = 0; r < MVR; ++r)
+#pragma unroll
+      for (int q = 0; q < MVM; ++q) acc[r][q] = cadd(acc[r][q], cmul(a[r], b[q]));
+  }
+#pragma unroll
+  for (int r = 0; r < MVR; ++r)
+#pragma unroll
+    for (int q = 0; q < MVM; ++q) {
+      double2 v = acc[r][q];
+      for (int off = 32; off > 0; off >>= 1) {
+        v.x += __shfl_xor(v.x, off);
+        v.y += __shfl_xor(v.y, off);
+      }
+      if (lane == 0 && row0 + r < ns && m0 + q < m) y[(long)(m0 + q) * dim + row0 + r] = v;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1188,18 +1415,15 @@ adc2_status ensure_ws(adc2_handle h, int m, bool zb) {
 // ---------------------------------------------------------------------------
 constexpr size_t NOALLOC_SCRATCH_BYTES = size_t(128) << 20;   // adc2_sigma_noalloc's work space
 
-// Which requests take it: those whose work spaces are past the reach of
-// adc2_sigma_noalloc (which runs the MFMA engines, and gives adc2_sigma's
-// results bit for bit), with enough terms per entry in both products to pay
-// for the conversions (32 B written and read per entry of operand and product
-// besides the FP64 image).
-static bool rns_wanted(adc2_handle h, int m) {
-  const Dims& d = h->d;
-  const long kx = d.naux, ky = (long)d.no * d.nv;
-  if (h->prec != ADC2_FP64 || h->rns_off || h->rns_mode == RNS_NEVER || kx > RNS_KMAX || ky > RNS_KMAX) return false;
-  if (h->rns_mode == RNS_ALWAYS) return true;
-  const double rows = (double)m * d.nc;
-  return kx >= 192 && ky >= 512 && 16.0 * rows * (2.0 * d.naux * d.nv + (double)d.no * d.nv * d.nv) > NOALLOC_SCRATCH_BYTES;
+// Products of a sigma of `rows` (vector, core) rows worth the conversions: the
+// engine is the faster one from about 10^7 terms a product on, whatever the
+// shape (FP64 MFMA against residues, us per sigma: nc=6 no=10 nv=40 naux=150, one
+// vector 193 / 150, 16 vectors 264 / 245; nc=6 no=12 nv=100 naux=300, four 509 /
+// 458; nc=6 no=15 nv=60 naux=200, eight 336 / 336; nc=6 no=20 nv=100 naux=400, three 692 /
+// 536; nc=6 no=60 nv=300 naux=1500, one 14686 / 6267).
+static bool rns_sized(const Dims& d, double rows) {
+  const double kx = d.naux, ky = (double)d.no * d.nv;
+  return kx <= RNS_KMAX && ky <= RNS_KMAX && kx >= 128 && ky >= 256 && rows * d.nv * kx * ky >= 1.2e7;
 }
 
 // Work space of a chunk of c (vector, core) rows, as offsets.
@@ -1207,7 +1431,8 @@ struct RnsPlan {
   int c;
   size_t f64, opnd, out, ex, norm, bytes;
 };
-static RnsPlan rns_plan(adc2_handle h, int rows) {
+static RnsPlan rns_plan(adc2_handle h, int rows, size_t target = 0) {
+  if (target == 0) target = h->rns_target;
   const Dims& d = h->d;
   const long ky = (long)d.no * d.nv;
   auto at = [&](int c) {
@@ -1229,7 +1454,7 @@ static RnsPlan rns_plan(adc2_handle h, int rows) {
     return p;
   };
   const double one = (double)at(1).bytes;
-  const int most = (int)std::max(1.0, std::min((double)rows, std::floor((double)h->rns_target / one)));
+  const int most = (int)std::max(1.0, std::min((double)rows, std::floor((double)target / one)));
   return at(cdiv(rows, cdiv(rows, most)));   // equal chunks
 }
 
@@ -1239,41 +1464,72 @@ static RnsSrc rns_lvo_rows(adc2_handle h) {
   return RnsSrc{h->Lvo + (long)d.nc * d.naux * d.nv, d.nv, (long)d.naux * d.nv, 1, 1 << 30, 0, d.nv, false};
 }
 
-// The residue engine's buffers for m vectors; false (and the MFMA engines from
-// then on) where the memory is not to be had.
-static adc2_status rns_ready(adc2_handle h, int m, hipStream_t st, bool* ok) {
+// Sigma work spaces besides the chunk's, with the most back-contraction splits.
+static size_t rns_fixed_bytes(const Dims& d, int m) {
+  auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
+  const size_t rows = (size_t)m * d.nc, xy = al(16 * rows * d.naux * d.nv);
+  const size_t njg = (d.no + LJG - 1) / LJG;
+  return 2 * xy + al(16 * rows * njg * d.nc * d.nv) + al(16 * rows * d.nv * std::min(256, d.naux));
+}
+
+// Whether a sigma of m vectors runs on the residue engine.  Where the MFMA
+// engines' work spaces fit adc2_sigma_noalloc's array, that entry point has to give
+// the same bits without allocating: there the engine is used only if its own fit as
+// well and its static operands have been there since the setup.
+static bool rns_wanted(adc2_handle h, int m) {
+  const Dims& d = h->d;
+  const double rows = (double)m * d.nc;
+  if (h->prec != ADC2_FP64 || h->rns_off || h->rns_mode == RNS_NEVER || d.naux > RNS_KMAX ||
+      (long)d.no * d.nv > RNS_KMAX)
+    return false;
+  if (h->rns_mode != RNS_ALWAYS && !rns_sized(d, rows)) return false;
+  if (16.0 * rows * (2.0 * d.naux * d.nv + (double)d.no * d.nv * d.nv) > NOALLOC_SCRATCH_BYTES) return true;
+  return h->rns_setup && rns_fixed_bytes(d, m) + rns_plan(h, m * d.nc, 1).bytes <= NOALLOC_SCRATCH_BYTES;
+}
+
+adc2_status rns_build_static(adc2_handle h, bool at_setup, hipStream_t st) {
   const Dims& d = h->d;
   const long ky = (long)d.no * d.nv;
-  *ok = false;
-  const RnsPlan p = rns_plan(h, m * d.nc);
-  const bool fresh = !h->rns_lvo || !h->rns_lvt;
-  const size_t wneed = std::max(p.bytes, fresh ? std::max(rns_norm_bytes(ky), rns_norm_bytes(d.naux)) : size_t(0));
-  if (!rns_reserve(h, wneed)) return ADC2_OK;
-  hipError_t e = hipSuccess;
-  if (fresh) {
-    e = dmalloc(h, &h->rns_lvo, rns_op_bytes(ky, d.naux) + rns_exp_bytes(ky));
-    if (e == hipSuccess && !h->rns_off) e = dmalloc(h, &h->rns_lvt, rns_op_bytes(d.naux, ky) + rns_exp_bytes(d.naux));
-  }
-  if (e != hipSuccess || h->rns_off) {
+  if (h->rns_lvo && h->rns_lvt) return ADC2_OK;
+  if (at_setup && (h->prec != ADC2_FP64 || h->rns_mode == RNS_NEVER ||
+                   (h->rns_mode != RNS_ALWAYS && !rns_sized(d, 16.0 * d.nc))))
+    return ADC2_OK;
+  if (h->rns_off || d.naux > RNS_KMAX || ky > RNS_KMAX) return ADC2_OK;
+  double* norm = nullptr;
+  hipError_t e = dmalloc(h, &norm, std::max(rns_norm_bytes(ky), rns_norm_bytes(d.naux)));
+  if (e == hipSuccess) e = dmalloc(h, &h->rns_lvo, rns_op_bytes(ky, d.naux) + rns_exp_bytes(ky));
+  if (e == hipSuccess && !h->rns_off) e = dmalloc(h, &h->rns_lvt, rns_op_bytes(d.naux, ky) + rns_exp_bytes(d.naux));
+  adc2_status rc = ADC2_OK;
+  if (e != hipSuccess || h->rns_off) {   // without the memory: the MFMA engines
     (void)hipGetLastError();
     rns_release(h);
     h->rns_off = true;
-    return ADC2_OK;
-  }
-  if (fresh) {
+  } else {
     RnsMat t;
-    double* norm = (double*)h->rns_ws;
-    adc2_status rc = rns_pack(rns_lvo_rows(h), (int)ky, d.naux, (int8_t*)h->rns_lvo, (int*)(h->rns_lvo + rns_op_bytes(ky, d.naux)), norm, &t, st);
+    rc = rns_pack(rns_lvo_rows(h), (int)ky, d.naux, (int8_t*)h->rns_lvo,
+                  (int*)(h->rns_lvo + rns_op_bytes(ky, d.naux)), norm, &t, st);
     if (rc == ADC2_OK)
-      rc = rns_pack(rns_kmajor(h->LvT, d.naux, (int)ky), d.naux, (int)ky, (int8_t*)h->rns_lvt, (int*)(h->rns_lvt + rns_op_bytes(d.naux, ky)), norm, &t, st);
-    if (rc != ADC2_OK) {
-      rns_release(h);
-      return rc;
+      rc = rns_pack(rns_kmajor(h->LvT, d.naux, (int)ky), d.naux, (int)ky, (int8_t*)h->rns_lvt,
+                    (int*)(h->rns_lvt + rns_op_bytes(d.naux, ky)), norm, &t, st);
+    if (hipStreamSynchronize(st) != hipSuccess && rc == ADC2_OK) {   // later calls may use other streams
+      set_error("residue operands: stream synchronisation failed");
+      rc = ADC2_ERR_HIP;
     }
-    ADC2_HIP(hipStreamSynchronize(st));   // later calls may use other streams
+    if (rc != ADC2_OK) rns_release(h);
+    else h->rns_setup = at_setup;
   }
-  *ok = true;
-  return ADC2_OK;
+  dfree(h, norm);
+  return rc;
+}
+
+// The residue engine's buffers for m vectors; *ok = false (and the MFMA engines
+// from then on) where the memory is not to be had.
+static adc2_status rns_ready(adc2_handle h, int m, hipStream_t st, bool* ok) {
+  *ok = false;
+  if (!rns_reserve(h, rns_plan(h, m * h->d.nc).bytes)) return ADC2_OK;
+  const adc2_status rc = rns_build_static(h, false, st);
+  *ok = rc == ADC2_OK && !h->rns_off;
+  return rc;
 }
 
 static RnsMat rns_static(char* mem, long rows, long K) {
@@ -1344,7 +1600,7 @@ static adc2_status rns_doubles_in(adc2_handle h, const SigReq& rq, RnsProf& pf, 
     });
     if (rc != ADC2_OK) return rc;
     rc = pf.run(2, [&]() -> adc2_status {
-      k_light1<double2><<<(unsigned)(c * njg * ((d.nv + 255) / 256)), 256, 0, st>>>(R, h->Vt, r0, c, d.nc, d.no, d.nv,
+      k_light1<double2><<<(unsigned)(c * njg * cdiv(d.nv, LC)), 256, 0, st>>>(R, h->Vt, r0, c, d.nc, d.no, d.nv,
                                                                                     h->Tp);
       ADC2_CHECK_LAUNCH();
       return ADC2_OK;
@@ -1645,7 +1901,7 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
     const Dims& d = h->d;
     const int rows = rq[q].m * d.nc;
     const int njg = (d.no + LJG - 1) / LJG;
-    const unsigned g = (unsigned)(rows * njg * ((d.nv + 255) / 256));
+    const unsigned g = (unsigned)(rows * njg * cdiv(d.nv, LC));
     if (h->prec != ADC2_FP64)
       k_light1<float2><<<g, 256, 0, st>>>((const float2*)h->Zb, h->Vt, 0, rows, d.nc, d.no, d.nv, h->Tp);
     else
@@ -1658,13 +1914,9 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
     adc2_handle h = rq[q].h;
     const Dims& d = h->d;
     const int rows = rq[q].m * d.nc;
-    const long nblk = (long)cdiv(rows, TM) * cdiv((long)d.naux * d.nv, TN);
-    if (h->prec != ADC2_FP64)
-      k_xbuild<float2><<<(unsigned)nblk, 256, 0, st>>>(rq[q].xin, d.dim, d.nc, d.nv, d.naux, rows, h->Lvv,
-                                                       (float2*)h->X);
-    else
-      k_xbuild<double2><<<(unsigned)nblk, 256, 0, st>>>(rq[q].xin, d.dim, d.nc, d.nv, d.naux, rows, h->Lvv, h->X);
-    ADC2_CHECK_LAUNCH();
+    rc = h->prec != ADC2_FP64 ? xbuild_launch(rq[q].xin, d, rows, h->Lvv, (float2*)h->X, st)
+                              : xbuild_launch(rq[q].xin, d, rows, h->Lvv, h->X, st);
+    if (rc != ADC2_OK) return rc;
   }
   for (int q = 0; q < nreq; ++q) {   // split-BF16: X into the blocked split layout
     adc2_handle h = rq[q].h;
@@ -1732,8 +1984,14 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
     adc2_handle h = rq[q].h;
     const Dims& d = h->d;
     const int rows = rq[q].m * d.nc;
-    const long nblk = (long)cdiv(rows, TM) * cdiv(d.nv, TN) * h->nsplit;
-    k_backc<<<(unsigned)nblk, 256, 0, st>>>(h->Y, h->Lvv, rows, d.nv, d.naux, h->nsplit, h->part);
+    const unsigned thin = (unsigned)(h->nsplit * cdiv(d.nv, 64));
+    const bool few = thin_rows(d, rows);
+    if (few && rows <= 16) k_backc_thin<1><<<thin, 256, 0, st>>>(h->Y, h->Lvv, rows, d.nv, d.naux, h->nsplit, h->part);
+    else if (few)
+      k_backc_thin<2><<<thin, 256, 0, st>>>(h->Y, h->Lvv, rows, d.nv, d.naux, h->nsplit, h->part);
+    else
+      k_backc<<<(unsigned)((long)cdiv(rows, TM) * cdiv(d.nv, TN) * h->nsplit), 256, 0, st>>>(
+          h->Y, h->Lvv, rows, d.nv, d.naux, h->nsplit, h->part);
     ADC2_CHECK_LAUNCH();
   }
   if ((rc = mark(7)) != ADC2_OK) return rc;
@@ -1742,17 +2000,17 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
     const Dims& d = h->d;
     const int m = rq[q].m;
     if (sgl[q]) {
-      adc2_status r2 = gemm_rr(m, (int)d.ns, (int)d.ns, rq[q].xin, d.dim, false, h->M11, d.ns, false, rq[q].sout,
-                               d.dim, 1.0, false, st);
-      if (r2 != ADC2_OK) return r2;
+      k_m11_mv<<<dim3(cdiv(d.ns, 4 * MVR), cdiv(m, MVM)), 256, 0, st>>>(h->M11, (int)d.ns, rq[q].xin, d.dim, m,
+                                                                       rq[q].sout);
+      ADC2_CHECK_LAUNCH();
     } else {
       k_zero_singles<<<grid_for(d.ns * m), 256, 0, st>>>(rq[q].sout, d.dim, d.ns, m);
       ADC2_CHECK_LAUNCH();
     }
     if (dbl[q]) {
       const int rows = m * d.nc;
-      k_sigma1_finish<<<grid_for((long)rows * d.nv, 256, 4096), 256, 0, st>>>(h->part, h->nsplit, h->Tp, m, d.nc,
-                                                                                d.no, d.nv, d.dim, rq[q].sout);
+      k_sigma1_finish<<<cdiv((long)rows * d.nv, 64), 64 * FW, 0, st>>>(h->part, h->nsplit, h->Tp, m, d.nc, d.no, d.nv,
+                                                                       d.dim, rq[q].sout);
       ADC2_CHECK_LAUNCH();
     }
   }
@@ -1900,16 +2158,26 @@ extern "C" adc2_status adc2_sigma_noalloc(adc2_handle h, int m, const void* X, v
     q += (b + 255) & ~size_t(255);
     return r;
   };
+  const bool rns = rns_wanted(h, m);   // then its own work spaces instead of Zb, in smaller chunks
+  char* sws_rns = h->rns_ws;
+  const size_t swsb = h->rns_ws_bytes, starget = h->rns_target;
   h->X = take(p.x);
-  h->Y = take(p.y);
-  h->Zb = take(p.zb);
+  h->Y = take(rns ? p.x : p.y);
+  h->Zb = rns ? nullptr : take(p.zb);
   h->Tp = take(p.tp);
   h->part = take(p.part);
+  if (rns) {
+    h->rns_ws = reinterpret_cast<char*>(q);
+    h->rns_target = h->rns_ws_bytes = NOALLOC_SCRATCH_BYTES - (size_t)(q - static_cast<unsigned char*>(base));
+  }
   h->ws_m = h->zb_m = m;
   h->ysplit = p.ysplit;
   h->nsplit = p.nsplit;
   const SigReq rq{h, m, static_cast<const double2*>(X), static_cast<double2*>(S), SIGMA_SINGLES_IN | SIGMA_DOUBLES_IN};
-  rc = sigma_multi(1, &rq, static_cast<hipStream_t>(stream), false);   // the residue engine has work spaces of its own
+  rc = sigma_multi(1, &rq, static_cast<hipStream_t>(stream), rns);
+  h->rns_ws = sws_rns;
+  h->rns_ws_bytes = swsb;
+  h->rns_target = starget;
   h->X = sX;
   h->Y = sY;
   h->Zb = sZb;

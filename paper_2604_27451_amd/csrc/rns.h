@@ -114,7 +114,8 @@ adc2_status rns_join(const RnsMat& A, const RnsMat& B, int col0, int ncols, int 
                      const RnsDst& dst, hipStream_t st);
 
 // dst(i, j) = sum_k A(i, k) B(j, k), i < M, j < N, in chunks of rows whose work
-// space is at most 2 h->rns_target (or that of one 256 x 128 tile).  *done = false (nothing written, no error)
+// space is at most 2 h->rns_target (or that of one 256 x 128 tile); the entry points
+// that use it give that back at their end (rns_tmp_release).  *done = false (nothing written, no error)
 // where the caller's own FP64 MFMA kernel, of `rate` flop/s at such sizes, is the
 // faster one (rate 0: the caller has asked rns_pays itself) or the memory is
 // not to be had: the caller then uses that.
@@ -129,8 +130,8 @@ adc2_status rns_product(adc2_handle h, const RnsSrc& A, int M, const RnsSrc& B, 
                         double rate, bool* done, hipStream_t st);
 // The size rule of rns_product
 bool rns_pays(adc2_handle h, long M, long N, long K, double rate);
-// At least `bytes` of the handle's work space, contents undefined; false where
-// it is not to be had.
+// At least `bytes` of the handle's sigma work space, contents undefined; false
+// where it is not to be had.
 bool rns_reserve(adc2_handle h, size_t bytes);
 
 }  // namespace adc2

@@ -592,16 +592,17 @@ bool rns_pays(adc2_handle h, long M, long N, long K, double rate) {
   return rns < 0.8 * terms * 8 / rate;
 }
 
-bool rns_reserve(adc2_handle h, size_t bytes) {
+static bool rns_grow(adc2_handle h, char** buf, size_t* have, size_t bytes) {
   if (h->rns_off) return false;
-  if (h->rns_ws_bytes >= bytes) return true;
+  if (*have >= bytes) return true;
   if (bytes > (size_t(256) << 20)) bytes = (bytes + (size_t(512) << 20) - 1) >> 29 << 29;   // few sizes: blocks are reused
-  dfree(h, h->rns_ws);
-  h->rns_ws = nullptr;
-  h->rns_ws_bytes = 0;
-  const hipError_t e = dmalloc(h, &h->rns_ws, bytes);
+  char* old = *buf;
+  *buf = nullptr;
+  *have = 0;
+  dfree(h, old);
+  const hipError_t e = dmalloc(h, buf, bytes);
   if (e == hipSuccess && !h->rns_off) {
-    h->rns_ws_bytes = bytes;
+    *have = bytes;
     return true;
   }
   (void)hipGetLastError();
@@ -610,13 +611,24 @@ bool rns_reserve(adc2_handle h, size_t bytes) {
   return false;
 }
 
+bool rns_reserve(adc2_handle h, size_t bytes) { return rns_grow(h, &h->rns_ws, &h->rns_ws_bytes, bytes); }
+
+void rns_tmp_release(adc2_handle h) {
+  char* t = h->rns_tmp;
+  h->rns_tmp = nullptr;
+  h->rns_tmp_bytes = 0;
+  dfree(h, t);
+}
+
 void rns_release(adc2_handle h) {
   char *a = h->rns_lvo, *b = h->rns_lvt, *c = h->rns_ws;
   h->rns_lvo = h->rns_lvt = h->rns_ws = nullptr;
   h->rns_ws_bytes = 0;
+  h->rns_setup = false;
   dfree(h, a);
   dfree(h, b);
   dfree(h, c);
+  rns_tmp_release(h);
 }
 
 adc2_status rns_product(adc2_handle h, const RnsSrc& A, int M, const RnsSrc& B, int N, int K, const RnsDst& dst,
@@ -638,8 +650,8 @@ adc2_status rns_product(adc2_handle h, const RnsSrc& A, int M, const RnsSrc& B, 
     if (mc > 256 && (mc >= nc || nc <= 128)) mc = (mc / 2 + 255) / 256 * 256;
     else nc = (nc / 2 + 127) / 128 * 128;
   }
-  if (!rns_reserve(h, need(mc, nc))) return ADC2_OK;
-  char* q = h->rns_ws;
+  if (!rns_grow(h, &h->rns_tmp, &h->rns_tmp_bytes, need(mc, nc))) return ADC2_OK;
+  char* q = h->rns_tmp;
   auto take = [&](size_t b) {
     char* r = q;
     q += al(b);

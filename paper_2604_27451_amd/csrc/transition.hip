@@ -720,6 +720,7 @@ extern "C" ADC2_API adc2_status adc2_transition(adc2_handle h, const void* dip, 
     rc = ADC2_ERR_HIP;
     msg = "hipStreamSynchronize";
   }
+  rns_tmp_release(h);
   dfree(h, F);
   dfree(h, tau);
   dfree(h, dpairs);

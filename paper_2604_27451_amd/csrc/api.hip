@@ -278,7 +278,7 @@ static void pool_free(void* p) {
   P.idle.push_back(b);
 }
 
-static hipError_t dmalloc_once(adc2_handle h, void** p, size_t bytes) {
+hipError_t dmalloc_try(adc2_handle h, void** p, size_t bytes) {
   if (!h || !h->alloc.alloc) return pool_alloc(p, bytes);
   if (bytes == 0) {          // as hipMalloc: success, no memory
     *p = nullptr;
@@ -291,12 +291,12 @@ static hipError_t dmalloc_once(adc2_handle h, void** p, size_t bytes) {
 // A request that fails while the handle holds residue-engine memory is tried
 // again without it (that engine is an option, the request is not).
 hipError_t dmalloc_raw(adc2_handle h, void** p, size_t bytes) {
-  hipError_t e = dmalloc_once(h, p, bytes);
+  hipError_t e = dmalloc_try(h, p, bytes);
   if (e == hipErrorOutOfMemory && h && (h->rns_lvo || h->rns_lvt || h->rns_ws || h->rns_tmp)) {
     (void)hipGetLastError();
     rns_release(h);
     h->rns_off = true;
-    e = dmalloc_once(h, p, bytes);
+    e = dmalloc_try(h, p, bytes);
   }
   return e;
 }

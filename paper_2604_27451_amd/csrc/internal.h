@@ -27,6 +27,8 @@ void set_error(const std::string& msg);
 // Device memory of a handle: through its callbacks when set, else hipMalloc / hipFree
 // (dfree waits for the device first, as hipFree does; NULL is ignored).
 hipError_t dmalloc_raw(adc2_handle h, void** p, size_t bytes);
+// the same without the second try below (residue-engine memory given back)
+hipError_t dmalloc_try(adc2_handle h, void** p, size_t bytes);
 void dfree(adc2_handle h, void* p);
 template <class T>
 inline hipError_t dmalloc(adc2_handle h, T** p, size_t bytes) {
@@ -108,7 +110,7 @@ struct adc2_handle_s {
   bool rns_setup = false;   // the static operands were built by adc2_setup
   char* rns_tmp = nullptr;  // work space of the general products, held during an entry point
   size_t rns_tmp_bytes = 0;
-  size_t rns_target = size_t(3) << 30;   // bytes a chunk's work space aims at (environment ADC2_RNS_MB)
+  size_t rns_target = size_t(6) << 30;   // bytes a chunk's work space aims at (environment ADC2_RNS_MB)
   // method: ADC2_METHOD_ADC2 or ADC2_METHOD_ADC2X (first-order doubles block, adc2x.hip)
   int method = 0;
   double2* Vpp = nullptr;   // ADC(2)-x: [(a<b)][(c<d)] <ab||cd>

@@ -252,7 +252,7 @@ static adc2_status wbuild_rns(adc2_handle h, const int2* dpairs, double2* W, dou
   const long nv2 = (long)nv * nv, lds = (long)d.naux * nv;
   *done = false;
   if (!rns_pays(h, (long)o * nv, (long)o * nv / 2, d.naux, RNS_VS_BIG)) return ADC2_OK;
-  const int g = (int)std::max<long>(1, std::min<long>(o, (long)(h->rns_target / 2) / (16 * o * nv2)));   // k per group
+  const int g = (int)std::max<long>(1, std::min<long>(o, (long)(h->rns_target / 6) / (16 * o * nv2)));   // k per group
   double2* V = nullptr;
   if (dmalloc(h, &V, sizeof(double2) * g * o * nv2) != hipSuccess) {
     (void)hipGetLastError();

@@ -1447,7 +1447,7 @@ static RnsPlan rns_plan(adc2_handle h, int rows, size_t target = 0) {
     };
     p.f64 = take(sizeof(double2) * r * ky);
     p.opnd = take(std::max(rns_op_bytes(r, ky), rns_op_bytes(r, d.naux)));
-    p.out = take(std::max(rns_out_bytes(d.naux, r), rns_out_bytes(r, ky)));
+    p.out = take(std::max(rns_out_bytes(d.naux, r) * rns_long_splits(ky), rns_out_bytes(r, ky) * rns_long_splits(d.naux)));
     p.ex = take(rns_exp_bytes(r));
     p.norm = take(rns_norm_bytes(r));
     p.bytes = q;
@@ -1526,7 +1526,15 @@ adc2_status rns_build_static(adc2_handle h, bool at_setup, hipStream_t st) {
 // from then on) where the memory is not to be had.
 static adc2_status rns_ready(adc2_handle h, int m, hipStream_t st, bool* ok) {
   *ok = false;
-  if (!rns_reserve(h, rns_plan(h, m * h->d.nc).bytes)) return ADC2_OK;
+  // smaller chunks where the target's memory is not to be had
+  while (!rns_reserve(h, rns_plan(h, m * h->d.nc).bytes)) {
+    if (h->rns_off || rns_plan(h, m * h->d.nc).c <= 1) {
+      rns_release(h);
+      h->rns_off = true;
+      return ADC2_OK;
+    }
+    h->rns_target /= 2;
+  }
   const adc2_status rc = rns_build_static(h, false, st);
   *ok = rc == ADC2_OK && !h->rns_off;
   return rc;
@@ -1611,10 +1619,11 @@ static adc2_status rns_doubles_in(adc2_handle h, const SigReq& rq, RnsProf& pf, 
       const int ncol = c * d.nv;
       adc2_status r = rns_pack(rns_kmajor(R, ncol, K), ncol, K, (int8_t*)(h->rns_ws + p.opnd), (int*)(h->rns_ws + p.ex),
                                (double*)(h->rns_ws + p.norm), &B, st);
-      if (r == ADC2_OK) r = rns_gemm(L, B, 0, ncol, 1, out, st);
+      const int ns = rns_long_splits(K);
+      if (r == ADC2_OK) r = rns_gemm(L, B, 0, ncol, ns, out, st);
       // Y[mI][P][c], columns (mI, c)
       const RnsDst y{h->Y + (long)r0 * d.naux * d.nv, 1 << 30, 0, d.nv, d.nv, (long)d.naux * d.nv, 1, 1.0, false};
-      if (r == ADC2_OK) r = rns_join(L, B, 0, ncol, 1, out, y, st);
+      if (r == ADC2_OK) r = rns_join(L, B, 0, ncol, ns, out, y, st);
       return r;
     });
     if (rc != ADC2_OK) return rc;
@@ -1638,10 +1647,11 @@ static adc2_status rns_singles_in(adc2_handle h, const SigReq& rq, int with_d, R
       const RnsSrc x{h->X + (long)r0 * d.naux * d.nv, d.nv, (long)d.naux * d.nv, 1, 1 << 30, 0, d.nv, false};
       adc2_status r = rns_pack(x, c * d.nv, d.naux, (int8_t*)(h->rns_ws + p.opnd), (int*)(h->rns_ws + p.ex),
                                (double*)(h->rns_ws + p.norm), &A, st);
-      if (r == ADC2_OK) r = rns_gemm(A, L, 0, N, 1, out, st);
+      const int ns = rns_long_splits(d.naux);
+      if (r == ADC2_OK) r = rns_gemm(A, L, 0, N, ns, out, st);
       // Z[mI][j][a][b], rows (mI, a), columns (j, b)
       const RnsDst z{Z, d.nv, (long)d.no * d.nv * d.nv, d.nv, d.nv, (long)d.nv * d.nv, 1, 1.0, false};
-      if (r == ADC2_OK) r = rns_join(A, L, 0, N, 1, out, z, st);
+      if (r == ADC2_OK) r = rns_join(A, L, 0, N, ns, out, z, st);
       return r;
     });
     if (rc != ADC2_OK) return rc;

@@ -26,11 +26,10 @@
 // 1.2e-16 of the rms entry, 2.1e-15 on the FP64 MFMA engine; singles from random
 // doubles at nc=6 no=20 nv=100 naux=400: 8.8e-16 against 1.2e-15.
 //
-// What bounds it.  The INT8 products draw the card to its power limit: a
-// loop of v_mfma_i32_32x32x32_i8 on random bytes alone runs at 3047 TOPS (4320 on
-// zeros), the product of M=1500, N=K=18000 at 1914 (2800 on zeros), as 239
-// TFLOP/s of complex products; the FP64 MFMA engine reaches 67.
-// One 10-vector sigma at nc=6 no=60 nv=300 naux=1500: 124.8 ms before, 56.5 ms so.
+// What bounds it.  The INT8 products draw the card to its power limit: a loop of
+// v_mfma_i32_16x16x64_i8 on random bytes alone runs at 4085 TOPS (4850 on zeros), the
+// product of M=3072, N=9000, K=18000 at 2338, as 292 TFLOP/s of complex products; the
+// FP64 MFMA engine reaches 67.
 //
 // Rows with NaN or Inf give NaN in every product with them; rows of zeros
 // give exact zeros.
@@ -48,8 +47,8 @@ constexpr long RNS_KMAX = 131072;       // K 121^2 < 2^31
 
 // An operand in residues.  Plane q (modulus q / 2, sign q % 2), row block rt,
 // k block kc is the 8 KB run at ((q * nrt + rt) * nkc + kc) * RNS_BLK, laid
-// out [k / 16][row][k % 16], which is both the LDS image of the GEMM and
-// conflict-free for its 16-byte fragment reads.
+// out [row / 16][k / 16][row % 16][k % 16]: the LDS image of the GEMM, in which a
+// 16 x 64 fragment is 1 KB in lane order.
 struct RnsMat {
   int8_t* p = nullptr;
   int* e = nullptr;        // row exponents (RNS_NAN: a row that is not finite)
@@ -100,6 +99,11 @@ inline RnsDst rns_rows(double2* C, long ldc, double alpha = 1.0, bool add = fals
   return RnsDst{C, 1 << 30, 0, ldc, 1 << 30, 0, 1, alpha, add};
 }
 
+// K-splits of a long product: workgroups that walk 10^5 terms drift apart and lose
+// each other's panels in L2; runs of about 9000 keep them together (M=3072, N=1280, K=72000:
+// 2074 TOPS in one run, 2282 in eight; no difference at K = 18000).
+inline int rns_long_splits(long K) { return K > 20480 ? (int)((K + 9215) / 9216) : 1; }
+
 // Residues of an operand; buf, ebuf and nbuf hold the sizes above.
 adc2_status rns_pack(const RnsSrc& src, int rows, int K, int8_t* buf, int* ebuf, double* nbuf, RnsMat* out,
                      hipStream_t st);
@@ -114,7 +118,7 @@ adc2_status rns_join(const RnsMat& A, const RnsMat& B, int col0, int ncols, int 
                      const RnsDst& dst, hipStream_t st);
 
 // dst(i, j) = sum_k A(i, k) B(j, k), i < M, j < N, in chunks of rows whose work
-// space is at most 2 h->rns_target (or that of one 256 x 128 tile); the entry points
+// space is at most h->rns_target (or that of one 256 x 128 tile); the entry points
 // that use it give that back at their end (rns_tmp_release).  *done = false (nothing written, no error)
 // where the caller's own FP64 MFMA kernel, of `rate` flop/s at such sizes, is the
 // faster one (rate 0: the caller has asked rns_pays itself) or the memory is

@@ -8,7 +8,6 @@
 namespace adc2 {
 
 typedef int i4v __attribute__((ext_vector_type(4)));
-typedef int i16v __attribute__((ext_vector_type(16)));
 
 static inline int rcdiv(long a, long b) { return (int)((a + b - 1) / b); }
 
@@ -298,7 +297,7 @@ __global__ __launch_bounds__(256) void k_rns_pack(const RnsSrc src, int rows, in
     d[u].w = b;
   }
   const float magic = 12582912.0f;
-  int8_t* out = dst + ((long)(rb >> 1) * nkc + kc) * RNS_BLK + kg * (RNS_RT * 16) + ((rb & 1) * 64 + lane) * 16;
+  int8_t* out = dst + ((long)(rb >> 1) * nkc + kc) * RNS_BLK + ((rb & 1) * 4 + (lane >> 4)) * 1024 + kg * 256 + (lane & 15) * 16;
   const long ps = (long)nrt * nkc * RNS_BLK;
   for (int q = 0; q < RNS_NM; ++q) {
     const RnsSplit c = RNS_C.split[q];
@@ -355,10 +354,15 @@ adc2_status rns_pack(const RnsSrc& src, int rows, int K, int8_t* buf, int* ebuf,
 // ---------------------------------------------------------------------------
 // the product of one plane:  C[i][j] = sum_k A[i][k] B[j][k] mod p
 // ---------------------------------------------------------------------------
-// Tiles of 128 WM x 64 WN on WM WN waves of 128 x 64 (v_mfma_i32_32x32x32_i8,
-// 4 x 2 blocks, 128 accumulators a lane).  Chunks of 64 k go from global
+// Tiles of 128 WM x 64 WN on WM WN waves of 128 x 64 (v_mfma_i32_16x16x64_i8,
+// 8 x 4 blocks, 128 accumulators a lane).  Chunks of 64 k go from global
 // memory straight into an LDS ring of NB stages (the operand layout is the
-// LDS image), NB - 1 chunks ahead; one barrier a chunk.
+// LDS image, and a fragment is 1 KB of it in lane order), NB - 1 chunks ahead;
+// one barrier a chunk.  The card's power limit sets the rate: on random bytes a
+// loop of this instruction alone runs at 4085 TOPS, of 32x32x32 at 3498 (both about 4850
+// on zeros), and the whole product at 2240 to 2340 against 1950 to 2050 at K = 18000,
+// 1960 to 1990 against 1710 to 1840 at K = 1500.  Two workgroups a CU, so that one's
+// reduction runs under the other's products.
 template <int WM, int WN, int NB>
 __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm(
     const int8_t* __restrict__ A, const int8_t* __restrict__ B, int nrtA, int nrtB, int brt0, int nkca, int nkcs, int nbm,
@@ -399,13 +403,11 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm
       __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) void*)(src[q] + tc),
                                        (__attribute__((address_space(3))) void*)(d + (q * T + w * 64) * 16), 16, 0, 0);
   };
-  i16v acc[4][2];
+  i4v acc[8][4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int x = 0; x < 16; ++x) acc[i][j][x] = 0;
+    for (int j = 0; j < 4; ++j) acc[i][j] = i4v{0, 0, 0, 0};
   const int wm = w % WM, wn = w / WM;
 #pragma unroll
   for (int t = 0; t < NB - 1; ++t) load(t);
@@ -419,22 +421,18 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm
     asm volatile("" ::: "memory");
     load(t + NB - 1);
     const int8_t* p = s[t % NB];
-    const int8_t* pa = p + wm * RNS_BLK + (lane >> 5) * (RNS_RT * 16) + (lane & 31) * 16;
-    const int8_t* pb = p + BM * RNS_KC + (wn >> 1) * RNS_BLK + (lane >> 5) * (RNS_RT * 16) +
-                       ((wn & 1) * 64 + (lane & 31)) * 16;
+    const int8_t* pa = p + wm * RNS_BLK + lane * 16;
+    const int8_t* pb = p + BM * RNS_KC + (wn >> 1) * RNS_BLK + (wn & 1) * (RNS_BLK / 2) + lane * 16;
+    i4v a[8], b[4];
 #pragma unroll
-    for (int k2 = 0; k2 < 2; ++k2) {
-      i4v a[4], b[2];
+    for (int j = 0; j < 4; ++j) b[j] = *(const i4v*)(pb + j * 1024);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) b[j] = *(const i4v*)(pb + k2 * (2 * RNS_RT * 16) + j * 512);
+    for (int i = 0; i < 8; ++i) a[i] = *(const i4v*)(pa + i * 1024);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = *(const i4v*)(pa + k2 * (2 * RNS_RT * 16) + i * 512);
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
+      for (int j = 0; j < 4; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i], b[j], acc[i][j], 0, 0, 0);
   }
   __builtin_amdgcn_s_waitcnt(0x0f70);
   const RnsSplit c = RNS_C.split[pl >> 1];
@@ -447,7 +445,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm
   const bool far = nkc > 64;
   const float invf = c.inv * (1.0f / 1024.0f);
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 4; ++i)   // 32 x 32 blocks: two row blocks, two column blocks
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       i4v o;
@@ -456,7 +454,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm
         int rr[4];
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
-          int v = acc[i][j][q * 4 + x];
+          int v = acc[2 * i + (q & 1)][2 * j + (q >> 1)][x];
           if (far) {
             const float t = fmaf((float)v, invf, magic);
             v -= __mul24(__float_as_int(t) - RNS_MAGIC, pi * 1024);
@@ -474,9 +472,20 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm
 
 adc2_status rns_gemm(const RnsMat& A, const RnsMat& B, int col0, int ncols, int nsplit, int8_t* out, hipStream_t st) {
   const int nrb = rcdiv(A.rows, 32), ncb = rcdiv(ncols, 32);
-  const int nbm = rcdiv(A.rows, 256), nbn = rcdiv(ncols, 128);
-  k_rns_gemm<2, 2, 3><<<(unsigned)((long)nsplit * RNS_PL * nbm * nbn), 256, 0, st>>>(
-      A.p, B.p, A.nrt, B.nrt, col0 / RNS_RT, A.nkc, rcdiv(A.nkc, nsplit), nbm, nbn, nrb, ncb, out);
+  // 256 x 128 or 128 x 256 tiles: the one that pads less, weighed by its rate (256 x
+  // 128 is 2% the faster one at K = 1500, the other 1 to 4% from K = 3000 on)
+  const int nkcs = rcdiv(A.nkc, nsplit);
+  const double tall = 256.0 * rcdiv(A.rows, 256) * 128.0 * rcdiv(ncols, 128);
+  const double flat = 128.0 * rcdiv(A.rows, 128) * 256.0 * rcdiv(ncols, 256) * (nkcs < 40 ? 1.02 : 0.98);
+  if (tall <= flat) {
+    const int nbm = rcdiv(A.rows, 256), nbn = rcdiv(ncols, 128);
+    k_rns_gemm<2, 2, 3><<<(unsigned)((long)nsplit * RNS_PL * nbm * nbn), 256, 0, st>>>(
+        A.p, B.p, A.nrt, B.nrt, col0 / RNS_RT, A.nkc, nkcs, nbm, nbn, nrb, ncb, out);
+  } else {
+    const int nbm = rcdiv(A.rows, 128), nbn = rcdiv(ncols, 256);
+    k_rns_gemm<1, 4, 3><<<(unsigned)((long)nsplit * RNS_PL * nbm * nbn), 256, 0, st>>>(
+        A.p, B.p, A.nrt, B.nrt, col0 / RNS_RT, A.nkc, nkcs, nbm, nbn, nrb, ncb, out);
+  }
   ADC2_CHECK_LAUNCH();
   return ADC2_OK;
 }
@@ -499,8 +508,8 @@ __global__ __launch_bounds__(256) void k_rns_join(const int8_t* __restrict__ R, 
   const int cb = 2 * (blockIdx.x % ncp) + (threadIdx.x >> 7);
   if (cb >= ncb) return;
   const int item = threadIdx.x & 127, lane = item >> 1, half = item & 1;
-  const int col = cb * 32 + (lane & 31);
-  const int row0 = rb * 32 + 16 * half + 4 * (lane >> 5);   // rows row0 + {0..3} and row0 + 8 + {0..3}
+  const int col = cb * 32 + 16 * half + (lane & 15);
+  const int row0 = rb * 32 + 4 * (lane >> 4);   // rows row0 + {0..3} and row0 + 16 + {0..3}
   const long ps = (long)nrb * ncb * 1024;
   const int8_t* src = R + ((long)rb * ncb + cb) * 1024 + item * 8;
   double fr[8], fi[8], gr[8], gi[8];
@@ -548,7 +557,7 @@ __global__ __launch_bounds__(256) void k_rns_join(const int8_t* __restrict__ R, 
   double2* pc = dst.C + (long)cg * dst.jg + (long)(jj - cg * dst.ji) * dst.jx;
 #pragma unroll
   for (int x = 0; x < 8; ++x) {
-    const int row = row0 + (x >> 2) * 8 + (x & 3);
+    const int row = row0 + (x >> 2) * 16 + (x & 3);
     if (row >= rows) continue;
     const int er = ea[row];
     double re = M * ((fr[x] - rint(fr[x])) + gr[x]), im = M * ((fi[x] - rint(fi[x])) + gi[x]);
@@ -592,7 +601,7 @@ bool rns_pays(adc2_handle h, long M, long N, long K, double rate) {
   return rns < 0.8 * terms * 8 / rate;
 }
 
-static bool rns_grow(adc2_handle h, char** buf, size_t* have, size_t bytes) {
+static bool rns_grow(adc2_handle h, char** buf, size_t* have, size_t bytes, bool last) {
   if (h->rns_off) return false;
   if (*have >= bytes) return true;
   if (bytes > (size_t(256) << 20)) bytes = (bytes + (size_t(512) << 20) - 1) >> 29 << 29;   // few sizes: blocks are reused
@@ -600,18 +609,22 @@ static bool rns_grow(adc2_handle h, char** buf, size_t* have, size_t bytes) {
   *buf = nullptr;
   *have = 0;
   dfree(h, old);
-  const hipError_t e = dmalloc(h, buf, bytes);
-  if (e == hipSuccess && !h->rns_off) {
+  const hipError_t e = dmalloc_try(h, reinterpret_cast<void**>(buf), bytes);
+  if (e == hipSuccess) {
     *have = bytes;
     return true;
   }
   (void)hipGetLastError();
-  rns_release(h);
-  h->rns_off = true;
+  if (last) {
+    rns_release(h);
+    h->rns_off = true;
+  }
   return false;
 }
 
-bool rns_reserve(adc2_handle h, size_t bytes) { return rns_grow(h, &h->rns_ws, &h->rns_ws_bytes, bytes); }
+bool rns_reserve(adc2_handle h, size_t bytes) {
+  return rns_grow(h, &h->rns_ws, &h->rns_ws_bytes, bytes, false);
+}
 
 void rns_tmp_release(adc2_handle h) {
   char* t = h->rns_tmp;
@@ -635,10 +648,10 @@ adc2_status rns_product(adc2_handle h, const RnsSrc& A, int M, const RnsSrc& B, 
                         double rate, bool* done, hipStream_t st) {
   *done = false;
   if (M <= 0 || N <= 0 || K <= 0 || h->rns_off || (rate > 0.0 && !rns_pays(h, M, N, K, rate))) return ADC2_OK;
-  // K-splits: within the INT32 range, and enough tiles for two a CU
+  // K-splits: within the INT32 range (RNS_KMAX a split), and enough tiles for two a CU
   const long tiles = (long)RNS_PL * rcdiv(M, 256) * rcdiv(N, 128);
   const int nkc = rcdiv(K, RNS_KC);
-  int ns = std::max(rcdiv(K, RNS_KMAX), (int)std::min<long>({(long)RNS_SPLITS, (1024 + tiles - 1) / tiles, std::max(1, nkc / 8)}));
+  int ns = std::max(std::max(rcdiv(K, RNS_KMAX), std::min(rns_long_splits(K), RNS_SPLITS)), (int)std::min<long>({(long)RNS_SPLITS, (1024 + tiles - 1) / tiles, std::max(1, nkc / 8)}));
   ns = rcdiv(nkc, rcdiv(nkc, ns));   // no empty split
   auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
   auto need = [&](long m, long n) {
@@ -646,11 +659,11 @@ adc2_status rns_product(adc2_handle h, const RnsSrc& A, int M, const RnsSrc& B, 
            al(rns_exp_bytes(n)) + al(rns_norm_bytes(std::max(m, n)));
   };
   long mc = M, nc = N;
-  while (need(mc, nc) > 2 * h->rns_target && (mc > 256 || nc > 128)) {
+  while (need(mc, nc) > h->rns_target && (mc > 256 || nc > 128)) {
     if (mc > 256 && (mc >= nc || nc <= 128)) mc = (mc / 2 + 255) / 256 * 256;
     else nc = (nc / 2 + 127) / 128 * 128;
   }
-  if (!rns_grow(h, &h->rns_tmp, &h->rns_tmp_bytes, need(mc, nc))) return ADC2_OK;
+  if (!rns_grow(h, &h->rns_tmp, &h->rns_tmp_bytes, need(mc, nc), true)) return ADC2_OK;
   char* q = h->rns_tmp;
   auto take = [&](size_t b) {
     char* r = q;

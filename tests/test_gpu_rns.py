@@ -168,11 +168,13 @@ def test_without_its_memory_the_mfma_engine_serves(monkeypatch):
     monkeypatch.setenv("ADC2_ZGEMM", "rns")
     base = A.torch_allocator()
     state = {"count": None, "refused": 0}
+    zb = 16 * 2 * s.nc * s.no * s.nv * s.nv
 
     def _alloc(nbytes, ctx):
         if state["count"] is not None:
             state["count"] += 1
-            if state["count"] == 5:      # after X, Y, Tp and the back-contraction partials
+            # after X, Y, Tp and the back-contraction partials: every chunk size, not the MFMA engine's doubles
+            if state["count"] >= 5 and nbytes != zb:
                 state["refused"] += 1
                 return None
         return base.alloc(nbytes, ctx)
@@ -182,7 +184,7 @@ def test_without_its_memory_the_mfma_engine_serves(monkeypatch):
     state["count"] = 0
     print("[case] rns without its memory", flush=True)
     got = A.adc2_sigma(h, x)
-    assert state["refused"] == 1 and torch.equal(got[:, h.ns:], want[:, h.ns:])
+    assert state["refused"] >= 1 and torch.equal(got[:, h.ns:], want[:, h.ns:])
     assert float((got - want).abs().max() / want.abs().max()) < 1e-12
     n = state["count"]
     assert torch.equal(A.adc2_sigma(h, x), got) and state["count"] == n

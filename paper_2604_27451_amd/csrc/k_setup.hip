@@ -198,12 +198,12 @@ __global__ __launch_bounds__(256) void k_wbuild(const double2* __restrict__ Lvo,
 // 16 B read, 16 B written per entry).
 constexpr int WS = 32;
 __global__ __launch_bounds__(256) void k_w_from_v(const double2* __restrict__ V, const double* __restrict__ eps,
-                                                   const int2* __restrict__ pairs, int p0, int k0, int nl, int nv, int o,
+                                                   const int2* __restrict__ pairs, int k0, int nl, int nv, int o,
                                                    double2* __restrict__ W, double* __restrict__ epart) {
   __shared__ double2 t[WS][WS + 1], u[WS][WS + 1];
   __shared__ double red[256];
   const int nb = (nv + TM - 1) / TM, ntp = nb * (nb + 1) / 2;
-  const int p = p0 + blockIdx.x / ntp;
+  const int p = blockIdx.x / ntp;
   int ab, cb;
   tile_pair(blockIdx.x % ntp, nb, ab, cb);
   const int2 kl = pairs[p];
@@ -241,57 +241,77 @@ __global__ __launch_bounds__(256) void k_w_from_v(const double2* __restrict__ V,
   if (tid == 0) epart[(long)p * ntp + blockIdx.x % ntp] = red[0];
 }
 
-// W and the energy partials of every pair on the residue engine: (ak|cl) for
-// groups of k against all l >= k as one product over the Cholesky index, then
-// antisymmetrised.  The same terms as k_wbuild (each pair once); nc=6 no=60
-// nv=300 naux=1500: 71 ms -> 16 ms.
+// k per group of the pair products: about 1 GiB of (ak|cl) whatever the work-space
+// target, so that the FP64 sums over the groups do not depend on it.
+static int pair_group(const Dims& d) {
+  return (int)std::max<long>(1, std::min<long>(d.o, (1L << 30) / (16L * d.o * d.nv * d.nv)));
+}
+
+// W and energy partials of the pairs k0 <= k < k1, k < l, into W (np pairs from p0
+// on in pair order; the partials at their absolute place): (ak|cl) for the group
+// against all l >= k0 as one residue product over the Cholesky index into V, then
+// antisymmetrised.  The same terms as k_wbuild (each pair once).
+static adc2_status w_group(adc2_handle h, int k0, int k1, const int2* dpairs, int p0, int np, double2* V, double2* W,
+                           double* epart, bool* ok, hipStream_t st) {
+  const Dims& d = h->d;
+  const int nv = d.nv, nl = d.o - k0;
+  const long nv2 = (long)nv * nv, lds = (long)d.naux * nv;
+  const int nb = (nv + TM - 1) / TM, ntp = nb * (nb + 1) / 2;
+  const RnsSrc rows{h->Lvo + k0 * lds, nv, lds, 1, 1 << 30, 0, nv, false};
+  const adc2_status rc = rns_product(h, rows, (k1 - k0) * nv, rows, nl * nv, d.naux,
+                                     RnsDst{V, nv, nl * nv2, nv, nv, nv2, 1, 1.0, false}, 0.0, ok, st);
+  if (rc != ADC2_OK || !*ok || np == 0) return rc;
+  k_w_from_v<<<(unsigned)((long)np * ntp), 256, 0, st>>>(V, h->eps, dpairs + p0, k0, nl, nv, d.o, W,
+                                                         epart + (long)p0 * ntp);
+  ADC2_CHECK_LAUNCH();
+  return ADC2_OK;
+}
+
+static bool w_pays(adc2_handle h) {
+  const Dims& d = h->d;
+  return rns_pays(h, (long)d.o * d.nv, (long)d.o * d.nv / 2, d.naux, RNS_VS_BIG);
+}
+
+// W of every pair on the residue engine (adjoint, transition moments); nc=6
+// no=60 nv=300 naux=1500: 71 ms on the FP64 MFMA tiles, 16 ms so.
 static adc2_status wbuild_rns(adc2_handle h, const int2* dpairs, double2* W, double* epart, bool* done,
                               hipStream_t st) {
   const Dims& d = h->d;
-  const int o = d.o, nv = d.nv;
-  const long nv2 = (long)nv * nv, lds = (long)d.naux * nv;
+  const int o = d.o;
+  const long nv2 = (long)d.nv * d.nv;
   *done = false;
-  if (!rns_pays(h, (long)o * nv, (long)o * nv / 2, d.naux, RNS_VS_BIG)) return ADC2_OK;
-  const int g = (int)std::max<long>(1, std::min<long>(o, (long)(h->rns_target / 6) / (16 * o * nv2)));   // k per group
+  if (!w_pays(h)) return ADC2_OK;
+  const int g = pair_group(d);
   double2* V = nullptr;
   if (dmalloc(h, &V, sizeof(double2) * g * o * nv2) != hipSuccess) {
     (void)hipGetLastError();
     return ADC2_OK;
   }
-  const int nb = (nv + TM - 1) / TM, ntp = nb * (nb + 1) / 2;
   int p0 = 0;
+  bool ok = true;
   adc2_status rc = ADC2_OK;
-  for (int k0 = 0; k0 < o - 1 && rc == ADC2_OK; k0 += g) {
-    const int k1 = std::min(k0 + g, o), nl = o - k0;
-    const RnsSrc rows{h->Lvo + k0 * lds, nv, lds, 1, 1 << 30, 0, nv, false};
-    bool ok = false;
-    rc = rns_product(h, rows, (k1 - k0) * nv, rows, nl * nv, d.naux, RnsDst{V, nv, nl * nv2, nv, nv, nv2, 1, 1.0, false},
-                     0.0, &ok, st);
-    if (rc != ADC2_OK || !ok) break;   // (without its memory: the MFMA kernel does every pair)
+  for (int k0 = 0; k0 < o - 1 && rc == ADC2_OK && ok; k0 += g) {
+    const int k1 = std::min(k0 + g, o);
     int np = 0;
     for (int k = k0; k < k1; ++k) np += o - 1 - k;
-    k_w_from_v<<<(unsigned)((long)np * ntp), 256, 0, st>>>(V, h->eps, dpairs, p0, k0, nl, nv, o, W, epart);
-    if (hipGetLastError() != hipSuccess) {
-      set_error("k_w_from_v launch failed");
-      rc = ADC2_ERR_HIP;
-    }
+    rc = w_group(h, k0, k1, dpairs, p0, np, V, W + p0 * nv2, epart, &ok, st);
     p0 += np;
-    *done = k1 >= o - 1;
   }
   if (hipStreamSynchronize(st) != hipSuccess && rc == ADC2_OK) {
     set_error("wbuild: stream synchronisation failed");
     rc = ADC2_ERR_HIP;
   }
   dfree(h, V);
+  *done = ok && rc == ADC2_OK;   // (without its memory: the MFMA kernel does every pair)
   return rc;
 }
 
-// T[t][c][a] = W_p[c][a] / D for the pairs p = p0 + t (antisymmetric like W).
+// T[t][c][a] = W[t][c][a] / D for the pairs pairs[t] (antisymmetric like W).
 __global__ void k_tau_chunk(const double2* __restrict__ W, const double* __restrict__ eps, const int2* __restrict__ pairs,
-                            int p0, int o, int nv, double2* __restrict__ T) {
-  const int2 kl = pairs[p0 + blockIdx.y];
+                            int o, int nv, double2* __restrict__ T) {
+  const int2 kl = pairs[blockIdx.y];
   const double ekl = eps[kl.x] + eps[kl.y];
-  const double2* w = W + (long)(p0 + blockIdx.y) * nv * nv;
+  const double2* w = W + (long)blockIdx.y * nv * nv;
   double2* t = T + (long)blockIdx.y * nv * nv;
   for (int e = blockIdx.x * 256 + threadIdx.x; e < nv * nv; e += gridDim.x * 256) {
     const int c = e / nv, a = e - c * nv;
@@ -299,81 +319,33 @@ __global__ void k_tau_chunk(const double2* __restrict__ W, const double* __restr
   }
 }
 
-// Wc[I][k][c][a] = <ca||Ik> and Tc the same over its denominator, every core I
-// and occupied k (zero at k = I).
-__global__ void k_core_rows(const double2* __restrict__ W, const double* __restrict__ eps, const int* __restrict__ pidx,
-                            int o, int nv, double2* __restrict__ Wc, double2* __restrict__ Tc) {
-  const int k = blockIdx.y % o, I = blockIdx.y / o;
-  const long base = (long)blockIdx.y * nv * nv;
-  const double s = I < k ? 1.0 : -1.0, eIk = eps[I] + eps[k];
-  const double2* w = W + (k == I ? 0L : (long)pidx[I * o + k] * nv * nv);
+// Rows of the core pairs among W[t], pairs[t] (core first spinor): Wc[I][k][c][a] =
+// <ca||Ik> and Tc the same over its denominator, I core, k any occupied; a pair of
+// two core spinors fills both of its rows.
+__global__ void k_core_rows(const double2* __restrict__ W, const double* __restrict__ eps, const int2* __restrict__ pairs,
+                            int nc, int o, int nv, double2* __restrict__ Wc, double2* __restrict__ Tc) {
+  const int2 kl = pairs[blockIdx.y];
+  const double ekl = eps[kl.x] + eps[kl.y];
+  const long nv2 = (long)nv * nv;
+  const double2* w = W + blockIdx.y * nv2;
+  const long r1 = ((long)kl.x * o + kl.y) * nv2, r2 = kl.y < nc ? ((long)kl.y * o + kl.x) * nv2 : -1;
   for (int e = blockIdx.x * 256 + threadIdx.x; e < nv * nv; e += gridDim.x * 256) {
     const int c = e / nv, a = e - c * nv;
-    const double2 v = k == I ? czero() : cscale(w[e], s);
-    Wc[base + e] = v;
-    Tc[base + e] = (k == I || a == c) ? czero() : cscale(v, 1.0 / (eps[o + a] + eps[o + c] - eIk));
+    const double2 v = w[e];
+    const double2 t = (a == c) ? czero() : cscale(v, 1.0 / (eps[o + a] + eps[o + c] - ekl));
+    Wc[r1 + e] = v;
+    Tc[r1 + e] = t;
+    if (r2 >= 0) {
+      Wc[r2 + e] = cneg(v);
+      Tc[r2 + e] = cneg(t);
+    }
   }
 }
 
-// Terms (i) and (iii) on the residue engine.  W is antisymmetric in its two
-// virtuals, so both operands of sum_c tau_ac conj(W_bc) are read as
-// (p, c) x a, contiguous in a (the two signs cancel).
-//   Bm[a][b] = sum_{p,c} T_p[c][a] conj(W_p[c][b]), tau formed for a chunk of pairs at a time
-//   E[I][J][a][b] = sum_{k,c} Tc[I][k][c][a] conj(Wc[J][k][c][b])
-static adc2_status pair_terms_rns(adc2_handle h, const double2* W, const int2* dpairs, int npairs, const int* dpidx,
-                                  double2* Bm, double2* E, bool* done_i, bool* done_iii, hipStream_t st) {
-  const Dims& d = h->d;
-  const int o = d.o, nv = d.nv, nc = d.nc;
-  const long nv2 = (long)nv * nv;
-  const unsigned gx = (unsigned)std::min<long>(64, (nv2 + 255) / 256);
-  adc2_status rc = ADC2_OK;
-  *done_i = *done_iii = false;
-  // pairs per chunk: K of about 10^5 terms (1.5 MB of tau per virtual), whatever
-  // the work-space target, so that the FP64 sum of the chunks does not depend on it
-  const long per = std::max<long>(1, std::min<long>({(long)npairs, 98304L / nv, 65535L}));
-  if (npairs > 0 && rns_pays(h, nv, nv, per * nv, rns_vs_tile(nv * 8L, nv * 8L))) {
-    double2* T = nullptr;
-    bool ok = dmalloc(h, &T, sizeof(double2) * per * nv2) == hipSuccess;
-    if (!ok) (void)hipGetLastError();
-    for (long p0 = 0; p0 < npairs && ok && rc == ADC2_OK; p0 += per) {
-      const int np = (int)std::min<long>(per, npairs - p0);
-      k_tau_chunk<<<dim3(gx, np), 256, 0, st>>>(W, h->eps, dpairs, (int)p0, o, nv, T);
-      if (hipGetLastError() != hipSuccess) {
-        set_error("k_tau_chunk launch failed");
-        rc = ADC2_ERR_HIP;
-        break;
-      }
-      rc = rns_product(h, rns_kmajor(T, nv, np * nv), nv, rns_kmajor(W + p0 * nv2, nv, np * nv, true), nv, np * nv,
-                       rns_rows(Bm, nv, 1.0, p0 > 0), 0.0, &ok, st);
-    }
-    *done_i = ok && rc == ADC2_OK;
-    (void)hipStreamSynchronize(st);
-    dfree(h, T);
-    if (rc != ADC2_OK) return rc;
-  }
-  if (rns_pays(h, (long)nc * nv, (long)nc * nv, (long)o * nv, rns_vs_tile((long)nc * nv, (long)nc * nv)) &&
-      (long)nc * o <= 65535) {
-    double2 *Wc = nullptr, *Tc = nullptr;
-    bool ok = dmalloc(h, &Wc, sizeof(double2) * nc * o * nv2) == hipSuccess &&
-              dmalloc(h, &Tc, sizeof(double2) * nc * o * nv2) == hipSuccess;
-    if (!ok) (void)hipGetLastError();
-    if (ok) {
-      k_core_rows<<<dim3(gx, nc * o), 256, 0, st>>>(W, h->eps, dpidx, o, nv, Wc, Tc);
-      if (hipGetLastError() != hipSuccess) {
-        set_error("k_core_rows launch failed");
-        rc = ADC2_ERR_HIP;
-      } else {
-        RnsSrc A{Tc, nv, o * nv2, 1, 1 << 30, 0, nv, false}, B{Wc, nv, o * nv2, 1, 1 << 30, 0, nv, true};
-        rc = rns_product(h, A, nc * nv, B, nc * nv, o * nv, RnsDst{E, nv, nc * nv2, nv, nv, nv2, 1, 1.0, false}, 0.0, &ok,
-                         st);
-      }
-    }
-    *done_iii = ok && rc == ADC2_OK;
-    (void)hipStreamSynchronize(st);
-    dfree(h, Wc);
-    dfree(h, Tc);
-  }
-  return rc;
+// Wc[I][I] = Tc[I][I] = 0
+__global__ void k_core_diag(int o, int nv, double2* __restrict__ Wc, double2* __restrict__ Tc) {
+  const long nv2 = (long)nv * nv, base = ((long)blockIdx.y * o + blockIdx.y) * nv2;
+  for (long e = blockIdx.x * 256 + threadIdx.x; e < nv2; e += gridDim.x * 256) Wc[base + e] = Tc[base + e] = czero();
 }
 
 // ---------------------------------------------------------------------------
@@ -466,6 +438,8 @@ __global__ void k_sum_splits(const double2* __restrict__ part, int nsplit, long 
 // Term (ii):  Q_IJ = 1/4 sum_k s sum_cd conj(W[pJ][c][d]) W[pI][c][d] (1/D^{cd}_{Ik} + 1/D^{cd}_{Jk})
 // one workgroup per (I, J, k); partials summed on the host side of assembly.
 // ---------------------------------------------------------------------------
+// CORE: W holds the signed core rows [I][k] (zero at k = I) instead of the pairs.
+template <bool CORE>
 __global__ __launch_bounds__(256) void k_qterm(const double2* __restrict__ W, const double* __restrict__ eps,
                                                 const int* __restrict__ pidx, int nc, int o, int nv,
                                                 double2* __restrict__ qpart) {
@@ -476,10 +450,10 @@ __global__ __launch_bounds__(256) void k_qterm(const double2* __restrict__ W, co
   const int tid = threadIdx.x;
   double2 acc = make_double2(0, 0);
   if (k != I && k != J) {
-    const int pI = pidx[I * o + k], pJ = pidx[J * o + k];
-    const double sI = (I < k) ? 1.0 : -1.0, sJ = (J < k) ? 1.0 : -1.0;
-    const double2* WI = W + (long)pI * nv * nv;
-    const double2* WJ = W + (long)pJ * nv * nv;
+    const long pI = CORE ? (long)I * o + k : pidx[I * o + k], pJ = CORE ? (long)J * o + k : pidx[J * o + k];
+    const double sI = (CORE || I < k) ? 1.0 : -1.0, sJ = (CORE || J < k) ? 1.0 : -1.0;
+    const double2* WI = W + pI * nv * nv;
+    const double2* WJ = W + pJ * nv * nv;
     const double eIk = eps[I] + eps[k], eJk = eps[J] + eps[k];
     for (long e = tid; e < (long)nv * nv; e += 256) {
       const int c = (int)(e / nv), dd = (int)(e % nv);
@@ -497,6 +471,92 @@ __global__ __launch_bounds__(256) void k_qterm(const double2* __restrict__ W, co
     __syncthreads();
   }
   if (tid == 0) qpart[blockIdx.x] = red[0];
+}
+
+// Terms (i) to (iii) of the singles block on the residue engine, without ever holding W
+// of all pairs (43 GB at nc=6 no=120 nv=600): group by group W is formed, its core
+// rows are kept, and tau W^H is added up.  W is antisymmetric in its two virtuals, so
+// both operands of sum_c tau_ac conj(W_bc) are read as (p, c) x a, contiguous in a
+// (the two signs cancel).
+//   Bm[a][b] = sum_{p,c} T_p[c][a] conj(W_p[c][b]), tau formed for about 10^5 terms at a time
+//   E[I][J][a][b] = sum_{k,c} Tc[I][k][c][a] conj(Wc[J][k][c][b])
+//   qpart by k_qterm from the core rows.
+// nc=6 no=60 nv=300 naux=1500: W, (i) and (iii) took 71 + 18 + 18 ms on FP64 MFMA tiles, 29 ms so.
+static adc2_status pair_terms_rns(adc2_handle h, const int2* dpairs, int npairs, double2* Bm, double2* E,
+                                  double2* qpart, double* epart, bool* done, hipStream_t st) {
+  const Dims& d = h->d;
+  const int o = d.o, nv = d.nv, nc = d.nc;
+  const long nv2 = (long)nv * nv;
+  const unsigned gx = (unsigned)std::min<long>(64, (nv2 + 255) / 256);
+  *done = false;
+  if (npairs == 0 || !w_pays(h)) return ADC2_OK;
+  const int g = pair_group(d);
+  long npmax = 0, p0 = 0;
+  for (int k0 = 0; k0 < o; k0 += g) {
+    long np = 0;
+    for (int k = k0; k < std::min(k0 + g, o); ++k) np += o - 1 - k;
+    npmax = std::max(npmax, np);
+  }
+  const long per = std::max<long>(1, std::min<long>({npmax, 98304L / nv, 65535L}));   // pairs per tau chunk
+  double2 *V = nullptr, *W = nullptr, *T = nullptr, *Wc = nullptr, *Tc = nullptr;
+  auto release = [&]() {
+    (void)hipStreamSynchronize(st);
+    for (double2* q : {V, W, T, Wc, Tc}) dfree(h, q);
+  };
+  if (dmalloc(h, &V, sizeof(double2) * g * o * nv2) != hipSuccess ||
+      dmalloc(h, &W, sizeof(double2) * std::max(1L, npmax) * nv2) != hipSuccess ||
+      dmalloc(h, &T, sizeof(double2) * per * nv2) != hipSuccess ||
+      dmalloc(h, &Wc, sizeof(double2) * nc * o * nv2) != hipSuccess ||
+      dmalloc(h, &Tc, sizeof(double2) * nc * o * nv2) != hipSuccess) {
+    (void)hipGetLastError();
+    release();
+    return ADC2_OK;
+  }
+  adc2_status rc = ADC2_OK;
+  auto launched = [&](const char* what) {
+    if (rc == ADC2_OK && hipGetLastError() != hipSuccess) {
+      set_error(std::string(what) + " launch failed");
+      rc = ADC2_ERR_HIP;
+    }
+    return rc == ADC2_OK;
+  };
+  bool ok = true;
+  k_core_diag<<<dim3(gx, nc), 256, 0, st>>>(o, nv, Wc, Tc);
+  launched("k_core_diag");
+  for (int k0 = 0; k0 < o - 1 && rc == ADC2_OK && ok; k0 += g) {
+    const int k1 = std::min(k0 + g, o);
+    int np = 0, ncore = 0;   // the group's pairs, and those with a core first spinor (they come first)
+    for (int k = k0; k < k1; ++k) {
+      np += o - 1 - k;
+      if (k < nc) ncore += o - 1 - k;
+    }
+    rc = w_group(h, k0, k1, dpairs, (int)p0, np, V, W, epart, &ok, st);
+    if (rc != ADC2_OK || !ok) break;
+    for (int q = 0; q < ncore; q += 65535) {
+      const int n = std::min(65535, ncore - q);
+      k_core_rows<<<dim3(gx, n), 256, 0, st>>>(W + q * nv2, h->eps, dpairs + p0 + q, nc, o, nv, Wc, Tc);
+      if (!launched("k_core_rows")) break;
+    }
+    for (long q = 0; q < np && rc == ADC2_OK && ok; q += per) {
+      const int n = (int)std::min<long>(per, np - q);
+      k_tau_chunk<<<dim3(gx, n), 256, 0, st>>>(W + q * nv2, h->eps, dpairs + p0 + q, o, nv, T);
+      if (!launched("k_tau_chunk")) break;
+      rc = rns_product(h, rns_kmajor(T, nv, n * nv), nv, rns_kmajor(W + q * nv2, nv, n * nv, true), nv, n * nv,
+                       rns_rows(Bm, nv, 1.0, p0 + q > 0), 0.0, &ok, st);
+    }
+    p0 += np;
+  }
+  if (rc == ADC2_OK && ok) {
+    const RnsSrc A{Tc, nv, o * nv2, 1, 1 << 30, 0, nv, false}, B{Wc, nv, o * nv2, 1, 1 << 30, 0, nv, true};
+    rc = rns_product(h, A, nc * nv, B, nc * nv, o * nv, RnsDst{E, nv, nc * nv2, nv, nv, nv2, 1, 1.0, false}, 0.0, &ok, st);
+  }
+  if (rc == ADC2_OK && ok) {
+    k_qterm<true><<<nc * nc * o, 256, 0, st>>>(Wc, h->eps, nullptr, nc, o, nv, qpart);
+    launched("k_qterm");
+  }
+  release();
+  *done = ok && rc == ADC2_OK;
+  return rc;
 }
 
 // ---------------------------------------------------------------------------
@@ -814,7 +874,6 @@ adc2_status build_m11(adc2_handle h, hipStream_t st) {
   SETUP_HIP(dmalloc(h, &dent, sizeof(int4) * std::max<size_t>(1, ent.size())));
   SETUP_HIP(dmalloc(h, &dsgn, sizeof(double) * std::max<size_t>(1, sgn.size())));
   SETUP_HIP(dmalloc(h, &doff, sizeof(int) * off.size()));
-  SETUP_HIP(dmalloc(h, &W, sizeof(double2) * std::max<long>(1, (long)npairs * nv2)));
   SETUP_HIP(dmalloc(h, &Bm, sizeof(double2) * nv2));
   SETUP_HIP(dmalloc(h, &E, sizeof(double2) * nc * nc * nv2));
   SETUP_HIP(dmalloc(h, &G2, sizeof(double2) * nc * nc * nv2));
@@ -826,43 +885,40 @@ adc2_status build_m11(adc2_handle h, hipStream_t st) {
   SETUP_HIP(hipMemcpyAsync(dsgn, sgn.data(), sizeof(double) * sgn.size(), hipMemcpyHostToDevice, st));
   SETUP_HIP(hipMemcpyAsync(doff, off.data(), sizeof(int) * off.size(), hipMemcpyHostToDevice, st));
 
-  // MP2 amplitudes / W for every occupied pair
-  bool done_w = false, done_i = false, done_iii = false;
-  if (npairs > 0) {
-    adc2_status rc = wbuild_rns(h, dpairs, W, epart, &done_w, st);
-    if (rc == ADC2_OK && !done_w) {
-      k_wbuild<<<(unsigned)nwblk, 256, 0, st>>>(h->Lvo, h->eps, dpairs, npairs, naux, nv, o, W, epart);
-      SETUP_HIP(hipGetLastError());
-    }
-    if (rc == ADC2_OK) rc = pair_terms_rns(h, W, dpairs, npairs, dpidx, Bm, E, &done_i, &done_iii, st);
+  bool done = false;
+  {
+    const adc2_status rc = pair_terms_rns(h, dpairs, npairs, Bm, E, qpart, epart, &done, st);
     if (rc != ADC2_OK) {
       hipStreamSynchronize(st);
       cleanup();
       return rc;
     }
   }
-  if (!done_i || !done_iii) SETUP_HIP(dmalloc(h, &part, sizeof(double2) * part_len));
-  // term (i): B = sum_{k<l} tau^{kl} W^{kl H}
-  if (npairs > 0 && !done_i) {
-    dim3 g(nb * nb * nsplit_i, 1);
-    k_pairc<<<g, 256, 0, st>>>(W, h->eps, dent, dsgn, doff, o, nv, nsplit_i, part);
-    SETUP_HIP(hipGetLastError());
-    k_sum_splits<<<grid_for(nv2), 256, 0, st>>>(part, nsplit_i, nv2, 1, Bm);
-    SETUP_HIP(hipGetLastError());
-  } else if (npairs == 0) {
-    SETUP_HIP(hipMemsetAsync(Bm, 0, sizeof(double2) * nv2, st));
-  }
-  // term (iii): E^{IJ} = sum_k tau^{Ik} W^{Jk H}
-  if (!done_iii) {
+  if (!done) {   // W of every pair and its contractions on FP64 MFMA tiles
+    SETUP_HIP(dmalloc(h, &W, sizeof(double2) * std::max<long>(1, (long)npairs * nv2)));
+    SETUP_HIP(dmalloc(h, &part, sizeof(double2) * part_len));
+    // term (i): B = sum_{k<l} tau^{kl} W^{kl H}
+    if (npairs > 0) {
+      k_wbuild<<<(unsigned)nwblk, 256, 0, st>>>(h->Lvo, h->eps, dpairs, npairs, naux, nv, o, W, epart);
+      SETUP_HIP(hipGetLastError());
+      dim3 g(nb * nb * nsplit_i, 1);
+      k_pairc<<<g, 256, 0, st>>>(W, h->eps, dent, dsgn, doff, o, nv, nsplit_i, part);
+      SETUP_HIP(hipGetLastError());
+      k_sum_splits<<<grid_for(nv2), 256, 0, st>>>(part, nsplit_i, nv2, 1, Bm);
+      SETUP_HIP(hipGetLastError());
+    } else {
+      SETUP_HIP(hipMemsetAsync(Bm, 0, sizeof(double2) * nv2, st));
+    }
+    // term (iii): E^{IJ} = sum_k tau^{Ik} W^{Jk H}
     dim3 g(nb * nb * nsplit_iii, nc * nc);
     k_pairc<<<g, 256, 0, st>>>(W, h->eps, dent, dsgn, doff + 1, o, nv, nsplit_iii, part);
     SETUP_HIP(hipGetLastError());
     k_sum_splits<<<grid_for(nv2 * nc * nc), 256, 0, st>>>(part, nsplit_iii, nv2, nc * nc, E);
     SETUP_HIP(hipGetLastError());
+    // term (ii)
+    k_qterm<false><<<nc * nc * o, 256, 0, st>>>(W, h->eps, dpidx, nc, o, nv, qpart);
+    SETUP_HIP(hipGetLastError());
   }
-  // term (ii)
-  k_qterm<<<nc * nc * o, 256, 0, st>>>(W, h->eps, dpidx, nc, o, nv, qpart);
-  SETUP_HIP(hipGetLastError());
   // first order
   {
     const long lds = (long)naux * nv;

@@ -213,19 +213,23 @@ __global__ __launch_bounds__(256) void k_cheb_mfma(const double2* __restrict__ U
       }
 }
 
-// K[m][i][jq] = sum_chb part of k_cheb_mfma   for m < MM, i < s, jq < qc
-__global__ void k_cheb_mfma_reduce(const double2* __restrict__ part, int s, int qc, int TP, int NM, int nz, int nchb,
-                                   int MM, double2* __restrict__ K) {
-  const long total = (long)MM * s * qc;
-  for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < total; e += (long)gridDim.x * blockDim.x) {
-    const int m = (int)(e / ((long)s * qc));
-    const int p = (int)(e % ((long)s * qc));          // i * qc + jq
-    const int tile = p / TP, pl = p % TP;
-    const int z = m / NM, mm = m % NM;
-    const double2* src = part + (long)(tile * nz + z) * nchb * ((long)TP * NM) + (long)pl * NM + mm;
-    double2 a = make_double2(0.0, 0.0);
-    for (int b = 0; b < nchb; ++b) a = cadd(a, src[(long)b * TP * NM]);
-    K[e] = a;
+// K[m][i][jq] = sum_chb part of k_cheb_mfma   for m < MM, i < s, jq < qc: a workgroup owns the NM
+// moments of 64 / NM pairs (64 consecutive partials), its 16 waves share the slices
+__global__ __launch_bounds__(1024) void k_cheb_mfma_reduce(const double2* __restrict__ part, int s, int qc, int TP,
+                                                           int NM, int nz, int nchb, int MM, double2* __restrict__ K) {
+  __shared__ double2 red[16][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, z = blockIdx.y;
+  const int p = blockIdx.x * (64 / NM) + lane / NM, m = z * NM + lane % NM;
+  const int tile = blockIdx.x * (64 / NM) / TP, o = blockIdx.x * 64 - tile * TP * NM + lane;
+  const double2* src = part + (long)(tile * nz + z) * nchb * ((long)TP * NM) + o;
+  double2 a = czero();
+#pragma unroll 4
+  for (int b = w; b < nchb; b += 16) a = cadd(a, src[(long)b * TP * NM]);
+  red[w][lane] = a;
+  __syncthreads();
+  if (w == 0 && p < s * qc && m < MM) {
+    for (int t = 1; t < 16; ++t) a = cadd(a, red[t][lane]);
+    K[(long)m * s * qc + p] = a;
   }
 }
 
@@ -544,7 +548,8 @@ adc2_status fold_davidson(adc2_handle h, int k, const adc2_dav_opts* opt, const 
   } while (0)
 
   int nchb = (int)std::max<long>(1, std::min<long>(512, nd / 4096));
-  if (const char* v = getenv("ADC2_CHEB_NCHB")) nchb = (int)std::max<long>(1, std::min<long>(1024, atol(v)));
+  const char* nchb_env = getenv("ADC2_CHEB_NCHB");
+  if (const char* v = nchb_env) nchb = (int)std::max<long>(1, std::min<long>(1024, atol(v)));
   const int nmb = FMM / FMB;
   const long part_len = (long)((FSMAX + FGB - 1) / FGB) * nmb * nchb * FMB * 256;   // split-K partials of the moments
   const int nrb = fold_resid_blocks(ns);
@@ -581,8 +586,7 @@ adc2_status fold_davidson(adc2_handle h, int k, const adc2_dav_opts* opt, const 
   FD_TRY(dalloc((void**)&PG, sizeof(double2) * JMAX * k));
   FD_TRY(dalloc((void**)&gref, sizeof(double2) * k * ns));
   FD_TRY(dalloc((void**)&gsc, sizeof(double2) * 16L * dav_nblk(ns) * 256));
-  double *hw, *lam, *npart, *ov, *gnd, *omd, *scd, *pnu_d, *pdb_d, *mm;
-  FD_TRY(dalloc((void**)&hw, sizeof(double) * JMAX));
+  double *lam, *npart, *ov, *gnd, *omd, *scd, *pnu_d, *pdb_d, *mm;
   FD_TRY(dalloc((void**)&lam, sizeof(double) * JMAX));
   FD_TRY(dalloc((void**)&npart, sizeof(double) * k * nrb));
   FD_TRY(dalloc((void**)&ov, sizeof(double) * k * nbr));
@@ -717,7 +721,6 @@ adc2_status fold_davidson(adc2_handle h, int k, const adc2_dav_opts* opt, const 
     for (int c0 = j0; c0 < j0 + q; c0 += FGB) {
       const int qc = std::min(FGB, j0 + q - c0);
       const int mm_ = mblocks * FMB;
-      const long tot = (long)mm_ * srows * qc;
       // 16 or 32 moments per pass (z-slices for more); 128 or 256 pairs per workgroup
       const int ncb = mm_ > 16 ? 2 : 1;
       const int nm = 16 * ncb;
@@ -726,7 +729,10 @@ adc2_status fold_davidson(adc2_handle h, int k, const adc2_dav_opts* opt, const 
       const int rb = npair > 128 ? 4 : 2;
       const int tp = 64 * rb;
       const int ntile = (npair + tp - 1) / tp;
-      int nch_m = (int)std::max<long>(1, std::min<long>(nchb, (nd + MKC - 1) / MKC));
+      // slices of the doubles: two workgroups on each of the 256 compute units where the doubles have
+      // that many chunks (one slice per 4096 doubles left 145 workgroups for 0.6 M doubles, 0.9 ms a call)
+      const long want = nchb_env ? nchb : std::max<long>(nchb, 512 / ((long)ntile * nz));
+      int nch_m = (int)std::max<long>(1, std::min<long>(want, (nd + MKC - 1) / MKC));
       while (nch_m > 1 && (long)ntile * nz * nch_m * tp * nm > part_len) nch_m /= 2;
       dim3 g(nch_m, ntile, nz);
 #define CHEB_MFMA(NCB_, RB_)                                                                              \
@@ -738,8 +744,7 @@ adc2_status fold_davidson(adc2_handle h, int k, const adc2_dav_opts* opt, const 
       else CHEB_MFMA(2, 2);
 #undef CHEB_MFMA
       ADC2_CHECK_LAUNCH();
-      k_cheb_mfma_reduce<<<(unsigned)std::min<long>(4096, (tot + 255) / 256), 256, 0, st>>>(part, srows, qc, tp,
-                                                                                            nm, nz, nch_m, mm_, Kt);
+      k_cheb_mfma_reduce<<<dim3((npair * nm + 63) / 64, nz), 1024, 0, st>>>(part, srows, qc, tp, nm, nz, nch_m, mm_, Kt);
       ADC2_CHECK_LAUNCH();
       adc2_status r = fold_cheb_scatter(Kt, mm_, srows, c0, qc, Kall, st);
       if (r != ADC2_OK) return r;
@@ -864,7 +869,6 @@ adc2_status fold_davidson(adc2_handle h, int k, const adc2_dav_opts* opt, const 
   for (it = 1; it <= max_iter; ++it) {
     // ---- projected nonlinear problem: one workgroup per root, lowest eigenvalue of H11 first ----
     const auto tp0 = now();
-    FD_TRY(dav_heevj(Hd, s, JMAX, hw, nullptr, JMAX, st));
     // a pole at |x| >= 1.05 has r = |x| - sqrt(x^2 - 1) < 0.73 and r^126 < 1e-17,
     // so at most 126 Chebyshev terms: with the shifted inverse, roots closer
     // to min D than about 0.025 (min D - w0) are out of reach of this solver
@@ -875,7 +879,7 @@ adc2_status fold_davidson(adc2_handle h, int k, const adc2_dav_opts* opt, const 
         ent[b] = FoldEntry{R.branch, R.slot, R.zsize, have_omega ? 1 : 0, R.omega};
       }
       FD_TRY(up(entd, ent.data(), sizeof(FoldEntry) * nbr));
-      FD_TRY(fold_solve_launch(Hd, Kall, s, FMB * mcomp, fmap(), Dmin, hi0, tol, hw, entd, nbr, resd, Ybr, Zbr, bndd,
+      FD_TRY(fold_solve_launch(Hd, Kall, s, FMB * mcomp, fmap(), Dmin, hi0, tol, entd, nbr, resd, Ybr, Zbr, bndd,
                                st));
       FD_TRY(down(rres.data(), resd, sizeof(FoldResult) * nbr));
       int need = 0;

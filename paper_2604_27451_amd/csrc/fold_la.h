@@ -41,7 +41,7 @@ struct FoldBounds {
 };
 
 adc2_status fold_solve_launch(const double2* H, const double2* K, int s, int Mmax, const FoldMap& map, double Dmin,
-                              double hi0, double tol, const double* hw, const FoldEntry* ent, int n,
+                              double hi0, double tol, const FoldEntry* ent, int n,
                               FoldResult* res, double2* Ybr, double2* Zbr, FoldBounds* bnd, hipStream_t st);
 adc2_status fold_gather_y(const double2* Ybr, const int* slot, const double* scale, int s, int q, double2* Y,
                           hipStream_t st);

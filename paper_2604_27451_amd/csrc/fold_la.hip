@@ -113,6 +113,41 @@ __device__ __forceinline__ void fold_hermitian(JacobiSmem& S, int s) {
   __syncthreads();
 }
 
+// s x s product fa(i, k) fb(k, j) in FP64 matrix instructions, one 16 x 16 tile a wave of the
+// 16: row 16 (w / 4) + lane / 16 + 4 r, column 16 (w % 4) + lane % 16 in re[r], im[r].
+// fa and fb are only called inside the matrix.  (As sums of one thread an entry a product
+// of 48 x 48 read 400 KB of LDS an operand, 20 us.)
+template <class FA, class FB>
+__device__ __forceinline__ void fold_mm(int s, FA fa, FB fb, d4& re, d4& im) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int i = 16 * (w >> 2) + (lane & 15), j = 16 * (w & 3) + (lane & 15);
+  re = im = d4{0.0, 0.0, 0.0, 0.0};
+  if (16 * (w >> 2) >= s || 16 * (w & 3) >= s) return;   // the same for the whole wave
+  for (int k0 = 0; k0 < s; k0 += 4) {
+    const int k = k0 + (lane >> 4);
+    const double2 a = i < s && k < s ? fa(i, k) : czero(), b = j < s && k < s ? fb(k, j) : czero();
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, im, 0, 0, 0);
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.y, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.x, im, 0, 0, 0);
+  }
+}
+
+// the product of fold_mm into S.ar / S.ai, after every wave has read its operands (ends with a barrier)
+__device__ __forceinline__ void fold_mm_store(JacobiSmem& S, int s, const d4& re, const d4& im) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int i = 16 * (w >> 2) + (lane >> 4) + 4 * r, j = 16 * (w & 3) + (lane & 15);
+    if (i < s && j < s) {
+      S.ar[i][j] = re[r];
+      S.ai[i][j] = im[r];
+    }
+  }
+  __syncthreads();
+}
+
 // S.zt[c][r] = Zp[r][c], the stored warm x warm eigenvectors padded with the identity to s
 __device__ __forceinline__ void fold_load_z(JacobiSmem& S, const double2* Zg, int warm, int s) {
   for (int e = threadIdx.x; e < JMAX * JMAX; e += JTHR) {
@@ -124,8 +159,7 @@ __device__ __forceinline__ void fold_load_z(JacobiSmem& S, const double2* Zg, in
 
 __global__ __launch_bounds__(JTHR) void k_fold_solve(const double2* __restrict__ H, const double2* __restrict__ K,
                                                      int s, int Mmax, FoldMap map, double Dmin, double hi0,
-                                                     double tol, const double* __restrict__ hw,
-                                                     const FoldEntry* __restrict__ ent,
+                                                     double tol, const FoldEntry* __restrict__ ent,
                                                      FoldResult* __restrict__ res, double2* __restrict__ Ybr,
                                                      double2* __restrict__ Zbr, FoldBounds* __restrict__ bnd) {
   __shared__ JacobiSmem S;
@@ -142,10 +176,31 @@ __global__ __launch_bounds__(JTHR) void k_fold_solve(const double2* __restrict__
   R.status = R.need = R.ysize = R.zsize = 0;
   const int j = E.branch;
   double2* Zg = Zbr + (long)E.slot * JMAX * JMAX;
+  // lower bound of the eigenvalues of H11 (Gershgorin's discs; the bracket only needs a
+  // bound, and an eigensolve of H11 took 0.37 ms an iteration) and the trace of K_0
+  if (tid < 64) {
+    double lo = 1e300, t0 = 0.0;
+    if (tid < s) {
+      lo = H[(long)tid * JMAX + tid].x;
+      for (int l = 0; l < s; ++l)
+        if (l != tid) {
+          const double2 a = H[(long)l * JMAX + tid], b = H[(long)tid * JMAX + l];
+          lo -= fmax(sqrt(a.x * a.x + a.y * a.y), sqrt(b.x * b.x + b.y * b.y));
+        }
+      t0 = K[(long)tid * JMAX + tid].x;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+      lo = fmin(lo, __shfl_xor(lo, off));
+      t0 += __shfl_xor(t0, off);
+    }
+    if (tid == 0) {
+      wsh[0] = lo;
+      wsh[1] = t0;
+    }
+  }
+  __syncthreads();
   if (tid == 0) {
-    double T0 = 0.0;
-    for (int i = 0; i < s; ++i) T0 += K[(long)i * JMAX + i].x;
-    const double lam_min = hw[0];
+    const double T0 = wsh[1], lam_min = wsh[0];
     const double zb = 0.5 * (-(lam_min - Dmin) + sqrt((lam_min - Dmin) * (lam_min - Dmin) + 4.0 * fmax(T0, 0.0))) + 1.0;
     const double lo0 = Dmin - zb;
     const double wlo = map.inv ? fmax(lo0, map.w0 + 0.1 * (Dmin - map.w0)) : lo0;
@@ -207,46 +262,16 @@ __global__ __launch_bounds__(JTHR) void k_fold_solve(const double2* __restrict__
       // (column c of Zp into S.zt[c], then G Zp, then the product from the left)
       fold_load_z(S, Zg, warm, s);
       __syncthreads();
-      double2 t[4];   // this thread's entries of G Zp
-  #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int e = tid + u * JTHR, i = e & 63, c = e >> 6;
-        double2 a = czero();
-        if (i < s && c < s)
-          for (int l = 0; l < s; ++l) a = cadd(a, cmul(make_double2(S.ar[i][l], S.ai[i][l]), S.zt[c][l]));
-        t[u] = a;
-      }
-      __syncthreads();
-  #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int e = tid + u * JTHR, i = e & 63, c = e >> 6;
-        if (i < s && c < s) {
-          S.ar[i][c] = t[u].x;
-          S.ai[i][c] = t[u].y;
-        }
-      }
-      __syncthreads();
-  #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int e = tid + u * JTHR, c = e & 63, r = e >> 6;
-        double2 a = czero();
-        if (r < s && c < s)
-          for (int i = 0; i < s; ++i) a = cadd(a, cmul(cconj(S.zt[r][i]), make_double2(S.ar[i][c], S.ai[i][c])));
-        t[u] = a;
-      }
-      __syncthreads();
-  #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int e = tid + u * JTHR, c = e & 63, r = e >> 6;
-        if (r < s && c < s) {
-          S.ar[r][c] = t[u].x;
-          S.ai[r][c] = t[u].y;
-        }
-      }
-      __syncthreads();
+      d4 re, im;
+      fold_mm(s, [&](int i, int k) { return make_double2(S.ar[i][k], S.ai[i][k]); },
+              [&](int k, int c) { return S.zt[c][k]; }, re, im);
+      fold_mm_store(S, s, re, im);
+      fold_mm(s, [&](int r, int k) { return cconj(S.zt[r][k]); },
+              [&](int k, int c) { return make_double2(S.ar[k][c], S.ai[k][c]); }, re, im);
+      fold_mm_store(S, s, re, im);
       fold_hermitian(S, s);
     }
-    jacobi_lds<true>(S, s);
+    jacobi_lds(S, s);
     if (!S.done) {
       status = 5;
       if (tid == 0) R.status = 5;
@@ -264,30 +289,10 @@ __global__ __launch_bounds__(JTHR) void k_fold_solve(const double2* __restrict__
       S.ai[r][c] = z.y;
     }
     __syncthreads();
-    double2 zn[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = tid + u * JTHR, r = e & 63, c = e >> 6;
-      double2 a = czero();
-      if (r < s && c < s) {
-        const double2* z = S.zt[S.perm[c]];
-        if (r < warm)
-          for (int i = 0; i < warm; ++i) a = cadd(a, cmul(make_double2(S.ar[r][i], S.ai[r][i]), z[i]));
-        else
-          a = z[r];
-      }
-      zn[u] = a;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = tid + u * JTHR, r = e & 63, c = e >> 6;
-      if (r < s && c < s) {
-        S.ar[r][c] = zn[u].x;
-        S.ai[r][c] = zn[u].y;
-      }
-    }
-    __syncthreads();
+    d4 re, im;
+    fold_mm(s, [&](int r, int k) { return make_double2(S.ar[r][k], S.ai[r][k]); },
+            [&](int k, int c) { return S.zt[S.perm[c]][k]; }, re, im);
+    fold_mm_store(S, s, re, im);
     for (int e = tid; e < JMAX * JMAX; e += JTHR) {
       const int r = e >> 6, c = e & 63;
       if (r < s && c < s) Zg[(long)r * JMAX + c] = make_double2(S.ar[r][c], S.ai[r][c]);
@@ -362,39 +367,51 @@ __global__ void k_fold_gather_y(const double2* __restrict__ Ybr, const int* __re
 
 // For the c-th of q roots (grid (blocks over e, q)): x1 = V y_c, r1 = S1 y_c + Sx[c] - om_c x1 (Sx: the
 // M12 x2 part, singles of rows with stride ldx), written to row row[c] of X1 and R1 (row c without a
-// row list); npart[c][blk] = the block's share of |r1|^2.
-__global__ __launch_bounds__(256) void k_fold_resid(const double2* __restrict__ V, const double2* __restrict__ S1,
-                                                     int s, long ns, const double2* __restrict__ Y, int q,
-                                                     const double* __restrict__ om, const double2* __restrict__ Sx,
-                                                     long ldx, const int* __restrict__ row,
-                                                     double2* __restrict__ X1, double2* __restrict__ R1,
-                                                     double* __restrict__ npart) {
+// row list); npart[c][blk] = the block's share of |r1|^2.  A workgroup owns 64 entries, its waves
+// share the basis vectors (one thread an entry walked them all: 94 us for three roots, 48 vectors of 600).
+constexpr int RW = 16;
+__global__ __launch_bounds__(64 * RW) void k_fold_resid(const double2* __restrict__ V, const double2* __restrict__ S1,
+                                                        int s, long ns, const double2* __restrict__ Y, int q,
+                                                        const double* __restrict__ om, const double2* __restrict__ Sx,
+                                                        long ldx, const int* __restrict__ row,
+                                                        double2* __restrict__ X1, double2* __restrict__ R1,
+                                                        double* __restrict__ npart) {
   __shared__ double2 yc[JMAX];
-  __shared__ double red[256];
+  __shared__ double2 red[2][RW][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int j = blockIdx.y;
   const long orow = row ? row[j] : j;
-  for (int i = threadIdx.x; i < s; i += 256) yc[i] = Y[(long)i * q + j];
-  __syncthreads();
+  for (int i = threadIdx.x; i < s; i += 64 * RW) yc[i] = Y[(long)i * q + j];
   double acc = 0.0;
-  for (long e = blockIdx.x * 256L + threadIdx.x; e < ns; e += (long)gridDim.x * 256) {
-    double2 x = make_double2(0.0, 0.0), r = Sx[(long)j * ldx + e];
-    for (int i = 0; i < s; ++i) {
-      x = cadd(x, cmul(V[(long)i * ns + e], yc[i]));
-      r = cadd(r, cmul(S1[(long)i * ns + e], yc[i]));
-    }
-    r.x -= om[j] * x.x;
-    r.y -= om[j] * x.y;
-    X1[orow * ns + e] = x;
-    R1[orow * ns + e] = r;
-    acc += r.x * r.x + r.y * r.y;
-  }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
-    if (threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
+  for (long e0 = blockIdx.x * 64L; e0 < ns; e0 += (long)gridDim.x * 64) {
+    const long e = e0 + lane, ec = e < ns ? e : ns - 1;
     __syncthreads();
+    double2 x = czero(), r = czero();
+#pragma unroll 4
+    for (int i = w; i < s; i += RW) {
+      x = cadd(x, cmul(V[(long)i * ns + ec], yc[i]));
+      r = cadd(r, cmul(S1[(long)i * ns + ec], yc[i]));
+    }
+    red[0][w][lane] = x;
+    red[1][w][lane] = r;
+    __syncthreads();
+    if (w == 0 && e < ns) {
+      r = cadd(r, Sx[(long)j * ldx + e]);
+      for (int t = 1; t < RW; ++t) {
+        x = cadd(x, red[0][t][lane]);
+        r = cadd(r, red[1][t][lane]);
+      }
+      r.x -= om[j] * x.x;
+      r.y -= om[j] * x.y;
+      X1[orow * ns + e] = x;
+      R1[orow * ns + e] = r;
+      acc += r.x * r.x + r.y * r.y;
+    }
   }
-  if (threadIdx.x == 0) npart[(long)j * gridDim.x + blockIdx.x] = red[0];
+  if (w == 0) {
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+    if (lane == 0) npart[(long)j * gridDim.x + blockIdx.x] = acc;
+  }
 }
 
 // T[c][e] = r1[root_c][e] / (om_c - d11_e - nu_e / (om_c - Dbar_e)), the approximate diagonal of the
@@ -631,13 +648,13 @@ __global__ __launch_bounds__(1024) void k_fold_mgs(double2* __restrict__ T, int 
 // Host launchers
 // ---------------------------------------------------------------------------
 adc2_status fold_solve_launch(const double2* H, const double2* K, int s, int Mmax, const FoldMap& map, double Dmin,
-                              double hi0, double tol, const double* hw, const FoldEntry* ent, int n,
+                              double hi0, double tol, const FoldEntry* ent, int n,
                               FoldResult* res, double2* Ybr, double2* Zbr, FoldBounds* bnd, hipStream_t st) {
   if (s <= 0 || s > JMAX || n <= 0) {
     set_error("adc2_davidson (folded): projected problem size out of range");
     return ADC2_ERR_ARG;
   }
-  k_fold_solve<<<n, JTHR, 0, st>>>(H, K, s, Mmax, map, Dmin, hi0, tol, hw, ent, res, Ybr, Zbr, bnd);
+  k_fold_solve<<<n, JTHR, 0, st>>>(H, K, s, Mmax, map, Dmin, hi0, tol, ent, res, Ybr, Zbr, bnd);
   ADC2_CHECK_LAUNCH();
   return ADC2_OK;
 }
@@ -649,14 +666,14 @@ adc2_status fold_gather_y(const double2* Ybr, const int* slot, const double* sca
   return ADC2_OK;
 }
 
-int fold_resid_blocks(long ns) { return (int)std::max<long>(1, std::min<long>(256, (ns + 1023) / 1024)); }
+int fold_resid_blocks(long ns) { return (int)std::max<long>(1, std::min<long>(256, (ns + 63) / 64)); }
 
 adc2_status fold_resid(const double2* V, const double2* S1, int s, long ns, const double2* Y, int q, const double* om,
                        const double2* Sx, long ldx, const int* row, double2* X1, double2* R1, double* npart,
                        hipStream_t st) {
   if (q <= 0) return ADC2_OK;
   dim3 g(fold_resid_blocks(ns), q);
-  k_fold_resid<<<g, 256, 0, st>>>(V, S1, s, ns, Y, q, om, Sx, ldx, row, X1, R1, npart);
+  k_fold_resid<<<g, 64 * RW, 0, st>>>(V, S1, s, ns, Y, q, om, Sx, ldx, row, X1, R1, npart);
   ADC2_CHECK_LAUNCH();
   return ADC2_OK;
 }

@@ -20,7 +20,11 @@ namespace adc2 {
 constexpr int GB = 16;     // Gram tile (rows of V x rows of W)
 constexpr int GCH = 64;    // elements per LDS chunk
 
-int dav_nblk(long dim) { return (int)std::max<long>(1, std::min<long>(1024, (dim + 4095) / 4096)); }
+// (short vectors, as the singles of the folded solver: up to 64 blocks of 256 elements;
+// on one block a Gram product of 48 x 3 vectors of 600 took 33 us)
+int dav_nblk(long dim) {
+  return (int)std::max<long>({1L, std::min<long>(64, (dim + 255) / 256), std::min<long>(1024, (dim + 4095) / 4096)});
+}
 
 // partial[blk][ii][jj] = sum_{e in this block's chunks} conj(V[i0+ii][e]) W[j0+jj][e]
 __global__ __launch_bounds__(256) void k_gram_part(const double2* __restrict__ V, int s,
@@ -282,36 +286,24 @@ adc2_status dav_unit_guess(double2* V, int g, long dim, const int* idx, hipStrea
 // the parallel cyclic Jacobi of jacobi.h; ascending eigenvalues w[n] and
 // eigenvectors as columns of Z (row-major, ldz).
 // ---------------------------------------------------------------------------
-// Z may be NULL: eigenvalues only.
-template <bool VEC>
 __global__ __launch_bounds__(JTHR) void k_heevj(const double2* __restrict__ G, int n, int ldg, double* __restrict__ w,
                                                 double2* __restrict__ Z, int ldz) {
   __shared__ JacobiSmem S;
   const int tid = threadIdx.x;
   for (int e = tid; e < JMAX * JMAX; e += JTHR) {
     const int i = e >> 6, j = e & 63;
-    if (i >= n || j >= n) continue;
-    double x, y;
-    if (i <= j) {
-      const double2 g = G[(long)i * ldg + j];
-      x = g.x;
-      y = (i == j) ? 0.0 : g.y;
-    } else {
-      const double2 g = G[(long)j * ldg + i];
-      x = g.x;
-      y = -g.y;
-    }
-    S.ar[i][j] = x;
-    S.ai[i][j] = y;
+    if (i > j || j >= n) continue;
+    const double2 g = G[(long)i * ldg + j];
+    S.ar[i][j] = g.x;
+    S.ai[i][j] = i == j ? 0.0 : g.y;
   }
   __syncthreads();
-  jacobi_lds<VEC>(S, n);
+  jacobi_lds(S, n);
   if (tid < n) w[tid] = S.ar[S.perm[tid]][S.perm[tid]];
-  if (VEC)
-    for (int e = tid; e < JMAX * JMAX; e += JTHR) {
-      const int r = e >> 6, c = e & 63;
-      if (r < n && c < n) Z[(long)r * ldz + c] = S.zt[S.perm[c]][r];
-    }
+  for (int e = tid; e < JMAX * JMAX; e += JTHR) {
+    const int r = e >> 6, c = e & 63;
+    if (r < n && c < n) Z[(long)r * ldz + c] = S.zt[S.perm[c]][r];
+  }
 }
 
 adc2_status dav_heevj(const double2* G, int n, int ldg, double* w, double2* Z, int ldz, hipStream_t st) {
@@ -319,8 +311,7 @@ adc2_status dav_heevj(const double2* G, int n, int ldg, double* w, double2* Z, i
     set_error("dav_heevj: subspace dimension out of range");
     return ADC2_ERR_ARG;
   }
-  if (Z) k_heevj<true><<<1, JTHR, 0, st>>>(G, n, ldg, w, Z, ldz);
-  else k_heevj<false><<<1, JTHR, 0, st>>>(G, n, ldg, w, Z, ldz);
+  k_heevj<<<1, JTHR, 0, st>>>(G, n, ldg, w, Z, ldz);
   ADC2_CHECK_LAUNCH();
   return ADC2_OK;
 }

@@ -969,17 +969,22 @@ __global__ __launch_bounds__(256) void k_lvo_transpose(const double2* __restrict
 constexpr int LJG = 4;
 constexpr int LC = 64;   // columns a workgroup
 constexpr int LD = 64;   // d per staged run of coefficients
-template <class TI>
-__global__ __launch_bounds__(256) void k_light1(const TI* __restrict__ Rt, const double2* __restrict__ Vt, int mI0,
-                                                 int nrow, int nc, int no, int nv, double2* __restrict__ Tp) {
-  __shared__ double2 vs[LJG][LD][8];
+// DS waves share the d of a run
+template <class TI, int DS>
+__global__ __launch_bounds__(256 * DS) void k_light1(const TI* __restrict__ Rt, const double2* __restrict__ Vt, int mI0,
+                                                      int nrow, int nc, int no, int nv, double2* __restrict__ Tp) {
+  constexpr int NW = LJG * DS;
+  constexpr int NQ = DS > 1 ? 4 : 8;   // values of q reduced at a time
+  static_assert(NQ * (NW - 1) * 64 <= 64 * 64, "LDS");
+  __shared__ double2 sh[NW * NQ * 64 > LJG * LD * 8 ? NW * NQ * 64 : LJG * LD * 8];
+  double2(*vs)[LD][8] = (double2(*)[LD][8])sh;
   const int ncb = (nv + LC - 1) / LC;
   const int njg = (no + LJG - 1) / LJG;
   const int cb = blockIdx.x % ncb;
   const int jg = (blockIdx.x / ncb) % njg;
   const int ml = blockIdx.x / (ncb * njg), mI = mI0 + ml;
   const int I = mI % nc;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, w = wave % LJG, ds = wave / LJG;
   const int c = cb * LC + lane;
   const int cs = c < nv ? c : 0;
   const int j = jg * LJG + w;
@@ -993,16 +998,16 @@ __global__ __launch_bounds__(256) void k_light1(const TI* __restrict__ Rt, const
     for (int q = 0; q < 8; ++q) acc[q] = czero();
     for (int d0 = 0; d0 < nv; d0 += LD) {
       __syncthreads();
-      for (int e = lane; e < 8 * LD; e += 64) {
-        const int q = e / LD, dd = e % LD;
-        const int K = K0 + q, d = d0 + dd;
-        vs[w][dd][q] = (jok && K < nc && d < nv) ? cconj(V[(long)K * nv + d]) : czero();
+#pragma unroll
+      for (int u = 0; u < 8 / DS; ++u) {
+        const int q = u * DS + ds, K = K0 + q, d = d0 + lane;
+        vs[w][lane][q] = (jok && K < nc && d < nv) ? cconj(V[(long)K * nv + d]) : czero();
       }
       __syncthreads();
-      const int dend = min(LD, nv - d0);
+      const int dend = min((ds + 1) * (LD / DS), nv - d0);
       // eight loads in flight a lane; past the end of the run the last row is read again and its
       // coefficients are zero; a lane past the last column reads column 0, its sums are never stored
-      for (int dd = 0; dd < dend; dd += 8) {
+      for (int dd = ds * (LD / DS); dd < dend; dd += 8) {
         TI r[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) r[u] = R[(long)min(d0 + dd + u, nv - 1) * ld];
@@ -1014,21 +1019,38 @@ __global__ __launch_bounds__(256) void k_light1(const TI* __restrict__ Rt, const
         }
       }
     }
-    __syncthreads();
-    double2* red = &vs[0][0][0];   // 3 x 8 x 64
-    if (w > 0)
 #pragma unroll
-      for (int q = 0; q < 8; ++q) red[((w - 1) * 8 + q) * 64 + lane] = acc[q];
-    __syncthreads();
-    if (w == 0 && c < nv)
+    for (int q0 = 0; q0 < 8; q0 += NQ) {
+      __syncthreads();
+      if (wave > 0)
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        if (K0 + q >= nc) break;
-        double2 t = acc[q];
-        for (int v = 0; v < 3; ++v) t = cadd(t, red[(v * 8 + q) * 64 + lane]);
-        Tp[(((long)mI * njg + jg) * nc + K0 + q) * nv + c] = t;
-      }
+        for (int q = 0; q < NQ; ++q) sh[((wave - 1) * NQ + q) * 64 + lane] = acc[q0 + q];
+      __syncthreads();
+      if (wave == 0 && c < nv)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+          if (K0 + q0 + q >= nc) break;
+          double2 t = acc[q0 + q];
+          for (int v = 0; v < NW - 1; ++v) t = cadd(t, sh[(v * NQ + q) * 64 + lane]);
+          Tp[(((long)mI * njg + jg) * nc + K0 + q0 + q) * nv + c] = t;
+        }
+    }
   }
+}
+
+// the partials of nrow rows from mI0 on (R: their unpacked doubles)
+template <class TI>
+static void light1_launch(const TI* R, const double2* Vt, int mI0, int nrow, const Dims& d, double2* Tp,
+                          hipStream_t st) {
+  const int per = cdiv(d.no, LJG) * cdiv(d.nv, LC);
+  // By the system alone, not by the rows: every chunking of a block sums in the same order.
+  // Up to 128 workgroups a vector four waves share a run: 23 us against 42 us with one (24 rows
+  // of no=12 nv=100), 12 against 18 (6 rows of no=10 nv=40).  From there the chip is full with
+  // one: 0.30 ms against 0.32 ms with four (a chunk of 12 rows of no=60 nv=300).
+  if (per * d.nc <= 128)
+    k_light1<TI, 4><<<(unsigned)((long)nrow * per), 1024, 0, st>>>(R, Vt, mI0, nrow, d.nc, d.no, d.nv, Tp);
+  else
+    k_light1<TI, 1><<<(unsigned)((long)nrow * per), 256, 0, st>>>(R, Vt, mI0, nrow, d.nc, d.no, d.nv, Tp);
 }
 
 // sigma2 = Z_ab - Z_ba + D r2 + sum_K (<Ka||Ij> r1_Kb - r1_Ka <Kb||Ij>), a < b, packed.
@@ -1597,7 +1619,7 @@ static adc2_status rns_doubles_in(adc2_handle h, const SigReq& rq, RnsProf& pf, 
   double2* R = (double2*)(h->rns_ws + p.f64);
   int8_t* out = (int8_t*)(h->rns_ws + p.out);
   const RnsMat L = rns_static(h->rns_lvt, d.naux, K);
-  const int nb = cdiv(d.nv, UT), njg = (d.no + LJG - 1) / LJG;
+  const int nb = cdiv(d.nv, UT);
   for (int r0 = 0; r0 < rows; r0 += p.c) {
     const int c = std::min(p.c, rows - r0);
     adc2_status rc = pf.run(0, [&]() -> adc2_status {
@@ -1608,8 +1630,7 @@ static adc2_status rns_doubles_in(adc2_handle h, const SigReq& rq, RnsProf& pf, 
     });
     if (rc != ADC2_OK) return rc;
     rc = pf.run(2, [&]() -> adc2_status {
-      k_light1<double2><<<(unsigned)(c * njg * cdiv(d.nv, LC)), 256, 0, st>>>(R, h->Vt, r0, c, d.nc, d.no, d.nv,
-                                                                                    h->Tp);
+      light1_launch(R, h->Vt, r0, c, d, h->Tp, st);
       ADC2_CHECK_LAUNCH();
       return ADC2_OK;
     });
@@ -1910,12 +1931,8 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
     adc2_handle h = rq[q].h;
     const Dims& d = h->d;
     const int rows = rq[q].m * d.nc;
-    const int njg = (d.no + LJG - 1) / LJG;
-    const unsigned g = (unsigned)(rows * njg * cdiv(d.nv, LC));
-    if (h->prec != ADC2_FP64)
-      k_light1<float2><<<g, 256, 0, st>>>((const float2*)h->Zb, h->Vt, 0, rows, d.nc, d.no, d.nv, h->Tp);
-    else
-      k_light1<double2><<<g, 256, 0, st>>>(h->Zb, h->Vt, 0, rows, d.nc, d.no, d.nv, h->Tp);
+    if (h->prec != ADC2_FP64) light1_launch((const float2*)h->Zb, h->Vt, 0, rows, d, h->Tp, st);
+    else light1_launch(h->Zb, h->Vt, 0, rows, d, h->Tp, st);
     ADC2_CHECK_LAUNCH();
   }
   if ((rc = mark(3)) != ADC2_OK) return rc;

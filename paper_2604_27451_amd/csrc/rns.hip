@@ -197,15 +197,30 @@ __global__ __launch_bounds__(256) void k_rns_norm_k(const RnsSrc src, int rows, 
   }
 }
 
-// e[row]: the largest e with ||row|| 2^e <= 2^RNS_G; rows past the end 0.
-__global__ void k_rns_expo(const double* __restrict__ part, int nsplit, int rows, int padded, int* __restrict__ e) {
-  const int row = blockIdx.x * blockDim.x + threadIdx.x;
-  if (row >= padded) return;
+// e[row]: the largest e with ||row|| 2^e <= 2^RNS_G; rows past the end 0.  A workgroup
+// owns 64 rows, its 16 waves share the slices of the norm (one thread a row read up to
+// 192 values in turn: 22 us).
+__global__ __launch_bounds__(1024) void k_rns_expo(const double* __restrict__ part, int nsplit, int rows, int padded,
+                                                   int* __restrict__ e) {
+  __shared__ double red[16][3][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int row = blockIdx.x * 64 + lane;
+  double s[3] = {0.0, 0.0, 0.0};
+  if (row < rows)
+#pragma unroll 4
+    for (int t = w; t < nsplit; t += 16)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) s[q] += part[((long)t * 3 + q) * rows + row];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) red[w][q][lane] = s[q];
+  __syncthreads();
+  if (w != 0 || row >= padded) return;
   int ex = 0;
   if (row < rows) {
-    double s[3] = {0.0, 0.0, 0.0};
-    for (int t = 0; t < nsplit; ++t)
-      for (int q = 0; q < 3; ++q) s[q] += part[((long)t * 3 + q) * rows + row];
+    const int nw = nsplit < 16 ? nsplit : 16;
+    for (int t = 1; t < nw; ++t)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) s[q] += red[t][q][lane];
     double l2;   // log2 of the norm
     if (s[0] >= 0x1p-900 && s[0] <= 0x1p1000) l2 = 0.5 * log2(s[0]);
     else if (s[0] > 1.0) l2 = 0.5 * log2(s[1]) + 540.0;   // above 2^500 (Inf where a row is not finite)
@@ -227,7 +242,10 @@ __global__ void k_rns_expo(const double* __restrict__ part, int nsplit, int rows
 // vector instructions (about 250 per entry) and its 32-byte writes per entry:
 // 0.29 ms for the 27 M entries of a 18000 x 1500 operand, 4 TB/s.  Operands
 // contiguous along k go through LDS, so that both their reads and the writes
-// are whole lines.
+// are whole lines: in two halves of 33 KB, so that four workgroups share a
+// compute unit (in one of 66 KB, two of them: 1.84 ms for 128 M entries against
+// 1.27 ms).  Grids too short for the chip are split over the moduli
+// (blockIdx.y), each part rounding the entries again.
 constexpr int RNS_MAGIC = 0x4B400000;   // 1.5 * 2^23 as a float: float(MAGIC + x) = 1.5 * 2^23 + x
 template <bool KLANE>
 __global__ __launch_bounds__(256) void k_rns_pack(const RnsSrc src, int rows, int K, const int* __restrict__ e, int nrt,
@@ -239,22 +257,31 @@ __global__ __launch_bounds__(256) void k_rns_pack(const RnsSrc src, int rows, in
   i4v d[16];   // re lo, re hi, im lo, im hi
   const bool ok = row < rows;
   if constexpr (KLANE) {
-    __shared__ double2 t[64][65];
+    __shared__ double2 t[32][65];
     const int k = kc * RNS_KC + lane;
     const double2* p = src.p + (k < K ? rns_k(src, k) : 0);
-#pragma unroll 4
+    double2 v[16];
+#pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int rr = rb * 64 + kg * 16 + r;
-      t[kg * 16 + r][lane] = (rr < rows && k < K) ? p[rns_row(src, rr)] : make_double2(0.0, 0.0);
+      v[r] = (rr < rows && k < K) ? p[rns_row(src, rr)] : make_double2(0.0, 0.0);
     }
-    __syncthreads();
+    // rows 16 g + r with r < 8, then those with r >= 8
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const double2 v = t[lane][kg * 16 + u];
-      d[u].x = __double2loint(v.x);
-      d[u].y = __double2hiint(v.x);
-      d[u].z = __double2loint(v.y);
-      d[u].w = __double2hiint(v.y);
+    for (int half = 0; half < 2; ++half) {
+      if (half) __syncthreads();
+#pragma unroll
+      for (int r = 0; r < 8; ++r) t[kg * 8 + r][lane] = v[half * 8 + r];
+      __syncthreads();
+      if (((lane >> 3) & 1) == half)
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+          const double2 x = t[(lane >> 4) * 8 + (lane & 7)][kg * 16 + u];
+          d[u].x = __double2loint(x.x);
+          d[u].y = __double2hiint(x.x);
+          d[u].z = __double2loint(x.y);
+          d[u].w = __double2hiint(x.y);
+        }
     }
   } else {
     const double2* p = src.p + rns_row(src, ok ? row : 0);
@@ -299,7 +326,8 @@ __global__ __launch_bounds__(256) void k_rns_pack(const RnsSrc src, int rows, in
   const float magic = 12582912.0f;
   int8_t* out = dst + ((long)(rb >> 1) * nkc + kc) * RNS_BLK + ((rb & 1) * 4 + (lane >> 4)) * 1024 + kg * 256 + (lane & 15) * 16;
   const long ps = (long)nrt * nkc * RNS_BLK;
-  for (int q = 0; q < RNS_NM; ++q) {
+  const int nq = RNS_NM / gridDim.y;
+  for (int q = blockIdx.y * nq; q < (int)(blockIdx.y + 1) * nq; ++q) {
     const RnsSplit c = RNS_C.split[q];
     i4v o0, o1;
 #pragma unroll
@@ -342,11 +370,13 @@ adc2_status rns_pack(const RnsSrc& src, int rows, int K, int8_t* buf, int* ebuf,
   else k_rns_norm<<<dim3((unsigned)nrow, (unsigned)ns), 256, 0, st>>>(src, rows, K, nbuf);
   ADC2_CHECK_LAUNCH();
   const int padded = out->nrt * RNS_RT;
-  k_rns_expo<<<rcdiv(padded, 256), 256, 0, st>>>(nbuf, ns, rows, padded, ebuf);
+  k_rns_expo<<<rcdiv(padded, 64), 1024, 0, st>>>(nbuf, ns, rows, padded, ebuf);
   ADC2_CHECK_LAUNCH();
-  const unsigned nblk = (unsigned)((long)2 * out->nrt * out->nkc);
-  if (klane) k_rns_pack<true><<<nblk, 256, 0, st>>>(src, rows, K, ebuf, out->nrt, out->nkc, buf);
-  else k_rns_pack<false><<<nblk, 256, 0, st>>>(src, rows, K, ebuf, out->nrt, out->nkc, buf);
+  const long nblk = (long)2 * out->nrt * out->nkc;
+  // a block alone on its compute unit takes 15 us for the 16 moduli, 7 us for 4 of them
+  const dim3 grid((unsigned)nblk, nblk <= 256 ? 4 : (nblk <= 512 ? 2 : 1));
+  if (klane) k_rns_pack<true><<<grid, 256, 0, st>>>(src, rows, K, ebuf, out->nrt, out->nkc, buf);
+  else k_rns_pack<false><<<grid, 256, 0, st>>>(src, rows, K, ebuf, out->nrt, out->nkc, buf);
   ADC2_CHECK_LAUNCH();
   return ADC2_OK;
 }

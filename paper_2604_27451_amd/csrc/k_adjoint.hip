@@ -267,34 +267,64 @@ struct EpAdd {  // C[i*ld + j] += alpha v
   }
 };
 
-// T[I][j][K][a] = sum_{k,b} conj(R~_{kIj}[a][b]) r1[k][K][b],  batch b = I*no + j
-// with R~_{kIj}[a][b] = Rt[(j*nv + b)*ld + (k*nc + I)*nv + a]
-struct SrcRtc {  // (kk = (k, b), i = a)
-  static constexpr int MAP = KMAJOR;
-  const double2* Rt;
-  long ld;
-  int nc, nv, no;
-  __device__ double2 get(int kk, int i, int bt) const {
-    const int k = kk / nv, bv = kk - k * nv;
-    const int I = bt / no, j = bt - I * no;
-    return cconj(Rt[((long)j * nv + bv) * ld + ((long)k * nc + I) * nv + i]);
+// T[I][j][K][a] = sum_{k,b} conj(R~_{kIj}[a][b]) r1[k][K][b],  batch I*no + j,
+// with R~_{kIj}[a][b] = Rt[(j*nv + b)*ld + (k*nc + I)*nv + a].
+// As products of matrix instructions its nc columns fill a tenth of a tile (1.36 ms at
+// nc=6 no=35 nv=250, six vectors): instead one workgroup per batch and 64 values
+// of a, a lane holding the sums of eight K, coefficients from LDS; each wave takes 16 of the
+// 64 staged b.  Bound by the one read of Rt (0.63 GB: 0.32 ms).
+constexpr int TCB = 64;
+__global__ __launch_bounds__(256) void k_tcoup(const double2* __restrict__ Rt, long ld, const double2* __restrict__ x,
+                                                long dim, int m, int nc, int no, int nv, double2* __restrict__ T) {
+  __shared__ double2 sh[3 * 8 * 64];
+  double2(*cf)[8] = (double2(*)[8])sh;   // cf[b][K]
+  const int ncb = cdv(nv, 64), cb = blockIdx.x % ncb, bt = blockIdx.x / ncb;
+  const int I = bt / no, j = bt - I * no;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int a = cb * 64 + lane, as = a < nv ? a : 0;   // a lane past the end reads column 0, its sums are not stored
+  for (int K0 = 0; K0 < nc; K0 += 8) {
+    double2 acc[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) acc[q] = czero();
+    for (int k = 0; k < m; ++k) {
+      const double2* R = Rt + (long)j * nv * ld + ((long)k * nc + I) * nv + as;
+      for (int b0 = 0; b0 < nv; b0 += TCB) {
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int q = 2 * w + u, K = K0 + q, b = b0 + lane;
+          cf[lane][q] = (K < nc && b < nv) ? x[(long)k * dim + (long)K * nv + b] : czero();
+        }
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int bb = w * 16 + h * 8;
+          if (b0 + bb >= nv) break;
+          double2 r[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) r[u] = R[(long)min(b0 + bb + u, nv - 1) * ld];   // zero coefficients past the end
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) acc[q] = cadd(acc[q], cmul(cconj(r[u]), cf[bb + u][q]));
+        }
+      }
+    }
+    __syncthreads();
+    if (w > 0)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) sh[((w - 1) * 8 + q) * 64 + lane] = acc[q];
+    __syncthreads();
+    if (w == 0 && a < nv)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        if (K0 + q >= nc) break;
+        double2 t = acc[q];
+        for (int v = 0; v < 3; ++v) t = cadd(t, sh[(v * 8 + q) * 64 + lane]);
+        T[((long)bt * nc + K0 + q) * nv + a] = t;
+      }
   }
-};
-struct SrcR1kb {  // (kk = (k, b), j = K) = r1[k][K][b]
-  static constexpr int MAP = RMAJOR;
-  const double2* x;
-  long dim;
-  int nv;
-  __device__ double2 get(int kk, int K, int) const {
-    const int k = kk / nv, bv = kk - k * nv;
-    return x[(long)k * dim + (long)K * nv + bv];
-  }
-};
-struct EpT {
-  double2* T;
-  int nc, nv;
-  __device__ void operator()(int a, int K, int bt, double2 v) const { T[((long)bt * nc + K) * nv + a] = v; }
-};
+}
 
 // Light coupling terms <Ka||Ij> = (KI|aj) - (Kj|aI) against T.
 // (9a) hvo[nc+j][P][a] += 2 sum_{K,I} conj(T[I][j][K][a]) conj(Loo[P][K][I])      batch j
@@ -641,27 +671,19 @@ __global__ void k_tau(double2* __restrict__ WT, long npairs, const double* __res
 // Antisymmetrised E for every occupied pair p = (k<l), written in both
 // orders as Ef[k][l][c][a] = E^A_{ac,kl} = -Ef[l][k][c][a], and the per-pair
 // denominator-derivative row sums hr[p][a] = sum_{c != a} (h(a,c) + h(c,a)).
-// One workgroup per (p, 16-row block of a); 16x16 tiles through LDS so that
-// both the (a,c) and the (c,a) reads are coalesced.
+// One workgroup per (p, 16-row block of a).  A thread's a runs along the lanes, so (c,a)
+// entries are read where they are used and only the (a,c) ones go through LDS, in 28 KB for
+// five workgroups a compute unit (both through LDS: two, 2.1 ms at nc=6 no=35 nv=250; now 1.3 ms).
 constexpr int ET = 16;
-struct TilePair {
-  double2 ac[ET][ET + 1];
-  double2 ca[ET][ET + 1];
-};
-__device__ __forceinline__ void load_pair(TilePair& t, const double2* base, long rs, int a0, int c0, int nv,
-                                          int tid) {
-  const int r = tid / ET, q = tid % ET;
-  const int a = a0 + r, c = c0 + q;
-  t.ac[r][q] = (a < nv && c < nv) ? base[(long)a * rs + c] : czero();
-  const int c2 = c0 + r, a2 = a0 + q;
-  t.ca[r][q] = (a2 < nv && c2 < nv) ? base[(long)c2 * rs + a2] : czero();
+__device__ __forceinline__ double2 tile_get(const double2* base, long rs, int r, int c, int nv) {
+  return r < nv && c < nv ? base[(long)r * rs + c] : czero();
 }
 
 __global__ __launch_bounds__(256) void k_efill(const double2* __restrict__ W, const double2* __restrict__ PQ,
                                                 const double2* __restrict__ PQG, const double* __restrict__ eps,
                                                 int nc, int o, int nv, long npairs, double2* __restrict__ Ef,
                                                 double* __restrict__ hr) {
-  __shared__ TilePair tw, tpi, tqi, tpk, tqk, tpl, tql;
+  __shared__ double2 t[6][ET][ET + 1];   // [a - a0][c - c0] of the six products
   __shared__ double hs[ET][ET + 1];
   const int nab = (nv + ET - 1) / ET;
   const long p = blockIdx.x / nab;
@@ -686,16 +708,18 @@ __global__ __launch_bounds__(256) void k_efill(const double2* __restrict__ W, co
   double2* Eflk = Ef + ((long)l * o + k) * nv2;
   for (int c0 = 0; c0 < nv; c0 += ET) {
     __syncthreads();
-    load_pair(tw, W + p * nv2, nv, a0, c0, nv, tid);
-    load_pair(tpi, PQ + p * nv2, nv, a0, c0, nv, tid);
-    load_pair(tqi, PQ + (npairs + p) * nv2, nv, a0, c0, nv, tid);
-    if (kc) {
-      load_pair(tpk, PQG + ((long)k * nv) * ldo + (long)l * nv, ldo, a0, c0, nv, tid);
-      load_pair(tqk, PQG + (ns + (long)k * nv) * ldo + (long)l * nv, ldo, a0, c0, nv, tid);
-    }
-    if (lc) {
-      load_pair(tpl, PQG + ((long)l * nv) * ldo + (long)k * nv, ldo, a0, c0, nv, tid);
-      load_pair(tql, PQG + (ns + (long)l * nv) * ldo + (long)k * nv, ldo, a0, c0, nv, tid);
+    // (row c, column a) is read where it is used, (row a, column c) goes through LDS
+    const double2* b[6] = {PQ + p * nv2, PQ + (npairs + p) * nv2,
+                           PQG + ((long)k * nv) * ldo + (long)l * nv, PQG + (ns + (long)k * nv) * ldo + (long)l * nv,
+                           PQG + ((long)l * nv) * ldo + (long)k * nv, PQG + (ns + (long)l * nv) * ldo + (long)k * nv};
+    double2 ca[6];
+    const double2 wca = tile_get(W + p * nv2, nv, c0 + ty, a, nv);
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+      if ((q >= 2 && !kc) || (q >= 4 && !lc)) continue;
+      const long rs = q < 2 ? nv : ldo;
+      t[q][ty][tx] = tile_get(b[q], rs, a0 + ty, c0 + tx, nv);
+      ca[q] = tile_get(b[q], rs, c0 + ty, a, nv);
     }
     __syncthreads();
     const int c = c0 + ty;
@@ -704,25 +728,25 @@ __global__ __launch_bounds__(256) void k_efill(const double2* __restrict__ W, co
       if (a != c) {
         const double D = ea + eps[o + c] - ekl;
         const double iD = 1.0 / D, iD2 = iD * iD;
-        const double2 w = tw.ac[tx][ty];
+        const double2 w = cneg(wca);   // W_ac
         // (i): A_ac[Q + P/D]
-        const double2 pac = tpi.ac[tx][ty], pca = tpi.ca[ty][tx];
-        const double2 Eac = cadd(tqi.ac[tx][ty], cscale(pac, iD));
-        const double2 Eca = cadd(tqi.ca[ty][tx], cscale(pca, iD));
+        const double2 pac = t[0][tx][ty], pca = ca[0];
+        const double2 Eac = cadd(t[1][tx][ty], cscale(pac, iD));
+        const double2 Eca = cadd(ca[1], cscale(pca, iD));
         v = cscale(csub(Eac, Eca), 0.5);
         // h(a,c) + h(c,a) with W_ca = -W_ac
         double hh = -4.0 * (w.x * pac.x + w.y * pac.y) + 4.0 * (w.x * pca.x + w.y * pca.y);
         if (kc) {
-          const double2 gac = tpk.ac[tx][ty], gca = tpk.ca[ty][tx];
-          const double2 Fac = cadd(tqk.ac[tx][ty], cscale(gac, iD));
-          const double2 Fca = cadd(tqk.ca[ty][tx], cscale(gca, iD));
+          const double2 gac = t[2][tx][ty], gca = ca[2];
+          const double2 Fac = cadd(t[3][tx][ty], cscale(gac, iD));
+          const double2 Fca = cadd(ca[3], cscale(gca, iD));
           v = cadd(v, cscale(csub(Fac, Fca), 0.25));
           hh += -2.0 * (w.x * gac.x + w.y * gac.y) + 2.0 * (w.x * gca.x + w.y * gca.y);
         }
         if (lc) {
-          const double2 gac = tpl.ac[tx][ty], gca = tpl.ca[ty][tx];
-          const double2 Fac = cadd(tql.ac[tx][ty], cscale(gac, iD));
-          const double2 Fca = cadd(tql.ca[ty][tx], cscale(gca, iD));
+          const double2 gac = t[4][tx][ty], gca = ca[4];
+          const double2 Fac = cadd(t[5][tx][ty], cscale(gac, iD));
+          const double2 Fca = cadd(ca[5], cscale(gca, iD));
           v = csub(v, cscale(csub(Fac, Fca), 0.25));
           hh += 2.0 * (w.x * gac.x + w.y * gac.y) - 2.0 * (w.x * gca.x + w.y * gca.y);
         }
@@ -741,6 +765,16 @@ __global__ __launch_bounds__(256) void k_efill(const double2* __restrict__ W, co
   }
 }
 
+// X[I][k][a][c] = X_{ac,Ik}, I core (blockIdx.y = (I, k)), from the pair store with the sign of (I, k)
+__global__ void k_xcore(const double2* __restrict__ W, int o, int nv, double2* __restrict__ X) {
+  const int I = blockIdx.y / o, k = blockIdx.y - I * o;
+  const long nv2 = (long)nv * nv;
+  const double2* w = W + (I == k ? 0 : I < k ? pair_id(I, k, o) : pair_id(k, I, o)) * nv2;
+  double2* x = X + blockIdx.y * nv2;
+  for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < nv2; e += (long)gridDim.x * blockDim.x)
+    x[e] = I == k ? czero() : (I < k ? w[e] : cneg(w[e]));
+}
+
 // Ef[k][k] = 0
 __global__ void k_zero_diag_blocks(double2* __restrict__ Ef, int o, int nv) {
   const long nv2 = (long)nv * nv;
@@ -750,10 +784,11 @@ __global__ void k_zero_diag_blocks(double2* __restrict__ Ef, int o, int nv) {
   }
 }
 
-// Doubles diagonal: rho_{Ijab} = sum_k w_k |r2_{k,Ijab}|^2 (a<b).  One
-// workgroup per (I, j): Sv[(I,j)][a] = sum_b rho over pairs containing a,
-// Sv[(I,j)][nv] = sum of rho over the block.
-__global__ __launch_bounds__(256) void k_rho(const double2* __restrict__ xin, long dim, int m, int nc, int no,
+// Doubles diagonal: rho_{Ijab} = w_k |r2_{k,Ijab}|^2 (a<b).  One workgroup
+// per (I, j) and vector k: Sv[k][(I,j)][a] = sum_b rho over pairs containing
+// a, Sv[k][(I,j)][nv] = sum of rho over the block (a workgroup that walked all
+// vectors left 210 of them for the chip: 1.28 ms at nc=6 no=35 nv=250, six vectors; now 0.30 ms).
+__global__ __launch_bounds__(256) void k_rho(const double2* __restrict__ xin, long dim, int nc, int no,
                                               int nv, const double* __restrict__ wts, double* __restrict__ Sv) {
   extern __shared__ double sm[];
   __shared__ double red4[4];
@@ -767,22 +802,23 @@ __global__ __launch_bounds__(256) void k_rho(const double2* __restrict__ xin, lo
   for (int b = tid; b < nv; b += 256) col[b] = 0.0;
   for (int e = tid; e < 4 * nv; e += 256) row[e] = 0.0;
   __syncthreads();
-  for (int mv = 0; mv < m; ++mv) {
-    const double2* r2 = xin + (long)mv * dim + ns + ((long)I * no + j) * npair;
-    const double w = wts[mv];
-    for (int a = 0; a < nv - 1; ++a) {
-      double rs = 0.0;
-      for (int b = tid; b < nv; b += 256) {
-        if (b > a) {
-          const double2 v = r2[pair_off(a, b, nv)];
-          const double q = w * (v.x * v.x + v.y * v.y);
-          col[b] += q;   // b is owned by this thread
-          rs += q;
-        }
+  const int mv = blockIdx.y;
+  const double2* r2 = xin + (long)mv * dim + ns + ((long)I * no + j) * npair;
+  const double w = wts[mv];
+  Sv += (long)mv * nc * no * (nv + 1);
+#pragma unroll 4
+  for (int a = 0; a < nv - 1; ++a) {
+    double rs = 0.0;
+    for (int b = tid; b < nv; b += 256) {
+      if (b > a) {
+        const double2 v = r2[pair_off(a, b, nv)];
+        const double q = w * (v.x * v.x + v.y * v.y);
+        col[b] += q;   // b is owned by this thread
+        rs += q;
       }
-      for (int off = 32; off > 0; off >>= 1) rs += __shfl_xor(rs, off);
-      if (lane == 0) row[a * 4 + wv] += rs;
     }
+    for (int off = 32; off > 0; off >>= 1) rs += __shfl_xor(rs, off);
+    if (lane == 0) row[a * 4 + wv] = rs;
   }
   __syncthreads();
   double tot = 0.0;
@@ -802,7 +838,7 @@ __global__ __launch_bounds__(256) void k_rho(const double2* __restrict__ xin, lo
 // d eps, one workgroup per spinor (one thread each read 0.8 MB serially: 1.7 ms
 // at nc=6 no=35 nv=250).
 __global__ __launch_bounds__(256) void k_eps_final(const double2* __restrict__ gam, const double* __restrict__ Sv,
-                                                    const double* __restrict__ hr, int nc, int no, int nv,
+                                                    const double* __restrict__ hr, int m, int nc, int no, int nv,
                                                     double* __restrict__ deps) {
   __shared__ double red[256];
   const int o = nc + no;
@@ -812,16 +848,16 @@ __global__ __launch_bounds__(256) void k_eps_final(const double2* __restrict__ g
   if (q >= o) {
     const int a = q - o;
     for (int I = tid; I < nc; I += 256) v += gam[((long)I * nv + a) * ns + (long)I * nv + a].x;
-    for (int g = tid; g < nc * no; g += 256) v += Sv[(long)g * (nv + 1) + a];
+    for (int g = tid; g < m * nc * no; g += 256) v += Sv[(long)g * (nv + 1) + a];
     const long npairs = (long)o * (o - 1) / 2;
     for (long p = tid; p < npairs; p += 256) v += hr[p * nv + a];
   } else {
     if (q < nc) {
       for (int a = tid; a < nv; a += 256) v -= gam[((long)q * nv + a) * ns + (long)q * nv + a].x;
-      for (int j = tid; j < no; j += 256) v -= Sv[((long)q * no + j) * (nv + 1) + nv];
+      for (int e = tid; e < m * no; e += 256) v -= Sv[((long)(e / no * nc + q) * no + e % no) * (nv + 1) + nv];
     } else {
       const int j = q - nc;
-      for (int I = tid; I < nc; I += 256) v -= Sv[((long)I * no + j) * (nv + 1) + nv];
+      for (int e = tid; e < m * nc; e += 256) v -= Sv[((long)e * no + j) * (nv + 1) + nv];   // e = (vector, I)
     }
     double hp = 0.0;
     for (int l = 0; l < o; ++l) {
@@ -1011,8 +1047,8 @@ adc2_status omega_backward(adc2_handle h, int m, const double2* X, const double*
   if (!done) BW_TRY(ybuild_fp64(h, m, st));
   const long ldrt = (long)m * nc * nv;
   // T[I][j][K][a]
-  BW_TRY(fgemm(nv, nc, m * nv, nc * no, SrcRtc{h->Zb, ldrt, nc, nv, no}, SrcR1kb{X, dim, nv}, EpT{T, nc, nv}, S,
-               st));
+  k_tcoup<<<(unsigned)(nc * no * cdv(nv, 64)), 256, 0, st>>>(h->Zb, ldrt, X, dim, m, nc, no, nv, T);
+  BW_HIP(hipGetLastError());
   // gvv += 2 Y conj(r1)
   BW_TRY(fgemm((int)((long)naux * nv), nv, m * nc, 1, SrcYk{h->Y, (long)naux * nv}, SrcR1cK{X, dim, nc, nv},
                EpAdd{gvv, nv, 2.0}, S, st));
@@ -1067,14 +1103,26 @@ adc2_status omega_backward(adc2_handle h, int m, const double2* X, const double*
     BW_TRY(alloc((void**)&PQ, sizeof(double2) * 2 * npairs * nv2));
     BW_TRY(alloc((void**)&PQG, sizeof(double2) * 2 * ns * o * nv));
     BW_TRY(alloc((void**)&hr, sizeof(double) * npairs * nv));
-    BW_TRY(alloc((void**)&Sv, sizeof(double) * nc * no * (nv + 1)));
+    BW_TRY(alloc((void**)&Sv, sizeof(double) * m * nc * no * (nv + 1)));
     BW_TRY(wbuild(h, WT, st));
     k_tau<<<dim3(grid1(nv2, 256, 64), (unsigned)npairs), 256, 0, st>>>(WT, npairs, h->eps, o, nv);
     BW_HIP(hipGetLastError());
     BW_TRY(fgemm(nv, (int)(2 * npairs * nv), nv, 1, SrcGam4{Gam, nv}, SrcWT{WT, nv}, EpPQ{PQ, nv}, S, st));
-    BW_TRY(fgemm((int)ns, o * nv, (int)ns, 2, SrcMatK{Gc, ns}, SrcWcore{WT, npairs, nv, o},
-                 EpPQG{PQG, ns, (long)o * nv}, S, st));
     BW_TRY(alloc((void**)&Ef, sizeof(double2) * (long)o * o * nv2));
+    // (13) on the residue engine with the rows of X^h laid out in Ef, which is filled only after
+    // (50 TFLOP/s of the general product, 7.6 ms at nc=6 no=35 nv=250; 2.0 ms here)
+    done = false;
+    for (int hh = 0; hh < 2; ++hh) {
+      if (hh == 0 && ((long)nc * o > 65535 || !rns_pays(h, ns, (long)o * nv, ns, 50e12))) break;
+      k_xcore<<<dim3(grid1(nv2, 256, 64), (unsigned)(nc * o)), 256, 0, st>>>(WT + hh * npairs * nv2, o, nv, Ef);
+      BW_HIP(hipGetLastError());
+      BW_TRY(rns_product(h, rns_kmajor(Gc, ns, (int)ns), (int)ns, RnsSrc{Ef, nv, nv2, 1, nv, (long)o * nv2, nv, false},
+                         o * nv, (int)ns, rns_rows(PQG + (long)hh * ns * o * nv, (long)o * nv), 0.0, &done, st));
+      if (!done) break;
+    }
+    if (!done)
+      BW_TRY(fgemm((int)ns, o * nv, (int)ns, 2, SrcMatK{Gc, ns}, SrcWcore{WT, npairs, nv, o},
+                   EpPQG{PQG, ns, (long)o * nv}, S, st));
     k_zero_diag_blocks<<<grid1((long)o * nv2), 256, 0, st>>>(Ef, o, nv);
     BW_HIP(hipGetLastError());
     k_efill<<<(unsigned)(npairs * cdv(nv, ET)), 256, 0, st>>>(WT, PQ, PQG, h->eps, nc, o, nv, npairs, Ef, hr);
@@ -1100,9 +1148,9 @@ adc2_status omega_backward(adc2_handle h, int m, const double2* X, const double*
       BW_HIP(hipGetLastError());
     }
     // eps
-    k_rho<<<nc * no, 256, sizeof(double) * 5 * nv, st>>>(X, dim, m, nc, no, nv, wts, Sv);
+    k_rho<<<dim3(nc * no, m), 256, sizeof(double) * 5 * nv, st>>>(X, dim, nc, no, nv, wts, Sv);
     BW_HIP(hipGetLastError());
-    k_eps_final<<<d.n, 256, 0, st>>>(gam, Sv, hr, nc, no, nv, deps);
+    k_eps_final<<<d.n, 256, 0, st>>>(gam, Sv, hr, m, nc, no, nv, deps);
     BW_HIP(hipGetLastError());
   }
 

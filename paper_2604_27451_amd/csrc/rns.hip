@@ -619,16 +619,16 @@ adc2_status rns_join(const RnsMat& A, const RnsMat& B, int col0, int ncols, int 
 // general products
 // ---------------------------------------------------------------------------
 // Where the conversions pay: per term of the product 8 / 225e12 s against 8 / rate
-// on the FP64 MFMA kernel, per operand entry about 1.6e-11 s (norm, residues and
-// their reads in the product), per output entry 1.8e-11 s; about 60 us of
+// on the FP64 MFMA kernel, per operand entry 1.25e-11 s (norm and residues), per
+// output entry 1e-11 s; about 60 us of
 // launches and part-filled rounds.
 bool rns_pays(adc2_handle h, long M, long N, long K, double rate) {
   if (h->rns_mode == RNS_ALWAYS) return K <= RNS_KMAX * RNS_SPLITS;
   if (h->rns_off || h->rns_mode == RNS_NEVER || K > RNS_KMAX * RNS_SPLITS) return false;
   const double terms = (double)M * N * K;
   const double padded = 256.0 * rcdiv(M, 256) * 128.0 * rcdiv(N, 128) * K;
-  const double rns = 6e-5 + padded * 8 / 225e12 + 1.6e-11 * ((double)M * K + (double)N * K) + 1.8e-11 * (double)M * N;
-  return rns < 0.8 * terms * 8 / rate;
+  const double rns = 6e-5 + padded * 8 / 225e12 + 1.25e-11 * ((double)M * K + (double)N * K) + 1e-11 * (double)M * N;
+  return rns < 0.85 * terms * 8 / rate;
 }
 
 static bool rns_grow(adc2_handle h, char** buf, size_t* have, size_t bytes, bool last) {

@@ -101,20 +101,20 @@ struct SrcR1Rows {   // element (k=c, i=mI) = r1 of vector m, core I
   }
 };
 
-template <class TO>
+template <class TO, int MR>
 __global__ __launch_bounds__(256) void k_xbuild(const double2* __restrict__ x, long dim, int nc, int nv, int naux,
                                                  int nrows, const double2* __restrict__ Lvv,
                                                  TO* __restrict__ X) {
   __shared__ TileSmem s;
   const long ncol = (long)naux * nv;
   const int nbj = cdiv(ncol, TN);
-  const long nblocks = (long)cdiv(nrows, TM) * nbj;
+  const long nblocks = (long)cdiv(nrows, MR) * nbj;
   const long lid = xcd_remap(blockIdx.x, nblocks);
-  const int i0 = (int)(lid / nbj) * TM;
+  const int i0 = (int)(lid / nbj) * MR;
   const long j0 = (lid % nbj) * TN;
   SrcR1Rows sa{x, dim, nc, nv, nrows, i0};
   SrcR<false> sb{Lvv + j0 * nv, nv, nv, (int)min((long)TN, ncol - j0), 1.0};
-  Acc acc;
+  AccT<MR> acc;
   acc.zero();
   mainloop(s, sa, sb, 0, cdiv(nv, TK), acc);
   for_each_acc(acc, [&](int r, int c, double2 v) {
@@ -125,95 +125,90 @@ __global__ __launch_bounds__(256) void k_xbuild(const double2* __restrict__ x, l
 }
 
 // ---------------------------------------------------------------------------
-// X-build and back-contraction of at most 32 rows (mI)
+// X-build and back-contraction of at most 16 rows (mI)
 // ---------------------------------------------------------------------------
-// Both read Lvv once and are bound by that where rows are few; 64-row tiles do
-// the matrix work of 64 rows whatever their number (nc=6 no=120 nv=600
-// naux=3000, two vectors: 8.9 and 9.0 ms).  Here a wave multiplies RT tiles of 16
-// rows with 64 columns of Lvv on the 16x16x4 FP64 MFMA, operands straight from
-// global memory: a lane's element of a column tile is Lvv[column][k] with four
-// k of a column in one 64-byte piece and four steps of k unrolled, so whole lines are
-// used; the row operand stays in cache.
+// Both read Lvv once and are bound by that where rows are few; tiles of 64
+// rows do the matrix work of 64 rows whatever their number (nc=6 no=120 nv=600
+// naux=3000, two vectors: 8.9 and 9.0 ms; of 32 rows 5.0 and 5.6).  Here a wave
+// multiplies 16 rows with 64 columns of Lvv on the 16x16x4 FP64 MFMA (4.0 ms
+// each), operands straight from global memory: a lane's element of a column tile
+// is Lvv[column][k] with four k of a column in one 64-byte piece and four steps
+// of k unrolled, so whole lines are used; the row operand stays in cache.
 //
-// acc[t][c] += A(rows 16 t + .., k) B(k, columns 16 c + ..) over k < K; a(t, k) and
-// b(c, k) give this lane's elements, zero past the ends.
-template <int RT, class FA, class FB>
-__device__ __forceinline__ void thin_mma(int K, d4 (&re)[RT][4], d4 (&im)[RT][4], FA&& fa, FB&& fb) {
+// acc[c] += A(rows, k) B(k, columns 16 c + ..) over k < K; a(k) and b(c, k) give
+// this lane's elements, zero past the ends.
+template <class FA, class FB>
+__device__ __forceinline__ void thin_mma(int K, d4 (&re)[4], d4 (&im)[4], FA&& fa, FB&& fb) {
   const int lk = (threadIdx.x & 63) >> 4;
   for (int k0 = 0; k0 < K; k0 += 16) {
-    double2 a[4][RT], b[4][4];
+    double2 a[4], b[4][4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-#pragma unroll
-      for (int t = 0; t < RT; ++t) a[u][t] = fa(t, k0 + 4 * u + lk);
+      a[u] = fa(k0 + 4 * u + lk);
 #pragma unroll
       for (int c = 0; c < 4; ++c) b[u][c] = fb(c, k0 + 4 * u + lk);
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u)
 #pragma unroll
-      for (int t = 0; t < RT; ++t)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          re[t][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][t].x, b[u][c].x, re[t][c], 0, 0, 0);
-          re[t][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[u][t].y, b[u][c].y, re[t][c], 0, 0, 0);
-          im[t][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][t].x, b[u][c].y, im[t][c], 0, 0, 0);
-          im[t][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][t].y, b[u][c].x, im[t][c], 0, 0, 0);
-        }
+      for (int c = 0; c < 4; ++c) {
+        re[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].x, b[u][c].x, re[c], 0, 0, 0);
+        re[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[u].y, b[u][c].y, re[c], 0, 0, 0);
+        im[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].x, b[u][c].y, im[c], 0, 0, 0);
+        im[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].y, b[u][c].x, im[c], 0, 0, 0);
+      }
   }
 }
 
-// Where the thin kernels are the faster ones: Lvv of at least 2^23 entries (few
-// workgroups below: nc=6 no=10 nv=40 naux=150, one vector, 14 and 16 us against 13
-// and 13 on 64-row tiles) for up to 16 rows, 2^25 for up to 32 (nc=6 no=12 nv=100
-// naux=300, four vectors: back-contraction 78 us against 45).
+// Where the thin kernels are the faster ones: up to 16 rows of an Lvv of at least 2^23
+// entries (few workgroups below: nc=6 no=10 nv=40 naux=150, one vector, 14 and 16 us
+// against 7 and 8 on 32-row tiles).
 static bool thin_rows(const Dims& d, int rows) {
-  const double lvv = (double)d.naux * d.nv * d.nv;
-  return rows <= 16 ? lvv >= 8388608.0 : rows <= 32 && lvv >= 33554432.0;
+  return rows <= 16 && (double)d.naux * d.nv * d.nv >= 8388608.0;
 }
 
-template <class TO, int RT>
+// Rows of the LDS tiles, 32, 48 or 64: those that pad the rows least, the larger on a
+// tie (no=12 nv=100, 24 rows: 24 and 30 us on 32-row tiles, 37 and 46 on 64-row ones;
+// no=25 nv=380, 30 rows: 1.00 and 1.04 ms, two thin tiles of 16 rows 1.22 and 1.46;
+// no=45 nv=310, 42 rows: 1.09 and 0.97 ms on 48-row tiles, 1.23 and 1.12 on 64).
+static int row_tile(int rows) {
+  int best = 64;
+  for (int t : {48, 32})
+    if (cdiv(rows, t) * t < cdiv(rows, best) * best) best = t;
+  return best;
+}
+
+template <class TO>
 __global__ __launch_bounds__(256) void k_xbuild_thin(const double2* __restrict__ x, long dim, int nc, int nv, int naux,
                                                      int nrows, const double2* __restrict__ Lvv, TO* __restrict__ X) {
   const int lane = threadIdx.x & 63, li = lane & 15;
   const long ncol = (long)naux * nv;
   const long j0 = (xcd_remap(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6)) * 64;
   if (j0 >= ncol) return;
-  const double2* pa[RT];
-  bool oka[RT];
-#pragma unroll
-  for (int t = 0; t < RT; ++t) {
-    const int mi = 16 * t + li;
-    oka[t] = mi < nrows;
-    const int mm = oka[t] ? mi : 0, m = mm / nc;
-    pa[t] = x + (long)m * dim + (long)(mm - m * nc) * nv;
-  }
+  const bool oka = li < nrows;
+  const int mm = oka ? li : 0, m = mm / nc;
+  const double2* pa = x + (long)m * dim + (long)(mm - m * nc) * nv;
   const double2* pb[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) pb[c] = Lvv + min(j0 + 16 * c + li, ncol - 1) * nv;   // past the end: never stored
-  d4 re[RT][4], im[RT][4];
+  d4 re[4], im[4];
 #pragma unroll
-  for (int t = 0; t < RT; ++t)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) re[t][c] = im[t][c] = d4{0.0, 0.0, 0.0, 0.0};
-  thin_mma<RT>(
-      nv, re, im, [&](int t, int k) { return oka[t] && k < nv ? pa[t][k] : czero(); },
+  for (int c = 0; c < 4; ++c) re[c] = im[c] = d4{0.0, 0.0, 0.0, 0.0};
+  thin_mma(
+      nv, re, im, [&](int k) { return oka && k < nv ? pa[k] : czero(); },
       [&](int c, int k) { return k < nv ? pb[c][k] : czero(); });
 #pragma unroll
-  for (int t = 0; t < RT; ++t)
+  for (int c = 0; c < 4; ++c)
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int mi = 16 * t + (lane >> 4) + 4 * r;
-        const long j = j0 + 16 * c + li;
-        if (mi < nrows && j < ncol) X[(long)mi * ncol + j] = from_d2<TO>(make_double2(re[t][c][r], im[t][c][r]));
-      }
+    for (int r = 0; r < 4; ++r) {
+      const int mi = (lane >> 4) + 4 * r;
+      const long j = j0 + 16 * c + li;
+      if (mi < nrows && j < ncol) X[(long)mi * ncol + j] = from_d2<TO>(make_double2(re[c][r], im[c][r]));
+    }
 }
 
 // part[split][mI][a] = sum_{P in split} sum_c Y[mI][P][c] Lvv[P][a][c]: a workgroup
 // owns a split and 64 values of a, its waves share the split's P.
-template <int RT>
 __global__ __launch_bounds__(256) void k_backc_thin(const double2* __restrict__ Y, const double2* __restrict__ Lvv,
                                                     int nrows, int nv, int naux, int nsplit, double2* __restrict__ part) {
   __shared__ double2 red[3][64][17];
@@ -222,64 +217,50 @@ __global__ __launch_bounds__(256) void k_backc_thin(const double2* __restrict__ 
   const int split = blockIdx.x / nba, a0 = (blockIdx.x % nba) * 64;
   const int per = (naux + nsplit - 1) / nsplit;
   const int P0 = split * per, P1 = min(naux, P0 + per);
-  d4 re[RT][4], im[RT][4];
+  const bool oka = li < nrows;
+  d4 re[4], im[4];
 #pragma unroll
-  for (int t = 0; t < RT; ++t)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) re[t][c] = im[t][c] = d4{0.0, 0.0, 0.0, 0.0};
+  for (int c = 0; c < 4; ++c) re[c] = im[c] = d4{0.0, 0.0, 0.0, 0.0};
   for (int P = P0 + w; P < P1; P += 4) {
     const double2* pb[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) pb[c] = Lvv + ((long)P * nv + min(a0 + 16 * c + li, nv - 1)) * nv;
-    const double2* pa[RT];
-    bool oka[RT];
-#pragma unroll
-    for (int t = 0; t < RT; ++t) {
-      oka[t] = 16 * t + li < nrows;
-      pa[t] = Y + ((long)(oka[t] ? 16 * t + li : 0) * naux + P) * nv;
-    }
-    thin_mma<RT>(
-        nv, re, im, [&](int t, int k) { return oka[t] && k < nv ? pa[t][k] : czero(); },
+    const double2* pa = Y + ((long)(oka ? li : 0) * naux + P) * nv;
+    thin_mma(
+        nv, re, im, [&](int k) { return oka && k < nv ? pa[k] : czero(); },
         [&](int c, int k) { return k < nv ? pb[c][k] : czero(); });
   }
   double2* out = part + (long)split * nrows * nv;
-  for (int t = 0; t < RT; ++t) {   // the four waves' sums, in order, one row tile at a time
-    __syncthreads();
-    if (w > 0)
+  if (w > 0)   // the four waves' sums, in order
 #pragma unroll
-      for (int tt = 0; tt < RT; ++tt)
-        if (tt == t)
+    for (int c = 0; c < 4; ++c)
 #pragma unroll
-          for (int c = 0; c < 4; ++c)
+      for (int r = 0; r < 4; ++r) red[w - 1][lane][4 * c + r] = make_double2(re[c][r], im[c][r]);
+  __syncthreads();
+  if (w > 0) return;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) red[w - 1][lane][4 * c + r] = make_double2(re[tt][c][r], im[tt][c][r]);
-    __syncthreads();
-    if (w == 0)
+  for (int c = 0; c < 4; ++c)
 #pragma unroll
-      for (int tt = 0; tt < RT; ++tt)
-        if (tt == t)
+    for (int r = 0; r < 4; ++r) {
+      double2 v = make_double2(re[c][r], im[c][r]);
 #pragma unroll
-          for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              double2 v = make_double2(re[tt][c][r], im[tt][c][r]);
-#pragma unroll
-              for (int q = 0; q < 3; ++q) v = cadd(v, red[q][lane][4 * c + r]);
-              const int mi = 16 * t + (lane >> 4) + 4 * r, a = a0 + 16 * c + li;
-              if (mi < nrows && a < nv) out[(long)mi * nv + a] = v;
-            }
-  }
+      for (int q = 0; q < 3; ++q) v = cadd(v, red[q][lane][4 * c + r]);
+      const int mi = (lane >> 4) + 4 * r, a = a0 + 16 * c + li;
+      if (mi < nrows && a < nv) out[(long)mi * nv + a] = v;
+    }
 }
 
 template <class TO>
 static adc2_status xbuild_launch(const double2* x, const Dims& d, int rows, const double2* Lvv, TO* X, hipStream_t st) {
   if (thin_rows(d, rows)) {
     const unsigned nblk = (unsigned)cdiv((long)d.naux * d.nv, 256);
-    if (rows <= 16) k_xbuild_thin<TO, 1><<<nblk, 256, 0, st>>>(x, d.dim, d.nc, d.nv, d.naux, rows, Lvv, X);
-    else k_xbuild_thin<TO, 2><<<nblk, 256, 0, st>>>(x, d.dim, d.nc, d.nv, d.naux, rows, Lvv, X);
+    k_xbuild_thin<TO><<<nblk, 256, 0, st>>>(x, d.dim, d.nc, d.nv, d.naux, rows, Lvv, X);
   } else {
-    const long nblk = (long)cdiv(rows, TM) * cdiv((long)d.naux * d.nv, TN);
-    k_xbuild<TO><<<(unsigned)nblk, 256, 0, st>>>(x, d.dim, d.nc, d.nv, d.naux, rows, Lvv, X);
+    const int mr = row_tile(rows);
+    const unsigned nblk = (unsigned)((long)cdiv(rows, mr) * cdiv((long)d.naux * d.nv, TN));
+    if (mr == 32) k_xbuild<TO, 32><<<nblk, 256, 0, st>>>(x, d.dim, d.nc, d.nv, d.naux, rows, Lvv, X);
+    else if (mr == 48) k_xbuild<TO, 48><<<nblk, 256, 0, st>>>(x, d.dim, d.nc, d.nv, d.naux, rows, Lvv, X);
+    else k_xbuild<TO, 64><<<nblk, 256, 0, st>>>(x, d.dim, d.nc, d.nv, d.naux, rows, Lvv, X);
   }
   ADC2_CHECK_LAUNCH();
   return ADC2_OK;
@@ -1184,23 +1165,24 @@ struct SrcLvvT {     // element (k=(P,c), i=a) = Lvv[P][a][c]
   }
 };
 
+template <int MR>
 __global__ __launch_bounds__(256) void k_backc(const double2* __restrict__ Y, const double2* __restrict__ Lvv,
                                                 int nrows, int nv, int naux, int nsplit,
                                                 double2* __restrict__ part) {
   __shared__ TileSmem s;
-  const int nbi = cdiv(nrows, TM), nba = cdiv(nv, TN);
+  const int nbi = cdiv(nrows, MR), nba = cdiv(nv, TN);
   const long nblocks = (long)nbi * nba * nsplit;
   const long lid = xcd_remap(blockIdx.x, nblocks);
   const int split = (int)(lid / ((long)nbi * nba));
   const int tile = (int)(lid % ((long)nbi * nba));
-  const int i0 = (tile / nba) * TM, a0 = (tile % nba) * TN;
+  const int i0 = (tile / nba) * MR, a0 = (tile % nba) * TN;
   const int cpe = cdiv(nv, TK);
   const int nchunks = naux * cpe;
   const int per = cdiv(nchunks, nsplit);
   const int kc0 = split * per, kc1 = min(nchunks, kc0 + per);
   SrcYrows A{Y, naux, nv, cpe, nrows, i0};
   SrcLvvT B{Lvv, nv, cpe, a0};
-  Acc acc;
+  AccT<MR> acc;
   acc.zero();
   mainloop(s, A, B, kc0, kc1, acc);
   double2* out = part + (long)split * nrows * nv;
@@ -2033,14 +2015,12 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
     adc2_handle h = rq[q].h;
     const Dims& d = h->d;
     const int rows = rq[q].m * d.nc;
-    const unsigned thin = (unsigned)(h->nsplit * cdiv(d.nv, 64));
-    const bool few = thin_rows(d, rows);
-    if (few && rows <= 16) k_backc_thin<1><<<thin, 256, 0, st>>>(h->Y, h->Lvv, rows, d.nv, d.naux, h->nsplit, h->part);
-    else if (few)
-      k_backc_thin<2><<<thin, 256, 0, st>>>(h->Y, h->Lvv, rows, d.nv, d.naux, h->nsplit, h->part);
-    else
-      k_backc<<<(unsigned)((long)cdiv(rows, TM) * cdiv(d.nv, TN) * h->nsplit), 256, 0, st>>>(
-          h->Y, h->Lvv, rows, d.nv, d.naux, h->nsplit, h->part);
+    const int mr = thin_rows(d, rows) ? 0 : row_tile(rows);
+    const unsigned nblk = (unsigned)((long)(mr ? cdiv(rows, mr) : 1) * cdiv(d.nv, TN) * h->nsplit);
+    if (mr == 0) k_backc_thin<<<nblk, 256, 0, st>>>(h->Y, h->Lvv, rows, d.nv, d.naux, h->nsplit, h->part);
+    else if (mr == 32) k_backc<32><<<nblk, 256, 0, st>>>(h->Y, h->Lvv, rows, d.nv, d.naux, h->nsplit, h->part);
+    else if (mr == 48) k_backc<48><<<nblk, 256, 0, st>>>(h->Y, h->Lvv, rows, d.nv, d.naux, h->nsplit, h->part);
+    else k_backc<64><<<nblk, 256, 0, st>>>(h->Y, h->Lvv, rows, d.nv, d.naux, h->nsplit, h->part);
     ADC2_CHECK_LAUNCH();
   }
   if ((rc = mark(7)) != ADC2_OK) return rc;

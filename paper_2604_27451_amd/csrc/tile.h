@@ -35,10 +35,12 @@ struct TileSmem {
   double b_im[TK][LDP];
 };
 
-// Four complex values a thread carries from global memory to LDS.
-struct Regs {
-  double2 v[4];
+// Complex values a thread carries from global memory to LDS: four for 64 rows.
+template <int NE>
+struct RegsT {
+  double2 v[NE];
 };
+using Regs = RegsT<4>;
 
 __device__ __forceinline__ double2 czero() { return make_double2(0.0, 0.0); }
 __device__ __forceinline__ double2 cconj(double2 a) { return make_double2(a.x, -a.y); }
@@ -74,20 +76,20 @@ __device__ __forceinline__ void elem_coords(int tid, int e, int& kk, int& ii) {
 
 // A source S provides:  static constexpr int MAP;  double2 get(int k, int i) const
 // returning the (already conjugated / scaled) element or zero out of range.
-template <class S>
-__device__ __forceinline__ void fetch(const S& s, int k0, Regs& r, int tid) {
+template <class S, int NE>
+__device__ __forceinline__ void fetch(const S& s, int k0, RegsT<NE>& r, int tid) {
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
+  for (int e = 0; e < NE; ++e) {
     int kk, ii;
     elem_coords<S::MAP>(tid, e, kk, ii);
     r.v[e] = s.get(k0 + kk, ii);
   }
 }
 
-template <int MAP>
-__device__ __forceinline__ void stash(double (*re)[LDP], double (*im)[LDP], const Regs& r, int tid) {
+template <int MAP, int NE>
+__device__ __forceinline__ void stash(double (*re)[LDP], double (*im)[LDP], const RegsT<NE>& r, int tid) {
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
+  for (int e = 0; e < NE; ++e) {
     int kk, ii;
     elem_coords<MAP>(tid, e, kk, ii);
     re[kk][ii] = r.v[e].x;
@@ -95,36 +97,49 @@ __device__ __forceinline__ void stash(double (*re)[LDP], double (*im)[LDP], cons
   }
 }
 
-struct Acc {
-  d4 re[2][2];
-  d4 im[2][2];
+// Accumulator of a tile of MR rows and 64 columns: four waves of 32 x 32 for MR = 64, of
+// MR x 16 for MR = 32 and 48 (few rows).
+template <int MR>
+struct AccT {
+  static constexpr int NA = MR == 64 ? 2 : MR / 16, NB = MR == 64 ? 2 : 1;
+  d4 re[NA][NB];
+  d4 im[NA][NB];
+  static __device__ __forceinline__ int row0(int w) { return MR == 64 ? (w >> 1) * 32 : 0; }
+  static __device__ __forceinline__ int col0(int w) { return MR == 64 ? (w & 1) * 32 : w * 16; }
   __device__ __forceinline__ void zero() {
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < NA; ++a)
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
+      for (int b = 0; b < NB; ++b) {
         re[a][b] = d4{0.0, 0.0, 0.0, 0.0};
         im[a][b] = d4{0.0, 0.0, 0.0, 0.0};
       }
   }
 };
 
-__device__ __forceinline__ void mma_chunk(const TileSmem& s, Acc& acc, int wr, int wc, int lane) {
+using Acc = AccT<64>;
+
+template <int MR>
+__device__ __forceinline__ void mma_chunk(const TileSmem& s, AccT<MR>& acc, int wr, int wc, int lane) {
+  constexpr int NA = AccT<MR>::NA, NB = AccT<MR>::NB;
   const int li = lane & 15, lk = lane >> 4;
 #pragma unroll
   for (int kg = 0; kg < TK; kg += 4) {
-    double ar[2], ai[2], br[2], bi[2];
+    double ar[NA], ai[NA], br[NB], bi[NB];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; t < NA; ++t) {
       ar[t] = s.a_re[kg + lk][wr + 16 * t + li];
       ai[t] = s.a_im[kg + lk][wr + 16 * t + li];
+    }
+#pragma unroll
+    for (int t = 0; t < NB; ++t) {
       br[t] = s.b_re[kg + lk][wc + 16 * t + li];
       bi[t] = s.b_im[kg + lk][wc + 16 * t + li];
     }
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < NA; ++a)
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
+      for (int b = 0; b < NB; ++b) {
         acc.re[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[a], br[b], acc.re[a][b], 0, 0, 0);
         acc.re[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(-ai[a], bi[b], acc.re[a][b], 0, 0, 0);
         acc.im[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[a], bi[b], acc.im[a][b], 0, 0, 0);
@@ -134,14 +149,15 @@ __device__ __forceinline__ void mma_chunk(const TileSmem& s, Acc& acc, int wr, i
 }
 
 // C += sum over chunks [kc0, kc1) of A(k, i) B(k, j): A and B are sources
-// already positioned at the tile origin (get(k, i) with i in [0, 64)).
-template <class SA, class SB>
-__device__ __forceinline__ void mainloop(TileSmem& s, const SA& A, const SB& B, int kc0, int kc1, Acc& acc) {
+// already positioned at the tile origin (get(k, i) with i in [0, 64), [0, MR) for A).
+template <class SA, class SB, int MR>
+__device__ __forceinline__ void mainloop(TileSmem& s, const SA& A, const SB& B, int kc0, int kc1, AccT<MR>& acc) {
   const int tid = threadIdx.x;
   const int lane = tid & 63, w = tid >> 6;
-  const int wr = (w >> 1) * 32, wc = (w & 1) * 32;
+  const int wr = AccT<MR>::row0(w), wc = AccT<MR>::col0(w);
   if (kc0 >= kc1) return;
-  Regs ra, rb;
+  RegsT<MR / 16> ra;
+  Regs rb;
   fetch(A, kc0 * TK, ra, tid);
   fetch(B, kc0 * TK, rb, tid);
   for (int c = kc0; c < kc1; ++c) {
@@ -158,15 +174,15 @@ __device__ __forceinline__ void mainloop(TileSmem& s, const SA& A, const SB& B, 
 }
 
 // Visit every accumulator element with its tile-local (row, col).
-template <class F>
-__device__ __forceinline__ void for_each_acc(const Acc& acc, F&& f) {
+template <int MR, class F>
+__device__ __forceinline__ void for_each_acc(const AccT<MR>& acc, F&& f) {
   const int tid = threadIdx.x;
   const int lane = tid & 63, w = tid >> 6;
-  const int wr = (w >> 1) * 32, wc = (w & 1) * 32;
+  const int wr = AccT<MR>::row0(w), wc = AccT<MR>::col0(w);
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < AccT<MR>::NA; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < AccT<MR>::NB; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = wr + 16 * a + (lane >> 4) + 4 * r;

@@ -45,8 +45,8 @@ def test_setup_and_sigma(nc, no, nv, naux, m):
     h.close()
 
 
-# X and the back contraction on few rows of a large Lvv: up to 16 rows from 2^23 entries on, 17 to
-# 32 from 2^25 (the larger system against its own calls of few rows)
+# X and the back contraction: up to 16 rows of an Lvv of 2^23 entries and more on the kernels for
+# few rows, others on tiles of 32, 48 or 64 rows, which give the same sums to rounding
 def test_few_rows_of_a_large_lvv():
     print("[case] few rows, naux nv^2 above 2^23", flush=True)
     s = make_system(2, 2, 131, 500, seed=731)
@@ -56,14 +56,17 @@ def test_few_rows_of_a_large_lvv():
     assert off(S[:3].cpu(), O.Adc2(s.L, s.eps, 2, 2, 131).sigma(torch.from_numpy(x[:3]))) < TOL
     assert off(A.adc2_sigma(h, dev(x[3:5])), S[3:5]) < TOL
     h.close()
-    print("[case] few rows, naux nv^2 above 2^25", flush=True)
-    s = make_system(2, 1, 184, 1000, seed=732)
+
+
+@pytest.mark.parametrize("m", [1, 16, 17, 24, 25, 32, 33, 40, 49])
+def test_row_tiles(m):
+    """2 m rows of X around the tiles of 32, 48 and 64 rows."""
+    s = make_system(2, 2, 21, 40, seed=732)
     h = handle(s)
-    x = dev(random_vectors(13, 16, h.dim))
-    want = torch.cat([A.adc2_sigma(h, x[:7]), A.adc2_sigma(h, x[7:])])   # 14 and 18 rows
-    assert off(A.adc2_sigma(h, x), want) < TOL                           # 32 rows
-    xx = torch.cat([x, x[:1]])
-    assert off(A.adc2_sigma(h, xx)[:16], want) < TOL                     # 34 rows: the general kernels
+    print(f"[case] {2 * m} rows", flush=True)
+    x = random_vectors(13, m, h.dim)
+    ref = O.Adc2(s.L, s.eps, 2, 2, 21).sigma(torch.from_numpy(x))
+    assert off(A.adc2_sigma(h, dev(x)).cpu(), ref) < TOL
     h.close()
 
 

@@ -721,12 +721,16 @@ adc2_status fold_davidson(adc2_handle h, int k, const adc2_dav_opts* opt, const 
     for (int c0 = j0; c0 < j0 + q; c0 += FGB) {
       const int qc = std::min(FGB, j0 + q - c0);
       const int mm_ = mblocks * FMB;
-      // 16 or 32 moments per pass (z-slices for more); 128 or 256 pairs per workgroup
+      // 16 or 32 moments per pass (z-slices for more); 128, 192 or 256 pairs per workgroup
       const int ncb = mm_ > 16 ? 2 : 1;
       const int nm = 16 * ncb;
       const int nz = (mm_ + nm - 1) / nm;
       const int npair = srows * qc;
-      const int rb = npair > 128 ? 4 : 2;
+      // the tile that pads the pairs least, the larger on a tie (six new columns of an 18 to 60 vector
+      // space, nd = 0.6 M: 0.58 ms a call on tiles of 256 alone, 0.42 ms)
+      int rb = 4;
+      for (int t : {3, 2})
+        if ((npair + 64 * t - 1) / (64 * t) * t < (npair + 64 * rb - 1) / (64 * rb) * rb) rb = t;
       const int tp = 64 * rb;
       const int ntile = (npair + tp - 1) / tp;
       // slices of the doubles: two workgroups on each of the 256 compute units where the doubles have
@@ -739,8 +743,10 @@ adc2_status fold_davidson(adc2_handle h, int k, const adc2_dav_opts* opt, const 
   k_cheb_mfma<NCB_, RB_><<<g, 256, 0, st>>>(Uro, dim, nd, srows, c0, qc, Ddev, rmap.c, rmap.ih, rmap.inv, \
                                            rmap.w0, nch_m, nz, part)
       if (ncb == 1 && rb == 4) CHEB_MFMA(1, 4);
+      else if (ncb == 1 && rb == 3) CHEB_MFMA(1, 3);
       else if (ncb == 1) CHEB_MFMA(1, 2);
       else if (rb == 4) CHEB_MFMA(2, 4);
+      else if (rb == 3) CHEB_MFMA(2, 3);
       else CHEB_MFMA(2, 2);
 #undef CHEB_MFMA
       ADC2_CHECK_LAUNCH();

@@ -95,19 +95,17 @@ __device__ int fold_coeffs(const FoldMap& r, double omega, int mmax, double* b, 
 // expansion at omega, 3 more moments needed (need), 4 below the shifted
 // map's range, 5 eigensolve did not converge, 6 branch beyond the space.
 // ---------------------------------------------------------------------------
-// Hermitian part of the s x s matrix in S.ar / S.ai (ends with a barrier)
+// Hermitian part of the s x s matrix in S.a (ends with a barrier)
 __device__ __forceinline__ void fold_hermitian(JacobiSmem& S, int s) {
   for (int e = threadIdx.x; e < JMAX * JMAX; e += JTHR) {
     const int i = e >> 6, l = e & 63;
     if (i >= s || l >= s) continue;
     if (i < l) {
-      const double xr = 0.5 * (S.ar[i][l] + S.ar[l][i]), xi = 0.5 * (S.ai[i][l] - S.ai[l][i]);
-      S.ar[i][l] = xr;
-      S.ai[i][l] = xi;
-      S.ar[l][i] = xr;
-      S.ai[l][i] = -xi;
+      const double2 x = cscale(cadd(S.a[i][l], cconj(S.a[l][i])), 0.5);
+      S.a[i][l] = x;
+      S.a[l][i] = cconj(x);
     } else if (i == l) {
-      S.ai[i][i] = 0.0;
+      S.a[i][i].y = 0.0;
     }
   }
   __syncthreads();
@@ -133,17 +131,14 @@ __device__ __forceinline__ void fold_mm(int s, FA fa, FB fb, d4& re, d4& im) {
   }
 }
 
-// the product of fold_mm into S.ar / S.ai, after every wave has read its operands (ends with a barrier)
+// the product of fold_mm into S.a, after every wave has read its operands (ends with a barrier)
 __device__ __forceinline__ void fold_mm_store(JacobiSmem& S, int s, const d4& re, const d4& im) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int i = 16 * (w >> 2) + (lane >> 4) + 4 * r, j = 16 * (w & 3) + (lane & 15);
-    if (i < s && j < s) {
-      S.ar[i][j] = re[r];
-      S.ai[i][j] = im[r];
-    }
+    if (i < s && j < s) S.a[i][j] = make_double2(re[r], im[r]);
   }
   __syncthreads();
 }
@@ -240,7 +235,7 @@ __global__ __launch_bounds__(JTHR) void k_fold_solve(const double2* __restrict__
       break;
     }
     const int M = sM;
-    // G = H11 + sum_m g_m K_m into S.ar / S.ai, its Hermitian part
+    // G = H11 + sum_m g_m K_m into S.a, its Hermitian part
     for (int e = tid; e < JMAX * JMAX; e += JTHR) {
       const int i = e >> 6, l = e & 63;
       if (i >= s || l >= s) continue;
@@ -252,8 +247,7 @@ __global__ __launch_bounds__(JTHR) void k_fold_solve(const double2* __restrict__
         a.x += cg[m] * v.x;
         a.y += cg[m] * v.y;
       }
-      S.ar[i][l] = a.x;
-      S.ai[i][l] = a.y;
+      S.a[i][l] = a;
     }
     __syncthreads();
     fold_hermitian(S, s);
@@ -263,11 +257,11 @@ __global__ __launch_bounds__(JTHR) void k_fold_solve(const double2* __restrict__
       fold_load_z(S, Zg, warm, s);
       __syncthreads();
       d4 re, im;
-      fold_mm(s, [&](int i, int k) { return make_double2(S.ar[i][k], S.ai[i][k]); },
+      fold_mm(s, [&](int i, int k) { return S.a[i][k]; },
               [&](int k, int c) { return S.zt[c][k]; }, re, im);
       fold_mm_store(S, s, re, im);
       fold_mm(s, [&](int r, int k) { return cconj(S.zt[r][k]); },
-              [&](int k, int c) { return make_double2(S.ar[k][c], S.ai[k][c]); }, re, im);
+              [&](int k, int c) { return S.a[k][c]; }, re, im);
       fold_mm_store(S, s, re, im);
       fold_hermitian(S, s);
     }
@@ -277,27 +271,25 @@ __global__ __launch_bounds__(JTHR) void k_fold_solve(const double2* __restrict__
       if (tid == 0) R.status = 5;
       break;
     }
-    if (tid < s) wsh[tid] = S.ar[S.perm[tid]][S.perm[tid]];
+    if (tid < s) wsh[tid] = S.a[S.perm[tid]][S.perm[tid]].x;
     __syncthreads();
-    // eigenvectors of G in ascending order: Z = Zp Z' (Zp through S.ar / S.ai, then
+    // eigenvectors of G in ascending order: Z = Zp Z' (Zp through S.a, then
     // Z in its place), then to the slot
     for (int e = tid; e < JMAX * JMAX; e += JTHR) {
       const int r = e >> 6, c = e & 63;
       if (r >= s || c >= s) continue;
-      const double2 z = (r < warm && c < warm) ? Zg[(long)r * JMAX + c] : make_double2(r == c ? 1.0 : 0.0, 0.0);
-      S.ar[r][c] = z.x;
-      S.ai[r][c] = z.y;
+      S.a[r][c] = (r < warm && c < warm) ? Zg[(long)r * JMAX + c] : make_double2(r == c ? 1.0 : 0.0, 0.0);
     }
     __syncthreads();
     d4 re, im;
-    fold_mm(s, [&](int r, int k) { return make_double2(S.ar[r][k], S.ai[r][k]); },
+    fold_mm(s, [&](int r, int k) { return S.a[r][k]; },
             [&](int k, int c) { return S.zt[S.perm[c]][k]; }, re, im);
     fold_mm_store(S, s, re, im);
     for (int e = tid; e < JMAX * JMAX; e += JTHR) {
       const int r = e >> 6, c = e & 63;
-      if (r < s && c < s) Zg[(long)r * JMAX + c] = make_double2(S.ar[r][c], S.ai[r][c]);
+      if (r < s && c < s) Zg[(long)r * JMAX + c] = S.a[r][c];
     }
-    if (tid < s) ys[tid] = make_double2(S.ar[tid][j], S.ai[tid][j]);
+    if (tid < s) ys[tid] = S.a[tid][j];
     warm = s;
     __syncthreads();
     // |x2|^2 = y^H (sum_m h_m K_m) y

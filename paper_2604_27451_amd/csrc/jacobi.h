@@ -10,15 +10,17 @@
 // applied together.  Sweeps stop when the off-diagonal Frobenius norm is
 // below 1e-15 of the whole (squared: 1e-30).
 //
-// A chain of short rounds (N - 1 a sweep, 6 to 10 sweeps): latency and LDS traffic
-// count.  1024 threads; an item is the 2 x 2 block of the pairs i <= j, to which both
-// sides of the rotation are applied at once; only the upper triangle is read and
-// kept (the mirror cost a third of the traffic).  A round is two barriers: the first
-// wave forms the rotations of a round while the others apply those of the round before
-// to the eigenvectors.  Rows padded to an odd number of doubles, since columns are
-// accessed as often as rows (unpadded, 64 lanes met one bank); two reciprocal square
-// roots a rotation instead of three square roots and four divisions; eigenvalues ranked by
-// counting, not by one thread.
+// A chain of short rounds (N - 1 a sweep, 6 to 10 sweeps): latency, instructions
+// and LDS traffic count.  1024 threads; an item is the 2 x 2 block of the pairs i <= j,
+// to which both sides of the rotation are applied at once; only the upper triangle
+// is read and kept.  The players of a round sit at fixed places, pair t at t and
+// t + N/2, and the tournament moves the data: what an item writes goes where the
+// next round finds it, so all addresses are constants of a thread (players of
+// changing index cost more instructions than the rotations: 3500 cycles a round of 48).
+// While the first wave forms the rotations of a round, the others apply those of the
+// round before to the eigenvectors.  Rows padded to 65 entries, so that neither rows nor
+// columns meet one bank; two reciprocal square roots a rotation instead of three square
+// roots and four divisions; eigenvalues ranked by counting, not by one thread.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -32,13 +34,12 @@ constexpr int JSWEEPS = 40;
 constexpr int JTHR = 1024;   // blockDim.x of every kernel that calls jacobi_lds
 
 struct JacobiSmem {
-  double ar[JMAX][JLD];     // real and imaginary parts of A (upper triangle)
-  double ai[JMAX][JLD];
+  double2 a[JMAX][JLD];     // A (upper triangle)
   double2 zt[JMAX][JMAX];   // accumulated rotations: eigenvector c in row c
   double rc[2][JMAX / 2];   // rotations of this round and of the one before
   double2 rw[2][JMAX / 2];
   double red[2][JTHR / 64];
-  int perm[JMAX];           // ascending order of the eigenvalues ar[perm[i]][perm[i]]
+  int perm[JMAX];           // ascending order of the eigenvalues a[perm[i]][perm[i]].x
   int done;                 // 1 once the sweeps converged
 };
 
@@ -61,68 +62,80 @@ __device__ __forceinline__ void jacobi_sum2(JacobiSmem& S, double& x, double& y)
   __syncthreads();
 }
 
-// A (n x n, its upper triangle and a real diagonal) in S.ar / S.ai; blockDim.x == JTHR.
+// A (n x n, its upper triangle and a real diagonal) in S.a; blockDim.x == JTHR.
 // On return (after a barrier): S.zt[c] holds eigenvector c in the
-// unsorted order of the diagonal of S.ar, S.perm the ascending order, S.done
+// unsorted order of the diagonal of S.a, S.perm the ascending order, S.done
 // whether the sweeps converged within JSWEEPS.
 __device__ inline void jacobi_lds(JacobiSmem& S, int n) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int N = (n + 1) & ~1;   // even number of players: a decoupled zero row joins an odd n
-  const int npair = N / 2;
+  const int np = N / 2;
   for (int e = tid; e < JMAX * JMAX; e += JTHR) {
     const int c = e >> 6, r = e & 63;
     S.zt[c][r] = make_double2(r == c ? 1.0 : 0.0, 0.0);
   }
-  if (N > n && tid < N) S.ar[tid][n] = S.ai[tid][n] = 0.0;
-  __syncthreads();
+  if (N > n && tid < N) S.a[tid][n] = make_double2(0.0, 0.0);
+  // where the player at place x is in the next round: 0 stays, the others go round
+  // 1 .. np - 1 downwards, then np .. N - 1 upwards
+  auto next = [&](int x) {
+    if (x == 0 || np == 1) return x;
+    if (x < np) return x == 1 ? np : x - 1;
+    return x == N - 1 ? np - 1 : x + 1;
+  };
   // item tid = pj (pj + 1) / 2 + pi of the block update, pi <= pj
   int pj = (int)((sqrtf(8.0f * (float)tid + 1.0f) - 1.0f) * 0.5f);
   if (pj * (pj + 1) / 2 > tid) --pj;
   if ((pj + 1) * (pj + 2) / 2 <= tid) ++pj;
   const int pi = tid - pj * (pj + 1) / 2;
-  // the players of pair t in a round: player 0 fixed, players 1..N-1 rotate
-  auto players = [&](int t, int round, int& p, int& q) {
-    int a = 0, b = 1 + round;
-    if (t > 0) {
-      a = round + t;
-      a = 1 + (a >= N - 1 ? a - (N - 1) : a);
-      b = round - t;
-      b = 1 + (b < 0 ? b + (N - 1) : b);
-    }
-    p = min(a, b);
-    q = max(a, b);
-  };
-  auto geta = [&](int x, int y) {   // A[x][y]
-    const int i = min(x, y), j = max(x, y);
-    const double im = S.ai[i][j];
-    return make_double2(S.ar[i][j], x > y ? -im : im);
-  };
-  auto puta = [&](int x, int y, double2 v) {
-    const int i = min(x, y), j = max(x, y);
-    S.ar[i][j] = v.x;
-    S.ai[i][j] = x > y ? -v.y : v.y;
-  };
-  // eigenvector columns of the pairs t = t0, t0 + dt, ... under the rotations of a round
-  auto vectors = [&](int round, int buf, int t0, int dt) {
-    for (int t = t0; t < npair; t += dt) {
-      const double c = S.rc[buf][t];
-      const double2 w = S.rw[buf][t];
-      if (lane < n && (w.x != 0.0 || w.y != 0.0)) {
-        int p, q;
-        players(t, round, p, q);
-        const double2 zx = S.zt[p][lane], zy = S.zt[q][lane];
-        S.zt[p][lane] = csub(cscale(zx, c), cmul(cconj(w), zy));
-        S.zt[q][lane] = cadd(cmul(w, zx), cscale(zy, c));
+  const bool item = pj < np;
+  // its entries (pi, pj), (pi, pj + np), (pi + np, pj) and (pi + np, pj + np), the third kept as
+  // the conjugate of (pj, pi + np); where they go, and which go below the diagonal
+  const int pic = item ? pi : 0, pjc = item ? pj : 0;
+  double2* const r00 = &S.a[pic][pjc];
+  double2* const r01 = &S.a[pic][pjc + np];
+  double2* const r10 = &S.a[pjc][pic + np];
+  double2* const r11 = &S.a[pic + np][pjc + np];
+  const int xi = next(pic), yi = next(pic + np), xj = next(pjc), yj = next(pjc + np);
+  double2* const w00 = &S.a[min(xi, xj)][max(xi, xj)];
+  double2* const w01 = &S.a[min(xi, yj)][max(xi, yj)];
+  double2* const w10 = &S.a[min(yi, xj)][max(yi, xj)];
+  double2* const w11 = &S.a[min(yi, yj)][max(yi, yj)];
+  const double s00 = xi > xj ? -1.0 : 1.0, s01 = xi > yj ? -1.0 : 1.0, s10 = yi > xj ? -1.0 : 1.0,
+               s11 = yi > yj ? -1.0 : 1.0;
+  // eigenvectors: waves 1 .. 15 take the pairs wv - 1 + 15 u
+  constexpr int NZ = (JMAX / 2 + JTHR / 64 - 2) / (JTHR / 64 - 1);
+  double2 zx[NZ], zy[NZ];
+  auto zturn = [&](int buf) {
+#pragma unroll
+    for (int u = 0; u < NZ; ++u) {
+      const int t = wv - 1 + (JTHR / 64 - 1) * u;
+      if (wv > 0 && t < np) {
+        const double c = S.rc[buf][t];
+        const double2 w = S.rw[buf][t], x = S.zt[t][lane], y = S.zt[t + np][lane];
+        zx[u] = csub(cscale(x, c), cmul(cconj(w), y));
+        zy[u] = cadd(cmul(w, x), cscale(y, c));
       }
     }
   };
+  auto zmove = [&]() {
+#pragma unroll
+    for (int u = 0; u < NZ; ++u) {
+      const int t = wv - 1 + (JTHR / 64 - 1) * u;
+      if (wv > 0 && t < np) {
+        S.zt[next(t)][lane] = zx[u];
+        S.zt[next(t + np)][lane] = zy[u];
+      }
+    }
+  };
+  __syncthreads();
   bool conv = false;
   for (int sweep = 0; sweep <= JSWEEPS; ++sweep) {
     double off = 0.0, tot = 0.0;
     for (int e = tid; e < JMAX * JMAX; e += JTHR) {
       const int i = e >> 6, j = e & 63;
       if (i <= j && j < n) {
-        const double v = S.ar[i][j] * S.ar[i][j] + S.ai[i][j] * S.ai[i][j];
+        const double2 x = S.a[i][j];
+        const double v = x.x * x.x + x.y * x.y;
         tot += i == j ? v : 2.0 * v;
         if (i != j) off += 2.0 * v;
       }
@@ -133,14 +146,12 @@ __device__ inline void jacobi_lds(JacobiSmem& S, int n) {
     for (int round = 0; round < N - 1; ++round) {
       const int buf = round & 1;
       if (wv == 0) {
-        if (lane < npair) {
-          int p, q;
-          players(lane, round, p, q);
+        if (lane < np) {
           double c = 1.0;
           double2 w = make_double2(0.0, 0.0);
-          const double br = S.ar[p][q], bi = S.ai[p][q];
-          const double b2 = br * br + bi * bi;
-          const double app = S.ar[p][p], aqq = S.ar[q][q];
+          const double2 b = S.a[lane][lane + np];
+          const double b2 = b.x * b.x + b.y * b.y;
+          const double app = S.a[lane][lane].x, aqq = S.a[lane + np][lane + np].x;
           const double sc = fabs(app) + fabs(aqq);
           if (b2 > 1e-290 && b2 > 1e-36 * sc * sc) {
             const double a = 0.5 * (aqq - app);
@@ -149,51 +160,54 @@ __device__ inline void jacobi_lds(JacobiSmem& S, int n) {
             const double ic = rsqrt(c2);
             c = c2 * ic;
             const double f = (a >= 0.0 ? 0.5 : -0.5) * ir * ic;
-            w = make_double2(f * br, f * bi);
+            w = make_double2(f * b.x, f * b.y);
           }
           S.rc[buf][lane] = c;
           S.rw[buf][lane] = w;
         }
       } else if (round > 0) {
-        vectors(round - 1, buf ^ 1, wv - 1, JTHR / 64 - 1);
+        zturn(buf ^ 1);
       }
       __syncthreads();
-      if (pj < npair) {
-        int p, q, x, y;
-        players(pi, round, p, q);
-        players(pj, round, x, y);
+      if (round > 0) zmove();
+      double2 v00, v01, v10, v11;
+      if (item) {
         const double ci = S.rc[buf][pi], cj = S.rc[buf][pj];
         const double2 wi = S.rw[buf][pi], wj = S.rw[buf][pj], wjc = cconj(wj), wic = cconj(wi);
-        const double2 a00 = geta(p, x), a01 = geta(p, y), a10 = geta(q, x), a11 = geta(q, y);
+        const double2 a00 = *r00, a01 = *r01, a10 = cconj(*r10), a11 = *r11;
         // columns: new_x = c x - conj(w) y, new_y = w x + c y
         const double2 u00 = csub(cscale(a00, cj), cmul(wjc, a01)), u01 = cadd(cmul(wj, a00), cscale(a01, cj));
         const double2 u10 = csub(cscale(a10, cj), cmul(wjc, a11)), u11 = cadd(cmul(wj, a10), cscale(a11, cj));
         // rows: new_p = c p - w q, new_q = conj(w) p + c q
-        double2 v00 = csub(cscale(u00, ci), cmul(wi, u10)), v01 = csub(cscale(u01, ci), cmul(wi, u11));
-        double2 v10 = cadd(cmul(wic, u00), cscale(u10, ci)), v11 = cadd(cmul(wic, u01), cscale(u11, ci));
+        v00 = csub(cscale(u00, ci), cmul(wi, u10));
+        v01 = csub(cscale(u01, ci), cmul(wi, u11));
+        v10 = cadd(cmul(wic, u00), cscale(u10, ci));
+        v11 = cadd(cmul(wic, u01), cscale(u11, ci));
         if (pi == pj) {
           v00.y = v11.y = 0.0;
           if (wi.x != 0.0 || wi.y != 0.0) v01 = make_double2(0.0, 0.0);
-          puta(p, p, v00);
-          puta(p, q, v01);
-          puta(q, q, v11);
-        } else {
-          puta(p, x, v00);
-          puta(p, y, v01);
-          puta(q, x, v10);
-          puta(q, y, v11);
         }
       }
       __syncthreads();
+      if (item) {
+        *w00 = make_double2(v00.x, s00 * v00.y);
+        *w01 = make_double2(v01.x, s01 * v01.y);
+        if (pi != pj) *w10 = make_double2(v10.x, s10 * v10.y);
+        *w11 = make_double2(v11.x, s11 * v11.y);
+      }
+      __syncthreads();
     }
-    vectors(N - 2, N & 1, wv, JTHR / 64);
+    zturn(N & 1);   // the last round, N - 2
+    __syncthreads();
+    zmove();
+    __syncthreads();
   }
   if (tid == 0) S.done = conv ? 1 : 0;
   if (tid < n) {   // rank of each eigenvalue
-    const double v = S.ar[tid][tid];
+    const double v = S.a[tid][tid].x;
     int rank = 0;
     for (int j = 0; j < n; ++j) {
-      const double u = S.ar[j][j];
+      const double u = S.a[j][j].x;
       rank += (u < v || (u == v && j < tid)) ? 1 : 0;
     }
     S.perm[rank] = tid;

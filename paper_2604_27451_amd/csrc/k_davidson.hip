@@ -294,12 +294,11 @@ __global__ __launch_bounds__(JTHR) void k_heevj(const double2* __restrict__ G, i
     const int i = e >> 6, j = e & 63;
     if (i > j || j >= n) continue;
     const double2 g = G[(long)i * ldg + j];
-    S.ar[i][j] = g.x;
-    S.ai[i][j] = i == j ? 0.0 : g.y;
+    S.a[i][j] = make_double2(g.x, i == j ? 0.0 : g.y);
   }
   __syncthreads();
   jacobi_lds(S, n);
-  if (tid < n) w[tid] = S.ar[S.perm[tid]][S.perm[tid]];
+  if (tid < n) w[tid] = S.a[S.perm[tid]][S.perm[tid]].x;
   for (int e = tid; e < JMAX * JMAX; e += JTHR) {
     const int r = e >> 6, c = e & 63;
     if (r < n && c < n) Z[(long)r * ldz + c] = S.zt[S.perm[c]][r];

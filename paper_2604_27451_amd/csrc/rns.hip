@@ -142,6 +142,17 @@ struct RnsSums {
 // Partial sums of squares of the rows, K split over blockIdx.y.  HBM-bound (one
 // read of the operand): lane = row where rows are contiguous, a wave per row
 // where k is.
+// The largest e with ||row|| 2^e <= 2^RNS_G from the row's three sums
+__device__ __forceinline__ int rns_exponent(double s0, double s1, double s2) {
+  double l2;   // log2 of the norm
+  if (s0 >= 0x1p-900 && s0 <= 0x1p1000) l2 = 0.5 * log2(s0);
+  else if (s0 > 1.0) l2 = 0.5 * log2(s1) + 540.0;   // above 2^500 (Inf where a row is not finite)
+  else if (s2 > 0.0) l2 = 0.5 * log2(s2) - 540.0;   // below 2^-450
+  else if (s0 == 0.0) l2 = RNS_G;                   // zero row: e = 0
+  else l2 = s0;                                     // NaN
+  return isfinite(l2) ? (int)floor(RNS_G - 1e-9 - l2) : RNS_NAN;
+}
+
 __global__ __launch_bounds__(256) void k_rns_norm(const RnsSrc src, int rows, int K, double* __restrict__ part) {
   __shared__ double red[4][3][64];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -176,15 +187,31 @@ __global__ __launch_bounds__(256) void k_rns_norm(const RnsSrc src, int rows, in
   }
 }
 
-__global__ __launch_bounds__(256) void k_rns_norm_k(const RnsSrc src, int rows, int K, double* __restrict__ part) {
+// (one slice: the exponents themselves)
+__global__ __launch_bounds__(256) void k_rns_norm_k(const RnsSrc src, int rows, int K, int padded,
+                                                    double* __restrict__ part, int* __restrict__ e) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;
+  if (row >= rows) {
+    if (gridDim.y == 1 && lane == 0 && row < padded) e[row] = 0;
+    return;
+  }
   const double2* p = src.p + rns_row(src, row);
   const int per = (K + gridDim.y - 1) / gridDim.y;
   const int k0 = blockIdx.y * per, k1 = min(K, k0 + per);
   RnsSums t{{0.0, 0.0, 0.0}};
-  for (int k = k0 + lane; k < k1; k += 64) {
+  int k = k0 + lane;
+  for (; k + 192 < k1; k += 256) {
+    double2 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = p[rns_k(src, k + 64 * u)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      t.add(v[u].x);
+      t.add(v[u].y);
+    }
+  }
+  for (; k < k1; k += 64) {
     const double2 v = p[rns_k(src, k)];
     t.add(v.x);
     t.add(v.y);
@@ -193,8 +220,13 @@ __global__ __launch_bounds__(256) void k_rns_norm_k(const RnsSrc src, int rows, 
   for (int q = 0; q < 3; ++q) {
     double v = t.s[q];
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    if (lane == 0) part[((long)blockIdx.y * 3 + q) * rows + row] = v;
+    t.s[q] = v;
   }
+  if (lane != 0) return;
+  if (gridDim.y == 1) e[row] = rns_exponent(t.s[0], t.s[1], t.s[2]);
+  else
+#pragma unroll
+    for (int q = 0; q < 3; ++q) part[((long)blockIdx.y * 3 + q) * rows + row] = t.s[q];
 }
 
 // e[row]: the largest e with ||row|| 2^e <= 2^RNS_G; rows past the end 0.  A workgroup
@@ -215,21 +247,11 @@ __global__ __launch_bounds__(1024) void k_rns_expo(const double* __restrict__ pa
   for (int q = 0; q < 3; ++q) red[w][q][lane] = s[q];
   __syncthreads();
   if (w != 0 || row >= padded) return;
-  int ex = 0;
-  if (row < rows) {
-    const int nw = nsplit < 16 ? nsplit : 16;
-    for (int t = 1; t < nw; ++t)
+  const int nw = nsplit < 16 ? nsplit : 16;
+  for (int t = 1; t < nw; ++t)
 #pragma unroll
-      for (int q = 0; q < 3; ++q) s[q] += red[t][q][lane];
-    double l2;   // log2 of the norm
-    if (s[0] >= 0x1p-900 && s[0] <= 0x1p1000) l2 = 0.5 * log2(s[0]);
-    else if (s[0] > 1.0) l2 = 0.5 * log2(s[1]) + 540.0;   // above 2^500 (Inf where a row is not finite)
-    else if (s[2] > 0.0) l2 = 0.5 * log2(s[2]) - 540.0;   // below 2^-450
-    else if (s[0] == 0.0) l2 = RNS_G;                      // zero row: e = 0
-    else l2 = s[0];                                        // NaN
-    ex = isfinite(l2) ? (int)floor(RNS_G - 1e-9 - l2) : RNS_NAN;
-  }
-  e[row] = ex;
+    for (int q = 0; q < 3; ++q) s[q] += red[t][q][lane];
+  e[row] = row < rows ? rns_exponent(s[0], s[1], s[2]) : 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -366,12 +388,17 @@ adc2_status rns_pack(const RnsSrc& src, int rows, int K, int8_t* buf, int* ebuf,
   // enough blocks to fill the chip, at least 16 (64) k a block
   const int nrow = rcdiv(rows, klane ? 4 : 64);
   const int ns = std::max(1, std::min({NORM_SPLIT, rcdiv(4096, nrow), rcdiv(K, klane ? 64 : 16)}));
-  if (klane) k_rns_norm_k<<<dim3((unsigned)nrow, (unsigned)ns), 256, 0, st>>>(src, rows, K, nbuf);
-  else k_rns_norm<<<dim3((unsigned)nrow, (unsigned)ns), 256, 0, st>>>(src, rows, K, nbuf);
-  ADC2_CHECK_LAUNCH();
   const int padded = out->nrt * RNS_RT;
-  k_rns_expo<<<rcdiv(padded, 64), 1024, 0, st>>>(nbuf, ns, rows, padded, ebuf);
+  if (klane) {
+    k_rns_norm_k<<<dim3((unsigned)rcdiv(padded, 4), (unsigned)ns), 256, 0, st>>>(src, rows, K, padded, nbuf, ebuf);
+  } else {
+    k_rns_norm<<<dim3((unsigned)nrow, (unsigned)ns), 256, 0, st>>>(src, rows, K, nbuf);
+  }
   ADC2_CHECK_LAUNCH();
+  if (!klane || ns > 1) {
+    k_rns_expo<<<rcdiv(padded, 64), 1024, 0, st>>>(nbuf, ns, rows, padded, ebuf);
+    ADC2_CHECK_LAUNCH();
+  }
   const long nblk = (long)2 * out->nrt * out->nkc;
   // a block alone on its compute unit takes 15 us for the 16 moduli, 7 us for 4 of them
   const dim3 grid((unsigned)nblk, nblk <= 256 ? 4 : (nblk <= 512 ? 2 : 1));

@@ -289,13 +289,13 @@ hipError_t dmalloc_try(adc2_handle h, void** p, size_t bytes) {
 }
 
 // A request that fails while the handle holds residue-engine memory is tried
-// again without it (that engine is an option, the request is not).
+// again without it (that engine is an option, the request is not); its next
+// product asks for it anew.
 hipError_t dmalloc_raw(adc2_handle h, void** p, size_t bytes) {
   hipError_t e = dmalloc_try(h, p, bytes);
   if (e == hipErrorOutOfMemory && h && (h->rns_lvo || h->rns_lvt || h->rns_ws || h->rns_tmp)) {
     (void)hipGetLastError();
     rns_release(h);
-    h->rns_off = true;
     e = dmalloc_try(h, p, bytes);
   }
   return e;

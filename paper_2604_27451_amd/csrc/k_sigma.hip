@@ -1522,14 +1522,14 @@ adc2_status rns_build_static(adc2_handle h, bool at_setup, hipStream_t st) {
     return ADC2_OK;
   if (h->rns_off || d.naux > RNS_KMAX || ky > RNS_KMAX) return ADC2_OK;
   double* norm = nullptr;
-  hipError_t e = dmalloc(h, &norm, std::max(rns_norm_bytes(ky), rns_norm_bytes(d.naux)));
-  if (e == hipSuccess) e = dmalloc(h, &h->rns_lvo, rns_op_bytes(ky, d.naux) + rns_exp_bytes(ky));
-  if (e == hipSuccess && !h->rns_off) e = dmalloc(h, &h->rns_lvt, rns_op_bytes(d.naux, ky) + rns_exp_bytes(d.naux));
+  hipError_t e = dmalloc_try(h, (void**)&norm, std::max(rns_norm_bytes(ky), rns_norm_bytes(d.naux)));
+  if (e == hipSuccess) e = dmalloc_try(h, (void**)&h->rns_lvo, rns_op_bytes(ky, d.naux) + rns_exp_bytes(ky));
+  if (e == hipSuccess)
+    e = dmalloc_try(h, (void**)&h->rns_lvt, rns_op_bytes(d.naux, ky) + rns_exp_bytes(d.naux));
   adc2_status rc = ADC2_OK;
-  if (e != hipSuccess || h->rns_off) {   // without the memory: the MFMA engines
+  if (e != hipSuccess) {   // without the memory: none of it
     (void)hipGetLastError();
     rns_release(h);
-    h->rns_off = true;
   } else {
     RnsMat t;
     rc = rns_pack(rns_lvo_rows(h), (int)ky, d.naux, (int8_t*)h->rns_lvo,
@@ -1549,21 +1549,37 @@ adc2_status rns_build_static(adc2_handle h, bool at_setup, hipStream_t st) {
 }
 
 // The residue engine's buffers for m vectors; *ok = false (and the MFMA engines
-// from then on) where the memory is not to be had.
+// from then on) where the memory is not to be had.  Where it is short, first the
+// scratch of the MFMA engines and of the split-BF16 form goes (it is allocated again when
+// used: a two-stage solve at nc=6 no=120 nv=600 naux=3000 leaves 60 GB of it beside
+// a search space of 153 GB, and its FP64 stage took 1.9 s a sigma of ten vectors
+// on the MFMA engines, 0.63 s here), then chunks get smaller.
 static adc2_status rns_ready(adc2_handle h, int m, hipStream_t st, bool* ok) {
   *ok = false;
-  // smaller chunks where the target's memory is not to be had
-  while (!rns_reserve(h, rns_plan(h, m * h->d.nc).bytes)) {
-    if (h->rns_off || rns_plan(h, m * h->d.nc).c <= 1) {
+  auto spare = [&]() {
+    if (!h->Zb && !h->XB && !h->RB) return false;
+    dfree(h, h->Zb);
+    dfree(h, h->XB);
+    dfree(h, h->RB);
+    h->Zb = nullptr;
+    h->XB = h->RB = nullptr;
+    h->zb_m = h->wsb_m = 0;
+    return true;
+  };
+  for (;;) {
+    const adc2_status rc = rns_build_static(h, false, st);
+    if (rc != ADC2_OK) return rc;
+    if (h->rns_lvo && h->rns_lvt && rns_reserve(h, rns_plan(h, m * h->d.nc).bytes)) break;
+    if (spare()) continue;
+    if (!h->rns_lvo || !h->rns_lvt || rns_plan(h, m * h->d.nc).c <= 1) {
       rns_release(h);
       h->rns_off = true;
       return ADC2_OK;
     }
     h->rns_target /= 2;
   }
-  const adc2_status rc = rns_build_static(h, false, st);
-  *ok = rc == ADC2_OK && !h->rns_off;
-  return rc;
+  *ok = true;
+  return ADC2_OK;
 }
 
 static RnsMat rns_static(char* mem, long rows, long K) {

@@ -658,7 +658,7 @@ bool rns_pays(adc2_handle h, long M, long N, long K, double rate) {
   return rns < 0.85 * terms * 8 / rate;
 }
 
-static bool rns_grow(adc2_handle h, char** buf, size_t* have, size_t bytes, bool last) {
+static bool rns_grow(adc2_handle h, char** buf, size_t* have, size_t bytes) {
   if (h->rns_off) return false;
   if (*have >= bytes) return true;
   if (bytes > (size_t(256) << 20)) bytes = (bytes + (size_t(512) << 20) - 1) >> 29 << 29;   // few sizes: blocks are reused
@@ -672,15 +672,11 @@ static bool rns_grow(adc2_handle h, char** buf, size_t* have, size_t bytes, bool
     return true;
   }
   (void)hipGetLastError();
-  if (last) {
-    rns_release(h);
-    h->rns_off = true;
-  }
   return false;
 }
 
 bool rns_reserve(adc2_handle h, size_t bytes) {
-  return rns_grow(h, &h->rns_ws, &h->rns_ws_bytes, bytes, false);
+  return rns_grow(h, &h->rns_ws, &h->rns_ws_bytes, bytes);
 }
 
 void rns_tmp_release(adc2_handle h) {
@@ -720,7 +716,7 @@ adc2_status rns_product(adc2_handle h, const RnsSrc& A, int M, const RnsSrc& B, 
     if (mc > 256 && (mc >= nc || nc <= 128)) mc = (mc / 2 + 255) / 256 * 256;
     else nc = (nc / 2 + 127) / 128 * 128;
   }
-  if (!rns_grow(h, &h->rns_tmp, &h->rns_tmp_bytes, need(mc, nc), true)) return ADC2_OK;
+  if (!rns_grow(h, &h->rns_tmp, &h->rns_tmp_bytes, need(mc, nc))) return ADC2_OK;
   char* q = h->rns_tmp;
   auto take = [&](size_t b) {
     char* r = q;

@@ -189,3 +189,45 @@ def test_without_its_memory_the_mfma_engine_serves(monkeypatch):
     n = state["count"]
     assert torch.equal(A.adc2_sigma(h, x), got) and state["count"] == n
     h.close()
+
+
+def test_short_of_memory_other_scratch_goes_first(monkeypatch):
+    """No memory beyond what the handle holds after a split-BF16 sigma: the
+    FP64 sigma gives back that form's scratch and runs on the engine (the bits
+    of a handle with all the memory it wants), and the split-BF16 sigma takes
+    its scratch again once there is memory.  (300 vectors: work spaces beyond
+    adc2_sigma_noalloc's array, within which a handle set up in a precision
+    form stays on the MFMA engine.)"""
+    monkeypatch.setenv("ADC2_ZGEMM", "rns")
+    s = make_system(2, 6, 40, 70, seed=941)
+    h = handle(s)
+    x = dev(random_vectors(6, 300, h.dim))
+    want = A.adc2_sigma(h, x)
+    h.close()
+    base = A.torch_allocator()
+    live, limit = {}, [None]
+
+    def _alloc(nbytes, ctx):
+        if limit[0] is not None and sum(live.values()) + nbytes > limit[0]:
+            return None
+        p = base.alloc(nbytes, ctx)
+        if p:
+            live[p] = nbytes
+        return p
+
+    def _release(p, ctx):
+        live.pop(p, None)
+        base.release(p, ctx)
+
+    al = A.Alloc(A._ALLOC_FN(_alloc), A._RELEASE_FN(_release), None)
+    h = handle(s, alloc=al, prec=A.ADC2_BF16X3)
+    split = A.adc2_sigma(h, x)
+    A.adc2_set_precision(h, A.ADC2_FP64)
+    limit[0] = sum(live.values()) + (1 << 16)
+    print("[case] rns short of memory", flush=True)
+    assert torch.equal(A.adc2_sigma(h, x), want)
+    assert sum(live.values()) <= limit[0]
+    limit[0] = None
+    A.adc2_set_precision(h, A.ADC2_BF16X3)
+    assert torch.equal(A.adc2_sigma(h, x), split)
+    h.close()

@@ -57,11 +57,11 @@ typedef enum {
 } adc2_status;
 
 typedef enum {
-  ADC2_FP64 = 0,               /* complex FP64 contractions: on the FP64 MFMA, and
-                                  where the work spaces exceed the reach of
-                                  adc2_sigma_noalloc as exact integer products on
-                                  the INT8 MFMA (operands rounded at 2^-57 of
-                                  their row norm; errors below the FP64 MFMA's)   */
+  ADC2_FP64 = 0,               /* complex FP64 contractions: the large ones as exact
+                                  integer products on the INT8 MFMA (operands
+                                  rounded at 2^-58 of their row norm; errors below
+                                  the FP64 MFMA's), the smallest and those without
+                                  the memory for it on the FP64 MFMA             */
   ADC2_C64 = 1                 /* precision form: the two heavy sigma
                                   contractions on complex64 operands with the
                                   FP32 MFMA and FP32 accumulation; setup,
@@ -178,7 +178,8 @@ ADC2_API adc2_status adc2_sigma(adc2_handle h, int m, const void* X, void* S, vo
  * scratch memory it has not written in the same call.  Calls that overlap on
  * one device (concurrent streams or threads) race on the array and must not
  * be issued.  Results equal adc2_sigma's in the FP64 form: the same kernels
- * with the same split counts.
+ * with the same split counts, the integer products in smaller chunks (which
+ * leaves their results as they are).
  *   m  >= 1; the work spaces of m vectors must fit the array: about
  *      16 m nc (naux nv (1 + ysplit) + no nv^2) bytes (c1: nc=6, no=10,
  *      nv=40, naux=150 fits m up to about 16).
@@ -483,7 +484,9 @@ ADC2_API adc2_status adc2_fns(adc2_handle h, const void* L, double threshold, in
  * workgroups a launch has against extra partial traffic and a summation
  * pass, and in the FP64 form its engine decides the tile shape (128 x 128 on
  * eight waves, 128 x 64 at two workgroups per CU, 128 x 128 on four waves, or
- * 128 x 64 three-multiplication).
+ * 128 x 64 three-multiplication).  In the FP64 form these are the engines of
+ * the FP64 MFMA; sigmas that run as integer products on the INT8 MFMA do not
+ * depend on the choice.
  * adc2_autotune times the Y-build of h's current precision form at block size
  * m: in the FP64 form first each engine at its own size-rule K-split (unless
  * the environment variable ADC2_ZGEMM fixes the engine), then, for the

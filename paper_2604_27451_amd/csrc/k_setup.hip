@@ -273,7 +273,7 @@ static bool w_pays(adc2_handle h) {
 }
 
 // W of every pair on the residue engine (adjoint, transition moments); nc=6
-// no=60 nv=300 naux=1500: 71 ms on the FP64 MFMA tiles, 16 ms so.
+// no=60 nv=300 naux=1500: 71 ms on the FP64 MFMA tiles, 17 ms so.
 static adc2_status wbuild_rns(adc2_handle h, const int2* dpairs, double2* W, double* epart, bool* done,
                               hipStream_t st) {
   const Dims& d = h->d;
@@ -481,7 +481,7 @@ __global__ __launch_bounds__(256) void k_qterm(const double2* __restrict__ W, co
 //   Bm[a][b] = sum_{p,c} T_p[c][a] conj(W_p[c][b]), tau formed for about 10^5 terms at a time
 //   E[I][J][a][b] = sum_{k,c} Tc[I][k][c][a] conj(Wc[J][k][c][b])
 //   qpart by k_qterm from the core rows.
-// nc=6 no=60 nv=300 naux=1500: W, (i) and (iii) took 71 + 18 + 18 ms on FP64 MFMA tiles, 29 ms so.
+// nc=6 no=60 nv=300 naux=1500: W, (i) and (iii) took 71 + 18 + 18 ms on FP64 MFMA tiles, 33 ms so.
 static adc2_status pair_terms_rns(adc2_handle h, const int2* dpairs, int npairs, double2* Bm, double2* E,
                                   double2* qpart, double* epart, bool* done, hipStream_t st) {
   const Dims& d = h->d;

@@ -41,6 +41,9 @@ static void free_handle(adc2_handle h) {
   dfree(h, h->LvT32);
   dfree(h, h->LvB);
   dfree(h, h->LvTB);
+  if (h->side) (void)hipStreamDestroy(h->side);
+  if (h->side_fork) (void)hipEventDestroy(h->side_fork);
+  if (h->side_join) (void)hipEventDestroy(h->side_join);
   dfree(h, h->XB);
   dfree(h, h->RB);
   dfree(h, h->eps);
@@ -413,6 +416,11 @@ adc2_status adc2_setup(const void* L, const double* eps, int nc, int no, int nv,
   rc = build_m11(h, st);
   if (rc == ADC2_OK) rc = build_lvt(h, st);
   if (rc == ADC2_OK) rc = rns_build_static(h, true, st);
+  if (rc == ADC2_OK && h->rns_setup &&
+      (hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking) != hipSuccess ||
+       hipEventCreateWithFlags(&h->side_fork, hipEventDisableTiming) != hipSuccess ||
+       hipEventCreateWithFlags(&h->side_join, hipEventDisableTiming) != hipSuccess))
+    rc = fail(ADC2_ERR_HIP, "adc2_setup: no stream for the second half of small sigmas");
   if (rc == ADC2_OK && hipStreamSynchronize(st) != hipSuccess) rc = fail(ADC2_ERR_HIP, "adc2_setup: sync failed");
   if (rc != ADC2_OK) {
     free_handle(h);

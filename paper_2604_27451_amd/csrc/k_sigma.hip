@@ -1548,6 +1548,14 @@ adc2_status rns_build_static(adc2_handle h, bool at_setup, hipStream_t st) {
   return rc;
 }
 
+// Terms of a product up to which the two halves of a sigma run side by side (sigma_overlapped), us
+// one after the other / side by side: no=12 nv=100 naux=300, one vector (2e8) 201 / 158, four (9e8)
+// 364 / 329; no=20 nv=200 naux=800, two (8e9) 1363 / 1303, four (1.5e10) 2285 / 2293; no=45
+// nv=310 naux=1240, one (3e10), 4240 / 4470.
+constexpr double OVERLAP_TERMS = 1e10;
+static bool overlap_sized(const Dims& d, double rows) { return rows * d.nv * d.naux * d.no * d.nv <= OVERLAP_TERMS; }
+static size_t overlap_base(adc2_handle h, int rows) { return (rns_plan(h, rows).bytes + 255) & ~size_t(255); }
+
 // The residue engine's buffers for m vectors; *ok = false (and the MFMA engines
 // from then on) where the memory is not to be had.  Where it is short, first the
 // scratch of the MFMA engines and of the split-BF16 form goes (it is allocated again when
@@ -1569,7 +1577,11 @@ static adc2_status rns_ready(adc2_handle h, int m, hipStream_t st, bool* ok) {
   for (;;) {
     const adc2_status rc = rns_build_static(h, false, st);
     if (rc != ADC2_OK) return rc;
-    if (h->rns_lvo && h->rns_lvt && rns_reserve(h, rns_plan(h, m * h->d.nc).bytes)) break;
+    if (h->rns_lvo && h->rns_lvt) {
+      const size_t one = rns_plan(h, m * h->d.nc).bytes;
+      if (h->side && !h->rns_lent && overlap_sized(h->d, m * h->d.nc) && rns_reserve(h, 2 * overlap_base(h, m * h->d.nc))) break;
+      if (rns_reserve(h, one)) break;
+    }
     if (spare()) continue;
     if (!h->rns_lvo || !h->rns_lvt || rns_plan(h, m * h->d.nc).c <= 1) {
       rns_release(h);
@@ -1673,12 +1685,12 @@ static adc2_status rns_doubles_in(adc2_handle h, const SigReq& rq, RnsProf& pf, 
 }
 
 // sigma2 of the singles input (X built), chunk by chunk.
-static adc2_status rns_singles_in(adc2_handle h, const SigReq& rq, int with_d, RnsProf& pf, hipStream_t st) {
+static adc2_status rns_singles_in(adc2_handle h, const SigReq& rq, int with_d, RnsProf& pf, char* ws, hipStream_t st) {
   const Dims& d = h->d;
   const int rows = rq.m * d.nc, N = d.no * d.nv;
   const RnsPlan p = rns_plan(h, rows);
-  double2* Z = (double2*)(h->rns_ws + p.f64);
-  int8_t* out = (int8_t*)(h->rns_ws + p.out);
+  double2* Z = (double2*)(ws + p.f64);
+  int8_t* out = (int8_t*)(ws + p.out);
   const RnsMat L = rns_static(h->rns_lvo, N, d.naux);
   const int nb = cdiv(d.nv, PT);
   for (int r0 = 0; r0 < rows; r0 += p.c) {
@@ -1686,8 +1698,8 @@ static adc2_status rns_singles_in(adc2_handle h, const SigReq& rq, int with_d, R
     adc2_status rc = pf.run(4, [&]() -> adc2_status {
       RnsMat A;
       const RnsSrc x{h->X + (long)r0 * d.naux * d.nv, d.nv, (long)d.naux * d.nv, 1, 1 << 30, 0, d.nv, false};
-      adc2_status r = rns_pack(x, c * d.nv, d.naux, (int8_t*)(h->rns_ws + p.opnd), (int*)(h->rns_ws + p.ex),
-                               (double*)(h->rns_ws + p.norm), &A, st);
+      adc2_status r = rns_pack(x, c * d.nv, d.naux, (int8_t*)(ws + p.opnd), (int*)(ws + p.ex),
+                               (double*)(ws + p.norm), &A, st);
       const int ns = rns_long_splits(d.naux);
       if (r == ADC2_OK) r = rns_gemm(A, L, 0, N, ns, out, st);
       // Z[mI][j][a][b], rows (mI, a), columns (j, b)
@@ -1866,6 +1878,70 @@ static adc2_status grouped_gemm(int nreq, const SigReq* rq, const std::vector<ch
   return flush();
 }
 
+static adc2_status backc_launch(adc2_handle h, int m, hipStream_t st) {
+  const Dims& d = h->d;
+  const int rows = m * d.nc;
+  const int mr = thin_rows(d, rows) ? 0 : row_tile(rows);
+  const unsigned nblk = (unsigned)((long)(mr ? cdiv(rows, mr) : 1) * cdiv(d.nv, TN) * h->nsplit);
+  if (mr == 0) k_backc_thin<<<nblk, 256, 0, st>>>(h->Y, h->Lvv, rows, d.nv, d.naux, h->nsplit, h->part);
+  else if (mr == 32) k_backc<32><<<nblk, 256, 0, st>>>(h->Y, h->Lvv, rows, d.nv, d.naux, h->nsplit, h->part);
+  else if (mr == 48) k_backc<48><<<nblk, 256, 0, st>>>(h->Y, h->Lvv, rows, d.nv, d.naux, h->nsplit, h->part);
+  else k_backc<64><<<nblk, 256, 0, st>>>(h->Y, h->Lvv, rows, d.nv, d.naux, h->nsplit, h->part);
+  ADC2_CHECK_LAUNCH();
+  return ADC2_OK;
+}
+
+static adc2_status m11_launch(adc2_handle h, const SigReq& rq, hipStream_t st) {
+  const Dims& d = h->d;
+  k_m11_mv<<<dim3(cdiv(d.ns, 4 * MVR), cdiv(rq.m, MVM)), 256, 0, st>>>(h->M11, (int)d.ns, rq.xin, d.dim, rq.m, rq.sout);
+  ADC2_CHECK_LAUNCH();
+  return ADC2_OK;
+}
+
+static adc2_status finish_launch(adc2_handle h, const SigReq& rq, hipStream_t st) {
+  const Dims& d = h->d;
+  k_sigma1_finish<<<cdiv((long)rq.m * d.nc * d.nv, 64), 64 * FW, 0, st>>>(h->part, h->nsplit, h->Tp, rq.m, d.nc, d.no,
+                                                                          d.nv, d.dim, rq.sout);
+  ADC2_CHECK_LAUNCH();
+  return ADC2_OK;
+}
+
+// Small sigmas on the residue engine run their two halves side by side: the
+// doubles-in chain on the caller's stream, the singles-in chain on the handle's own,
+// between two events on the caller's stream, in two halves of the work space.  Each
+// chain is eight or nine launches that fill a part of the chip each.  Not under
+// capture and not while the kernels are timed.
+static bool overlap_wanted(adc2_handle h, const SigReq& rq, hipStream_t st) {
+  const int rows = rq.m * h->d.nc;
+  if (!h->side || h->rns_lent || !overlap_sized(h->d, rows) || h->profiling || !(rq.parts & SIGMA_SINGLES_IN) ||
+      !(rq.parts & SIGMA_DOUBLES_IN) || h->rns_ws_bytes < 2 * overlap_base(h, rows))
+    return false;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return cs == hipStreamCaptureStatusNone;
+}
+
+static adc2_status sigma_overlapped(adc2_handle h, const SigReq& rq, RnsProf& rp, hipStream_t st) {
+  const int rows = rq.m * h->d.nc;
+  ADC2_HIP(hipEventRecord(h->side_fork, st));
+  ADC2_HIP(hipStreamWaitEvent(h->side, h->side_fork, 0));
+  adc2_status rc = rns_doubles_in(h, rq, rp, st);
+  if (rc == ADC2_OK) rc = backc_launch(h, rq.m, st);
+  if (rc == ADC2_OK) rc = xbuild_launch(rq.xin, h->d, rows, h->Lvv, h->X, h->side);
+  if (rc == ADC2_OK) rc = rns_singles_in(h, rq, 1, rp, h->rns_ws + overlap_base(h, rows), h->side);
+  if (rc == ADC2_OK) rc = m11_launch(h, rq, h->side);
+  // joined whatever happened
+  if (hipEventRecord(h->side_join, h->side) != hipSuccess || hipStreamWaitEvent(st, h->side_join, 0) != hipSuccess) {
+    (void)hipStreamSynchronize(h->side);
+    set_error("adc2_sigma: the two halves could not be joined");
+    if (rc == ADC2_OK) rc = ADC2_ERR_HIP;
+  }
+  return rc == ADC2_OK ? finish_launch(h, rq, st) : rc;
+}
+
 // Several sigma requests (possibly of different systems) on one stream.  Each
 // phase runs for every request before the next phase; with more than one
 // request the two heavy GEMMs of the requests in the complex64 and split-BF16
@@ -1898,6 +1974,10 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
   for (int q = 0; q < nreq; ++q) {
     sgl[q] = (rq[q].parts & SIGMA_SINGLES_IN) != 0;
     dbl[q] = (rq[q].parts & SIGMA_DOUBLES_IN) != 0;
+  }
+  if (nreq == 1 && rns[0] && overlap_wanted(h0, rq[0], st)) {
+    if ((rc = sigma_overlapped(h0, rq[0], rp, st)) != ADC2_OK) return rc;
+    return h0->method == ADC2_METHOD_ADC2X ? adc2x_apply(h0, rq[0].m, rq[0].xin, rq[0].sout, st) : ADC2_OK;
   }
   // precision forms that have a grouped GEMM and more than one request
   auto grouped = [&](const std::vector<char>& use, int prec) {
@@ -1982,7 +2062,7 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
     const Dims& d = h->d;
     const int rows = rq[q].m * d.nc;
     if (rns[q]) {
-      if ((rc = rns_singles_in(h, rq[q], dbl[q] ? 1 : 0, rp, st)) != ADC2_OK) return rc;
+      if ((rc = rns_singles_in(h, rq[q], dbl[q] ? 1 : 0, rp, h->rns_ws, st)) != ADC2_OK) return rc;
       continue;
     }
     if (h->prec != ADC2_FP64) {
@@ -2028,16 +2108,7 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
   if ((rc = mark(6)) != ADC2_OK) return rc;
   for (int q = 0; q < nreq; ++q) {
     if (!dbl[q]) continue;
-    adc2_handle h = rq[q].h;
-    const Dims& d = h->d;
-    const int rows = rq[q].m * d.nc;
-    const int mr = thin_rows(d, rows) ? 0 : row_tile(rows);
-    const unsigned nblk = (unsigned)((long)(mr ? cdiv(rows, mr) : 1) * cdiv(d.nv, TN) * h->nsplit);
-    if (mr == 0) k_backc_thin<<<nblk, 256, 0, st>>>(h->Y, h->Lvv, rows, d.nv, d.naux, h->nsplit, h->part);
-    else if (mr == 32) k_backc<32><<<nblk, 256, 0, st>>>(h->Y, h->Lvv, rows, d.nv, d.naux, h->nsplit, h->part);
-    else if (mr == 48) k_backc<48><<<nblk, 256, 0, st>>>(h->Y, h->Lvv, rows, d.nv, d.naux, h->nsplit, h->part);
-    else k_backc<64><<<nblk, 256, 0, st>>>(h->Y, h->Lvv, rows, d.nv, d.naux, h->nsplit, h->part);
-    ADC2_CHECK_LAUNCH();
+    if ((rc = backc_launch(rq[q].h, rq[q].m, st)) != ADC2_OK) return rc;
   }
   if ((rc = mark(7)) != ADC2_OK) return rc;
   for (int q = 0; q < nreq; ++q) {
@@ -2045,19 +2116,12 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
     const Dims& d = h->d;
     const int m = rq[q].m;
     if (sgl[q]) {
-      k_m11_mv<<<dim3(cdiv(d.ns, 4 * MVR), cdiv(m, MVM)), 256, 0, st>>>(h->M11, (int)d.ns, rq[q].xin, d.dim, m,
-                                                                       rq[q].sout);
-      ADC2_CHECK_LAUNCH();
+      if ((rc = m11_launch(h, rq[q], st)) != ADC2_OK) return rc;
     } else {
       k_zero_singles<<<grid_for(d.ns * m), 256, 0, st>>>(rq[q].sout, d.dim, d.ns, m);
       ADC2_CHECK_LAUNCH();
     }
-    if (dbl[q]) {
-      const int rows = m * d.nc;
-      k_sigma1_finish<<<cdiv((long)rows * d.nv, 64), 64 * FW, 0, st>>>(h->part, h->nsplit, h->Tp, m, d.nc, d.no, d.nv,
-                                                                       d.dim, rq[q].sout);
-      ADC2_CHECK_LAUNCH();
-    }
+    if (dbl[q] && (rc = finish_launch(h, rq[q], st)) != ADC2_OK) return rc;
   }
   if ((rc = mark(8)) != ADC2_OK) return rc;
   // ADC(2)-x: the first-order doubles block (FP64), on whole sigma requests only
@@ -2213,6 +2277,7 @@ extern "C" adc2_status adc2_sigma_noalloc(adc2_handle h, int m, const void* X, v
   h->part = take(p.part);
   if (rns) {
     h->rns_ws = reinterpret_cast<char*>(q);
+    h->rns_lent = true;
     h->rns_target = h->rns_ws_bytes = NOALLOC_SCRATCH_BYTES - (size_t)(q - static_cast<unsigned char*>(base));
   }
   h->ws_m = h->zb_m = m;
@@ -2220,6 +2285,7 @@ extern "C" adc2_status adc2_sigma_noalloc(adc2_handle h, int m, const void* X, v
   h->nsplit = p.nsplit;
   const SigReq rq{h, m, static_cast<const double2*>(X), static_cast<double2*>(S), SIGMA_SINGLES_IN | SIGMA_DOUBLES_IN};
   rc = sigma_multi(1, &rq, static_cast<hipStream_t>(stream), rns);
+  h->rns_lent = false;
   h->rns_ws = sws_rns;
   h->rns_ws_bytes = swsb;
   h->rns_target = starget;

@@ -661,6 +661,7 @@ bool rns_pays(adc2_handle h, long M, long N, long K, double rate) {
 static bool rns_grow(adc2_handle h, char** buf, size_t* have, size_t bytes) {
   if (h->rns_off) return false;
   if (*have >= bytes) return true;
+  if (h->rns_lent) return false;
   if (bytes > (size_t(256) << 20)) bytes = (bytes + (size_t(512) << 20) - 1) >> 29 << 29;   // few sizes: blocks are reused
   char* old = *buf;
   *buf = nullptr;

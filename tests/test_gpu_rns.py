@@ -154,6 +154,33 @@ def test_batch_and_graph_replays_equal_separate(monkeypatch):
         h.close()
 
 
+@pytest.mark.parametrize("nc,no,nv,naux,m", [(2, 3, 21, 40, 1), (6, 12, 60, 200, 3)])
+def test_halves_side_by_side(nc, no, nv, naux, m, monkeypatch):
+    """Small sigmas run their halves on two streams; timed kernels and
+    adc2_sigma_noalloc run them one after the other.  The same bits, call after
+    call without a wait between them, on the default stream and another."""
+    monkeypatch.setenv("ADC2_ZGEMM", "rns")
+    s = make_system(nc, no, nv, naux, seed=961)
+    h = handle(s)
+    xs = [dev(random_vectors(40 + k, m, h.dim)) for k in range(6)]
+    A.adc2_profile(h, True)
+    want = [A.adc2_sigma(h, x) for x in xs]
+    A.adc2_profile(h, False)
+    print(f"[case] rns halves {(nc, no, nv, naux)} m={m}", flush=True)
+    for st in (None, torch.cuda.Stream()):
+        with torch.cuda.stream(st) if st else torch.cuda.stream(torch.cuda.default_stream()):
+            if st:
+                st.wait_stream(torch.cuda.default_stream())
+            got = [A.adc2_sigma(h, x) for _ in range(4) for x in xs]
+        torch.cuda.synchronize()
+        assert all(torch.equal(g, want[k % 6]) for k, g in enumerate(got))
+    S = torch.empty_like(xs[0])
+    A.adc2_sigma_noalloc(h, xs[0], S)
+    torch.cuda.synchronize()
+    assert torch.equal(S, want[0])
+    h.close()
+
+
 def test_without_its_memory_the_mfma_engine_serves(monkeypatch):
     """An allocator that refuses the engine's own buffers: the doubles are bit
     for bit those of the FP64 MFMA engine (the singles hold M11, which the two

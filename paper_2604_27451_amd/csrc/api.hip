@@ -416,7 +416,7 @@ adc2_status adc2_setup(const void* L, const double* eps, int nc, int no, int nv,
   rc = build_m11(h, st);
   if (rc == ADC2_OK) rc = build_lvt(h, st);
   if (rc == ADC2_OK) rc = rns_build_static(h, true, st);
-  if (rc == ADC2_OK && h->rns_setup &&
+  if (rc == ADC2_OK &&
       (hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking) != hipSuccess ||
        hipEventCreateWithFlags(&h->side_fork, hipEventDisableTiming) != hipSuccess ||
        hipEventCreateWithFlags(&h->side_join, hipEventDisableTiming) != hipSuccess))

@@ -108,7 +108,7 @@ struct adc2_handle_s {
   char* rns_ws = nullptr;
   size_t rns_ws_bytes = 0;
   bool rns_lent = false;    // rns_ws is adc2_sigma_noalloc's array: neither grown nor freed
-  hipStream_t side = nullptr;   // small sigmas: the singles-in half (with the residue engine's operands at setup)
+  hipStream_t side = nullptr;   // one half of a sigma (small ones), X-build and back-contraction (large ones)
   hipEvent_t side_fork = nullptr, side_join = nullptr;
   bool rns_setup = false;   // the static operands were built by adc2_setup
   char* rns_tmp = nullptr;  // work space of the general products, held during an entry point

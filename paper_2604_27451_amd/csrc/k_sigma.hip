@@ -1911,10 +1911,9 @@ static adc2_status finish_launch(adc2_handle h, const SigReq& rq, hipStream_t st
 // between two events on the caller's stream, in two halves of the work space.  Each
 // chain is eight or nine launches that fill a part of the chip each.  Not under
 // capture and not while the kernels are timed.
-static bool overlap_wanted(adc2_handle h, const SigReq& rq, hipStream_t st) {
-  const int rows = rq.m * h->d.nc;
-  if (!h->side || h->rns_lent || !overlap_sized(h->d, rows) || h->profiling || !(rq.parts & SIGMA_SINGLES_IN) ||
-      !(rq.parts & SIGMA_DOUBLES_IN) || h->rns_ws_bytes < 2 * overlap_base(h, rows))
+// Whether a request may use the handle's second stream.
+static bool side_wanted(adc2_handle h, const SigReq& rq, hipStream_t st) {
+  if (!h->side || h->rns_lent || h->profiling || !(rq.parts & SIGMA_SINGLES_IN) || !(rq.parts & SIGMA_DOUBLES_IN))
     return false;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
@@ -1975,7 +1974,9 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
     sgl[q] = (rq[q].parts & SIGMA_SINGLES_IN) != 0;
     dbl[q] = (rq[q].parts & SIGMA_DOUBLES_IN) != 0;
   }
-  if (nreq == 1 && rns[0] && overlap_wanted(h0, rq[0], st)) {
+  const bool side = nreq == 1 && side_wanted(h0, rq[0], st);
+  if (side && rns[0] && overlap_sized(h0->d, rq[0].m * h0->d.nc) &&
+      h0->rns_ws_bytes >= 2 * overlap_base(h0, rq[0].m * h0->d.nc)) {
     if ((rc = sigma_overlapped(h0, rq[0], rp, st)) != ADC2_OK) return rc;
     return h0->method == ADC2_METHOD_ADC2X ? adc2x_apply(h0, rq[0].m, rq[0].xin, rq[0].sout, st) : ADC2_OK;
   }
@@ -1988,6 +1989,24 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
   };
   auto is_grouped = [&](int q) { return nreq > 1 && rq[q].h->prec != ADC2_FP64; };
 
+  // One large request: X-build and back-contraction on the handle's stream, beside the products of
+  // the other half (no=45 nv=310, seven vectors: 24.0 -> 23.5 ms; split-BF16, no=60 nv=300, ten: 25.1
+  // -> 24.1).  Not in complex64, whose products leave the matrix cores no room (24.8 -> 25.1).
+  const bool aside = side && h0->prec != ADC2_C64;
+  struct Joined {   // an error between fork and join: waited for before the caller's vectors go
+    hipStream_t s;
+    ~Joined() {
+      if (s) (void)hipStreamSynchronize(s);
+    }
+  } joined{aside ? h0->side : nullptr};
+  if (aside) {
+    ADC2_HIP(hipEventRecord(h0->side_fork, st));
+    ADC2_HIP(hipStreamWaitEvent(h0->side, h0->side_fork, 0));
+    rc = h0->prec != ADC2_FP64 ? xbuild_launch(rq[0].xin, h0->d, rq[0].m * h0->d.nc, h0->Lvv, (float2*)h0->X, h0->side)
+                               : xbuild_launch(rq[0].xin, h0->d, rq[0].m * h0->d.nc, h0->Lvv, h0->X, h0->side);
+    ADC2_HIP(hipEventRecord(h0->side_join, h0->side));
+    if (rc != ADC2_OK) return rc;
+  }
   // kernel order (profiling slots): unpack, ygemm, light1, xbuild, zsig2, pack2, backc, m11mv+finish
   for (int q = 0; q < nreq; ++q)
     if (rns[q] && dbl[q] && (rc = rns_doubles_in(rq[q].h, rq[q], rp, st)) != ADC2_OK) return rc;
@@ -2036,8 +2055,16 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
     ADC2_CHECK_LAUNCH();
   }
   if ((rc = mark(3)) != ADC2_OK) return rc;
+  if (aside) {
+    ADC2_HIP(hipStreamWaitEvent(st, h0->side_join, 0));
+    ADC2_HIP(hipEventRecord(h0->side_fork, st));
+    ADC2_HIP(hipStreamWaitEvent(h0->side, h0->side_fork, 0));
+    rc = backc_launch(h0, rq[0].m, h0->side);
+    ADC2_HIP(hipEventRecord(h0->side_join, h0->side));
+    if (rc != ADC2_OK) return rc;
+  }
   for (int q = 0; q < nreq; ++q) {
-    if (!sgl[q]) continue;
+    if (!sgl[q] || aside) continue;
     adc2_handle h = rq[q].h;
     const Dims& d = h->d;
     const int rows = rq[q].m * d.nc;
@@ -2106,8 +2133,12 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
     ADC2_CHECK_LAUNCH();
   }
   if ((rc = mark(6)) != ADC2_OK) return rc;
+  if (aside) {
+    ADC2_HIP(hipStreamWaitEvent(st, h0->side_join, 0));
+    joined.s = nullptr;
+  }
   for (int q = 0; q < nreq; ++q) {
-    if (!dbl[q]) continue;
+    if (!dbl[q] || aside) continue;
     if ((rc = backc_launch(rq[q].h, rq[q].m, st)) != ADC2_OK) return rc;
   }
   if ((rc = mark(7)) != ADC2_OK) return rc;

@@ -154,14 +154,17 @@ def test_batch_and_graph_replays_equal_separate(monkeypatch):
         h.close()
 
 
-@pytest.mark.parametrize("nc,no,nv,naux,m", [(2, 3, 21, 40, 1), (6, 12, 60, 200, 3)])
-def test_halves_side_by_side(nc, no, nv, naux, m, monkeypatch):
-    """Small sigmas run their halves on two streams; timed kernels and
-    adc2_sigma_noalloc run them one after the other.  The same bits, call after
+@pytest.mark.parametrize("nc,no,nv,naux,m,prec", [(2, 3, 21, 40, 1, A.ADC2_FP64), (6, 12, 60, 200, 3, A.ADC2_FP64),
+                                                  (6, 30, 160, 500, 6, A.ADC2_FP64), (3, 6, 50, 70, 2, A.ADC2_BF16X3),
+                                                  (3, 6, 50, 70, 2, A.ADC2_C64)])
+def test_halves_side_by_side(nc, no, nv, naux, m, prec, monkeypatch):
+    """Small sigmas run their halves on two streams, large ones X-build and
+    back-contraction (the third case is above the 10^10 terms between them);
+    timed kernels and adc2_sigma_noalloc use one.  The same bits, call after
     call without a wait between them, on the default stream and another."""
     monkeypatch.setenv("ADC2_ZGEMM", "rns")
     s = make_system(nc, no, nv, naux, seed=961)
-    h = handle(s)
+    h = handle(s, prec=prec)
     xs = [dev(random_vectors(40 + k, m, h.dim)) for k in range(6)]
     A.adc2_profile(h, True)
     want = [A.adc2_sigma(h, x) for x in xs]
@@ -174,10 +177,11 @@ def test_halves_side_by_side(nc, no, nv, naux, m, monkeypatch):
             got = [A.adc2_sigma(h, x) for _ in range(4) for x in xs]
         torch.cuda.synchronize()
         assert all(torch.equal(g, want[k % 6]) for k, g in enumerate(got))
-    S = torch.empty_like(xs[0])
-    A.adc2_sigma_noalloc(h, xs[0], S)
-    torch.cuda.synchronize()
-    assert torch.equal(S, want[0])
+    if prec == A.ADC2_FP64 and nv < 100:
+        S = torch.empty_like(xs[0])
+        A.adc2_sigma_noalloc(h, xs[0], S)
+        torch.cuda.synchronize()
+        assert torch.equal(S, want[0])
     h.close()
 
 

@@ -1911,10 +1911,9 @@ static adc2_status finish_launch(adc2_handle h, const SigReq& rq, hipStream_t st
 // between two events on the caller's stream, in two halves of the work space.  Each
 // chain is eight or nine launches that fill a part of the chip each.  Not under
 // capture and not while the kernels are timed.
-// Whether a request may use the handle's second stream.
-static bool side_wanted(adc2_handle h, const SigReq& rq, hipStream_t st) {
-  if (!h->side || h->rns_lent || h->profiling || !(rq.parts & SIGMA_SINGLES_IN) || !(rq.parts & SIGMA_DOUBLES_IN))
-    return false;
+// Whether requests may use the first handle's second stream.
+static bool side_free(adc2_handle h, hipStream_t st) {
+  if (!h->side || h->rns_lent || h->profiling) return false;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
     (void)hipGetLastError();
@@ -1974,8 +1973,8 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
     sgl[q] = (rq[q].parts & SIGMA_SINGLES_IN) != 0;
     dbl[q] = (rq[q].parts & SIGMA_DOUBLES_IN) != 0;
   }
-  const bool side = nreq == 1 && side_wanted(h0, rq[0], st);
-  if (side && rns[0] && overlap_sized(h0->d, rq[0].m * h0->d.nc) &&
+  const bool side = side_free(h0, st), whole = nreq == 1 && sgl[0] && dbl[0];
+  if (side && whole && rns[0] && overlap_sized(h0->d, rq[0].m * h0->d.nc) &&
       h0->rns_ws_bytes >= 2 * overlap_base(h0, rq[0].m * h0->d.nc)) {
     if ((rc = sigma_overlapped(h0, rq[0], rp, st)) != ADC2_OK) return rc;
     return h0->method == ADC2_METHOD_ADC2X ? adc2x_apply(h0, rq[0].m, rq[0].xin, rq[0].sout, st) : ADC2_OK;
@@ -1989,24 +1988,54 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
   };
   auto is_grouped = [&](int q) { return nreq > 1 && rq[q].h->prec != ADC2_FP64; };
 
-  // One large request: X-build and back-contraction on the handle's stream, beside the products of
-  // the other half (no=45 nv=310, seven vectors: 24.0 -> 23.5 ms; split-BF16, no=60 nv=300, ten: 25.1
-  // -> 24.1).  Not in complex64, whose products leave the matrix cores no room (24.8 -> 25.1).
-  const bool aside = side && h0->prec != ADC2_C64;
+  // X-build and back-contraction on the first handle's stream.  ASIDE (one whole request): beside the
+  // products of the other half (no=45 nv=310, seven vectors: 24.0 -> 23.5 ms; split-BF16, no=60
+  // nv=300, ten: 25.1 -> 24.1).  BESIDE (complex64, whose products leave the matrix cores no room:
+  // 24.8 -> 25.1 aside; and batches of the precision forms): only beside the unpacking and the
+  // packing (eight systems at once: 19.9 -> 19.5 ms; one: 24.8 -> 24.7).
+  bool prec_all = true;
+  for (int q = 0; q < nreq; ++q) prec_all = prec_all && rq[q].h->prec != ADC2_FP64;
+  enum { SERIAL, ASIDE, BESIDE };
+  const int how = !side ? SERIAL
+                  : whole && h0->prec != ADC2_C64 ? ASIDE
+                  : (whole || nreq > 1) && prec_all ? BESIDE : SERIAL;
   struct Joined {   // an error between fork and join: waited for before the caller's vectors go
     hipStream_t s;
     ~Joined() {
       if (s) (void)hipStreamSynchronize(s);
     }
-  } joined{aside ? h0->side : nullptr};
-  if (aside) {
+  } joined{how != SERIAL ? h0->side : nullptr};
+  auto xbuild_all = [&](hipStream_t on) -> adc2_status {
+    for (int q = 0; q < nreq; ++q) {
+      if (!sgl[q]) continue;
+      adc2_handle h = rq[q].h;
+      const int rows = rq[q].m * h->d.nc;
+      const adc2_status r = h->prec != ADC2_FP64 ? xbuild_launch(rq[q].xin, h->d, rows, h->Lvv, (float2*)h->X, on)
+                                                 : xbuild_launch(rq[q].xin, h->d, rows, h->Lvv, h->X, on);
+      if (r != ADC2_OK) return r;
+    }
+    return ADC2_OK;
+  };
+  auto backc_all = [&](hipStream_t on) -> adc2_status {
+    for (int q = 0; q < nreq; ++q)
+      if (dbl[q]) {
+        const adc2_status r = backc_launch(rq[q].h, rq[q].m, on);
+        if (r != ADC2_OK) return r;
+      }
+    return ADC2_OK;
+  };
+  auto fork = [&](auto&& work) -> adc2_status {   // after what the stream holds so far
     ADC2_HIP(hipEventRecord(h0->side_fork, st));
     ADC2_HIP(hipStreamWaitEvent(h0->side, h0->side_fork, 0));
-    rc = h0->prec != ADC2_FP64 ? xbuild_launch(rq[0].xin, h0->d, rq[0].m * h0->d.nc, h0->Lvv, (float2*)h0->X, h0->side)
-                               : xbuild_launch(rq[0].xin, h0->d, rq[0].m * h0->d.nc, h0->Lvv, h0->X, h0->side);
+    const adc2_status r = work(h0->side);
     ADC2_HIP(hipEventRecord(h0->side_join, h0->side));
-    if (rc != ADC2_OK) return rc;
-  }
+    return r;
+  };
+  auto join = [&]() -> adc2_status {
+    ADC2_HIP(hipStreamWaitEvent(st, h0->side_join, 0));
+    return ADC2_OK;
+  };
+  if (how != SERIAL && (rc = fork(xbuild_all)) != ADC2_OK) return rc;
   // kernel order (profiling slots): unpack, ygemm, light1, xbuild, zsig2, pack2, backc, m11mv+finish
   for (int q = 0; q < nreq; ++q)
     if (rns[q] && dbl[q] && (rc = rns_doubles_in(rq[q].h, rq[q], rp, st)) != ADC2_OK) return rc;
@@ -2035,6 +2064,7 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
         ADC2_OK)
       return rc;
   }
+  if (how == BESIDE && (rc = join()) != ADC2_OK) return rc;
   if ((rc = mark(1)) != ADC2_OK) return rc;
   for (int prec : {ADC2_C64, ADC2_BF16X3})
     if (grouped(dbl, prec) && (rc = grouped_gemm(nreq, rq, dbl, prec, true, st)) != ADC2_OK) return rc;
@@ -2055,23 +2085,8 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
     ADC2_CHECK_LAUNCH();
   }
   if ((rc = mark(3)) != ADC2_OK) return rc;
-  if (aside) {
-    ADC2_HIP(hipStreamWaitEvent(st, h0->side_join, 0));
-    ADC2_HIP(hipEventRecord(h0->side_fork, st));
-    ADC2_HIP(hipStreamWaitEvent(h0->side, h0->side_fork, 0));
-    rc = backc_launch(h0, rq[0].m, h0->side);
-    ADC2_HIP(hipEventRecord(h0->side_join, h0->side));
-    if (rc != ADC2_OK) return rc;
-  }
-  for (int q = 0; q < nreq; ++q) {
-    if (!sgl[q] || aside) continue;
-    adc2_handle h = rq[q].h;
-    const Dims& d = h->d;
-    const int rows = rq[q].m * d.nc;
-    rc = h->prec != ADC2_FP64 ? xbuild_launch(rq[q].xin, d, rows, h->Lvv, (float2*)h->X, st)
-                              : xbuild_launch(rq[q].xin, d, rows, h->Lvv, h->X, st);
-    if (rc != ADC2_OK) return rc;
-  }
+  if (how == ASIDE && ((rc = join()) != ADC2_OK || (rc = fork(backc_all)) != ADC2_OK)) return rc;
+  if (how == SERIAL && (rc = xbuild_all(st)) != ADC2_OK) return rc;
   for (int q = 0; q < nreq; ++q) {   // split-BF16: X into the blocked split layout
     adc2_handle h = rq[q].h;
     if (!sgl[q] || h->prec != ADC2_BF16X3) continue;
@@ -2115,6 +2130,7 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
     }
     ADC2_CHECK_LAUNCH();
   }
+  if (how == BESIDE && (rc = fork(backc_all)) != ADC2_OK) return rc;
   if ((rc = mark(5)) != ADC2_OK) return rc;
   for (int q = 0; q < nreq; ++q) {
     if (!sgl[q] || rns[q]) continue;
@@ -2133,14 +2149,8 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
     ADC2_CHECK_LAUNCH();
   }
   if ((rc = mark(6)) != ADC2_OK) return rc;
-  if (aside) {
-    ADC2_HIP(hipStreamWaitEvent(st, h0->side_join, 0));
-    joined.s = nullptr;
-  }
-  for (int q = 0; q < nreq; ++q) {
-    if (!dbl[q] || aside) continue;
-    if ((rc = backc_launch(rq[q].h, rq[q].m, st)) != ADC2_OK) return rc;
-  }
+  if ((rc = how == SERIAL ? backc_all(st) : join()) != ADC2_OK) return rc;
+  joined.s = nullptr;
   if ((rc = mark(7)) != ADC2_OK) return rc;
   for (int q = 0; q < nreq; ++q) {
     adc2_handle h = rq[q].h;

@@ -58,10 +58,14 @@ typedef enum {
 
 typedef enum {
   ADC2_FP64 = 0,               /* complex FP64 contractions: the large ones as exact
-                                  integer products on the INT8 MFMA (operands
-                                  rounded at 2^-58 of their row norm; errors below
-                                  the FP64 MFMA's), the smallest and those without
-                                  the memory for it on the FP64 MFMA             */
+                                  integer products on the INT8 MFMA, operands
+                                  rounded at 2^-58.3 of the norm of their row, where
+                                  that is no more than a FP64 sum would be off
+                                  (every entry is looked at: sum |a_k| |b_k| at
+                                  least a tenth of ||a|| ||b||, or no common
+                                  terms); the other entries, the smallest
+                                  products and those without the memory for it
+                                  on the FP64 MFMA                               */
   ADC2_C64 = 1                 /* precision form: the two heavy sigma
                                   contractions on complex64 operands with the
                                   FP32 MFMA and FP32 accumulation; setup,

@@ -775,6 +775,30 @@ __global__ void k_xcore(const double2* __restrict__ W, int o, int nv, double2* _
     x[e] = I == k ? czero() : (I < k ? w[e] : cneg(w[e]));
 }
 
+// PQG[(J,b)][(k,c)] += 1/4 sum_I Gamma'[I][J] X[I][k][b][c] (blockIdx.y = k): the part of (13)
+// on the diagonal a = b of Gc.  HBM-bound: one read of X, one pass over PQG for each eight cores
+__global__ void k_core_diag_add(const double2* __restrict__ X, const double2* __restrict__ Gp, int nc, int o, int nv,
+                                double2* __restrict__ PQG) {
+  const int k = blockIdx.y;
+  const long nv2 = (long)nv * nv;
+  for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < nv2; e += (long)gridDim.x * blockDim.x) {
+    const int b = (int)(e / nv), c = (int)(e - (long)b * nv);
+    for (int I0 = 0; I0 < nc; I0 += 8) {
+      double2 x[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) x[q] = I0 + q < nc ? X[((long)(I0 + q) * o + k) * nv2 + e] : czero();
+      for (int J = 0; J < nc; ++J) {
+        double2 v = czero();
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+          if (I0 + q < nc) v = cadd(v, cmul(Gp[(I0 + q) * nc + J], x[q]));
+        double2* p = PQG + (((long)J * nv + b) * o + k) * nv + c;
+        *p = cadd(*p, cscale(v, 0.25));
+      }
+    }
+  }
+}
+
 // Ef[k][k] = 0
 __global__ void k_zero_diag_blocks(double2* __restrict__ Ef, int o, int nv) {
   const long nv2 = (long)nv * nv;
@@ -1110,15 +1134,20 @@ adc2_status omega_backward(adc2_handle h, int m, const double2* X, const double*
     BW_TRY(fgemm(nv, (int)(2 * npairs * nv), nv, 1, SrcGam4{Gam, nv}, SrcWT{WT, nv}, EpPQ{PQ, nv}, S, st));
     BW_TRY(alloc((void**)&Ef, sizeof(double2) * (long)o * o * nv2));
     // (13) on the residue engine with the rows of X^h laid out in Ef, which is filled only after
-    // (50 TFLOP/s of the general product, 7.6 ms at nc=6 no=35 nv=250; 2.0 ms here)
+    // (50 TFLOP/s of the general product, 7.6 ms at nc=6 no=35 nv=250; 2.0 ms here), the diagonal
+    // Gamma' of Gc, which far exceeds the rest of its rows, apart (as one operand every 64 x 64
+    // tile had entries that the integers do not serve)
     done = false;
     for (int hh = 0; hh < 2; ++hh) {
       if (hh == 0 && ((long)nc * o > 65535 || !rns_pays(h, ns, (long)o * nv, ns, 50e12))) break;
       k_xcore<<<dim3(grid1(nv2, 256, 64), (unsigned)(nc * o)), 256, 0, st>>>(WT + hh * npairs * nv2, o, nv, Ef);
       BW_HIP(hipGetLastError());
-      BW_TRY(rns_product(h, rns_kmajor(Gc, ns, (int)ns), (int)ns, RnsSrc{Ef, nv, nv2, 1, nv, (long)o * nv2, nv, false},
-                         o * nv, (int)ns, rns_rows(PQG + (long)hh * ns * o * nv, (long)o * nv), 0.0, &done, st));
+      BW_TRY(rns_product(h, rns_kmajor(gam, ns, (int)ns), (int)ns, RnsSrc{Ef, nv, nv2, 1, nv, (long)o * nv2, nv, false},
+                         o * nv, (int)ns, rns_rows(PQG + (long)hh * ns * o * nv, (long)o * nv, -0.5), 0.0, &done, st));
       if (!done) break;
+      k_core_diag_add<<<dim3(grid1(nv2, 256, 64), (unsigned)o), 256, 0, st>>>(Ef, Gp, nc, o, nv,
+                                                                              PQG + (long)hh * ns * o * nv);
+      BW_HIP(hipGetLastError());
     }
     if (!done)
       BW_TRY(fgemm((int)ns, o * nv, (int)ns, 2, SrcMatK{Gc, ns}, SrcWcore{WT, npairs, nv, o},

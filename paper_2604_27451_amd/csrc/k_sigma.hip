@@ -1594,8 +1594,9 @@ static adc2_status rns_ready(adc2_handle h, int m, hipStream_t st, bool* ok) {
   return ADC2_OK;
 }
 
-static RnsMat rns_static(char* mem, long rows, long K) {
+static RnsMat rns_static(char* mem, long rows, long K, const RnsSrc& src) {
   RnsMat a;
+  a.src = src;
   a.p = (int8_t*)mem;
   a.e = (int*)(mem + rns_op_bytes(rows, K));
   a.rows = (int)rows;
@@ -1650,7 +1651,7 @@ static adc2_status rns_doubles_in(adc2_handle h, const SigReq& rq, RnsProf& pf, 
   const RnsPlan p = rns_plan(h, rows);
   double2* R = (double2*)(h->rns_ws + p.f64);
   int8_t* out = (int8_t*)(h->rns_ws + p.out);
-  const RnsMat L = rns_static(h->rns_lvt, d.naux, K);
+  const RnsMat L = rns_static(h->rns_lvt, d.naux, K, rns_kmajor(h->LvT, d.naux, K));
   const int nb = cdiv(d.nv, UT);
   for (int r0 = 0; r0 < rows; r0 += p.c) {
     const int c = std::min(p.c, rows - r0);
@@ -1691,7 +1692,7 @@ static adc2_status rns_singles_in(adc2_handle h, const SigReq& rq, int with_d, R
   const RnsPlan p = rns_plan(h, rows);
   double2* Z = (double2*)(ws + p.f64);
   int8_t* out = (int8_t*)(ws + p.out);
-  const RnsMat L = rns_static(h->rns_lvo, N, d.naux);
+  const RnsMat L = rns_static(h->rns_lvo, N, d.naux, rns_lvo_rows(h));
   const int nb = cdiv(d.nv, PT);
   for (int r0 = 0; r0 < rows; r0 += p.c) {
     const int c = std::min(p.c, rows - r0);

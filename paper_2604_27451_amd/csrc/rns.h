@@ -2,10 +2,10 @@
 // through residues modulo 16 small moduli.
 //
 // C[i][j] = sum_k A(k, i) B(k, j) for complex128 A, B.  Each operand row is
-// scaled by a power of two, 2^e with ||row|| 2^e <= 2^58, and rounded to
+// scaled by a power of two, 2^e with ||row|| 2^e <= 2^58.33, and rounded to
 // Gaussian integers; the product of two such rows is then a Gaussian integer z
-// with |z| <= 2^116 (Cauchy-Schwarz), which its residues modulo
-// M = prod p_i > 2^117 determine.  Every p_i is a product of primes = 1 mod 4,
+// with |z| <= 2^116.66 (Cauchy-Schwarz), which its residues modulo
+// M = prod p_i > 2^117.6 determine.  Every p_i is a product of primes = 1 mod 4,
 // so -1 has a square root s_i modulo p_i and the map
 //   x + iy -> (x + s_i y, x - s_i y) mod p_i
 // turns one complex product into two real ones: 32 real INT8 products
@@ -13,13 +13,29 @@
 // The Chinese remainder theorem recovers z.  INT8 MFMA runs at 64 times the
 // FP64 MFMA rate, and 32 / 4 = 8 INT8 multiply-adds replace each FP64 one.
 //
-// Precision.  The integer products are exact, so the only errors are the
-// rounding of the operands, at most 2^-58 ||row|| sqrt(1/2) per entry (for rows
-// of K like entries 2^-58 sqrt(2K) of an entry), and the final rounding to
-// FP64.  Normwise this is below the accumulation error of the FP64 matrix
-// cores at every K (the error per product is sqrt(K) 2^-58 ||a|| ||b||, that
-// of a K-term FP64 sum of random signs about 0.2 sqrt(K) 2^-53 |a.b|).  The
-// result does not depend on tiles, chunks or the order of summation.
+// Precision.  The integer products are exact.  The errors are the rounding of
+// the operands, at most 2^-58.33 ||row|| in the real and the imaginary part of an
+// entry (||row|| 2^e lies in (2^57.33, 2^58.33], e being whole), that is about
+// 2^-59 ||a|| ||b|| rms in a product whatever K; the FP64 sum of the parts below
+// 2^-34 in the recombination, 2^-58 ||a|| ||b|| (times the number of K-runs, in
+// the worst case); and the final rounding to FP64.
+//
+// A rounding set by the norm of the row is a loss where the large entries of one
+// row meet small ones of the other (rows that are graded, or that share only their
+// small entries): the FP64 sum is off by about 2^-54 of sum |a_k| |b_k|, which may be far
+// below ||a|| ||b||.  So one more plane holds a code of each entry's magnitude, 16 at
+// the rms of its row, 1 to 127, 0 for an exact zero, and its products S bound
+// that sum from below: codes exceed the scaled magnitudes only where these are
+// below 1, which adds at most 32 K to S, so S >= RNS_SPREAD K = 57.6 K means
+//   sum |a_k| |b_k| >= (57.6 - 32.1) / 256 ||a|| ||b|| = 0.1 ||a|| ||b||,
+// down to which the FP64 sum's error is the larger one (0.4 2^-54 sum |a_k| |b_k|
+// against 2^-59 ||a|| ||b||).  Rows of like entries reach 187 K.  S = 0 means disjoint
+// rows: an exact zero on either engine (rows of blocks of a symmetry).  The
+// entries between, and those of rows that are not finite, are formed in FP64 by k_rns_fp64
+// (which ends at once where there are none); which they are depends on the two rows
+// and the K-splits alone, not on tiles or chunks.  The codes are one INT8 product
+// more to the 32 and a launch (nc=6 no=60 nv=300 naux=1500, ten vectors: 45.3 -> 46.9 ms;
+// the smallest sigma 106 -> 112 us).
 //
 // Measured against long double (nc=6 no=60 nv=300 naux=1500, a unit vector on a
 // singles entry, so that every doubles entry is one K = 1500 product): rms error
@@ -31,29 +47,21 @@
 // product of M=3072, N=9000, K=18000 at 2338, as 292 TFLOP/s of complex products; the
 // FP64 MFMA engine reaches 67.
 //
-// Rows with NaN or Inf give NaN in every product with them; rows of zeros
-// give exact zeros.
+// Rows with NaN or Inf give what the FP64 sum gives (NaN against rows of zeros);
+// rows of zeros give exact zeros.
 #pragma once
 #include "internal.h"
 
 namespace adc2 {
 
 constexpr int RNS_NM = 16;              // moduli
-constexpr int RNS_PL = 2 * RNS_NM;      // planes
+constexpr int RNS_PL = 2 * RNS_NM;      // residue planes
+constexpr int RNS_NP = RNS_PL + 1;      // planes held: the last one the magnitude codes
 constexpr int RNS_RT = 128;             // rows per operand block
 constexpr int RNS_KC = 64;              // k per operand block
 constexpr int RNS_BLK = RNS_RT * RNS_KC;
-constexpr long RNS_KMAX = 131072;       // K 121^2 < 2^31
+constexpr long RNS_KMAX = 131072;       // K 121^2 and K 127^2 < 2^31
 
-// An operand in residues.  Plane q (modulus q / 2, sign q % 2), row block rt,
-// k block kc is the 8 KB run at ((q * nrt + rt) * nkc + kc) * RNS_BLK, laid
-// out [row / 16][k / 16][row % 16][k % 16]: the LDS image of the GEMM, in which a
-// 16 x 64 fragment is 1 KB in lane order.
-struct RnsMat {
-  int8_t* p = nullptr;
-  int* e = nullptr;        // row exponents (RNS_NAN: a row that is not finite)
-  int rows = 0, K = 0, nrt = 0, nkc = 0;
-};
 constexpr int RNS_NAN = 1 << 20;
 
 constexpr int RNS_SPLITS = 32;          // most K-splits of a product
@@ -73,6 +81,18 @@ struct RnsSrc {
   long kg, kx;
   bool conj;
   int r0 = 0;
+};
+
+// An operand in residues.  Plane q (modulus q / 2, sign q % 2; q = RNS_PL the
+// codes), row block rt, k block kc is the 8 KB run at
+// ((q * nrt + rt) * nkc + kc) * RNS_BLK, laid out
+// [row / 16][k / 16][row % 16][k % 16]: the LDS image of the GEMM, in which a
+// 16 x 64 fragment is 1 KB in lane order.
+struct RnsMat {
+  int8_t* p = nullptr;
+  int* e = nullptr;        // row exponents (RNS_NAN: a row that is not finite), then the rows' code scales
+  RnsSrc src{};            // the FP64 entries, for what the integers do not serve
+  int rows = 0, K = 0, nrt = 0, nkc = 0;
 };
 // rows x K with unit stride along the rows, k stride ld
 inline RnsSrc rns_kmajor(const double2* p, long ld, int K, bool conj = false) {
@@ -111,11 +131,12 @@ adc2_status rns_pack(const RnsSrc& src, int rows, int K, int8_t* buf, int* ebuf,
 // out = residues of the products of the rows of A with the rows [col0,
 // col0 + ncols) of B (col0 a multiple of 128) over nsplit runs of K: split s, plane
 // q, 32 x 32 block (rb, cb) as a 1 KB run at
-// (((s * RNS_PL + q) * nrb + rb) * ncb + cb) * 1024, in MFMA register order.
+// (((s * RNS_NP + q) * nrb + rb) * ncb + cb) * 1024, in MFMA register order.
 adc2_status rns_gemm(const RnsMat& A, const RnsMat& B, int col0, int ncols, int nsplit, int8_t* out, hipStream_t st);
-// The products themselves out of those residues.
-adc2_status rns_join(const RnsMat& A, const RnsMat& B, int col0, int ncols, int nsplit, const int8_t* out,
-                     const RnsDst& dst, hipStream_t st);
+// The products themselves out of those residues, and in FP64 from A.src and B.src
+// those entries that the integers do not hold well enough.
+adc2_status rns_join(const RnsMat& A, const RnsMat& B, int col0, int ncols, int nsplit, int8_t* out, const RnsDst& dst,
+                     hipStream_t st);
 
 // dst(i, j) = sum_k A(i, k) B(j, k), i < M, j < N, in chunks of rows whose work
 // space is at most h->rns_target (or that of one 256 x 128 tile); the entry points

@@ -109,10 +109,14 @@ static_assert(rns_m() > 2.0 * (double)(1L << 58) * (double)(1L << 58) * 1.58, "2
 // sizes
 // ---------------------------------------------------------------------------
 constexpr int NORM_SPLIT = 64;
-size_t rns_op_bytes(long rows, long K) { return (size_t)RNS_PL * rcdiv(rows, RNS_RT) * rcdiv(K, RNS_KC) * RNS_BLK; }
-size_t rns_exp_bytes(long rows) { return sizeof(int) * (size_t)rcdiv(rows, RNS_RT) * RNS_RT; }
+constexpr float RNS_QRMS = 16.0f;      // magnitude code of an entry of its row's rms
+constexpr float RNS_SPREAD = 57.6f;    // least code product a term at which the integers serve (rns.h)
+constexpr int RNS_QUNIT = 64;          // its image in the bytes that the products of the codes are kept in
+size_t rns_op_bytes(long rows, long K) { return (size_t)RNS_NP * rcdiv(rows, RNS_RT) * rcdiv(K, RNS_KC) * RNS_BLK; }
+size_t rns_exp_bytes(long rows) { return (sizeof(int) + sizeof(float)) * (size_t)rcdiv(rows, RNS_RT) * RNS_RT; }
 size_t rns_norm_bytes(long rows) { return sizeof(double) * 3 * NORM_SPLIT * (size_t)rows; }
-size_t rns_out_bytes(long rows, long cols) { return (size_t)RNS_PL * rcdiv(rows, 32) * rcdiv(cols, 32) * 1024; }
+// (two bytes a 32 x 32 block: whether k_rns_fp64 has entries in it)
+size_t rns_out_bytes(long rows, long cols) { return (size_t)(RNS_NP * 1024 + 2) * rcdiv(rows, 32) * rcdiv(cols, 32); }
 
 // ---------------------------------------------------------------------------
 // row exponents
@@ -143,14 +147,17 @@ struct RnsSums {
 // read of the operand): lane = row where rows are contiguous, a wave per row
 // where k is.
 // The largest e with ||row|| 2^e <= 2^RNS_G from the row's three sums
-__device__ __forceinline__ int rns_exponent(double s0, double s1, double s2) {
+// (and the scale of its magnitude codes, in units of 2^32 of the scaled integers)
+__device__ __forceinline__ void rns_exponent(double s0, double s1, double s2, int K, int* e, float* w) {
   double l2;   // log2 of the norm
   if (s0 >= 0x1p-900 && s0 <= 0x1p1000) l2 = 0.5 * log2(s0);
   else if (s0 > 1.0) l2 = 0.5 * log2(s1) + 540.0;   // above 2^500 (Inf where a row is not finite)
   else if (s2 > 0.0) l2 = 0.5 * log2(s2) - 540.0;   // below 2^-450
   else if (s0 == 0.0) l2 = RNS_G;                   // zero row: e = 0
   else l2 = s0;                                     // NaN
-  return isfinite(l2) ? (int)floor(RNS_G - 1e-9 - l2) : RNS_NAN;
+  const int ex = isfinite(l2) ? (int)floor(RNS_G - 1e-9 - l2) : RNS_NAN;
+  *e = ex;
+  *w = ex == RNS_NAN ? 0.0f : RNS_QRMS * sqrtf((float)K) * exp2f(32.0f - (float)(l2 + ex));
 }
 
 __global__ __launch_bounds__(256) void k_rns_norm(const RnsSrc src, int rows, int K, double* __restrict__ part) {
@@ -192,8 +199,12 @@ __global__ __launch_bounds__(256) void k_rns_norm_k(const RnsSrc src, int rows, 
                                                     double* __restrict__ part, int* __restrict__ e) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  float* cw = (float*)(e + padded);
   if (row >= rows) {
-    if (gridDim.y == 1 && lane == 0 && row < padded) e[row] = 0;
+    if (gridDim.y == 1 && lane == 0 && row < padded) {
+      e[row] = 0;
+      cw[row] = 0.0f;
+    }
     return;
   }
   const double2* p = src.p + rns_row(src, row);
@@ -223,7 +234,7 @@ __global__ __launch_bounds__(256) void k_rns_norm_k(const RnsSrc src, int rows, 
     t.s[q] = v;
   }
   if (lane != 0) return;
-  if (gridDim.y == 1) e[row] = rns_exponent(t.s[0], t.s[1], t.s[2]);
+  if (gridDim.y == 1) rns_exponent(t.s[0], t.s[1], t.s[2], K, e + row, cw + row);
   else
 #pragma unroll
     for (int q = 0; q < 3; ++q) part[((long)blockIdx.y * 3 + q) * rows + row] = t.s[q];
@@ -232,8 +243,8 @@ __global__ __launch_bounds__(256) void k_rns_norm_k(const RnsSrc src, int rows, 
 // e[row]: the largest e with ||row|| 2^e <= 2^RNS_G; rows past the end 0.  A workgroup
 // owns 64 rows, its 16 waves share the slices of the norm (one thread a row read up to
 // 192 values in turn: 22 us).
-__global__ __launch_bounds__(1024) void k_rns_expo(const double* __restrict__ part, int nsplit, int rows, int padded,
-                                                   int* __restrict__ e) {
+__global__ __launch_bounds__(1024) void k_rns_expo(const double* __restrict__ part, int nsplit, int rows, int K,
+                                                   int padded, int* __restrict__ e) {
   __shared__ double red[16][3][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int row = blockIdx.x * 64 + lane;
@@ -251,7 +262,13 @@ __global__ __launch_bounds__(1024) void k_rns_expo(const double* __restrict__ pa
   for (int t = 1; t < nw; ++t)
 #pragma unroll
     for (int q = 0; q < 3; ++q) s[q] += red[t][q][lane];
-  e[row] = row < rows ? rns_exponent(s[0], s[1], s[2]) : 0;
+  float* cw = (float*)(e + padded);
+  if (row < rows) {
+    rns_exponent(s[0], s[1], s[2], K, e + row, cw + row);
+  } else {
+    e[row] = 0;
+    cw[row] = 0.0f;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -259,8 +276,8 @@ __global__ __launch_bounds__(1024) void k_rns_expo(const double* __restrict__ pa
 // ---------------------------------------------------------------------------
 // A thread owns 16 consecutive k of one row: it rounds them to 59-bit signed
 // integers, splits these into signed bytes once, and forms both residues for
-// each modulus from four 4-byte dot products and a float reduction; the 16
-// bytes of a plane are one store, so a wave writes 1 KB runs.  Bound by its
+// each modulus from four 4-byte dot products and a float reduction, and the codes of the
+// magnitudes from the upper four bytes; the 16 bytes of a plane are one store, so a wave writes 1 KB runs.  Bound by its
 // vector instructions (about 250 per entry) and its 32-byte writes per entry:
 // 0.29 ms for the 27 M entries of a 18000 x 1500 operand, 4 TB/s.  Operands
 // contiguous along k go through LDS, so that both their reads and the writes
@@ -270,8 +287,9 @@ __global__ __launch_bounds__(1024) void k_rns_expo(const double* __restrict__ pa
 // (blockIdx.y), each part rounding the entries again.
 constexpr int RNS_MAGIC = 0x4B400000;   // 1.5 * 2^23 as a float: float(MAGIC + x) = 1.5 * 2^23 + x
 template <bool KLANE>
-__global__ __launch_bounds__(256) void k_rns_pack(const RnsSrc src, int rows, int K, const int* __restrict__ e, int nrt,
-                                                   int nkc, int8_t* __restrict__ dst) {
+__global__ __launch_bounds__(256, KLANE ? 3 : 4) void k_rns_pack(const RnsSrc src, int rows, int K,
+                                                                 const int* __restrict__ e, int nrt, int nkc,
+                                                                 int8_t* __restrict__ dst) {
   const int lane = threadIdx.x & 63, kg = threadIdx.x >> 6;
   const int rb = blockIdx.x % (2 * nrt), kc = blockIdx.x / (2 * nrt);
   const int row = rb * 64 + lane;
@@ -325,6 +343,7 @@ __global__ __launch_bounds__(256) void k_rns_pack(const RnsSrc src, int rows, in
   const double cs = src.conj ? -1.0 : 1.0;
   int ex = e[ok ? row : 0];
   if (ex == RNS_NAN) ex = 0;
+  const float cw = ((const float*)(e + nrt * RNS_RT))[ok ? row : 0];
   auto digits = [&](double x, int& lo, int& hi) {
     x = rint(ldexp(x, ex));
     // x = h 2^32 + l, |x| < 2^59: exact
@@ -334,6 +353,10 @@ __global__ __launch_bounds__(256) void k_rns_pack(const RnsSrc src, int rows, in
     lo = (int)((unsigned)v ^ 0x80808080u);
     hi = (int)((unsigned)(v >> 32) ^ 0x80808080u);
   };
+  unsigned zeros = 0;   // exact zeros among the entries
+#pragma unroll
+  for (int u = 0; u < 16; ++u)
+    zeros |= (unsigned)((d[u].x | d[u].z | ((d[u].y | d[u].w) & 0x7fffffff)) == 0) << u;
 #pragma unroll
   for (int u = 0; u < 16; ++u) {
     const double re = __hiloint2double(d[u].y, d[u].x), im = cs * __hiloint2double(d[u].w, d[u].z);
@@ -345,9 +368,19 @@ __global__ __launch_bounds__(256) void k_rns_pack(const RnsSrc src, int rows, in
     d[u].z = a;
     d[u].w = b;
   }
+  __builtin_amdgcn_sched_barrier(0);   // (interleaved with the loop above the codes cost 50 registers)
+  auto top = [](int x) { return (float)(int)(((unsigned)x ^ 0x80808080u) - 0x80808080u); };   // the upper four bytes
+  i4v code;
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const float hr = top(d[u].y), hi = top(d[u].w);
+    const int c = (zeros >> u & 1) ? 0 : (int)fminf(fmaxf(cw * __builtin_amdgcn_sqrtf(fmaf(hr, hr, hi * hi)), 1.0f), 127.0f);
+    code[u >> 2] = (u & 3) ? code[u >> 2] | c << (8 * (u & 3)) : c;
+  }
   const float magic = 12582912.0f;
   int8_t* out = dst + ((long)(rb >> 1) * nkc + kc) * RNS_BLK + ((rb & 1) * 4 + (lane >> 4)) * 1024 + kg * 256 + (lane & 15) * 16;
   const long ps = (long)nrt * nkc * RNS_BLK;
+  if (blockIdx.y == 0) *(i4v*)(out + RNS_PL * ps) = code;
   const int nq = RNS_NM / gridDim.y;
   for (int q = blockIdx.y * nq; q < (int)(blockIdx.y + 1) * nq; ++q) {
     const RnsSplit c = RNS_C.split[q];
@@ -380,6 +413,7 @@ adc2_status rns_pack(const RnsSrc& src, int rows, int K, int8_t* buf, int* ebuf,
                      hipStream_t st) {
   out->p = buf;
   out->e = ebuf;
+  out->src = src;
   out->rows = rows;
   out->K = K;
   out->nrt = rcdiv(rows, RNS_RT);
@@ -396,7 +430,7 @@ adc2_status rns_pack(const RnsSrc& src, int rows, int K, int8_t* buf, int* ebuf,
   }
   ADC2_CHECK_LAUNCH();
   if (!klane || ns > 1) {
-    k_rns_expo<<<rcdiv(padded, 64), 1024, 0, st>>>(nbuf, ns, rows, padded, ebuf);
+    k_rns_expo<<<rcdiv(padded, 64), 1024, 0, st>>>(nbuf, ns, rows, K, padded, ebuf);
     ADC2_CHECK_LAUNCH();
   }
   const long nblk = (long)2 * out->nrt * out->nkc;
@@ -423,17 +457,21 @@ adc2_status rns_pack(const RnsSrc& src, int rows, int K, int8_t* buf, int* ebuf,
 template <int WM, int WN, int NB>
 __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm(
     const int8_t* __restrict__ A, const int8_t* __restrict__ B, int nrtA, int nrtB, int brt0, int nkca, int nkcs, int nbm,
-    int nbn, int nrb, int ncb, int8_t* __restrict__ C) {
+    int nbn, int nrb, int ncb, float qs, int8_t* __restrict__ C) {
   constexpr int BM = 128 * WM, BN = 64 * WN, T = 64 * WM * WN;
   constexpr int SB = (BM + BN) * RNS_KC, NL = SB / (T * 16), NLA = BM * RNS_KC / (T * 16);
   __shared__ __align__(16) int8_t s[NB][SB];
   const long nt = (long)nbm * nbn;
-  // planes in order, so that each XCD works on the tiles of few planes; tiles
-  // in groups of 8 row panels
-  const long lid = xcd_remap(blockIdx.x, gridDim.x);
-  const int sp = (int)(lid / nt);                     // K-split * RNS_PL + plane
-  const int t0 = (int)(lid - (long)sp * nt);
-  const int pl = sp % RNS_PL, kc0 = sp / RNS_PL * nkcs;
+  // planes in order, so that each XCD works on the tiles of few planes, the code planes of
+  // all splits after them (33 planes in order straddle the XCDs: 1% slower); tiles in
+  // groups of 8 row panels
+  const long ncode = gridDim.x / RNS_NP, nres = gridDim.x - ncode;   // a code tile for every 32 others
+  const bool codes = (long)blockIdx.x >= nres;
+  const long lid = codes ? xcd_remap(blockIdx.x - nres, ncode) : xcd_remap(blockIdx.x, nres);
+  const int g = (int)(lid / nt);                      // K-split * RNS_PL + plane, K-split
+  const int t0 = (int)(lid - (long)g * nt);
+  const int pl = codes ? RNS_PL : g % RNS_PL, split = codes ? g : g / RNS_PL;
+  const int sp = split * RNS_NP + pl, kc0 = split * nkcs;
   const int nkc = min(nkcs, nkca - kc0);              // chunks of this split
   const int per = 8 * nbn, grp = t0 / per, gm = min(8, nbm - grp * 8), r = t0 - grp * per;
   const int bm = grp * 8 + r % gm, bn = r / gm;
@@ -492,6 +530,28 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm
         acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i], b[j], acc[i][j], 0, 0, 0);
   }
   __builtin_amdgcn_s_waitcnt(0x0f70);
+  auto each = [&](auto&& byte) {   // the low byte of byte(acc) of every entry
+#pragma unroll
+    for (int i = 0; i < 4; ++i)   // 32 x 32 blocks: two row blocks, two column blocks
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        i4v o;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          int rr[4];
+#pragma unroll
+          for (int x = 0; x < 4; ++x) rr[x] = byte(acc[2 * i + (q & 1)][2 * j + (q >> 1)][x]);
+          o[q] = (int)__builtin_amdgcn_perm(__builtin_amdgcn_perm(rr[3], rr[2], 0x0c0c0400),
+                                            __builtin_amdgcn_perm(rr[1], rr[0], 0x0c0c0400), 0x05040100);
+        }
+        const int rb = (bm * BM + wm * 128) / 32 + i, cb = (bn * BN + wn * 64) / 32 + j;
+        if (rb < nrb && cb < ncb) *(i4v*)(C + (((long)sp * nrb + rb) * ncb + cb) * 1024 + lane * 16) = o;
+      }
+  };
+  if (codes) {   // 0: no common term; else 1 + the code product in units of its bound / RNS_QUNIT
+    each([&](int v) { return v == 0 ? 0 : 1 + (int)fminf((float)v * qs, 126.0f); });
+    return;
+  }
   const RnsSplit c = RNS_C.split[pl >> 1];
   const int pi = (int)c.p;
   const float magic = 12582912.0f;
@@ -501,30 +561,14 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm
   // up to 4096 k the second step alone ends within 126.
   const bool far = nkc > 64;
   const float invf = c.inv * (1.0f / 1024.0f);
-#pragma unroll
-  for (int i = 0; i < 4; ++i)   // 32 x 32 blocks: two row blocks, two column blocks
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      i4v o;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        int rr[4];
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-          int v = acc[2 * i + (q & 1)][2 * j + (q >> 1)][x];
-          if (far) {
-            const float t = fmaf((float)v, invf, magic);
-            v -= __mul24(__float_as_int(t) - RNS_MAGIC, pi * 1024);
-          }
-          const float t = fmaf((float)v, c.inv, magic);
-          rr[x] = v - __mul24(__float_as_int(t) - RNS_MAGIC, pi);
-        }
-        o[q] = (int)__builtin_amdgcn_perm(__builtin_amdgcn_perm(rr[3], rr[2], 0x0c0c0400),
-                                          __builtin_amdgcn_perm(rr[1], rr[0], 0x0c0c0400), 0x05040100);
-      }
-      const int rb = (bm * BM + wm * 128) / 32 + i, cb = (bn * BN + wn * 64) / 32 + j;
-      if (rb < nrb && cb < ncb) *(i4v*)(C + (((long)sp * nrb + rb) * ncb + cb) * 1024 + lane * 16) = o;
+  each([&](int v) {
+    if (far) {
+      const float t = fmaf((float)v, invf, magic);
+      v -= __mul24(__float_as_int(t) - RNS_MAGIC, pi * 1024);
     }
+    const float t = fmaf((float)v, c.inv, magic);
+    return v - __mul24(__float_as_int(t) - RNS_MAGIC, pi);
+  });
 }
 
 adc2_status rns_gemm(const RnsMat& A, const RnsMat& B, int col0, int ncols, int nsplit, int8_t* out, hipStream_t st) {
@@ -532,20 +576,30 @@ adc2_status rns_gemm(const RnsMat& A, const RnsMat& B, int col0, int ncols, int 
   // 256 x 128 or 128 x 256 tiles: the one that pads less, weighed by its rate (256 x
   // 128 is 2% the faster one at K = 1500, the other 1 to 4% from K = 3000 on)
   const int nkcs = rcdiv(A.nkc, nsplit);
+  const float qs = RNS_QUNIT / (RNS_SPREAD * (float)A.K);
   const double tall = 256.0 * rcdiv(A.rows, 256) * 128.0 * rcdiv(ncols, 128);
   const double flat = 128.0 * rcdiv(A.rows, 128) * 256.0 * rcdiv(ncols, 256) * (nkcs < 40 ? 1.02 : 0.98);
   if (tall <= flat) {
     const int nbm = rcdiv(A.rows, 256), nbn = rcdiv(ncols, 128);
-    k_rns_gemm<2, 2, 3><<<(unsigned)((long)nsplit * RNS_PL * nbm * nbn), 256, 0, st>>>(
-        A.p, B.p, A.nrt, B.nrt, col0 / RNS_RT, A.nkc, nkcs, nbm, nbn, nrb, ncb, out);
+    k_rns_gemm<2, 2, 3><<<(unsigned)((long)nsplit * RNS_NP * nbm * nbn), 256, 0, st>>>(
+        A.p, B.p, A.nrt, B.nrt, col0 / RNS_RT, A.nkc, nkcs, nbm, nbn, nrb, ncb, qs, out);
   } else {
     const int nbm = rcdiv(A.rows, 128), nbn = rcdiv(ncols, 256);
-    k_rns_gemm<1, 4, 3><<<(unsigned)((long)nsplit * RNS_PL * nbm * nbn), 256, 0, st>>>(
-        A.p, B.p, A.nrt, B.nrt, col0 / RNS_RT, A.nkc, nkcs, nbm, nbn, nrb, ncb, out);
+    k_rns_gemm<1, 4, 3><<<(unsigned)((long)nsplit * RNS_NP * nbm * nbn), 256, 0, st>>>(
+        A.p, B.p, A.nrt, B.nrt, col0 / RNS_RT, A.nkc, nkcs, nbm, nbn, nrb, ncb, qs, out);
   }
   ADC2_CHECK_LAUNCH();
   return ADC2_OK;
 }
+
+// ---------------------------------------------------------------------------
+// which entries the integers serve
+// ---------------------------------------------------------------------------
+// The bytes that k_rns_gemm keeps of the code products of an entry's K-runs, summed:
+// 2^16 a run with common terms, plus its code product in units of the bound / RNS_QUNIT
+__device__ __forceinline__ int rns_spread(int byte) { return byte == 0 ? 0 : 0x10000 + byte - 1; }
+// no common terms (an exact zero), or enough of them
+__device__ __forceinline__ bool rns_serves(int spread) { return spread == 0 || (spread & 0xffff) >= RNS_QUNIT; }
 
 // ---------------------------------------------------------------------------
 // recombination
@@ -557,7 +611,7 @@ adc2_status rns_gemm(const RnsMat& A, const RnsMat& B, int col0, int ncols, int 
 // modulo 1, those of lo added after.  Bound by the 32 bytes read and 16 written
 // per entry.
 template <bool SPLIT>
-__global__ __launch_bounds__(256) void k_rns_join(const int8_t* __restrict__ R, int nrb, int ncb, int rows, int cols,
+__global__ __launch_bounds__(256) void k_rns_join(int8_t* __restrict__ R, int nrb, int ncb, int rows, int cols,
                                                    int nsplit, const int* __restrict__ ea, const int* __restrict__ eb,
                                                    const RnsDst dst) {
   const int ncp = (ncb + 1) >> 1;
@@ -588,7 +642,7 @@ __global__ __launch_bounds__(256) void k_rns_join(const int8_t* __restrict__ R, 
       for (int s = 1; s < nsplit; ++s) {
         int2 v[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = *(const int2*)(src + ((long)s * RNS_PL + 4 * t + q) * ps);
+        for (int q = 0; q < 4; ++q) v[q] = *(const int2*)(src + ((long)s * RNS_NP + 4 * t + q) * ps);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -608,6 +662,24 @@ __global__ __launch_bounds__(256) void k_rns_join(const int8_t* __restrict__ R, 
     }
   }
   if (col >= cols) return;
+  int spread[8];
+  {
+    int2 v = *(const int2*)(src + RNS_PL * ps);
+#pragma unroll
+    for (int x = 0; x < 8; ++x) spread[x] = rns_spread(((x < 4 ? v.x : v.y) >> (8 * (x & 3))) & 255);
+    if constexpr (SPLIT)
+      for (int s = 1; s < nsplit; ++s) {
+        v = *(const int2*)(src + ((long)s * RNS_NP + RNS_PL) * ps);
+#pragma unroll
+        for (int x = 0; x < 8; ++x) spread[x] += rns_spread(((x < 4 ? v.x : v.y) >> (8 * (x & 3))) & 255);
+      }
+  }
+  bool left = false;   // entries for k_rns_fp64 (lane 0 has the block's first column, which is there)
+#pragma unroll
+  for (int x = 0; x < 8; ++x) left = left || (row0 + (x >> 2) * 16 + (x & 3) < rows && !rns_serves(spread[x]));
+  const bool any = __ballot(left) != 0;
+  if ((threadIdx.x & 63) == 0)
+    R[(long)nsplit * RNS_NP * ps + ((long)rb * ncb + cb) * 2 + (item >> 6)] = any;
   const int ec = eb[col];
   constexpr double M = rns_m();
   const int jj = dst.j0 + col, cg = jj / dst.ji;
@@ -615,7 +687,7 @@ __global__ __launch_bounds__(256) void k_rns_join(const int8_t* __restrict__ R, 
 #pragma unroll
   for (int x = 0; x < 8; ++x) {
     const int row = row0 + (x >> 2) * 16 + (x & 3);
-    if (row >= rows) continue;
+    if (row >= rows || !rns_serves(spread[x])) continue;
     const int er = ea[row];
     double re = M * ((fr[x] - rint(fr[x])) + gr[x]), im = M * ((fi[x] - rint(fi[x])) + gi[x]);
     if (er == RNS_NAN || ec == RNS_NAN) {
@@ -632,12 +704,96 @@ __global__ __launch_bounds__(256) void k_rns_join(const int8_t* __restrict__ R, 
   }
 }
 
-adc2_status rns_join(const RnsMat& A, const RnsMat& B, int col0, int ncols, int nsplit, const int8_t* out,
-                     const RnsDst& dst, hipStream_t st) {
+// The entries that the integers do not serve, as FP64 sums of the operands' own
+// entries, in 64 x 64 tiles on the tile engine of tile.h.  Two workgroups a compute unit take
+// them; where the join found none the launch ends after the read of eight bytes a tile (3 us).
+// K is not split, so that the sums do not depend on the rows and columns of a call.
+template <int MAP_>
+struct SrcRns {
+  static constexpr int MAP = MAP_;
+  RnsSrc s;
+  int row0, rows, K;
+  __device__ __forceinline__ double2 get(int k, int i) const {
+    if (k >= K || row0 + i >= rows) return czero();
+    const double2 v = s.p[rns_row(s, row0 + i) + rns_k(s, k)];
+    return make_double2(v.x, s.conj ? -v.y : v.y);
+  }
+};
+
+template <int MAPA, int MAPB>
+__global__ __launch_bounds__(256) void k_rns_fp64(const RnsSrc A, const RnsSrc B, int col0, int rows, int cols, int K,
+                                                   const int8_t* __restrict__ R, int nrb, int ncb, int nsplit,
+                                                   const RnsDst dst) {
+  __shared__ TileSmem s;
+  __shared__ unsigned char own[64][64];
+  __shared__ unsigned long long todo[4];   // the tiles that have such entries
+  const int nct = (ncb + 1) >> 1, ntile = ((nrb + 1) >> 1) * nct;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int br = (tid >> 6) & 1, bc = tid >> 7;   // a wave per 32 x 32 block
+  const unsigned short* left = (const unsigned short*)(R + (long)nsplit * RNS_NP * nrb * ncb * 1024);
+  for (int t0 = blockIdx.x; t0 < ntile; t0 += 256 * gridDim.x) {   // a thread looks at one tile of up to 256
+    const int tt = t0 + tid * gridDim.x, b0 = (tt / nct) * 2, c0 = (tt % nct) * 2;
+    unsigned any = 0;
+    if (tt < ntile)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (b0 + (q & 1) < nrb && c0 + (q >> 1) < ncb) any |= left[(b0 + (q & 1)) * (long)ncb + c0 + (q >> 1)];
+    const unsigned long long m = __ballot(any != 0);
+    if (lane == 0) todo[tid >> 6] = m;
+    __syncthreads();
+    for (int w = 0; w < 4; ++w)
+      for (unsigned long long t = todo[w]; t; t &= t - 1) {
+        const int tile = t0 + (w * 64 + __builtin_ctzll(t)) * gridDim.x;
+        const int i0 = (tile / nct) * 64, j0 = (tile % nct) * 64, rb = i0 / 32 + br, cb = j0 / 32 + bc;
+        int spread[16];
+#pragma unroll
+        for (int x = 0; x < 16; ++x) spread[x] = 0;
+        if (rb < nrb && cb < ncb)
+          for (int q = 0; q < nsplit; ++q) {
+            const i4v v = *(const i4v*)(R + ((((long)q * RNS_NP + RNS_PL) * nrb + rb) * ncb + cb) * 1024 + lane * 16);
+#pragma unroll
+            for (int x = 0; x < 16; ++x) spread[x] += rns_spread((v[x >> 2] >> (8 * (x & 3))) & 255);
+          }
+#pragma unroll
+        for (int x = 0; x < 16; ++x) {   // register order of the 16 x 16 blocks of k_rns_gemm
+          const int q = x >> 2, r = 32 * br + 16 * (q & 1) + 4 * (lane >> 4) + (x & 3);
+          const int c = 32 * bc + 16 * (q >> 1) + (lane & 15);
+          own[r][c] = (unsigned char)(!rns_serves(spread[x]) && i0 + r < rows && j0 + c < cols);
+        }
+        Acc acc;
+        acc.zero();
+        mainloop(s, SrcRns<MAPA>{A, i0, rows, K}, SrcRns<MAPB>{B, col0 + j0, col0 + cols, K}, 0, (K + TK - 1) / TK, acc);
+        for_each_acc(acc, [&](int r, int c, double2 v) {
+          if (!own[r][c]) return;
+          const int i = dst.i0 + i0 + r, rg = i / dst.ii, j = dst.j0 + j0 + c, cg = j / dst.ji;
+          double2* o = dst.C + (long)rg * dst.ig + (long)(i - rg * dst.ii) * dst.ix + (long)cg * dst.jg +
+                       (long)(j - cg * dst.ji) * dst.jx;
+          double2 u = cscale(v, dst.alpha);
+          if (dst.add) u = cadd(*o, u);
+          *o = u;
+        });
+        __syncthreads();   // own and s are free
+      }
+    __syncthreads();   // todo is free
+  }
+}
+
+adc2_status rns_join(const RnsMat& A, const RnsMat& B, int col0, int ncols, int nsplit, int8_t* out, const RnsDst& dst,
+                     hipStream_t st) {
   const int nrb = rcdiv(A.rows, 32), ncb = rcdiv(ncols, 32);
   const unsigned nblk = (unsigned)((long)nrb * ((ncb + 1) / 2));
   if (nsplit > 1) k_rns_join<true><<<nblk, 256, 0, st>>>(out, nrb, ncb, A.rows, ncols, nsplit, A.e, B.e + col0, dst);
   else k_rns_join<false><<<nblk, 256, 0, st>>>(out, nrb, ncb, A.rows, ncols, 1, A.e, B.e + col0, dst);
+  ADC2_CHECK_LAUNCH();
+  const unsigned ntile = (unsigned)std::min<long>(512, (long)((nrb + 1) / 2) * ((ncb + 1) / 2));
+#define RNS_FP64(MA_, MB_)                                                                                      \
+  k_rns_fp64<MA_, MB_><<<ntile, 256, 0, st>>>(A.src, B.src, col0, A.rows, ncols, A.K, out, nrb, ncb, nsplit, dst)
+  const bool ak = A.src.rx == 1, bk = B.src.rx == 1;   // contiguous along the rows
+  if (ak && bk) RNS_FP64(KMAJOR, KMAJOR);
+  else if (ak) RNS_FP64(KMAJOR, RMAJOR);
+  else if (bk) RNS_FP64(RMAJOR, KMAJOR);
+  else RNS_FP64(RMAJOR, RMAJOR);
+#undef RNS_FP64
   ADC2_CHECK_LAUNCH();
   return ADC2_OK;
 }

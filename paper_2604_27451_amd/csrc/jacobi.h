@@ -24,6 +24,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "eigorder.h"
 #include "tile.h"
 
 namespace adc2 {
@@ -206,10 +207,7 @@ __device__ inline void jacobi_lds(JacobiSmem& S, int n) {
   if (tid < n) {   // rank of each eigenvalue
     const double v = S.a[tid][tid].x;
     int rank = 0;
-    for (int j = 0; j < n; ++j) {
-      const double u = S.a[j][j].x;
-      rank += (u < v || (u == v && j < tid)) ? 1 : 0;
-    }
+    for (int j = 0; j < n; ++j) rank += eig_before(S.a[j][j].x, j, v, tid) ? 1 : 0;
     S.perm[rank] = tid;
   }
   __syncthreads();

@@ -129,9 +129,8 @@ __device__ inline void jacobi_lds(JacobiSmem& S, int n) {
     }
   };
   __syncthreads();
-  bool conv = false;
-  for (int sweep = 0; sweep <= JSWEEPS; ++sweep) {
-    double off = 0.0, tot = 0.0;
+  auto sums = [&](double& off, double& tot) {   // squares off the diagonal, and all
+    off = tot = 0.0;
     for (int e = tid; e < JMAX * JMAX; e += JTHR) {
       const int i = e >> 6, j = e & 63;
       if (i <= j && j < n) {
@@ -142,6 +141,33 @@ __device__ inline void jacobi_lds(JacobiSmem& S, int n) {
       }
     }
     jacobi_sum2(S, off, tot);
+  };
+  bool conv = false;
+  int up = 0;   // A is held times 2^up where its squares leave the range of the rotations
+  for (int sweep = 0; sweep <= JSWEEPS; ++sweep) {
+    double off, tot;
+    sums(off, tot);
+    if (sweep == 0 && !(tot > 1e-200 && tot < 1e200)) {
+      double big = 0.0;
+      for (int e = tid; e < JMAX * JMAX; e += JTHR) {
+        const int i = e >> 6, j = e & 63;
+        if (i <= j && j < n) big = fmax(big, fmax(fabs(S.a[i][j].x), fabs(S.a[i][j].y)));
+      }
+      for (int o = 32; o > 0; o >>= 1) big = fmax(big, __shfl_xor(big, o));
+      if (lane == 0) S.red[0][wv] = big;
+      __syncthreads();
+      for (int w = 0; w < JTHR / 64; ++w) big = fmax(big, S.red[0][w]);
+      __syncthreads();
+      if (big > 0.0 && big <= 0x1.fffffffffffffp1023) {
+        up = -ilogb(big);
+        for (int e = tid; e < JMAX * JMAX; e += JTHR) {
+          const int i = e >> 6, j = e & 63;
+          if (i <= j && j < n) S.a[i][j] = make_double2(ldexp(S.a[i][j].x, up), ldexp(S.a[i][j].y, up));
+        }
+        __syncthreads();
+        sums(off, tot);
+      }
+    }
     conv = off <= 1e-30 * tot || off == 0.0;
     if (conv || sweep == JSWEEPS) break;
     for (int round = 0; round < N - 1; ++round) {
@@ -201,6 +227,10 @@ __device__ inline void jacobi_lds(JacobiSmem& S, int n) {
     zturn(N & 1);   // the last round, N - 2
     __syncthreads();
     zmove();
+    __syncthreads();
+  }
+  if (up != 0) {
+    if (tid < n) S.a[tid][tid].x = ldexp(S.a[tid][tid].x, -up);
     __syncthreads();
   }
   if (tid == 0) S.done = conv ? 1 : 0;

@@ -183,7 +183,9 @@ ADC2_API adc2_status adc2_sigma(adc2_handle h, int m, const void* X, void* S, vo
  * one device (concurrent streams or threads) race on the array and must not
  * be issued.  Results equal adc2_sigma's in the FP64 form: the same kernels
  * with the same split counts, the integer products in smaller chunks (which
- * leaves their results as they are).
+ * leaves their results as they are).  (A handle that had to give the integer
+ * operands of its Cholesky blocks back, device memory being short, is served
+ * by the FP64 MFMA here until its next adc2_sigma has formed them again.)
  *   m  >= 1; the work spaces of m vectors must fit the array: about
  *      16 m nc (naux nv (1 + ysplit) + no nv^2) bytes (c1: nc=6, no=10,
  *      nv=40, naux=150 fits m up to about 16).
@@ -230,8 +232,10 @@ ADC2_API adc2_status adc2_davidson(adc2_handle h, int nroots, const adc2_dav_opt
 /*
  * adc2_set_precision -- switch the arithmetic of subsequent sigma builds
  * (adc2_sigma, adc2_davidson) on an existing handle.  ADC2_C64 builds its
- * complex64 operand copies on first use (stream-ordered).  ADC2_ERR_ARG for an
- * unknown precision.
+ * complex64 operand copies on first use (stream-ordered); ADC2_FP64 forms the
+ * integer operands of the Cholesky blocks at once where the sigmas of up to 16
+ * vectors use them and the handle does not hold them yet (synchronises; without
+ * the memory it does without).  ADC2_ERR_ARG for an unknown precision.
  */
 ADC2_API adc2_status adc2_set_precision(adc2_handle h, int prec);
 

@@ -292,11 +292,16 @@ hipError_t dmalloc_try(adc2_handle h, void** p, size_t bytes) {
 }
 
 // A request that fails while the handle holds residue-engine memory is tried
-// again without it (that engine is an option, the request is not); its next
-// product asks for it anew.
+// again without it (that engine is an option, the request is not): first without its
+// scratch, then without its static operands; its next product asks for them anew.
 hipError_t dmalloc_raw(adc2_handle h, void** p, size_t bytes) {
   hipError_t e = dmalloc_try(h, p, bytes);
-  if (e == hipErrorOutOfMemory && h && (h->rns_lvo || h->rns_lvt || h->rns_ws || h->rns_tmp)) {
+  if (e == hipErrorOutOfMemory && h && (h->rns_ws || h->rns_tmp)) {
+    (void)hipGetLastError();
+    rns_scratch_release(h);
+    e = dmalloc_try(h, p, bytes);
+  }
+  if (e == hipErrorOutOfMemory && h && (h->rns_lvo || h->rns_lvt)) {
     (void)hipGetLastError();
     rns_release(h);
     e = dmalloc_try(h, p, bytes);
@@ -415,7 +420,7 @@ adc2_status adc2_setup(const void* L, const double* eps, int nc, int no, int nv,
   }
   rc = build_m11(h, st);
   if (rc == ADC2_OK) rc = build_lvt(h, st);
-  if (rc == ADC2_OK) rc = rns_build_static(h, true, st);
+  if (rc == ADC2_OK) rc = rns_enter_fp64(h, st);
   if (rc == ADC2_OK &&
       (hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking) != hipSuccess ||
        hipEventCreateWithFlags(&h->side_fork, hipEventDisableTiming) != hipSuccess ||
@@ -443,7 +448,7 @@ adc2_status adc2_set_precision(adc2_handle h, int prec) {
   if (prec != ADC2_FP64 && prec != ADC2_C64 && prec != ADC2_BF16X3)
     return fail(ADC2_ERR_ARG, "adc2_set_precision: unknown precision");
   h->prec = prec;
-  return ADC2_OK;
+  return rns_enter_fp64(h, nullptr);
 }
 
 adc2_status adc2_rayleigh(adc2_handle h, int k, const void* X, double* omega, double* resnorm, void* stream) {

@@ -99,8 +99,8 @@ struct adc2_handle_s {
   int ysplit_tuned = 0;     // K-split fixed by adc2_autotune (0: the size heuristic)
   int zb_m = 0;             // vectors that Zb holds
   int zgemm = adc2::ZGEMM_WIDE;  // engine of the FP64 heavy GEMMs (ZGEMM_*)
-  // residue engine of the FP64 form (rns.h): the two static operands, built on
-  // first use, and the work space of one chunk of (vector, core) rows
+  // residue engine of the FP64 form (rns.h): the two static operands, built with the
+  // form or on first use, and the work space of one chunk of (vector, core) rows
   adc2::RnsMode rns_mode = adc2::RNS_AUTO;
   bool rns_off = false;     // its memory was not to be had: the FP64 MFMA engines serve this handle
   char* rns_lvo = nullptr;  // residues of the valence rows of Lvo (rows (j,b), K = P), then their exponents
@@ -110,7 +110,6 @@ struct adc2_handle_s {
   bool rns_lent = false;    // rns_ws is adc2_sigma_noalloc's array: neither grown nor freed
   hipStream_t side = nullptr;   // one half of a sigma (small ones), X-build and back-contraction (large ones)
   hipEvent_t side_fork = nullptr, side_join = nullptr;
-  bool rns_setup = false;   // the static operands were built by adc2_setup
   char* rns_tmp = nullptr;  // work space of the general products, held during an entry point
   size_t rns_tmp_bytes = 0;
   size_t rns_target = size_t(6) << 30;   // bytes a chunk's work space aims at (environment ADC2_RNS_MB)
@@ -169,11 +168,14 @@ adc2_status build_b3(adc2_handle h, hipStream_t st);
 adc2_status ensure_ws_b3(adc2_handle h, int m);
 // work spaces of m vectors; zb: also the unpacked doubles / sigma2 products of all of them
 adc2_status ensure_ws(adc2_handle h, int m, bool zb = true);
-// gives back what the residue engine holds on h
+// gives back what the residue engine holds on h: its scratch, and the static operands as well
+void rns_scratch_release(adc2_handle h);
 void rns_release(adc2_handle h);
 void rns_tmp_release(adc2_handle h);
-// the residue engine's static operands of the sigma, where the size rule may use them
-adc2_status rns_build_static(adc2_handle h, bool at_setup, hipStream_t st);
+// the residue engine's static operands of the sigma; with the FP64 form, where the size rule
+// may use them at up to 16 vectors
+adc2_status rns_build_static(adc2_handle h, hipStream_t st);
+adc2_status rns_enter_fp64(adc2_handle h, hipStream_t st);
 // K-split count of the Y-build by the size rule for h's form and engine at block size m
 int ysplit_rule(adc2_handle h, int m);
 adc2_status unpack_weighted(adc2_handle h, int m, const double2* xin, const double* wts, hipStream_t st);

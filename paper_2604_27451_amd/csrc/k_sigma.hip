@@ -1498,11 +1498,20 @@ static size_t rns_fixed_bytes(const Dims& d, int m) {
   return 2 * xy + al(16 * rows * njg * d.nc * d.nv) + al(16 * rows * d.nv * std::min(256, d.naux));
 }
 
+// Systems whose sigmas of up to 16 vectors may run on the residue engine: they get its
+// static operands with the FP64 form (at the setup, or when the form is set).
+static bool rns_system(adc2_handle h) {
+  const Dims& d = h->d;
+  if (h->rns_mode == RNS_NEVER || d.naux > RNS_KMAX || (long)d.no * d.nv > RNS_KMAX) return false;
+  return h->rns_mode == RNS_ALWAYS || rns_sized(d, 16.0 * d.nc);
+}
+
 // Whether a sigma of m vectors runs on the residue engine.  Where the MFMA
 // engines' work spaces fit adc2_sigma_noalloc's array, that entry point has to give
 // the same bits without allocating: there the engine is used only if its own fit as
-// well and its static operands have been there since the setup.
-static bool rns_wanted(adc2_handle h, int m) {
+// well and the system has its static operands from the start.  (A handle that had to
+// give them back gets them again from its next adc2_sigma; adc2_sigma_noalloc does without till then.)
+static bool rns_wanted(adc2_handle h, int m, bool noalloc = false) {
   const Dims& d = h->d;
   const double rows = (double)m * d.nc;
   if (h->prec != ADC2_FP64 || h->rns_off || h->rns_mode == RNS_NEVER || d.naux > RNS_KMAX ||
@@ -1510,16 +1519,18 @@ static bool rns_wanted(adc2_handle h, int m) {
     return false;
   if (h->rns_mode != RNS_ALWAYS && !rns_sized(d, rows)) return false;
   if (16.0 * rows * (2.0 * d.naux * d.nv + (double)d.no * d.nv * d.nv) > NOALLOC_SCRATCH_BYTES) return true;
-  return h->rns_setup && rns_fixed_bytes(d, m) + rns_plan(h, m * d.nc, 1).bytes <= NOALLOC_SCRATCH_BYTES;
+  if (!rns_system(h) || rns_fixed_bytes(d, m) + rns_plan(h, m * d.nc, 1).bytes > NOALLOC_SCRATCH_BYTES) return false;
+  return !noalloc || (h->rns_lvo && h->rns_lvt);
 }
 
-adc2_status rns_build_static(adc2_handle h, bool at_setup, hipStream_t st) {
+adc2_status rns_enter_fp64(adc2_handle h, hipStream_t st) {
+  return h->prec == ADC2_FP64 && rns_system(h) ? rns_build_static(h, st) : ADC2_OK;
+}
+
+adc2_status rns_build_static(adc2_handle h, hipStream_t st) {
   const Dims& d = h->d;
   const long ky = (long)d.no * d.nv;
   if (h->rns_lvo && h->rns_lvt) return ADC2_OK;
-  if (at_setup && (h->prec != ADC2_FP64 || h->rns_mode == RNS_NEVER ||
-                   (h->rns_mode != RNS_ALWAYS && !rns_sized(d, 16.0 * d.nc))))
-    return ADC2_OK;
   if (h->rns_off || d.naux > RNS_KMAX || ky > RNS_KMAX) return ADC2_OK;
   double* norm = nullptr;
   hipError_t e = dmalloc_try(h, (void**)&norm, std::max(rns_norm_bytes(ky), rns_norm_bytes(d.naux)));
@@ -1542,7 +1553,6 @@ adc2_status rns_build_static(adc2_handle h, bool at_setup, hipStream_t st) {
       rc = ADC2_ERR_HIP;
     }
     if (rc != ADC2_OK) rns_release(h);
-    else h->rns_setup = at_setup;
   }
   dfree(h, norm);
   return rc;
@@ -1575,7 +1585,7 @@ static adc2_status rns_ready(adc2_handle h, int m, hipStream_t st, bool* ok) {
     return true;
   };
   for (;;) {
-    const adc2_status rc = rns_build_static(h, false, st);
+    const adc2_status rc = rns_build_static(h, st);
     if (rc != ADC2_OK) return rc;
     if (h->rns_lvo && h->rns_lvt) {
       const size_t one = rns_plan(h, m * h->d.nc).bytes;
@@ -2309,7 +2319,7 @@ extern "C" adc2_status adc2_sigma_noalloc(adc2_handle h, int m, const void* X, v
     q += (b + 255) & ~size_t(255);
     return r;
   };
-  const bool rns = rns_wanted(h, m);   // then its own work spaces instead of Zb, in smaller chunks
+  const bool rns = rns_wanted(h, m, true);   // then its own work spaces instead of Zb, in smaller chunks
   char* sws_rns = h->rns_ws;
   const size_t swsb = h->rns_ws_bytes, starget = h->rns_target;
   h->X = take(p.x);

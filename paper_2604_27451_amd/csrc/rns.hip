@@ -843,15 +843,20 @@ void rns_tmp_release(adc2_handle h) {
   dfree(h, t);
 }
 
-void rns_release(adc2_handle h) {
-  char *a = h->rns_lvo, *b = h->rns_lvt, *c = h->rns_ws;
-  h->rns_lvo = h->rns_lvt = h->rns_ws = nullptr;
+void rns_scratch_release(adc2_handle h) {
+  char* c = h->rns_ws;
+  h->rns_ws = nullptr;
   h->rns_ws_bytes = 0;
-  h->rns_setup = false;
-  dfree(h, a);
-  dfree(h, b);
   dfree(h, c);
   rns_tmp_release(h);
+}
+
+void rns_release(adc2_handle h) {
+  char *a = h->rns_lvo, *b = h->rns_lvt;
+  h->rns_lvo = h->rns_lvt = nullptr;
+  dfree(h, a);
+  dfree(h, b);
+  rns_scratch_release(h);
 }
 
 adc2_status rns_product(adc2_handle h, const RnsSrc& A, int M, const RnsSrc& B, int N, int K, const RnsDst& dst,

@@ -1,0 +1,80 @@
+"""Which engine serves the FP64 sigmas of a small system (csrc/rns.h): the residue engine, whatever
+form the handle was set up in and whatever it had to give back in between; the bits are
+those of a handle that always had its memory.  (nc=6 no=10 nv=40 naux=150: within adc2_sigma_noalloc's array,
+above the size from which the engine is used.)"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2604_27451_amd as A
+from synth import make_system, random_vectors
+
+pytestmark = pytest.mark.gpu
+
+M = 3
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+@pytest.fixture(scope="module")
+def case():
+    s = make_system(6, 10, 40, 150, seed=951)
+    L, e = dev(s.L), dev(s.eps)
+    h = A.adc2_setup(L, e, s.nc, s.no, s.nv, s.naux)
+    x = dev(random_vectors(6, M, h.dim))
+    want = A.adc2_sigma(h, x)
+    h.close()
+    return s, L, e, x, want
+
+
+def noalloc(h, x):
+    S = torch.empty_like(x)
+    A.adc2_sigma_noalloc(h, x, S)
+    return S
+
+
+class Refusing:
+    """PyTorch's allocator that refuses the next `left` requests."""
+
+    def __init__(self):
+        self.base, self.left, self.count = A.torch_allocator(), 0, 0
+        self.alloc = A.Alloc(A._ALLOC_FN(self._alloc), self.base.release, None)
+
+    def _alloc(self, nbytes, ctx):
+        self.count += 1
+        if self.left > 0:
+            self.left -= 1
+            return None
+        return self.base.alloc(nbytes, ctx)
+
+
+@pytest.mark.parametrize("prec", [A.ADC2_C64, A.ADC2_BF16X3])
+def test_handle_switched_to_fp64(case, prec):
+    s, L, e, x, want = case
+    print(f"[case] set up in form {prec}, switched to FP64", flush=True)
+    for first in (noalloc, A.adc2_sigma):
+        h = A.adc2_setup(L, e, s.nc, s.no, s.nv, s.naux, prec=prec)
+        A.adc2_sigma(h, x)
+        A.adc2_set_precision(h, A.ADC2_FP64)
+        assert torch.equal(first(h, x), want)
+        assert torch.equal(A.adc2_sigma(h, x), want) and torch.equal(noalloc(h, x), want)
+        h.close()
+
+
+@pytest.mark.parametrize("refused", [1, 2])
+def test_after_a_refused_request(case, refused):
+    """A request of the handle refused once (its scratch goes) or twice (its static operands go too), then
+    served: the next sigma is what it was before."""
+    s, L, e, x, want = case
+    al = Refusing()
+    h = A.adc2_setup(L, e, s.nc, s.no, s.nv, s.naux, alloc=al.alloc)
+    assert torch.equal(A.adc2_sigma(h, x), want)
+    print(f"[case] {refused} refused", flush=True)
+    al.left = refused
+    w, _ = A.adc2_rayleigh(h, x)
+    assert al.left == 0 and np.all(np.isfinite(w))
+    assert torch.equal(A.adc2_sigma(h, x), want)
+    assert torch.equal(noalloc(h, x), want)
+    h.close()

@@ -102,7 +102,9 @@ struct adc2_handle_s {
   // residue engine of the FP64 form (rns.h): the two static operands, built with the
   // form or on first use, and the work space of one chunk of (vector, core) rows
   adc2::RnsMode rns_mode = adc2::RNS_AUTO;
-  bool rns_off = false;     // its memory was not to be had: the FP64 MFMA engines serve this handle
+  bool rns_off = false;     // its memory was not to be had: the FP64 MFMA engines serve the sigmas
+  size_t rns_short = 0;     // bytes a chunk aims at while memory is short (0: rns_target)
+  int rns_wait = 0;         // sigmas until what was short is asked for again (0: nothing was)
   char* rns_lvo = nullptr;  // residues of the valence rows of Lvo (rows (j,b), K = P), then their exponents
   char* rns_lvt = nullptr;  // residues of LvT (rows P, K = (j,d)), then their exponents
   char* rns_ws = nullptr;

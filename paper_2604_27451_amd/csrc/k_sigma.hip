@@ -1458,7 +1458,7 @@ struct RnsPlan {
   size_t f64, opnd, out, ex, norm, bytes;
 };
 static RnsPlan rns_plan(adc2_handle h, int rows, size_t target = 0) {
-  if (target == 0) target = h->rns_target;
+  if (target == 0) target = h->rns_short ? h->rns_short : h->rns_target;
   const Dims& d = h->d;
   const long ky = (long)d.no * d.nv;
   auto at = [&](int c) {
@@ -1566,14 +1566,27 @@ constexpr double OVERLAP_TERMS = 1e10;
 static bool overlap_sized(const Dims& d, double rows) { return rows * d.nv * d.naux * d.no * d.nv <= OVERLAP_TERMS; }
 static size_t overlap_base(adc2_handle h, int rows) { return (rns_plan(h, rows).bytes + 255) & ~size_t(255); }
 
-// The residue engine's buffers for m vectors; *ok = false (and the MFMA engines
-// from then on) where the memory is not to be had.  Where it is short, first the
+// The residue engine's buffers for m vectors; *ok = false (and the MFMA engines)
+// where the memory is not to be had.  Where it is short, first the
 // scratch of the MFMA engines and of the split-BF16 form goes (it is allocated again when
 // used: a two-stage solve at nc=6 no=120 nv=600 naux=3000 leaves 60 GB of it beside
 // a search space of 153 GB, and its FP64 stage took 1.9 s a sigma of ten vectors
-// on the MFMA engines, 0.63 s here), then chunks get smaller.
+// on the MFMA engines, 0.63 s here), then chunks get smaller.  What was short is
+// asked for again after RNS_WAIT sigmas of the handle (a request that fails and the
+// buffers freed and taken around it: some ms).
+constexpr int RNS_WAIT = 64;
+static void rns_tick(adc2_handle h, hipStream_t st) {
+  if (h->rns_wait == 0) return;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) != hipSuccess) (void)hipGetLastError();
+  if (cs != hipStreamCaptureStatusNone || --h->rns_wait > 0) return;
+  h->rns_short = 0;
+  h->rns_off = false;
+}
+
 static adc2_status rns_ready(adc2_handle h, int m, hipStream_t st, bool* ok) {
   *ok = false;
+  const Dims& d = h->d;
   auto spare = [&]() {
     if (!h->Zb && !h->XB && !h->RB) return false;
     dfree(h, h->Zb);
@@ -1588,17 +1601,21 @@ static adc2_status rns_ready(adc2_handle h, int m, hipStream_t st, bool* ok) {
     const adc2_status rc = rns_build_static(h, st);
     if (rc != ADC2_OK) return rc;
     if (h->rns_lvo && h->rns_lvt) {
-      const size_t one = rns_plan(h, m * h->d.nc).bytes;
-      if (h->side && !h->rns_lent && overlap_sized(h->d, m * h->d.nc) && rns_reserve(h, 2 * overlap_base(h, m * h->d.nc))) break;
-      if (rns_reserve(h, one)) break;
+      if (h->side && !h->rns_lent && h->rns_wait == 0 && overlap_sized(d, m * d.nc)) {
+        if (rns_reserve(h, 2 * overlap_base(h, m * d.nc))) break;
+        h->rns_wait = RNS_WAIT;
+      }
+      if (rns_reserve(h, rns_plan(h, m * d.nc).bytes)) break;
     }
+    if (h->rns_lent) return ADC2_OK;   // (sized before the array was lent)
     if (spare()) continue;
-    if (!h->rns_lvo || !h->rns_lvt || rns_plan(h, m * h->d.nc).c <= 1) {
+    h->rns_wait = RNS_WAIT;
+    if (!h->rns_lvo || !h->rns_lvt || rns_plan(h, m * d.nc).c <= 1) {
       rns_release(h);
       h->rns_off = true;
       return ADC2_OK;
     }
-    h->rns_target /= 2;
+    h->rns_short = (h->rns_short ? h->rns_short : h->rns_target) / 2;
   }
   *ok = true;
   return ADC2_OK;
@@ -1961,6 +1978,7 @@ adc2_status sigma_multi(int nreq, const SigReq* rq, hipStream_t st, bool allow_r
   std::vector<char> rns(nreq, 0);   // requests on the residue engine
   for (int q = 0; q < nreq; ++q) {
     adc2_handle h = rq[q].h;
+    if (!h->rns_lent) rns_tick(h, st);
     if (allow_rns && rns_wanted(h, rq[q].m)) {
       bool ok = false;
       if ((rc = ensure_ws(h, rq[q].m, false)) != ADC2_OK || (rc = rns_ready(h, rq[q].m, st, &ok)) != ADC2_OK) return rc;
@@ -2321,7 +2339,7 @@ extern "C" adc2_status adc2_sigma_noalloc(adc2_handle h, int m, const void* X, v
   };
   const bool rns = rns_wanted(h, m, true);   // then its own work spaces instead of Zb, in smaller chunks
   char* sws_rns = h->rns_ws;
-  const size_t swsb = h->rns_ws_bytes, starget = h->rns_target;
+  const size_t swsb = h->rns_ws_bytes, starget = h->rns_target, sshort = h->rns_short;
   h->X = take(p.x);
   h->Y = take(rns ? p.x : p.y);
   h->Zb = rns ? nullptr : take(p.zb);
@@ -2330,6 +2348,7 @@ extern "C" adc2_status adc2_sigma_noalloc(adc2_handle h, int m, const void* X, v
   if (rns) {
     h->rns_ws = reinterpret_cast<char*>(q);
     h->rns_lent = true;
+    h->rns_short = 0;
     h->rns_target = h->rns_ws_bytes = NOALLOC_SCRATCH_BYTES - (size_t)(q - static_cast<unsigned char*>(base));
   }
   h->ws_m = h->zb_m = m;
@@ -2341,6 +2360,7 @@ extern "C" adc2_status adc2_sigma_noalloc(adc2_handle h, int m, const void* X, v
   h->rns_ws = sws_rns;
   h->rns_ws_bytes = swsb;
   h->rns_target = starget;
+  h->rns_short = sshort;
   h->X = sX;
   h->Y = sY;
   h->Zb = sZb;

@@ -807,7 +807,7 @@ adc2_status rns_join(const RnsMat& A, const RnsMat& B, int col0, int ncols, int 
 // launches and part-filled rounds.
 bool rns_pays(adc2_handle h, long M, long N, long K, double rate) {
   if (h->rns_mode == RNS_ALWAYS) return K <= RNS_KMAX * RNS_SPLITS;
-  if (h->rns_off || h->rns_mode == RNS_NEVER || K > RNS_KMAX * RNS_SPLITS) return false;
+  if (h->rns_mode == RNS_NEVER || K > RNS_KMAX * RNS_SPLITS) return false;
   const double terms = (double)M * N * K;
   const double padded = 256.0 * rcdiv(M, 256) * 128.0 * rcdiv(N, 128) * K;
   const double rns = 6e-5 + padded * 8 / 225e12 + 1.25e-11 * ((double)M * K + (double)N * K) + 1e-11 * (double)M * N;
@@ -815,7 +815,6 @@ bool rns_pays(adc2_handle h, long M, long N, long K, double rate) {
 }
 
 static bool rns_grow(adc2_handle h, char** buf, size_t* have, size_t bytes) {
-  if (h->rns_off) return false;
   if (*have >= bytes) return true;
   if (h->rns_lent) return false;
   if (bytes > (size_t(256) << 20)) bytes = (bytes + (size_t(512) << 20) - 1) >> 29 << 29;   // few sizes: blocks are reused
@@ -862,7 +861,7 @@ void rns_release(adc2_handle h) {
 adc2_status rns_product(adc2_handle h, const RnsSrc& A, int M, const RnsSrc& B, int N, int K, const RnsDst& dst,
                         double rate, bool* done, hipStream_t st) {
   *done = false;
-  if (M <= 0 || N <= 0 || K <= 0 || h->rns_off || (rate > 0.0 && !rns_pays(h, M, N, K, rate))) return ADC2_OK;
+  if (M <= 0 || N <= 0 || K <= 0 || (rate > 0.0 && !rns_pays(h, M, N, K, rate))) return ADC2_OK;
   // K-splits: within the INT32 range (RNS_KMAX a split), and enough tiles for two a CU
   const long tiles = (long)RNS_PL * rcdiv(M, 256) * rcdiv(N, 128);
   const int nkc = rcdiv(K, RNS_KC);

@@ -78,3 +78,55 @@ def test_after_a_refused_request(case, refused):
     assert torch.equal(A.adc2_sigma(h, x), want)
     assert torch.equal(noalloc(h, x), want)
     h.close()
+
+
+class Sized(Refusing):
+    """PyTorch's allocator that refuses what `refuse` says, and notes the sizes."""
+
+    def __init__(self):
+        super().__init__()
+        self.refuse, self.sizes, self.refused = None, [], 0
+
+    def _alloc(self, nbytes, ctx):
+        self.sizes.append(nbytes)
+        if self.refuse is not None and self.refuse(nbytes):
+            self.refused += 1
+            return None
+        return self.base.alloc(nbytes, ctx)
+
+
+@pytest.mark.parametrize("case_", ["chunks", "engine"])
+def test_short_of_memory_for_a_while(monkeypatch, case_):
+    """Memory short during one sigma: smaller chunks, or (not even one row's work space) the FP64 MFMA engine;
+    64 sigmas later the handle asks for its whole work space again."""
+    monkeypatch.setenv("ADC2_ZGEMM", "rns")
+    s = make_system(2, 6, 40, 70, seed=952)
+    m = 8
+    al = Sized()
+    h = A.adc2_setup(dev(s.L), dev(s.eps), s.nc, s.no, s.nv, s.naux, alloc=al.alloc)
+    x = dev(random_vectors(7, m, h.dim))
+    al.sizes = []
+    want = A.adc2_sigma(h, x)
+    whole = max(al.sizes)
+    h.close()
+    zb = 16 * m * s.nc * s.no * s.nv * s.nv
+    one = 16 * s.nv * s.no * s.nv   # unpacked doubles of one row: less than its work space
+    print(f"[case] short for a while, {case_}, whole {whole}", flush=True)
+    al = Sized()
+    h = A.adc2_setup(dev(s.L), dev(s.eps), s.nc, s.no, s.nv, s.naux, alloc=al.alloc)
+    base = 16 * m * s.nc * s.naux * s.nv   # X, and Y in K-splits of it
+    al.refuse = (lambda n: n > whole // 8 and n % base) if case_ == "chunks" else (
+        lambda n: n > one and n != zb and n % base)
+    got = A.adc2_sigma(h, x)
+    assert al.refused > 0
+    assert torch.equal(got, want) == (case_ == "chunks")
+    assert float((got - want).abs().max() / want.abs().max()) < 1e-12
+    n = len(al.sizes)
+    assert torch.equal(A.adc2_sigma(h, x), got) and len(al.sizes) == n   # nothing is asked for meanwhile
+    al.refuse = None
+    for _ in range(64):
+        got = A.adc2_sigma(h, x)
+    assert whole in al.sizes[n:] and torch.equal(got, want)
+    n = len(al.sizes)
+    assert torch.equal(A.adc2_sigma(h, x), want) and len(al.sizes) == n
+    h.close()

@@ -1457,7 +1457,7 @@ struct RnsPlan {
   int c;
   size_t f64, opnd, out, ex, norm, bytes;
 };
-static RnsPlan rns_plan(adc2_handle h, int rows, size_t target = 0) {
+static RnsPlan rns_plan(adc2_handle h, int rows, size_t target = 0, bool whole = false) {
   if (target == 0) target = h->rns_short ? h->rns_short : h->rns_target;
   const Dims& d = h->d;
   const long ky = (long)d.no * d.nv;
@@ -1481,8 +1481,12 @@ static RnsPlan rns_plan(adc2_handle h, int rows, size_t target = 0) {
   };
   const double one = (double)at(1).bytes;
   const int most = (int)std::max(1.0, std::min((double)rows, std::floor((double)target / one)));
-  return at(cdiv(rows, cdiv(rows, most)));   // equal chunks
+  return at(whole ? most : cdiv(rows, cdiv(rows, most)));   // equal chunks
 }
+// Bytes that serve every block of up to `rows` rows (equal chunks of fewer rows may be the
+// longer ones): what a handle once had for m vectors is enough for fewer, so its buffers stay
+// where captured graphs found them.
+static size_t rns_most(adc2_handle h, int rows) { return rns_plan(h, rows, 0, true).bytes; }
 
 // Valence rows of Lvo as an operand: rows (j, b), K = P.
 static RnsSrc rns_lvo_rows(adc2_handle h) {
@@ -1597,15 +1601,17 @@ static adc2_status rns_ready(adc2_handle h, int m, hipStream_t st, bool* ok) {
     h->zb_m = h->wsb_m = 0;
     return true;
   };
+  // blocks of up to m vectors whose halves run side by side
+  const int side_m = (int)std::min<double>(m, OVERLAP_TERMS / ((double)d.nc * d.nv * d.naux * d.no * d.nv));
   for (;;) {
     const adc2_status rc = rns_build_static(h, st);
     if (rc != ADC2_OK) return rc;
     if (h->rns_lvo && h->rns_lvt) {
-      if (h->side && !h->rns_lent && h->rns_wait == 0 && overlap_sized(d, m * d.nc)) {
-        if (rns_reserve(h, 2 * overlap_base(h, m * d.nc))) break;
+      if (h->side && !h->rns_lent && h->rns_wait == 0 && side_m > 0) {
+        if (rns_reserve(h, std::max(rns_most(h, m * d.nc), 2 * ((rns_most(h, side_m * d.nc) + 255) & ~size_t(255))))) break;
         h->rns_wait = RNS_WAIT;
       }
-      if (rns_reserve(h, rns_plan(h, m * d.nc).bytes)) break;
+      if (rns_reserve(h, rns_most(h, m * d.nc))) break;
     }
     if (h->rns_lent) return ADC2_OK;   // (sized before the array was lent)
     if (spare()) continue;

@@ -130,3 +130,33 @@ def test_short_of_memory_for_a_while(monkeypatch, case_):
     n = len(al.sizes)
     assert torch.equal(A.adc2_sigma(h, x), want) and len(al.sizes) == n
     h.close()
+
+
+@pytest.mark.parametrize("nc,no,nv,naux,mb,most", [(1, 6, 40, 70, 8, 9), (6, 20, 200, 800, 0, 3)])
+def test_graph_outlives_smaller_sigmas(monkeypatch, nc, no, nv, naux, mb, most):
+    """A graph of a sigma of `most` vectors, then eager sigmas of fewer on the handle: the buffers stay where they
+    are.  (Fewer rows may make longer chunks: first case, 9 in three of 3, 8 in two of 4; fewer vectors may run
+    their halves side by side, each in a work space of its own: second case, two vectors of 3.8 10^9 terms.)"""
+    if mb:
+        monkeypatch.setenv("ADC2_ZGEMM", "rns")
+        monkeypatch.setenv("ADC2_RNS_MB", str(mb))
+    n = nc + no + nv
+    g = torch.Generator(device="cuda")
+    g.manual_seed(17)
+    L = 0.05 * torch.randn((naux, n, n), generator=g, dtype=torch.complex128, device="cuda")
+    L = 0.5 * (L + L.transpose(1, 2).conj()).contiguous()
+    e = dev(make_system(nc, no, nv, 1, seed=953).eps)
+    h = A.adc2_setup(L, e, nc, no, nv, naux)
+    del L
+    x = torch.randn((most, h.dim), generator=g, dtype=torch.complex128, device="cuda")
+    print(f"[case] graph and smaller sigmas {(nc, no, nv, naux)}", flush=True)
+    gr = A.adc2_graph_sigma_batch([h], [x])
+    want = A.adc2_sigma(h, x)
+    for m in range(1, most):
+        S = A.adc2_sigma(h, x[:m].contiguous())   # (X-build and back-contraction have other tiles for fewer rows)
+        assert float((S - want[:m]).abs().max() / want.abs().max()) < 1e-12
+        (got,) = gr.launch()
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+    gr.close()
+    h.close()

@@ -17,8 +17,8 @@
 // the operands, at most 2^-58.33 ||row|| in the real and the imaginary part of an
 // entry (||row|| 2^e lies in (2^57.33, 2^58.33], e being whole), that is about
 // 2^-59 ||a|| ||b|| rms in a product whatever K; the FP64 sum of the parts below
-// 2^-34 in the recombination, 2^-58 ||a|| ||b|| (times the number of K-runs, in
-// the worst case); and the final rounding to FP64.
+// 2^-34 in the recombination, at most 2^-60 ||a|| ||b|| for each K-run; and the final
+// rounding to FP64.
 //
 // A rounding set by the norm of the row is a loss where the large entries of one
 // row meet small ones of the other (rows that are graded, or that share only their
@@ -51,10 +51,10 @@
 // rows of zeros give exact zeros.
 #pragma once
 #include "internal.h"
+#include "rnsconst.h"
 
 namespace adc2 {
 
-constexpr int RNS_NM = 16;              // moduli
 constexpr int RNS_PL = 2 * RNS_NM;      // residue planes
 constexpr int RNS_NP = RNS_PL + 1;      // planes held: the last one the magnitude codes
 constexpr int RNS_RT = 128;             // rows per operand block

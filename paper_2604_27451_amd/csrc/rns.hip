@@ -11,95 +11,8 @@ typedef int i4v __attribute__((ext_vector_type(4)));
 
 static inline int rcdiv(long a, long b) { return (int)((a + b - 1) / b); }
 
-// ---------------------------------------------------------------------------
-// constants of the moduli
-// ---------------------------------------------------------------------------
-// Pairwise coprime products of primes = 1 mod 4 below 2^8 (221 = 13 * 17,
-// 205 = 5 * 41): the sixteen of largest product, log2 M = 117.7.
-constexpr int RNS_P[RNS_NM] = {241, 233, 229, 221, 205, 197, 193, 181, 173, 157, 149, 137, 113, 109, 101, 97};
-
-constexpr int cmod(long a, int p) { return (int)(((a % p) + p) % p); }
-constexpr int balanced(long a, int p) {
-  const int r = cmod(a, p);
-  return r > p / 2 ? r - p : r;
-}
-constexpr int inverse(long a, int p) {
-  for (int x = 1; x < p; ++x)
-    if (cmod(a * x, p) == 1) return x;
-  return 0;
-}
-constexpr int sqrt_m1(int p) {
-  for (int x = 1; x < p; ++x)
-    if (cmod((long)x * x, p) == p - 1) return x;
-  return 0;
-}
-
-// Split of an operand's scaled integers: v = sum_k d_k 256^k with signed bytes
-// d_k, so v mod p = sum_k d_k (256^k mod p): two 4-byte dot products.
-struct RnsSplit {
-  int re_lo, re_hi;    // bytes 256^k mod p
-  int im_lo, im_hi;    // bytes s 256^k mod p
-  float p, inv;
-};
-// Recombination of the moduli 2t and 2t + 1: with u = c+ + c- and w = c+ - c-,
-//   re / M = sum (u_1 kre1 + u_2 kre2) / (p1 p2) mod 1,  im / M the same with w, kim.
-struct RnsJoin {
-  int kre1, kre2, kim1, kim2;
-  double hi, lo;       // 1 / (p1 p2) = hi + lo, hi a multiple of 2^-34
-};
-struct RnsConst {
-  RnsSplit split[RNS_NM];
-  RnsJoin join[RNS_NM / 2];
-};
-
-constexpr RnsConst make_const() {
-  RnsConst c{};
-  for (int q = 0; q < RNS_NM; ++q) {
-    const int p = RNS_P[q], s = sqrt_m1(p);
-    unsigned r[2] = {0, 0}, m[2] = {0, 0};
-    long w = 1;
-    for (int k = 0; k < 8; ++k) {
-      r[k / 4] |= (unsigned)(balanced(w, p) & 255) << (8 * (k % 4));
-      m[k / 4] |= (unsigned)(balanced(w * s, p) & 255) << (8 * (k % 4));
-      w = (w * 256) % p;
-    }
-    c.split[q].re_lo = (int)r[0];
-    c.split[q].re_hi = (int)r[1];
-    c.split[q].im_lo = (int)m[0];
-    c.split[q].im_hi = (int)m[1];
-    c.split[q].p = (float)p;
-    c.split[q].inv = 1.0f / (float)p;
-  }
-  for (int t = 0; t < RNS_NM / 2; ++t) {
-    int kre[2] = {0, 0}, kim[2] = {0, 0};
-    for (int h = 0; h < 2; ++h) {
-      const int q = 2 * t + h, p = RNS_P[q], s = sqrt_m1(p);
-      long mp = 1;     // M / p mod p
-      for (int j = 0; j < RNS_NM; ++j)
-        if (j != q) mp = (mp * RNS_P[j]) % p;
-      const long ti = inverse(mp, p);
-      kre[h] = balanced(ti * inverse(2, p), p);
-      kim[h] = balanced(ti * inverse(2 * s, p), p);
-    }
-    const int p1 = RNS_P[2 * t], p2 = RNS_P[2 * t + 1];
-    const long pp = (long)p1 * p2, one = 1L << 34;
-    const long n = (one + pp / 2) / pp;
-    c.join[t].kre1 = kre[0] * p2;
-    c.join[t].kre2 = kre[1] * p1;
-    c.join[t].kim1 = kim[0] * p2;
-    c.join[t].kim2 = kim[1] * p1;
-    c.join[t].hi = (double)n / (double)one;
-    c.join[t].lo = (double)(one - n * pp) / (double)pp / (double)one;
-  }
-  return c;
-}
 __constant__ const RnsConst RNS_C = make_const();
 
-constexpr double rns_m() {
-  double m = 1.0;
-  for (int q = 0; q < RNS_NM; ++q) m *= RNS_P[q];
-  return m;
-}
 // 2^(2 G) <= M / 2: scaled rows of norm at most 2^G.  G = (log2 M - 1) / 2 less a margin
 // for the rounding of the entries (sqrt(2K) / 2 <= 2^8 against 2^58).
 constexpr double RNS_G = 58.33;
@@ -689,7 +602,7 @@ __global__ __launch_bounds__(256) void k_rns_join(int8_t* __restrict__ R, int nr
     const int row = row0 + (x >> 2) * 16 + (x & 3);
     if (row >= rows || !rns_serves(spread[x])) continue;
     const int er = ea[row];
-    double re = M * ((fr[x] - rint(fr[x])) + gr[x]), im = M * ((fi[x] - rint(fi[x])) + gi[x]);
+    double re = M * rns_frac(fr[x], gr[x]), im = M * rns_frac(fi[x], gi[x]);
     if (er == RNS_NAN || ec == RNS_NAN) {
       re = im = __builtin_nan("");
     } else {

@@ -1,0 +1,136 @@
+"""Recombination of the residue engine (csrc/rnsconst.h, rns.h) against whole-number arithmetic: the
+fraction z / M from residue sums of up to 32 K-runs, in the order of k_rns_join.
+
+Tolerance: the parts of hi are exact; the parts of lo are at most 0.018 (32 runs) and summed in eight
+FP64 fma, so the fraction is off by less than 8 * 0.018 * 2^-53 + 2^-54."""
+import ctypes
+import os
+import random
+import shutil
+import subprocess
+from fractions import Fraction
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "..", "paper_2604_27451_amd", "csrc")
+SHIM = r'''
+#include <cmath>
+#include "rnsconst.h"
+static constexpr adc2::RnsConst C = adc2::make_const();
+extern "C" void moduli(int* p) { for (int q = 0; q < adc2::RNS_NM; ++q) p[q] = adc2::RNS_P[q]; }
+extern "C" void join(const int* u, double* out) {   // u[2 q], u[2 q + 1]: sums of c+, c- of modulus q
+  double fr = 0, fi = 0, gr = 0, gi = 0;
+  for (int t = 0; t < adc2::RNS_NM / 2; ++t) {
+    const adc2::RnsJoin c = C.join[t];
+    const int* v = u + 4 * t;
+    const int yr = (v[0] + v[1]) * c.kre1 + (v[2] + v[3]) * c.kre2;
+    const int yi = (v[0] - v[1]) * c.kim1 + (v[2] - v[3]) * c.kim2;
+    fr = std::fma((double)yr, c.hi, fr);
+    gr = std::fma((double)yr, c.lo, gr);
+    fi = std::fma((double)yi, c.hi, fi);
+    gi = std::fma((double)yi, c.lo, gi);
+  }
+  out[0] = adc2::rns_frac(fr, gr);
+  out[1] = adc2::rns_frac(fi, gi);
+  out[2] = gr;
+  out[3] = gi;
+}
+'''
+G2 = 2.0 ** 116.66
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if not gxx:
+        pytest.skip("no g++")
+    d = tmp_path_factory.mktemp("rnsjoin")
+    (d / "shim.cpp").write_text(SHIM)
+    subprocess.run([gxx, "-O2", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(d / "shim.cpp"), "-o",
+                    str(d / "lib.so")], check=True)
+    return ctypes.CDLL(str(d / "lib.so"))
+
+
+def join(lib, u):
+    a, out = (ctypes.c_int * 32)(*u), (ctypes.c_double * 4)()
+    lib.join(a, out)
+    return list(out)
+
+
+def moduli(lib):
+    p = (ctypes.c_int * 16)()
+    lib.moduli(p)
+    return list(p)
+
+
+class Crt:
+    def __init__(self, P):
+        self.P, self.M = P, 1
+        for p in P:
+            self.M *= p
+        self.s = [next(x for x in range(1, p) if (x * x + 1) % p == 0) for p in P]
+        self.w = [self.M // p * pow(self.M // p, -1, p) for p in P]
+
+    def value(self, u):
+        """(re, im) in (-M/2, M/2] of the sums u of residues x + s y, x - s y."""
+        re = im = 0
+        for q, p in enumerate(self.P):
+            a, b = u[2 * q], u[2 * q + 1]
+            re += self.w[q] * ((a + b) * pow(2, -1, p) % p)
+            im += self.w[q] * ((a - b) * pow(2 * self.s[q], -1, p) % p)
+        half = self.M // 2
+        return tuple((v % self.M) - (self.M if v % self.M > half else 0) for v in (re, im))
+
+    def residues(self, re, im):
+        out = []
+        for q, p in enumerate(self.P):
+            for sg in (1, -1):
+                r = (re + sg * self.s[q] * im) % p
+                out.append(r - p if r > p // 2 else r)
+        return out
+
+
+TOL = 8 * 0.0185 * 2.0 ** -53 + 2.0 ** -54
+
+
+def check(lib, crt, u):
+    got = join(lib, u)
+    for g, z in zip(got, crt.value(u)):
+        if abs(z) > G2:
+            continue    # beyond what rows of norm 2^58.33 give
+        assert abs(Fraction(g) - Fraction(z, crt.M)) < TOL, (u, g, float(Fraction(z, crt.M)))
+    return got
+
+
+def test_products_of_one_and_more_runs(lib):
+    crt, rng = Crt(moduli(lib)), random.Random(5)
+    lim = int(G2)
+    for runs in (1, 2, 8, 32):
+        for _ in range(200):
+            re, im = rng.randint(-lim, lim), rng.randint(-lim, lim)
+            parts = [[rng.randint(-lim // runs, lim // runs) for _ in range(2)] for _ in range(runs - 1)]
+            parts.append([re - sum(p[0] for p in parts), im - sum(p[1] for p in parts)])
+            u = [sum(v) for v in zip(*(crt.residues(*p) for p in parts))]
+            assert crt.value(u) == (re, im)
+            check(lib, crt, u)
+
+
+def test_largest_low_parts(lib):
+    """Residue sums of 32 runs with every low part as large as it can be and of one sign, and z next to
+    the largest: the low parts take the fraction of the high ones past 1/2."""
+    crt, rng = Crt(moduli(lib)), random.Random(6)
+    P = crt.P
+    one = [join(lib, [1 if i == q else 0 for i in range(32)])[2:] for q in range(32)]   # low parts of each residue
+    past = 0
+    for part in (0, 1):
+        for sign in (1, -1):
+            for _ in range(6000):
+                u = []
+                for q in range(32):
+                    top = 32 * (P[q // 2] // 2)
+                    u.append((top if one[q][part] * sign > 0 else -top) if q < 28 else rng.randint(-top, top))
+                z = crt.value(u)[part]
+                got = check(lib, crt, u)
+                high = Fraction(z, crt.M) - Fraction(got[2 + part])
+                past += abs(z) <= G2 and abs(high) > Fraction(1, 2)
+    assert past > 0

@@ -421,9 +421,10 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm
   for (int t = 0; t < NB - 1; ++t) load(t);
   for (int t = 0; t < nkc; ++t) {
     // chunk t has landed when at most the NB - 2 later ones are outstanding;
-    // the barrier also ends every wave's reads of the stage that load() refills
+    // the barrier also ends every wave's reads of the stage that load() refills, so
+    // these have to have returned (lgkmcnt 0: the products before them need not stay before the barrier)
     constexpr int V = (NB - 2) * NL;
-    __builtin_amdgcn_s_waitcnt(0x0f70 | (V & 15) | ((V >> 4) << 14));
+    __builtin_amdgcn_s_waitcnt(0x0070 | (V & 15) | ((V >> 4) << 14));
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");

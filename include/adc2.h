@@ -125,7 +125,10 @@ typedef struct {
  * the returned memory must be device memory of the current device, aligned
  * to 256 bytes.  The library waits for the device to be idle before each
  * release, as hipFree does.  NULL, or alloc == NULL, selects hipMalloc and
- * hipFree.  The struct is copied at setup; ctx must stay valid for the
+ * hipFree; blocks that such handles free are kept for later requests of their
+ * size while a handle lives, at most 16 GiB a device (environment
+ * ADC2_POOL_MB; 0: none), none while less than an eighth of the device is
+ * free, and adc2_trim returns them.  The struct is copied at setup; ctx must stay valid for the
  * handle's lifetime.  Pinned host staging buffers and the handle-free
  * adc2_peak_probe still use the HIP allocators.
  */
@@ -156,6 +159,13 @@ typedef struct {
  */
 ADC2_API adc2_status adc2_setup(const void* L, const double* eps, int nc, int no, int nv,
                        int naux, int prec, const adc2_alloc* alloc, void* stream, adc2_handle* out);
+
+/*
+ * adc2_trim -- return the device blocks that are kept for later requests of
+ * handles on hipMalloc (see adc2_alloc) to the driver, on every device, for other
+ * allocators of the process.  *released (may be NULL): their bytes.  Any thread.
+ */
+ADC2_API adc2_status adc2_trim(size_t* released);
 
 /* Vector length nc*nv + nc*no*nv*(nv-1)/2 (0 for a NULL handle). */
 ADC2_API size_t adc2_dim(adc2_handle h);

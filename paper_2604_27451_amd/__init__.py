@@ -19,6 +19,7 @@ Functions mirror the C ABI names:
     adc2_get_m11(h) -> complex128 tensor
     adc2_get_diag(h) -> float64 tensor
     adc2_mp2_energy(h) -> float
+    adc2_trim() -> bytes returned to the driver
     adc2_destroy(h)
     adc2_last_error() -> str
 and the autograd wrapper
@@ -65,7 +66,7 @@ STATUS_NAMES = {0: "ADC2_OK", 1: "ADC2_ERR_ARG", 2: "ADC2_ERR_NOT_HERMITIAN", 3:
                 4: "ADC2_ERR_HIP", 5: "ADC2_ERR_NOCONV", 6: "ADC2_ERR_NONFINITE"}
 
 EXPORTS = ["adc2_setup", "adc2_dim", "adc2_sigma", "adc2_davidson", "adc2_set_precision",
-           "adc2_rayleigh", "adc2_omega_backward", "adc2_get_m11", "adc2_get_diag", "adc2_mp2_energy", "adc2_profile",
+           "adc2_rayleigh", "adc2_omega_backward", "adc2_get_m11", "adc2_get_diag", "adc2_mp2_energy", "adc2_trim", "adc2_profile",
            "adc2_kernel_stats", "adc2_destroy", "adc2_last_error", "adc2_setup_batch", "adc2_sigma_batch",
            "adc2_davidson_batch", "adc2_peak_probe", "adc2_autotune", "adc2_fns", "adc2_transition",
            "adc2_sigma_noalloc", "adc2_set_method", "adc2_graph_sigma_batch", "adc2_graph_launch",
@@ -191,6 +192,8 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.adc2_get_diag.restype = i
     lib.adc2_mp2_energy.argtypes = [vp, ctypes.POINTER(d)]
     lib.adc2_mp2_energy.restype = i
+    lib.adc2_trim.argtypes = [ctypes.POINTER(ctypes.c_size_t)]
+    lib.adc2_trim.restype = i
     lib.adc2_profile.argtypes = [vp, i]
     lib.adc2_profile.restype = i
     lib.adc2_kernel_stats.argtypes = [vp, ctypes.POINTER(KStat), i]
@@ -587,6 +590,13 @@ def adc2_get_diag(h: Handle, stream=None):
     out = torch.empty((h.dim,), dtype=torch.float64, device="cuda")
     _check(load().adc2_get_diag(h.ptr, ctypes.c_void_p(out.data_ptr()), _stream_ptr(stream)), "adc2_get_diag")
     return out
+
+
+def adc2_trim() -> int:
+    """Returns the device blocks kept for later requests of hipMalloc handles to the driver; their bytes."""
+    n = ctypes.c_size_t()
+    _check(load().adc2_trim(ctypes.byref(n)), "adc2_trim")
+    return int(n.value)
 
 
 def adc2_mp2_energy(h: Handle) -> float:

@@ -175,13 +175,23 @@ namespace adc2 {
 // up to several GB and give them back before they return; with a few handles
 // alive the driver then spent 0.1 to 1.8 s in single hipMalloc / hipFree calls
 // (a second-order transition of 0.1 s took up to 1.8 s).  Freed blocks are kept
-// for the next request of about their size: per device at most POOL_BYTES, all
-// of them returned to the driver when a request cannot be served and when the
-// last handle is destroyed.  A block enters the pool only after the device
+// for the next request of about their size: per device at most POOL_BYTES (environment
+// ADC2_POOL_MB, read once; 0: none), and none while less than an eighth of the
+// device is free, so that other allocators of the process are not short for it.
+// All of them go back to the driver when a request cannot be served, when the
+// last handle is destroyed and in adc2_trim.  A block enters the pool only after the device
 // was idle (as hipFree waits), so any stream and thread may take it.
 // ---------------------------------------------------------------------------
 namespace {
 constexpr size_t POOL_BYTES = size_t(16) << 30;
+constexpr size_t POOL_LOOK = size_t(64) << 20;   // blocks from this size on look at the free memory first
+size_t pool_cap() {
+  static const size_t cap = [] {
+    const char* v = getenv("ADC2_POOL_MB");
+    return v ? (size_t)std::max(0L, atol(v)) << 20 : POOL_BYTES;
+  }();
+  return cap;
+}
 struct Pool {
   std::mutex mu;
   int handles = 0;
@@ -198,9 +208,15 @@ struct Pool {
       if (b.dev == dev) n += b.bytes;
     return n;
   }
-  void flush() {
-    for (const Blk& b : idle) (void)hipFree(b.p);
-    idle.clear();
+  size_t flush(int dev = -1) {   // of one device, or of all
+    size_t n = 0;
+    for (size_t i = idle.size(); i-- > 0;) {
+      if (dev >= 0 && idle[i].dev != dev) continue;
+      n += idle[i].bytes;
+      (void)hipFree(idle[i].p);
+      idle.erase(idle.begin() + i);
+    }
+    return n;
   }
 };
 Pool& pool() {
@@ -262,7 +278,7 @@ static void pool_free(void* p) {
       P.live.erase(it);
     }
   }
-  if (b.bytes == 0 || b.bytes > POOL_BYTES / 2) {
+  if (b.bytes == 0 || b.bytes > pool_cap() / 2) {
     (void)hipFree(p);
     return;
   }
@@ -270,9 +286,16 @@ static void pool_free(void* p) {
   (void)hipGetDevice(&cur);
   if (cur != b.dev) (void)hipSetDevice(b.dev);
   (void)hipDeviceSynchronize();
+  size_t avail = 0, total = 0;
+  const bool tight = b.bytes >= POOL_LOOK && hipMemGetInfo(&avail, &total) == hipSuccess && avail < total / 8;
   if (cur != b.dev) (void)hipSetDevice(cur);
   std::lock_guard<std::mutex> lk(P.mu);
-  while (P.idle_bytes(b.dev) + b.bytes > POOL_BYTES) {   // the oldest go first
+  if (tight) {
+    (void)hipFree(p);
+    P.flush(b.dev);
+    return;
+  }
+  while (P.idle_bytes(b.dev) + b.bytes > pool_cap()) {   // the oldest go first
     int i = 0;
     while (P.idle[i].dev != b.dev) ++i;
     (void)hipFree(P.idle[i].p);
@@ -326,6 +349,13 @@ extern "C" {
 const char* adc2_last_error(void) { return g_last_error.c_str(); }
 
 size_t adc2_dim(adc2_handle h) { return h ? (size_t)h->d.dim : 0; }
+
+adc2_status adc2_trim(size_t* released) {
+  std::lock_guard<std::mutex> lk(pool().mu);
+  const size_t n = pool().flush();
+  if (released) *released = n;
+  return ADC2_OK;
+}
 
 adc2_status adc2_destroy(adc2_handle h) {
   free_handle(h);

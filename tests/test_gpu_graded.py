@@ -174,3 +174,26 @@ def test_setup_transition_and_adjoint(monkeypatch, nc, no, nv, naux):
     assert float((dL.cpu() - Lr).abs().max() / Lr.abs().max()) < 1e-12
     assert float((de.cpu() - er).abs().max() / er.abs().max()) < 1e-12
     h.close()
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
+def test_not_finite_as_the_fp64_sum(monkeypatch, bad):
+    """A singles and a doubles entry that are not finite: every doubles entry of sigma is NaN, infinite
+    (with its sign) or finite as on the FP64 MFMA engine."""
+    from synth import random_vectors
+    s = make_system(2, 3, 20, 30, seed=912)
+    x = random_vectors(4, 3, s.nc * s.nv + s.nc * s.no * s.nv * (s.nv - 1) // 2)
+    ns = s.nc * s.nv
+    x[1, ns + 5] = bad
+    x[1, 3] = bad
+    x[2] = 0.0
+    x[2, 7] = bad
+    got = {}
+    for engine in ("wide", "rns"):
+        monkeypatch.setenv("ADC2_ZGEMM", engine)
+        print(f"[case] {bad} on {engine}", flush=True)
+        h = A.adc2_setup(dev(s.L), dev(s.eps), s.nc, s.no, s.nv, s.naux)
+        S = torch.view_as_real(A.adc2_sigma(h, dev(x))[:, ns:])
+        got[engine] = (torch.isnan(S).cpu(), (torch.isinf(S) * torch.sign(S)).nan_to_num().cpu())
+        h.close()
+    assert all(torch.equal(a, b) for a, b in zip(got["wide"], got["rns"]))

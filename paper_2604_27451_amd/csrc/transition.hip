@@ -452,21 +452,29 @@ adc2_status tm_second_order(adc2_handle h, const double2* tau, const int2* dpair
   drop(ZA);
   drop(N1);
   drop(N2T);
-  // (kj|bc) at P1[(j,b)][(k,c)]
+  // (kj|bc) at P1[(j,b)][(k,c)]: rows (k, j), columns (b, c), straight into place on the residue
+  // engine; P1 takes the place of the MFMA tiles' intermediate, so that neither way holds both with
+  // the operands
   double2 *Koovv, *P1;
-  T2_TRY(alloc(&P1, (long)o * o * nv2));
-  // rows (k, j), columns (b, c), straight into place
-  T2_TRY(rns_product(h, rns_kmajor(h->Loo, (long)o * o, naux), o * o, rns_kmajor(h->Lvv, nv2, naux), (int)nv2, naux,
-                     RnsDst{P1, o, nv, nv * onv, nv, onv, 1, 1.0, false}, rns_vs_tile((long)o * o, nv2), &done, st));
+  done = false;
+  if (rns_pays(h, (long)o * o, nv2, naux, rns_vs_tile((long)o * o, nv2))) {
+    T2_TRY(alloc(&P1, (long)o * o * nv2));
+    T2_TRY(rns_product(h, rns_kmajor(h->Loo, (long)o * o, naux), o * o, rns_kmajor(h->Lvv, nv2, naux), (int)nv2, naux,
+                       RnsDst{P1, o, nv, nv * onv, nv, onv, 1, 1.0, false}, 0.0, &done, st));
+    if (!done) drop(P1);
+  }
   if (!done) {
     T2_TRY(alloc(&Koovv, (long)o * o * nv2));
     T2_TRY(gemm_rr(o * o, (int)nv2, naux, LooK, naux, false, LvvT, naux, false, Koovv, nv2, 1.0, false, st));
+  }
+  drop(LvvT);
+  drop(LooK);
+  if (!done) {
+    T2_TRY(alloc(&P1, (long)o * o * nv2));
     k_swap12<false><<<grid_for((long)o * o * nv2), 256, 0, st>>>(Koovv, o, onv, nv, P1);
     T2_TRY(launched("k_swap12"));
     drop(Koovv);
   }
-  drop(LvvT);
-  drop(LooK);
   // numerators of u for the pairs (I, j): hole ladder first (it writes Nt)
   double2 *Nt, *G;
   T2_TRY(alloc(&Nt, (long)nc * o * nv2));
@@ -481,9 +489,20 @@ adc2_status tm_second_order(adc2_handle h, const double2* tau, const int2* dpair
   // ring terms: R[I][a][(j,b)] and Rp[I][(j,b)][a], for every core I at once on
   // the residue engine, one core at a time on the MFMA tiles
   double2 *R, *Rp;
-  const int nI = rns_pays(h, nc * nv, onv, onv, rns_vs_tile(nv, onv)) ? nc : 1;
-  T2_TRY(alloc(&R, nI * nv * onv));
-  T2_TRY(alloc(&Rp, nI * onv * nv));
+  int nI = rns_pays(h, nc * nv, onv, onv, rns_vs_tile(nv, onv)) ? nc : 1;
+  if (nI > 1) {   // short of memory for all: one at a time
+    if (alloc(&R, nI * nv * onv) != ADC2_OK) {
+      nI = 1;
+    } else if (alloc(&Rp, nI * onv * nv) != ADC2_OK) {
+      drop(R);
+      nI = 1;
+    }
+    (void)hipGetLastError();
+  }
+  if (nI == 1) {
+    T2_TRY(alloc(&R, nv * onv));
+    T2_TRY(alloc(&Rp, onv * nv));
+  }
   for (int I = 0; I < nc; I += nI) {
     const int M = nI * nv;
     const double2 *Zi = ZT + (long)I * nv * naux, *Ti = Tph + (long)I * nv * onv;

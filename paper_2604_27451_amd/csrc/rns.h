@@ -33,9 +33,10 @@
 // rows: an exact zero on either engine (rows of blocks of a symmetry).  The
 // entries between, and those of rows that are not finite, are formed in FP64 by k_rns_fp64
 // (which ends at once where there are none); which they are depends on the two rows
-// and the K-splits alone, not on tiles or chunks.  The codes are one INT8 product
-// more to the 32 and a launch (nc=6 no=60 nv=300 naux=1500, ten vectors: 45.3 -> 46.9 ms;
-// the smallest sigma 106 -> 112 us).
+// and the K-splits alone, not on tiles or chunks.  Rows of like entries are known for that by the
+// counts of their codes (rns_flat), and tiles of such rows need no product of codes.  What the
+// codes cost there: nc=6 no=60 nv=300 naux=1500, ten vectors, 45.8 -> 46.6 ms; the smallest sigma
+// 106 -> 111 us.
 //
 // Measured against long double (nc=6 no=60 nv=300 naux=1500, a unit vector on a
 // singles entry, so that every doubles entry is one K = 1500 product): rms error
@@ -67,7 +68,7 @@ constexpr int RNS_NAN = 1 << 20;
 constexpr int RNS_SPLITS = 32;          // most K-splits of a product
 
 size_t rns_op_bytes(long rows, long K);                 // planes of an operand
-size_t rns_exp_bytes(long rows);                        // its exponents
+size_t rns_exp_bytes(long rows);                        // its exponents, code scales and counts
 size_t rns_norm_bytes(long rows);                       // work space of rns_pack
 size_t rns_out_bytes(long rows, long cols);             // planes of a product (one K-split)
 
@@ -90,7 +91,7 @@ struct RnsSrc {
 // 16 x 64 fragment is 1 KB in lane order.
 struct RnsMat {
   int8_t* p = nullptr;
-  int* e = nullptr;        // row exponents (RNS_NAN: a row that is not finite), then the rows' code scales
+  int* e = nullptr;        // row exponents (RNS_NAN: a row that is not finite), then the rows' code scales and counts
   RnsSrc src{};            // the FP64 entries, for what the integers do not serve
   int rows = 0, K = 0, nrt = 0, nkc = 0;
 };
@@ -122,6 +123,10 @@ inline RnsDst rns_rows(double2* C, long ldc, double alpha = 1.0, bool add = fals
 // K-splits of a long product: workgroups that walk 10^5 terms drift apart and lose
 // each other's panels in L2; runs of about 9000 keep them together (M=3072, N=1280, K=72000:
 // 2074 TOPS in one run, 2282 in eight; no difference at K = 18000).
+// (The number of runs decides which residues stand for a sum, and through the FP64 sums of the
+// low parts the last bits: it must not depend on the rows and columns of a chunk.  This one
+// and that of rns_product come from K, and from the whole M, N and K, so results are the same bits in
+// whatever chunks and tiles.)
 inline int rns_long_splits(long K) { return K > 20480 ? (int)((K + 9215) / 9216) : 1; }
 
 // Residues of an operand; buf, ebuf and nbuf hold the sizes above.

@@ -22,14 +22,14 @@ static_assert(rns_m() > 2.0 * (double)(1L << 58) * (double)(1L << 58) * 1.58, "2
 // sizes
 // ---------------------------------------------------------------------------
 constexpr int NORM_SPLIT = 64;
-constexpr float RNS_QRMS = 16.0f;      // magnitude code of an entry of its row's rms
-constexpr float RNS_SPREAD = 57.6f;    // least code product a term at which the integers serve (rns.h)
+constexpr size_t RNS_ROW = sizeof(int) + sizeof(float) + sizeof(unsigned long long);   // e, code scale, code counts of a row
 constexpr int RNS_QUNIT = 64;          // its image in the bytes that the products of the codes are kept in
 size_t rns_op_bytes(long rows, long K) { return (size_t)RNS_NP * rcdiv(rows, RNS_RT) * rcdiv(K, RNS_KC) * RNS_BLK; }
-size_t rns_exp_bytes(long rows) { return (sizeof(int) + sizeof(float)) * (size_t)rcdiv(rows, RNS_RT) * RNS_RT; }
+size_t rns_exp_bytes(long rows) { return RNS_ROW * (size_t)rcdiv(rows, RNS_RT) * RNS_RT; }
 size_t rns_norm_bytes(long rows) { return sizeof(double) * 3 * NORM_SPLIT * (size_t)rows; }
-// (two bytes a 32 x 32 block: whether k_rns_fp64 has entries in it)
-size_t rns_out_bytes(long rows, long cols) { return (size_t)(RNS_NP * 1024 + 2) * rcdiv(rows, 32) * rcdiv(cols, 32); }
+// (three bytes a 32 x 32 block more: two for k_rns_join to say whether k_rns_fp64 has entries in it, one for
+// k_rns_gemm, of which it uses one a tile, to say whether the tile's rows are flat)
+size_t rns_out_bytes(long rows, long cols) { return (size_t)(RNS_NP * 1024 + 3) * rcdiv(rows, 32) * rcdiv(cols, 32); }
 
 // ---------------------------------------------------------------------------
 // row exponents
@@ -60,8 +60,9 @@ struct RnsSums {
 // read of the operand): lane = row where rows are contiguous, a wave per row
 // where k is.
 // The largest e with ||row|| 2^e <= 2^RNS_G from the row's three sums
-// (and the scale of its magnitude codes, in units of 2^32 of the scaled integers)
-__device__ __forceinline__ void rns_exponent(double s0, double s1, double s2, int K, int* e, float* w) {
+// (and the scale of its magnitude codes, in units of 2^32 of the scaled integers, -1 for a zero row and
+// 0 for one that is not finite; the counts of its codes start at 0)
+__device__ __forceinline__ void rns_exponent(double s0, double s1, double s2, int K, int padded, int row, int* e) {
   double l2;   // log2 of the norm
   if (s0 >= 0x1p-900 && s0 <= 0x1p1000) l2 = 0.5 * log2(s0);
   else if (s0 > 1.0) l2 = 0.5 * log2(s1) + 540.0;   // above 2^500 (Inf where a row is not finite)
@@ -69,8 +70,17 @@ __device__ __forceinline__ void rns_exponent(double s0, double s1, double s2, in
   else if (s0 == 0.0) l2 = RNS_G;                   // zero row: e = 0
   else l2 = s0;                                     // NaN
   const int ex = isfinite(l2) ? (int)floor(RNS_G - 1e-9 - l2) : RNS_NAN;
-  *e = ex;
-  *w = ex == RNS_NAN ? 0.0f : RNS_QRMS * sqrtf((float)K) * exp2f(32.0f - (float)(l2 + ex));
+  e[row] = ex;
+  ((float*)(e + padded))[row] = ex == RNS_NAN ? 0.0f
+                                : s0 == 0.0 && s2 == 0.0 ? -1.0f
+                                                         : RNS_QRMS * sqrtf((float)K) * exp2f(32.0f - (float)(l2 + ex));
+  ((unsigned long long*)(e + 2 * padded))[row] = 0;
+}
+// (rows past the end: as zero rows)
+__device__ __forceinline__ void rns_no_row(int padded, int row, int* e) {
+  e[row] = 0;
+  ((float*)(e + padded))[row] = -1.0f;
+  ((unsigned long long*)(e + 2 * padded))[row] = 0;
 }
 
 __global__ __launch_bounds__(256) void k_rns_norm(const RnsSrc src, int rows, int K, double* __restrict__ part) {
@@ -112,12 +122,8 @@ __global__ __launch_bounds__(256) void k_rns_norm_k(const RnsSrc src, int rows, 
                                                     double* __restrict__ part, int* __restrict__ e) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  float* cw = (float*)(e + padded);
   if (row >= rows) {
-    if (gridDim.y == 1 && lane == 0 && row < padded) {
-      e[row] = 0;
-      cw[row] = 0.0f;
-    }
+    if (gridDim.y == 1 && lane == 0 && row < padded) rns_no_row(padded, row, e);
     return;
   }
   const double2* p = src.p + rns_row(src, row);
@@ -147,7 +153,7 @@ __global__ __launch_bounds__(256) void k_rns_norm_k(const RnsSrc src, int rows, 
     t.s[q] = v;
   }
   if (lane != 0) return;
-  if (gridDim.y == 1) rns_exponent(t.s[0], t.s[1], t.s[2], K, e + row, cw + row);
+  if (gridDim.y == 1) rns_exponent(t.s[0], t.s[1], t.s[2], K, padded, row, e);
   else
 #pragma unroll
     for (int q = 0; q < 3; ++q) part[((long)blockIdx.y * 3 + q) * rows + row] = t.s[q];
@@ -175,13 +181,8 @@ __global__ __launch_bounds__(1024) void k_rns_expo(const double* __restrict__ pa
   for (int t = 1; t < nw; ++t)
 #pragma unroll
     for (int q = 0; q < 3; ++q) s[q] += red[t][q][lane];
-  float* cw = (float*)(e + padded);
-  if (row < rows) {
-    rns_exponent(s[0], s[1], s[2], K, e + row, cw + row);
-  } else {
-    e[row] = 0;
-    cw[row] = 0.0f;
-  }
+  if (row < rows) rns_exponent(s[0], s[1], s[2], K, padded, row, e);
+  else rns_no_row(padded, row, e);
 }
 
 // ---------------------------------------------------------------------------
@@ -200,9 +201,10 @@ __global__ __launch_bounds__(1024) void k_rns_expo(const double* __restrict__ pa
 // (blockIdx.y), each part rounding the entries again.
 constexpr int RNS_MAGIC = 0x4B400000;   // 1.5 * 2^23 as a float: float(MAGIC + x) = 1.5 * 2^23 + x
 template <bool KLANE>
-__global__ __launch_bounds__(256, KLANE ? 3 : 4) void k_rns_pack(const RnsSrc src, int rows, int K,
-                                                                 const int* __restrict__ e, int nrt, int nkc,
+__global__ __launch_bounds__(256, KLANE ? 3 : 5) void k_rns_pack(const RnsSrc src, int rows, int K,
+                                                                 int* __restrict__ e, int nrt, int nkc,
                                                                  int8_t* __restrict__ dst) {
+  __shared__ unsigned cnt[4][64];   // codes of at least 4, 8 and 12, a byte each
   const int lane = threadIdx.x & 63, kg = threadIdx.x >> 6;
   const int rb = blockIdx.x % (2 * nrt), kc = blockIdx.x / (2 * nrt);
   const int row = rb * 64 + lane;
@@ -266,34 +268,48 @@ __global__ __launch_bounds__(256, KLANE ? 3 : 4) void k_rns_pack(const RnsSrc sr
     lo = (int)((unsigned)v ^ 0x80808080u);
     hi = (int)((unsigned)(v >> 32) ^ 0x80808080u);
   };
-  unsigned zeros = 0;   // exact zeros among the entries
-#pragma unroll
-  for (int u = 0; u < 16; ++u)
-    zeros |= (unsigned)((d[u].x | d[u].z | ((d[u].y | d[u].w) & 0x7fffffff)) == 0) << u;
-#pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    const double re = __hiloint2double(d[u].y, d[u].x), im = cs * __hiloint2double(d[u].w, d[u].z);
-    int a, b;
-    digits(re, a, b);
-    d[u].x = a;
-    d[u].y = b;
-    digits(im, a, b);
-    d[u].z = a;
-    d[u].w = b;
-  }
-  __builtin_amdgcn_sched_barrier(0);   // (interleaved with the loop above the codes cost 50 registers)
   auto top = [](int x) { return (float)(int)(((unsigned)x ^ 0x80808080u) - 0x80808080u); };   // the upper four bytes
-  i4v code;
-#pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    const float hr = top(d[u].y), hi = top(d[u].w);
-    const int c = (zeros >> u & 1) ? 0 : (int)fminf(fmaxf(cw * __builtin_amdgcn_sqrtf(fmaf(hr, hr, hi * hi)), 1.0f), 127.0f);
-    code[u >> 2] = (u & 3) ? code[u >> 2] | c << (8 * (u & 3)) : c;
-  }
-  const float magic = 12582912.0f;
   int8_t* out = dst + ((long)(rb >> 1) * nkc + kc) * RNS_BLK + ((rb & 1) * 4 + (lane >> 4)) * 1024 + kg * 256 + (lane & 15) * 16;
   const long ps = (long)nrt * nkc * RNS_BLK;
-  if (blockIdx.y == 0) *(i4v*)(out + RNS_PL * ps) = code;
+  int n4 = 0, n8 = 0, n12 = 0;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    bool zero[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int u = 4 * t + q;
+      const double re = __hiloint2double(d[u].y, d[u].x), im = cs * __hiloint2double(d[u].w, d[u].z);
+      zero[q] = (d[u].x | d[u].z | ((d[u].y | d[u].w) & 0x7fffffff)) == 0;
+      int a, b;
+      digits(re, a, b);
+      d[u].x = a;
+      d[u].y = b;
+      digits(im, a, b);
+      d[u].z = a;
+      d[u].w = b;
+    }
+    int cc = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float hr = top(d[4 * t + q].y), hi = top(d[4 * t + q].w);
+      const int c = zero[q] ? 0 : (int)fminf(fmaxf(cw * __builtin_amdgcn_sqrtf(fmaf(hr, hr, hi * hi)), 1.0f), 127.0f);
+      cc |= c << (8 * q);
+    }
+    n4 += __popc((cc + 0x7c7c7c7c) & 0x80808080);   // (codes are at most 127: no carry)
+    n8 += __popc((cc + 0x78787878) & 0x80808080);
+    n12 += __popc((cc + 0x74747474) & 0x80808080);
+    if (blockIdx.y == 0) *(int*)(out + RNS_PL * ps + 4 * t) = cc;
+    __builtin_amdgcn_sched_barrier(0);   // (all entries interleaved: 50 registers more)
+  }
+  const float magic = 12582912.0f;
+  cnt[kg][lane] = n4 | n8 << 8 | n12 << 16;
+  __syncthreads();
+  if (blockIdx.y == 0 && kg == 0 && ok) {
+    const unsigned n = cnt[0][lane] + cnt[1][lane] + cnt[2][lane] + cnt[3][lane];   // at most 64 each
+    if (n)
+      atomicAdd((unsigned long long*)(e + 2 * nrt * RNS_RT) + row,
+                (unsigned long long)(n & 255) | (unsigned long long)(n >> 8 & 255) << 21 | (unsigned long long)(n >> 16) << 42);
+  }
   const int nq = RNS_NM / gridDim.y;
   for (int q = blockIdx.y * nq; q < (int)(blockIdx.y + 1) * nq; ++q) {
     const RnsSplit c = RNS_C.split[q];
@@ -356,6 +372,36 @@ adc2_status rns_pack(const RnsSrc& src, int rows, int K, int8_t* buf, int* ebuf,
 }
 
 // ---------------------------------------------------------------------------
+// which entries the integers serve
+// ---------------------------------------------------------------------------
+// Two flat rows, of which at least 0.78 K codes are 4 or more, 0.60 K 8 or more and 0.36 K 12 or
+// more (RNS_FLAT; 0.94, 0.78 and 0.57 for normal complex entries), have, in whatever order, a sum of
+// |a_k| |b_k| of at least 28.8 / 256 ||a|| ||b|| (the smaller entries of each against the
+// larger of the other: 2 * 0.14 * 4 * 12 + 2 * 0.04 * 4 * 8 + 0.20 * 8 * 8), above the 0.1 of rns.h: their products
+// need no code product, and a tile of such rows forms none (with it in every tile the product took 4.4%
+// longer, so 1.3% at nc=6 no=60 nv=300).  A zero row likewise.
+struct RnsRows {
+  const int* e;      // exponents, then code scales and counts
+  int padded, n4, n8, n12;
+};
+__device__ __forceinline__ bool rns_flat(const RnsRows& r, int row) {
+  const float w = ((const float*)(r.e + r.padded))[row];
+  const unsigned long long n = ((const unsigned long long*)(r.e + 2 * r.padded))[row];
+  return w < 0.0f || (w > 0.0f && (int)(n & 0x1fffff) >= r.n4 && (int)(n >> 21 & 0x1fffff) >= r.n8 &&
+                      (int)(n >> 42) >= r.n12);
+}
+static RnsRows rns_rows_of(const RnsMat& m) {
+  return RnsRows{m.e, m.nrt * RNS_RT, (int)std::ceil(RNS_FLAT[0] * m.K), (int)std::ceil(RNS_FLAT[1] * m.K),
+                 (int)std::ceil(RNS_FLAT[2] * m.K)};
+}
+
+// The bytes that k_rns_gemm keeps of the code products of an entry's K-runs, summed:
+// 2^16 a run with common terms, plus its code product in units of the bound / RNS_QUNIT
+__device__ __forceinline__ int rns_spread(int byte) { return byte == 0 ? 0 : 0x10000 + byte - 1; }
+// no common terms (an exact zero), or enough of them
+__device__ __forceinline__ bool rns_serves(int spread) { return spread == 0 || (spread & 0xffff) >= RNS_QUNIT; }
+
+// ---------------------------------------------------------------------------
 // the product of one plane:  C[i][j] = sum_k A[i][k] B[j][k] mod p
 // ---------------------------------------------------------------------------
 // Tiles of 128 WM x 64 WN on WM WN waves of 128 x 64 (v_mfma_i32_16x16x64_i8,
@@ -370,7 +416,7 @@ adc2_status rns_pack(const RnsSrc& src, int rows, int K, int8_t* buf, int* ebuf,
 template <int WM, int WN, int NB>
 __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm(
     const int8_t* __restrict__ A, const int8_t* __restrict__ B, int nrtA, int nrtB, int brt0, int nkca, int nkcs, int nbm,
-    int nbn, int nrb, int ncb, float qs, int8_t* __restrict__ C) {
+    int nbn, int nrb, int ncb, float qs, const RnsRows ra, const RnsRows rb_, int8_t* __restrict__ C) {
   constexpr int BM = 128 * WM, BN = 64 * WN, T = 64 * WM * WN;
   constexpr int SB = (BM + BN) * RNS_KC, NL = SB / (T * 16), NLA = BM * RNS_KC / (T * 16);
   __shared__ __align__(16) int8_t s[NB][SB];
@@ -389,6 +435,18 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm
   const int per = 8 * nbn, grp = t0 / per, gm = min(8, nbm - grp * 8), r = t0 - grp * per;
   const int bm = grp * 8 + r % gm, bn = r / gm;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  if (codes) {   // none needed where all rows are flat (every wave looks: an LDS reduction beside the ring
+                 // would have the compiler wait for all loads before each fragment read)
+    bool uneven = false;
+    for (int r = lane; r < BM + BN; r += 64) {
+      const bool isa = r < BM;
+      const int row = isa ? bm * BM + r : brt0 * RNS_RT + bn * BN + r - BM;
+      if (row < (isa ? ra.padded : rb_.padded)) uneven = uneven || !rns_flat(isa ? ra : rb_, row);
+    }
+    const bool flat = __ballot(uneven) == 0;
+    if (tid == 0) C[(long)(gridDim.x / nt) * nrb * ncb * 1024 + 2L * nrb * ncb + bm * nbn + bn] = flat;
+    if (flat) return;
+  }
   // global address of each of this thread's NL pieces of a stage (chunk 0)
   const int8_t* src[NL];
 #pragma unroll
@@ -485,35 +543,31 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm
   });
 }
 
-adc2_status rns_gemm(const RnsMat& A, const RnsMat& B, int col0, int ncols, int nsplit, int8_t* out, hipStream_t st) {
-  const int nrb = rcdiv(A.rows, 32), ncb = rcdiv(ncols, 32);
+// 256 x 128 tiles rather than 128 x 256
+static bool rns_tall(const RnsMat& A, int ncols, int nsplit) {
   // 256 x 128 or 128 x 256 tiles: the one that pads less, weighed by its rate (256 x
   // 128 is 2% the faster one at K = 1500, the other 1 to 4% from K = 3000 on)
-  const int nkcs = rcdiv(A.nkc, nsplit);
-  const float qs = RNS_QUNIT / (RNS_SPREAD * (float)A.K);
   const double tall = 256.0 * rcdiv(A.rows, 256) * 128.0 * rcdiv(ncols, 128);
-  const double flat = 128.0 * rcdiv(A.rows, 128) * 256.0 * rcdiv(ncols, 256) * (nkcs < 40 ? 1.02 : 0.98);
-  if (tall <= flat) {
+  const double flat = 128.0 * rcdiv(A.rows, 128) * 256.0 * rcdiv(ncols, 256) * (rcdiv(A.nkc, nsplit) < 40 ? 1.02 : 0.98);
+  return tall <= flat;
+}
+
+adc2_status rns_gemm(const RnsMat& A, const RnsMat& B, int col0, int ncols, int nsplit, int8_t* out, hipStream_t st) {
+  const int nrb = rcdiv(A.rows, 32), ncb = rcdiv(ncols, 32), nkcs = rcdiv(A.nkc, nsplit);
+  const float qs = RNS_QUNIT / (RNS_SPREAD * (float)A.K);
+  const RnsRows ra = rns_rows_of(A), rb = rns_rows_of(B);
+  if (rns_tall(A, ncols, nsplit)) {
     const int nbm = rcdiv(A.rows, 256), nbn = rcdiv(ncols, 128);
     k_rns_gemm<2, 2, 3><<<(unsigned)((long)nsplit * RNS_NP * nbm * nbn), 256, 0, st>>>(
-        A.p, B.p, A.nrt, B.nrt, col0 / RNS_RT, A.nkc, nkcs, nbm, nbn, nrb, ncb, qs, out);
+        A.p, B.p, A.nrt, B.nrt, col0 / RNS_RT, A.nkc, nkcs, nbm, nbn, nrb, ncb, qs, ra, rb, out);
   } else {
     const int nbm = rcdiv(A.rows, 128), nbn = rcdiv(ncols, 256);
     k_rns_gemm<1, 4, 3><<<(unsigned)((long)nsplit * RNS_NP * nbm * nbn), 256, 0, st>>>(
-        A.p, B.p, A.nrt, B.nrt, col0 / RNS_RT, A.nkc, nkcs, nbm, nbn, nrb, ncb, qs, out);
+        A.p, B.p, A.nrt, B.nrt, col0 / RNS_RT, A.nkc, nkcs, nbm, nbn, nrb, ncb, qs, ra, rb, out);
   }
   ADC2_CHECK_LAUNCH();
   return ADC2_OK;
 }
-
-// ---------------------------------------------------------------------------
-// which entries the integers serve
-// ---------------------------------------------------------------------------
-// The bytes that k_rns_gemm keeps of the code products of an entry's K-runs, summed:
-// 2^16 a run with common terms, plus its code product in units of the bound / RNS_QUNIT
-__device__ __forceinline__ int rns_spread(int byte) { return byte == 0 ? 0 : 0x10000 + byte - 1; }
-// no common terms (an exact zero), or enough of them
-__device__ __forceinline__ bool rns_serves(int spread) { return spread == 0 || (spread & 0xffff) >= RNS_QUNIT; }
 
 // ---------------------------------------------------------------------------
 // recombination
@@ -526,8 +580,8 @@ __device__ __forceinline__ bool rns_serves(int spread) { return spread == 0 || (
 // per entry.
 template <bool SPLIT>
 __global__ __launch_bounds__(256) void k_rns_join(int8_t* __restrict__ R, int nrb, int ncb, int rows, int cols,
-                                                   int nsplit, const int* __restrict__ ea, const int* __restrict__ eb,
-                                                   const RnsDst dst) {
+                                                   int nsplit, const RnsRows ra, const RnsRows rb_, int col0,
+                                                   int tr, int tc, int nbn, const RnsDst dst) {
   const int ncp = (ncb + 1) >> 1;
   const int rb = blockIdx.x / ncp;
   const int cb = 2 * (blockIdx.x % ncp) + (threadIdx.x >> 7);
@@ -537,6 +591,31 @@ __global__ __launch_bounds__(256) void k_rns_join(int8_t* __restrict__ R, int nr
   const int row0 = rb * 32 + 4 * (lane >> 4);   // rows row0 + {0..3} and row0 + 16 + {0..3}
   const long ps = (long)nrb * ncb * 1024;
   const int8_t* src = R + ((long)rb * ncb + cb) * 1024 + item * 8;
+  if (col >= cols) return;
+  // which entries the integers serve: all of them in a tile of flat rows (tiles of 2^tr x 2^tc blocks)
+  const int8_t* fl = R + (long)nsplit * RNS_NP * ps;
+  unsigned serve = 255;
+  if (!fl[2L * nrb * ncb + (rb >> tr) * nbn + (cb >> tc)]) {
+    serve = 0;
+    int spread[8];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) spread[x] = 0;
+    for (int s = 0; s < nsplit; ++s) {
+      const int2 v = *(const int2*)(src + ((long)s * RNS_NP + RNS_PL) * ps);
+#pragma unroll
+      for (int x = 0; x < 8; ++x) spread[x] += rns_spread(((x < 4 ? v.x : v.y) >> (8 * (x & 3))) & 255);
+    }
+    const bool cflat = rns_flat(rb_, col0 + col);
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+      const int row = row0 + (x >> 2) * 16 + (x & 3);
+      serve |= (unsigned)(row >= rows || rns_serves(spread[x]) || (cflat && rns_flat(ra, row))) << x;
+    }
+  }
+  // (lane 0 has the block's first column, which is there)
+  const bool any = __ballot(serve != 255) != 0;
+  if ((threadIdx.x & 63) == 0)
+    R[(long)nsplit * RNS_NP * ps + ((long)rb * ncb + cb) * 2 + (item >> 6)] = any;
   double fr[8], fi[8], gr[8], gi[8];
 #pragma unroll
   for (int x = 0; x < 8; ++x) fr[x] = fi[x] = gr[x] = gi[x] = 0.0;
@@ -575,33 +654,15 @@ __global__ __launch_bounds__(256) void k_rns_join(int8_t* __restrict__ R, int nr
       gi[x] = fma(di, c.lo, gi[x]);
     }
   }
-  if (col >= cols) return;
-  int spread[8];
-  {
-    int2 v = *(const int2*)(src + RNS_PL * ps);
-#pragma unroll
-    for (int x = 0; x < 8; ++x) spread[x] = rns_spread(((x < 4 ? v.x : v.y) >> (8 * (x & 3))) & 255);
-    if constexpr (SPLIT)
-      for (int s = 1; s < nsplit; ++s) {
-        v = *(const int2*)(src + ((long)s * RNS_NP + RNS_PL) * ps);
-#pragma unroll
-        for (int x = 0; x < 8; ++x) spread[x] += rns_spread(((x < 4 ? v.x : v.y) >> (8 * (x & 3))) & 255);
-      }
-  }
-  bool left = false;   // entries for k_rns_fp64 (lane 0 has the block's first column, which is there)
-#pragma unroll
-  for (int x = 0; x < 8; ++x) left = left || (row0 + (x >> 2) * 16 + (x & 3) < rows && !rns_serves(spread[x]));
-  const bool any = __ballot(left) != 0;
-  if ((threadIdx.x & 63) == 0)
-    R[(long)nsplit * RNS_NP * ps + ((long)rb * ncb + cb) * 2 + (item >> 6)] = any;
-  const int ec = eb[col];
+  const int* ea = ra.e;
+  const int ec = rb_.e[col0 + col];
   constexpr double M = rns_m();
   const int jj = dst.j0 + col, cg = jj / dst.ji;
   double2* pc = dst.C + (long)cg * dst.jg + (long)(jj - cg * dst.ji) * dst.jx;
 #pragma unroll
   for (int x = 0; x < 8; ++x) {
     const int row = row0 + (x >> 2) * 16 + (x & 3);
-    if (row >= rows || !rns_serves(spread[x])) continue;
+    if (row >= rows || !(serve >> x & 1)) continue;
     const int er = ea[row];
     double re = M * rns_frac(fr[x], gr[x]), im = M * rns_frac(fi[x], gi[x]);
     if (er == RNS_NAN || ec == RNS_NAN) {
@@ -637,7 +698,7 @@ struct SrcRns {
 template <int MAPA, int MAPB>
 __global__ __launch_bounds__(256) void k_rns_fp64(const RnsSrc A, const RnsSrc B, int col0, int rows, int cols, int K,
                                                    const int8_t* __restrict__ R, int nrb, int ncb, int nsplit,
-                                                   const RnsDst dst) {
+                                                   const RnsRows ra, const RnsRows rb_, const RnsDst dst) {
   __shared__ TileSmem s;
   __shared__ unsigned char own[64][64];
   __shared__ unsigned long long todo[4];   // the tiles that have such entries
@@ -672,7 +733,8 @@ __global__ __launch_bounds__(256) void k_rns_fp64(const RnsSrc A, const RnsSrc B
         for (int x = 0; x < 16; ++x) {   // register order of the 16 x 16 blocks of k_rns_gemm
           const int q = x >> 2, r = 32 * br + 16 * (q & 1) + 4 * (lane >> 4) + (x & 3);
           const int c = 32 * bc + 16 * (q >> 1) + (lane & 15);
-          own[r][c] = (unsigned char)(!rns_serves(spread[x]) && i0 + r < rows && j0 + c < cols);
+          own[r][c] = (unsigned char)(i0 + r < rows && j0 + c < cols && !rns_serves(spread[x]) &&
+                                      !(rns_flat(ra, i0 + r) && rns_flat(rb_, col0 + j0 + c)));
         }
         Acc acc;
         acc.zero();
@@ -696,12 +758,18 @@ adc2_status rns_join(const RnsMat& A, const RnsMat& B, int col0, int ncols, int 
                      hipStream_t st) {
   const int nrb = rcdiv(A.rows, 32), ncb = rcdiv(ncols, 32);
   const unsigned nblk = (unsigned)((long)nrb * ((ncb + 1) / 2));
-  if (nsplit > 1) k_rns_join<true><<<nblk, 256, 0, st>>>(out, nrb, ncb, A.rows, ncols, nsplit, A.e, B.e + col0, dst);
-  else k_rns_join<false><<<nblk, 256, 0, st>>>(out, nrb, ncb, A.rows, ncols, 1, A.e, B.e + col0, dst);
+  const RnsRows ra = rns_rows_of(A), rb = rns_rows_of(B);
+  const bool tall = rns_tall(A, ncols, nsplit);
+  const int tr = tall ? 3 : 2, tc = tall ? 2 : 3, nbn = rcdiv(ncols, tall ? 128 : 256);
+  if (nsplit > 1)
+    k_rns_join<true><<<nblk, 256, 0, st>>>(out, nrb, ncb, A.rows, ncols, nsplit, ra, rb, col0, tr, tc, nbn, dst);
+  else
+    k_rns_join<false><<<nblk, 256, 0, st>>>(out, nrb, ncb, A.rows, ncols, 1, ra, rb, col0, tr, tc, nbn, dst);
   ADC2_CHECK_LAUNCH();
   const unsigned ntile = (unsigned)std::min<long>(512, (long)((nrb + 1) / 2) * ((ncb + 1) / 2));
-#define RNS_FP64(MA_, MB_)                                                                                      \
-  k_rns_fp64<MA_, MB_><<<ntile, 256, 0, st>>>(A.src, B.src, col0, A.rows, ncols, A.K, out, nrb, ncb, nsplit, dst)
+#define RNS_FP64(MA_, MB_)                                                                                \
+  k_rns_fp64<MA_, MB_><<<ntile, 256, 0, st>>>(A.src, B.src, col0, A.rows, ncols, A.K, out, nrb, ncb, nsplit, ra, \
+                                              rb, dst)
   const bool ak = A.src.rx == 1, bk = B.src.rx == 1;   // contiguous along the rows
   if (ak && bk) RNS_FP64(KMAJOR, KMAJOR);
   else if (ak) RNS_FP64(KMAJOR, RMAJOR);

@@ -89,6 +89,13 @@ constexpr double rns_m() {
   for (int q = 0; q < RNS_NM; ++q) m *= RNS_P[q];
   return m;
 }
+// Magnitude codes of the entries of an operand (rns.h): the code of an entry of its row's rms, the
+// least code product a term at which the integers serve an entry, and the parts of a flat row's codes that
+// are at least 4, 8 and 12.
+constexpr float RNS_QRMS = 16.0f;
+constexpr float RNS_SPREAD = 57.6f;
+constexpr double RNS_FLAT[3] = {0.78, 0.60, 0.36};
+
 // hi + lo modulo 1, in [-1/2, 1/2]; |hi| < 2^50.  hi comes as an exact sum, so its whole part goes
 // first; lo may carry the rest past 1/2 (0.018 at 32 K-runs, against 0.0106 between the largest
 // |z| / M and 1/2), so it is reduced as well.

@@ -17,6 +17,11 @@ SHIM = r'''
 #include <cmath>
 #include "rnsconst.h"
 static constexpr adc2::RnsConst C = adc2::make_const();
+extern "C" void rule(double* r) {
+  r[0] = adc2::RNS_QRMS;
+  r[1] = adc2::RNS_SPREAD;
+  for (int i = 0; i < 3; ++i) r[2 + i] = adc2::RNS_FLAT[i];
+}
 extern "C" void moduli(int* p) { for (int q = 0; q < adc2::RNS_NM; ++q) p[q] = adc2::RNS_P[q]; }
 extern "C" void join(const int* u, double* out) {   // u[2 q], u[2 q + 1]: sums of c+, c- of modulus q
   double fr = 0, fi = 0, gr = 0, gi = 0;
@@ -134,3 +139,64 @@ def test_largest_low_parts(lib):
                 high = Fraction(z, crt.M) - Fraction(got[2 + part])
                 past += abs(z) <= G2 and abs(high) > Fraction(1, 2)
     assert past > 0
+
+
+# ---- which entries the integers serve: sum |a| |b| >= 0.1 ||a|| ||b|| (csrc/rns.h) ----
+def rule(lib):
+    r = (ctypes.c_double * 5)()
+    lib.rule(r)
+    return list(r)
+
+
+def codes(a, qrms):
+    import numpy as np
+    q = np.floor(qrms * np.sqrt(len(a)) * np.abs(a) / np.sqrt((np.abs(a) ** 2).sum()))
+    return np.where(a == 0, 0, np.clip(q, 1, 127))
+
+
+def rows(K):
+    """Rows of many kinds: like entries, real ones, spread over decades, blocks, few large ones."""
+    import numpy as np
+    rng = np.random.default_rng(K)
+    g = lambda: rng.standard_normal(K) + 1j * rng.standard_normal(K)
+    out = [g(), rng.standard_normal(K) + 0j, np.ones(K) + 0j]
+    out += [g() * 10.0 ** (s * rng.standard_normal(K)) for s in (0.3, 0.6, 1.0, 2.0)]
+    out += [g() * np.where(np.arange(K) < f * K, 1.0, t) for f in (0.02, 0.3, 0.5, 0.8) for t in (0.0, 1e-8, 0.05, 0.3)]
+    out += [g() * np.where(np.arange(K) >= f * K, 1.0, t) for f in (0.1, 0.5, 0.7) for t in (0.0, 1e-8, 0.05, 0.3)]
+    out += [g() * 10.0 ** (-6.0 * np.arange(K) / K), g() * 10.0 ** (-6.0 * (K - np.arange(K)) / K)]
+    return out
+
+
+@pytest.mark.parametrize("K", [37, 150, 1500])
+def test_rows_that_the_integers_serve(lib, K):
+    import numpy as np
+    qrms, spread, *flat = rule(lib)
+    rs = rows(K)
+    qs = [codes(r, qrms) for r in rs]
+    fl = [all((q >= 4 * (i + 1)).sum() >= np.ceil(f * K) for i, f in enumerate(flat)) for q in qs]
+    served = refused = 0
+    for a, qa, fa in zip(rs, qs, fl):
+        for b, qb, fb in zip(rs, qs, fl):
+            cos = (np.abs(a) * np.abs(b)).sum() / np.sqrt((np.abs(a) ** 2).sum() * (np.abs(b) ** 2).sum())
+            if (qa * qb).sum() >= spread * K or (fa and fb):
+                served += 1
+                assert cos >= 0.099
+            else:
+                refused += 1
+    assert served and refused
+    if K == 1500:
+        assert fl[0] and not any(fl[4:7])   # normal complex entries are flat, entries over decades are not
+
+
+def test_bounds_of_the_rule(lib):
+    """The worst rows: code products of flat rows in opposite order; codes rounded up to 1."""
+    qrms, spread, f4, f8, f12 = rule(lib)
+    N = 10000
+    q = [0.0] * N                      # a flat row at its limits, smallest first
+    for f, c in ((f4, 4), (f8, 8), (f12, 12)):
+        for i in range(round((1 - f) * N), N):
+            q[i] = c
+    worst = sum(x * y for x, y in zip(q, reversed(q))) / N
+    assert worst >= 0.1 * qrms ** 2
+    # codes are at most the scaled magnitudes but where these are below 1: at most sqrt(K sum max(q, 1)^2) on each side
+    assert spread - 2 * (qrms ** 2 + 1) ** 0.5 >= 0.0995 * qrms ** 2

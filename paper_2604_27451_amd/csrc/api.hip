@@ -184,7 +184,9 @@ namespace adc2 {
 // ---------------------------------------------------------------------------
 namespace {
 constexpr size_t POOL_BYTES = size_t(16) << 30;
-constexpr size_t POOL_LOOK = size_t(64) << 20;   // blocks from this size on look at the free memory first
+// blocks from this size on look at the free memory first, at most every 50 ms (a look costs 30 us)
+constexpr size_t POOL_LOOK = size_t(64) << 20;
+constexpr std::chrono::milliseconds POOL_AGAIN(50);
 size_t pool_cap() {
   static const size_t cap = [] {
     const char* v = getenv("ADC2_POOL_MB");
@@ -202,6 +204,11 @@ struct Pool {
   };
   std::map<void*, std::pair<size_t, int>> live;   // size and device of the blocks handed out
   std::vector<Blk> idle;
+  struct Look {
+    std::chrono::steady_clock::time_point at{};
+    bool tight = false;
+  };
+  std::map<int, Look> looks;   // by device
   size_t idle_bytes(int dev) const {
     size_t n = 0;
     for (const Blk& b : idle)
@@ -286,11 +293,20 @@ static void pool_free(void* p) {
   (void)hipGetDevice(&cur);
   if (cur != b.dev) (void)hipSetDevice(b.dev);
   (void)hipDeviceSynchronize();
+  bool look = false;
+  if (b.bytes >= POOL_LOOK) {
+    std::lock_guard<std::mutex> lk(P.mu);
+    Pool::Look& l = P.looks[b.dev];
+    const auto now = std::chrono::steady_clock::now();
+    look = now - l.at >= POOL_AGAIN;
+    if (look) l.at = now;
+  }
   size_t avail = 0, total = 0;
-  const bool tight = b.bytes >= POOL_LOOK && hipMemGetInfo(&avail, &total) == hipSuccess && avail < total / 8;
+  const bool seen = look && hipMemGetInfo(&avail, &total) == hipSuccess;
   if (cur != b.dev) (void)hipSetDevice(cur);
   std::lock_guard<std::mutex> lk(P.mu);
-  if (tight) {
+  if (seen) P.looks[b.dev].tight = avail < total / 8;
+  if (b.bytes >= POOL_LOOK && P.looks[b.dev].tight) {
     (void)hipFree(p);
     P.flush(b.dev);
     return;

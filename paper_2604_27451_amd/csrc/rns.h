@@ -22,21 +22,17 @@
 //
 // A rounding set by the norm of the row is a loss where the large entries of one
 // row meet small ones of the other (rows that are graded, or that share only their
-// small entries): the FP64 sum is off by about 2^-54 of sum |a_k| |b_k|, which may be far
-// below ||a|| ||b||.  So one more plane holds a code of each entry's magnitude, 16 at
-// the rms of its row, 1 to 127, 0 for an exact zero, and its products S bound
-// that sum from below: codes exceed the scaled magnitudes only where these are
-// below 1, which adds at most 32 K to S, so S >= RNS_SPREAD K = 57.6 K means
-//   sum |a_k| |b_k| >= (57.6 - 32.1) / 256 ||a|| ||b|| = 0.1 ||a|| ||b||,
-// down to which the FP64 sum's error is the larger one (0.4 2^-54 sum |a_k| |b_k|
-// against 2^-59 ||a|| ||b||).  Rows of like entries reach 187 K.  S = 0 means disjoint
-// rows: an exact zero on either engine (rows of blocks of a symmetry).  The
-// entries between, and those of rows that are not finite, are formed in FP64 by k_rns_fp64
-// (which ends at once where there are none); which they are depends on the two rows
+// small entries): the FP64 sum is off by about 0.2 2^-53 sqrt(N sum |a_k|^2 |b_k|^2), N
+// common terms, which may be far below ||a|| ||b||.  So one more plane holds a code
+// of each entry's squared magnitude, 0 for an exact zero, and two products of it, the common
+// terms and the sum of the codes' products, bound that from below (rnsconst.h).
+// Entries that the integers would hold less well than the FP64 sum, and those of
+// rows that are not finite, are formed in FP64 by k_rns_fp64 (which ends at once
+// where there are none); which they are depends on the two rows
 // and the K-splits alone, not on tiles or chunks.  Rows of like entries are known for that by the
 // counts of their codes (rns_flat), and tiles of such rows need no product of codes.  What the
-// codes cost there: nc=6 no=60 nv=300 naux=1500, ten vectors, 45.8 -> 46.6 ms; the smallest sigma
-// 106 -> 111 us.
+// codes cost there: nc=6 no=60 nv=300 naux=1500, ten vectors, 46.6 -> 47.2 ms; the smallest sigma
+// 111 -> 113 us.
 //
 // Measured against long double (nc=6 no=60 nv=300 naux=1500, a unit vector on a
 // singles entry, so that every doubles entry is one K = 1500 product): rms error
@@ -57,11 +53,12 @@
 namespace adc2 {
 
 constexpr int RNS_PL = 2 * RNS_NM;      // residue planes
-constexpr int RNS_NP = RNS_PL + 1;      // planes held: the last one the magnitude codes
+constexpr int RNS_NP = RNS_PL + 1;      // planes of an operand: the last one the magnitude codes
+constexpr int RNS_OP = RNS_PL + 2;      // planes of a product: the last two of the codes
 constexpr int RNS_RT = 128;             // rows per operand block
 constexpr int RNS_KC = 64;              // k per operand block
 constexpr int RNS_BLK = RNS_RT * RNS_KC;
-constexpr long RNS_KMAX = 131072;       // K 121^2 and K 127^2 < 2^31
+constexpr long RNS_KMAX = 131072;       // K 121^2 and K 126^2 < 2^31
 
 constexpr int RNS_NAN = 1 << 20;
 
@@ -136,7 +133,7 @@ adc2_status rns_pack(const RnsSrc& src, int rows, int K, int8_t* buf, int* ebuf,
 // out = residues of the products of the rows of A with the rows [col0,
 // col0 + ncols) of B (col0 a multiple of 128) over nsplit runs of K: split s, plane
 // q, 32 x 32 block (rb, cb) as a 1 KB run at
-// (((s * RNS_NP + q) * nrb + rb) * ncb + cb) * 1024, in MFMA register order.
+// (((s * RNS_OP + q) * nrb + rb) * ncb + cb) * 1024, in MFMA register order.
 adc2_status rns_gemm(const RnsMat& A, const RnsMat& B, int col0, int ncols, int nsplit, int8_t* out, hipStream_t st);
 // The products themselves out of those residues, and in FP64 from A.src and B.src
 // those entries that the integers do not hold well enough.

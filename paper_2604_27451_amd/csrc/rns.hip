@@ -8,6 +8,7 @@
 namespace adc2 {
 
 typedef int i4v __attribute__((ext_vector_type(4)));
+typedef unsigned u4v __attribute__((ext_vector_type(4)));
 
 static inline int rcdiv(long a, long b) { return (int)((a + b - 1) / b); }
 
@@ -23,13 +24,12 @@ static_assert(rns_m() > 2.0 * (double)(1L << 58) * (double)(1L << 58) * 1.58, "2
 // ---------------------------------------------------------------------------
 constexpr int NORM_SPLIT = 64;
 constexpr size_t RNS_ROW = sizeof(int) + sizeof(float) + sizeof(unsigned long long);   // e, code scale, code counts of a row
-constexpr int RNS_QUNIT = 64;          // its image in the bytes that the products of the codes are kept in
 size_t rns_op_bytes(long rows, long K) { return (size_t)RNS_NP * rcdiv(rows, RNS_RT) * rcdiv(K, RNS_KC) * RNS_BLK; }
 size_t rns_exp_bytes(long rows) { return RNS_ROW * (size_t)rcdiv(rows, RNS_RT) * RNS_RT; }
 size_t rns_norm_bytes(long rows) { return sizeof(double) * 3 * NORM_SPLIT * (size_t)rows; }
 // (three bytes a 32 x 32 block more: two for k_rns_join to say whether k_rns_fp64 has entries in it, one for
 // k_rns_gemm, of which it uses one a tile, to say whether the tile's rows are flat)
-size_t rns_out_bytes(long rows, long cols) { return (size_t)(RNS_NP * 1024 + 3) * rcdiv(rows, 32) * rcdiv(cols, 32); }
+size_t rns_out_bytes(long rows, long cols) { return (size_t)(RNS_OP * 1024 + 3) * rcdiv(rows, 32) * rcdiv(cols, 32); }
 
 // ---------------------------------------------------------------------------
 // row exponents
@@ -60,7 +60,7 @@ struct RnsSums {
 // read of the operand): lane = row where rows are contiguous, a wave per row
 // where k is.
 // The largest e with ||row|| 2^e <= 2^RNS_G from the row's three sums
-// (and the scale of its magnitude codes, in units of 2^32 of the scaled integers, -1 for a zero row and
+// (and the scale of its squared magnitudes in units of 2^64 of the scaled integers', -1 for a zero row and
 // 0 for one that is not finite; the counts of its codes start at 0)
 __device__ __forceinline__ void rns_exponent(double s0, double s1, double s2, int K, int padded, int row, int* e) {
   double l2;   // log2 of the norm
@@ -73,7 +73,7 @@ __device__ __forceinline__ void rns_exponent(double s0, double s1, double s2, in
   e[row] = ex;
   ((float*)(e + padded))[row] = ex == RNS_NAN ? 0.0f
                                 : s0 == 0.0 && s2 == 0.0 ? -1.0f
-                                                         : RNS_QRMS * sqrtf((float)K) * exp2f(32.0f - (float)(l2 + ex));
+                                                         : RNS_QMEAN * (float)K * exp2f(64.0f - 2.0f * (float)(l2 + ex));
   ((unsigned long long*)(e + 2 * padded))[row] = 0;
 }
 // (rows past the end: as zero rows)
@@ -204,7 +204,7 @@ template <bool KLANE>
 __global__ __launch_bounds__(256, KLANE ? 3 : 5) void k_rns_pack(const RnsSrc src, int rows, int K,
                                                                  int* __restrict__ e, int nrt, int nkc,
                                                                  int8_t* __restrict__ dst) {
-  __shared__ unsigned cnt[4][64];   // codes of at least 4, 8 and 12, a byte each
+  __shared__ unsigned cnt[4][64];   // codes of at least 1, 2 and 3, a byte each
   const int lane = threadIdx.x & 63, kg = threadIdx.x >> 6;
   const int rb = blockIdx.x % (2 * nrt), kc = blockIdx.x / (2 * nrt);
   const int row = rb * 64 + lane;
@@ -271,7 +271,7 @@ __global__ __launch_bounds__(256, KLANE ? 3 : 5) void k_rns_pack(const RnsSrc sr
   auto top = [](int x) { return (float)(int)(((unsigned)x ^ 0x80808080u) - 0x80808080u); };   // the upper four bytes
   int8_t* out = dst + ((long)(rb >> 1) * nkc + kc) * RNS_BLK + ((rb & 1) * 4 + (lane >> 4)) * 1024 + kg * 256 + (lane & 15) * 16;
   const long ps = (long)nrt * nkc * RNS_BLK;
-  int n4 = 0, n8 = 0, n12 = 0;
+  int n1 = 0, n2 = 0, n3 = 0;
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     bool zero[4];
@@ -292,17 +292,17 @@ __global__ __launch_bounds__(256, KLANE ? 3 : 5) void k_rns_pack(const RnsSrc sr
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const float hr = top(d[4 * t + q].y), hi = top(d[4 * t + q].w);
-      const int c = zero[q] ? 0 : (int)fminf(fmaxf(cw * __builtin_amdgcn_sqrtf(fmaf(hr, hr, hi * hi)), 1.0f), 127.0f);
+      const int c = zero[q] ? 0 : 1 + (int)fminf(fmaxf(cw * fmaf(hr, hr, hi * hi), 0.0f), 126.0f);   // NaN: 1
       cc |= c << (8 * q);
     }
-    n4 += __popc((cc + 0x7c7c7c7c) & 0x80808080);   // (codes are at most 127: no carry)
-    n8 += __popc((cc + 0x78787878) & 0x80808080);
-    n12 += __popc((cc + 0x74747474) & 0x80808080);
+    n1 += __popc((cc + 0x7f7f7f7f) & 0x80808080);   // (codes are at most 127: no carry)
+    n2 += __popc((cc + 0x7e7e7e7e) & 0x80808080);
+    n3 += __popc((cc + 0x7d7d7d7d) & 0x80808080);
     if (blockIdx.y == 0) *(int*)(out + RNS_PL * ps + 4 * t) = cc;
     __builtin_amdgcn_sched_barrier(0);   // (all entries interleaved: 50 registers more)
   }
   const float magic = 12582912.0f;
-  cnt[kg][lane] = n4 | n8 << 8 | n12 << 16;
+  cnt[kg][lane] = n1 | n2 << 8 | n3 << 16;
   __syncthreads();
   if (blockIdx.y == 0 && kg == 0 && ok) {
     const unsigned n = cnt[0][lane] + cnt[1][lane] + cnt[2][lane] + cnt[3][lane];   // at most 64 each
@@ -372,34 +372,33 @@ adc2_status rns_pack(const RnsSrc& src, int rows, int K, int8_t* buf, int* ebuf,
 }
 
 // ---------------------------------------------------------------------------
-// which entries the integers serve
+// which entries the integers serve (the rule: rnsconst.h)
 // ---------------------------------------------------------------------------
-// Two flat rows, of which at least 0.78 K codes are 4 or more, 0.60 K 8 or more and 0.36 K 12 or
-// more (RNS_FLAT; 0.94, 0.78 and 0.57 for normal complex entries), have, in whatever order, a sum of
-// |a_k| |b_k| of at least 28.8 / 256 ||a|| ||b|| (the smaller entries of each against the
-// larger of the other: 2 * 0.14 * 4 * 12 + 2 * 0.04 * 4 * 8 + 0.20 * 8 * 8), above the 0.1 of rns.h: their products
-// need no code product, and a tile of such rows forms none (with it in every tile the product took 4.4%
-// longer, so 1.3% at nc=6 no=60 nv=300).  A zero row likewise.
 struct RnsRows {
   const int* e;      // exponents, then code scales and counts
-  int padded, n4, n8, n12;
+  int padded, n1, n2, n3;
 };
+// A flat row (RNS_FLAT), or a zero one
 __device__ __forceinline__ bool rns_flat(const RnsRows& r, int row) {
   const float w = ((const float*)(r.e + r.padded))[row];
   const unsigned long long n = ((const unsigned long long*)(r.e + 2 * r.padded))[row];
-  return w < 0.0f || (w > 0.0f && (int)(n & 0x1fffff) >= r.n4 && (int)(n >> 21 & 0x1fffff) >= r.n8 &&
-                      (int)(n >> 42) >= r.n12);
+  return w < 0.0f || (w > 0.0f && (int)(n & 0x1fffff) >= r.n1 && (int)(n >> 21 & 0x1fffff) >= r.n2 && (int)(n >> 42) >= r.n3);
 }
 static RnsRows rns_rows_of(const RnsMat& m) {
   return RnsRows{m.e, m.nrt * RNS_RT, (int)std::ceil(RNS_FLAT[0] * m.K), (int)std::ceil(RNS_FLAT[1] * m.K),
                  (int)std::ceil(RNS_FLAT[2] * m.K)};
 }
 
-// The bytes that k_rns_gemm keeps of the code products of an entry's K-runs, summed:
-// 2^16 a run with common terms, plus its code product in units of the bound / RNS_QUNIT
-__device__ __forceinline__ int rns_spread(int byte) { return byte == 0 ? 0 : 0x10000 + byte - 1; }
-// no common terms (an exact zero), or enough of them
-__device__ __forceinline__ bool rns_serves(int spread) { return spread == 0 || (spread & 0xffff) >= RNS_QUNIT; }
+// Sums over an entry's K-runs of the two bytes that k_rns_gemm keeps of its code products
+struct RnsSpread {
+  int terms = 0, part = 0, weight = 0;   // whether there are common terms; their number and sum in units of the bytes
+  __device__ __forceinline__ void add(int n, int s) {
+    terms |= n;
+    part += n ? n - 1 : 0;
+    weight += s;
+  }
+  __device__ __forceinline__ bool serves() const { return rns_spread_serves(terms, part, weight); }
+};
 
 // ---------------------------------------------------------------------------
 // the product of one plane:  C[i][j] = sum_k A[i][k] B[j][k] mod p
@@ -421,16 +420,17 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm
   constexpr int SB = (BM + BN) * RNS_KC, NL = SB / (T * 16), NLA = BM * RNS_KC / (T * 16);
   __shared__ __align__(16) int8_t s[NB][SB];
   const long nt = (long)nbm * nbn;
-  // planes in order, so that each XCD works on the tiles of few planes, the code planes of
-  // all splits after them (33 planes in order straddle the XCDs: 1% slower); tiles in
+  // planes in order, so that each XCD works on the tiles of few planes, the code products of
+  // all splits after them (34 planes in order straddle the XCDs: 1% slower); tiles in
   // groups of 8 row panels
-  const long ncode = gridDim.x / RNS_NP, nres = gridDim.x - ncode;   // a code tile for every 32 others
+  const long ncode = gridDim.x / RNS_OP * 2, nres = gridDim.x - ncode;
   const bool codes = (long)blockIdx.x >= nres;
   const long lid = codes ? xcd_remap(blockIdx.x - nres, ncode) : xcd_remap(blockIdx.x, nres);
-  const int g = (int)(lid / nt);                      // K-split * RNS_PL + plane, K-split
+  const int g = (int)(lid / nt);                      // K-split * RNS_PL + plane, 2 * K-split + product of codes
   const int t0 = (int)(lid - (long)g * nt);
-  const int pl = codes ? RNS_PL : g % RNS_PL, split = codes ? g : g / RNS_PL;
-  const int sp = split * RNS_NP + pl, kc0 = split * nkcs;
+  const int po = codes ? RNS_PL + (g & 1) : g % RNS_PL, split = codes ? g >> 1 : g / RNS_PL;
+  const int pl = codes ? RNS_PL : po;
+  const int sp = split * RNS_OP + po, kc0 = split * nkcs;
   const int nkc = min(nkcs, nkca - kc0);              // chunks of this split
   const int per = 8 * nbn, grp = t0 / per, gm = min(8, nbm - grp * 8), r = t0 - grp * per;
   const int bm = grp * 8 + r % gm, bn = r / gm;
@@ -477,30 +477,37 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm
   const int wm = w % WM, wn = w / WM;
 #pragma unroll
   for (int t = 0; t < NB - 1; ++t) load(t);
-  for (int t = 0; t < nkc; ++t) {
-    // chunk t has landed when at most the NB - 2 later ones are outstanding;
-    // the barrier also ends every wave's reads of the stage that load() refills, so
-    // these have to have returned (lgkmcnt 0: the products before them need not stay before the barrier)
-    constexpr int V = (NB - 2) * NL;
-    __builtin_amdgcn_s_waitcnt(0x0070 | (V & 15) | ((V >> 4) << 14));
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    load(t + NB - 1);
-    const int8_t* p = s[t % NB];
-    const int8_t* pa = p + wm * RNS_BLK + lane * 16;
-    const int8_t* pb = p + BM * RNS_KC + (wn >> 1) * RNS_BLK + (wn & 1) * (RNS_BLK / 2) + lane * 16;
-    i4v a[8], b[4];
+  auto sweep = [&](auto&& op) {
+    for (int t = 0; t < nkc; ++t) {
+      // chunk t has landed when at most the NB - 2 later ones are outstanding;
+      // the barrier also ends every wave's reads of the stage that load() refills, so
+      // these have to have returned (lgkmcnt 0: the products before them need not stay before the barrier)
+      constexpr int V = (NB - 2) * NL;
+      __builtin_amdgcn_s_waitcnt(0x0070 | (V & 15) | ((V >> 4) << 14));
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      load(t + NB - 1);
+      const int8_t* p = s[t % NB];
+      const int8_t* pa = p + wm * RNS_BLK + lane * 16;
+      const int8_t* pb = p + BM * RNS_KC + (wn >> 1) * RNS_BLK + (wn & 1) * (RNS_BLK / 2) + lane * 16;
+      i4v a[8], b[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) b[j] = *(const i4v*)(pb + j * 1024);
+      for (int j = 0; j < 4; ++j) b[j] = op(*(const i4v*)(pb + j * 1024));
 #pragma unroll
-    for (int i = 0; i < 8; ++i) a[i] = *(const i4v*)(pa + i * 1024);
+      for (int i = 0; i < 8; ++i) a[i] = op(*(const i4v*)(pa + i * 1024));
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+      for (int i = 0; i < 8; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i], b[j], acc[i][j], 0, 0, 0);
-  }
+        for (int j = 0; j < 4; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+  };
+  // code products: common terms, or codes less one
+  auto ones = [](i4v q) { return (i4v)((((u4v)q + 0x7f7f7f7fu) & 0x80808080u) >> 7); };   // (codes are at most 127)
+  if (!codes) sweep([](i4v q) { return q; });
+  else if (po == RNS_PL) sweep(ones);
+  else sweep([&](i4v q) { return q - ones(q); });
   __builtin_amdgcn_s_waitcnt(0x0f70);
   auto each = [&](auto&& byte) {   // the low byte of byte(acc) of every entry
 #pragma unroll
@@ -520,8 +527,9 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm
         if (rb < nrb && cb < ncb) *(i4v*)(C + (((long)sp * nrb + rb) * ncb + cb) * 1024 + lane * 16) = o;
       }
   };
-  if (codes) {   // 0: no common term; else 1 + the code product in units of its bound / RNS_QUNIT
-    each([&](int v) { return v == 0 ? 0 : 1 + (int)fminf((float)v * qs, 126.0f); });
+  if (codes) {
+    if (po == RNS_PL) each([&](int v) { return rns_terms_byte(v, qs); });
+    else each([&](int v) { return rns_weight_byte(v, qs); });
     return;
   }
   const RnsSplit c = RNS_C.split[pl >> 1];
@@ -554,15 +562,15 @@ static bool rns_tall(const RnsMat& A, int ncols, int nsplit) {
 
 adc2_status rns_gemm(const RnsMat& A, const RnsMat& B, int col0, int ncols, int nsplit, int8_t* out, hipStream_t st) {
   const int nrb = rcdiv(A.rows, 32), ncb = rcdiv(ncols, 32), nkcs = rcdiv(A.nkc, nsplit);
-  const float qs = RNS_QUNIT / (RNS_SPREAD * (float)A.K);
+  const float qs = 1.0f / (float)A.K;
   const RnsRows ra = rns_rows_of(A), rb = rns_rows_of(B);
   if (rns_tall(A, ncols, nsplit)) {
     const int nbm = rcdiv(A.rows, 256), nbn = rcdiv(ncols, 128);
-    k_rns_gemm<2, 2, 3><<<(unsigned)((long)nsplit * RNS_NP * nbm * nbn), 256, 0, st>>>(
+    k_rns_gemm<2, 2, 3><<<(unsigned)((long)nsplit * RNS_OP * nbm * nbn), 256, 0, st>>>(
         A.p, B.p, A.nrt, B.nrt, col0 / RNS_RT, A.nkc, nkcs, nbm, nbn, nrb, ncb, qs, ra, rb, out);
   } else {
     const int nbm = rcdiv(A.rows, 128), nbn = rcdiv(ncols, 256);
-    k_rns_gemm<1, 4, 3><<<(unsigned)((long)nsplit * RNS_NP * nbm * nbn), 256, 0, st>>>(
+    k_rns_gemm<1, 4, 3><<<(unsigned)((long)nsplit * RNS_OP * nbm * nbn), 256, 0, st>>>(
         A.p, B.p, A.nrt, B.nrt, col0 / RNS_RT, A.nkc, nkcs, nbm, nbn, nrb, ncb, qs, ra, rb, out);
   }
   ADC2_CHECK_LAUNCH();
@@ -593,29 +601,29 @@ __global__ __launch_bounds__(256) void k_rns_join(int8_t* __restrict__ R, int nr
   const int8_t* src = R + ((long)rb * ncb + cb) * 1024 + item * 8;
   if (col >= cols) return;
   // which entries the integers serve: all of them in a tile of flat rows (tiles of 2^tr x 2^tc blocks)
-  const int8_t* fl = R + (long)nsplit * RNS_NP * ps;
+  const int8_t* fl = R + (long)nsplit * RNS_OP * ps;
   unsigned serve = 255;
   if (!fl[2L * nrb * ncb + (rb >> tr) * nbn + (cb >> tc)]) {
     serve = 0;
-    int spread[8];
-#pragma unroll
-    for (int x = 0; x < 8; ++x) spread[x] = 0;
+    RnsSpread spread[8];
     for (int s = 0; s < nsplit; ++s) {
-      const int2 v = *(const int2*)(src + ((long)s * RNS_NP + RNS_PL) * ps);
+      const int2 n = *(const int2*)(src + ((long)s * RNS_OP + RNS_PL) * ps);
+      const int2 v = *(const int2*)(src + ((long)s * RNS_OP + RNS_PL + 1) * ps);
 #pragma unroll
-      for (int x = 0; x < 8; ++x) spread[x] += rns_spread(((x < 4 ? v.x : v.y) >> (8 * (x & 3))) & 255);
+      for (int x = 0; x < 8; ++x)
+        spread[x].add(((x < 4 ? n.x : n.y) >> (8 * (x & 3))) & 255, ((x < 4 ? v.x : v.y) >> (8 * (x & 3))) & 255);
     }
     const bool cflat = rns_flat(rb_, col0 + col);
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
       const int row = row0 + (x >> 2) * 16 + (x & 3);
-      serve |= (unsigned)(row >= rows || rns_serves(spread[x]) || (cflat && rns_flat(ra, row))) << x;
+      serve |= (unsigned)(row >= rows || spread[x].serves() || (cflat && rns_flat(ra, row))) << x;
     }
   }
   // (lane 0 has the block's first column, which is there)
   const bool any = __ballot(serve != 255) != 0;
   if ((threadIdx.x & 63) == 0)
-    R[(long)nsplit * RNS_NP * ps + ((long)rb * ncb + cb) * 2 + (item >> 6)] = any;
+    R[(long)nsplit * RNS_OP * ps + ((long)rb * ncb + cb) * 2 + (item >> 6)] = any;
   double fr[8], fi[8], gr[8], gi[8];
 #pragma unroll
   for (int x = 0; x < 8; ++x) fr[x] = fi[x] = gr[x] = gi[x] = 0.0;
@@ -635,7 +643,7 @@ __global__ __launch_bounds__(256) void k_rns_join(int8_t* __restrict__ R, int nr
       for (int s = 1; s < nsplit; ++s) {
         int2 v[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = *(const int2*)(src + ((long)s * RNS_NP + 4 * t + q) * ps);
+        for (int q = 0; q < 4; ++q) v[q] = *(const int2*)(src + ((long)s * RNS_OP + 4 * t + q) * ps);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -705,7 +713,7 @@ __global__ __launch_bounds__(256) void k_rns_fp64(const RnsSrc A, const RnsSrc B
   const int nct = (ncb + 1) >> 1, ntile = ((nrb + 1) >> 1) * nct;
   const int tid = threadIdx.x, lane = tid & 63;
   const int br = (tid >> 6) & 1, bc = tid >> 7;   // a wave per 32 x 32 block
-  const unsigned short* left = (const unsigned short*)(R + (long)nsplit * RNS_NP * nrb * ncb * 1024);
+  const unsigned short* left = (const unsigned short*)(R + (long)nsplit * RNS_OP * nrb * ncb * 1024);
   for (int t0 = blockIdx.x; t0 < ntile; t0 += 256 * gridDim.x) {   // a thread looks at one tile of up to 256
     const int tt = t0 + tid * gridDim.x, b0 = (tt / nct) * 2, c0 = (tt % nct) * 2;
     unsigned any = 0;
@@ -720,20 +728,19 @@ __global__ __launch_bounds__(256) void k_rns_fp64(const RnsSrc A, const RnsSrc B
       for (unsigned long long t = todo[w]; t; t &= t - 1) {
         const int tile = t0 + (w * 64 + __builtin_ctzll(t)) * gridDim.x;
         const int i0 = (tile / nct) * 64, j0 = (tile % nct) * 64, rb = i0 / 32 + br, cb = j0 / 32 + bc;
-        int spread[16];
-#pragma unroll
-        for (int x = 0; x < 16; ++x) spread[x] = 0;
+        RnsSpread spread[16];
         if (rb < nrb && cb < ncb)
           for (int q = 0; q < nsplit; ++q) {
-            const i4v v = *(const i4v*)(R + ((((long)q * RNS_NP + RNS_PL) * nrb + rb) * ncb + cb) * 1024 + lane * 16);
+            const int8_t* c = R + ((((long)q * RNS_OP + RNS_PL) * nrb + rb) * ncb + cb) * 1024 + lane * 16;
+            const i4v n = *(const i4v*)c, v = *(const i4v*)(c + (long)nrb * ncb * 1024);
 #pragma unroll
-            for (int x = 0; x < 16; ++x) spread[x] += rns_spread((v[x >> 2] >> (8 * (x & 3))) & 255);
+            for (int x = 0; x < 16; ++x) spread[x].add((n[x >> 2] >> (8 * (x & 3))) & 255, (v[x >> 2] >> (8 * (x & 3))) & 255);
           }
 #pragma unroll
         for (int x = 0; x < 16; ++x) {   // register order of the 16 x 16 blocks of k_rns_gemm
           const int q = x >> 2, r = 32 * br + 16 * (q & 1) + 4 * (lane >> 4) + (x & 3);
           const int c = 32 * bc + 16 * (q >> 1) + (lane & 15);
-          own[r][c] = (unsigned char)(i0 + r < rows && j0 + c < cols && !rns_serves(spread[x]) &&
+          own[r][c] = (unsigned char)(i0 + r < rows && j0 + c < cols && !spread[x].serves() &&
                                       !(rns_flat(ra, i0 + r) && rns_flat(rb_, col0 + j0 + c)));
         }
         Acc acc;

@@ -89,12 +89,24 @@ constexpr double rns_m() {
   for (int q = 0; q < RNS_NM; ++q) m *= RNS_P[q];
   return m;
 }
-// Magnitude codes of the entries of an operand (rns.h): the code of an entry of its row's rms, the
-// least code product a term at which the integers serve an entry, and the parts of a flat row's codes that
-// are at least 4, 8 and 12.
-constexpr float RNS_QRMS = 16.0f;
-constexpr float RNS_SPREAD = 57.6f;
-constexpr double RNS_FLAT[3] = {0.78, 0.60, 0.36};
+// Which entries of a product the integers serve.  Code of an entry a_k of an operand's row: 0 for an exact
+// zero, else 1 + q, q = |a_k|^2 in units of a quarter of the row's mean (RNS_QMEAN), rounded down, at most 126.
+// Two sums over the terms of an entry: N, the common terms that are not zero, and S = sum q_k(a) q_k(b), at
+// most 16 K^2 sum |a_k|^2 |b_k|^2 / (||a||^2 ||b||^2).  The entry is served if N = 0 (an exact zero on either engine)
+// or N S >= K^2 / 4, that is
+//   N sum |a_k|^2 |b_k|^2 >= ||a||^2 ||b||^2 / 64.
+// A FP64 sum of N terms in any order that knows nothing of them is off by about
+// 0.2 2^-53 sqrt(N sum |a_k|^2 |b_k|^2) rms (0.29 2^-53 of each partial sum), then 0.025 2^-53 ||a|| ||b||; the
+// integers by 2^-59 ||a|| ||b|| = 0.015 2^-53.
+// A flat row has at least RNS_FLAT K codes of 1, 2 and 3 and more (1, 0.78 and 0.61 of normal complex entries):
+// two of them have N >= 0.8 K and, the smaller codes of each against the larger of the other, S >= 0.32 K.
+constexpr float RNS_QMEAN = 4.0f;
+constexpr double RNS_FLAT[3] = {0.90, 0.60, 0.46};
+// The two sums of a run of terms as bytes (rk = 1 / K): N in units of K / 254, 0 for none, and S in units of K / 8
+constexpr int rns_terms_byte(int n, float rk) { return n == 0 ? 0 : 1 + (int)((float)n * (254.0f * rk) < 254.0f ? (float)n * (254.0f * rk) : 254.0f); }
+constexpr int rns_weight_byte(int s, float rk) { return (int)((float)s * (8.0f * rk) < 255.0f ? (float)s * (8.0f * rk) : 255.0f); }
+// ... and the rule on their sums over the runs
+constexpr bool rns_spread_serves(int terms, int part, int weight) { return terms == 0 || part * weight >= 254 * 8 / 4; }
 
 // hi + lo modulo 1, in [-1/2, 1/2]; |hi| < 2^50.  hi comes as an exact sum, so its whole part goes
 // first; lo may carry the rest past 1/2 (0.018 at 32 K-runs, against 0.0106 between the largest

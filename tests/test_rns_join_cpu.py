@@ -18,9 +18,18 @@ SHIM = r'''
 #include "rnsconst.h"
 static constexpr adc2::RnsConst C = adc2::make_const();
 extern "C" void rule(double* r) {
-  r[0] = adc2::RNS_QRMS;
-  r[1] = adc2::RNS_SPREAD;
-  for (int i = 0; i < 3; ++i) r[2 + i] = adc2::RNS_FLAT[i];
+  r[0] = adc2::RNS_QMEAN;
+  for (int i = 0; i < 3; ++i) r[1 + i] = adc2::RNS_FLAT[i];
+}
+extern "C" int serves(int runs, const int* n, const int* s, int K) {   // of an entry's sums by K-runs
+  int terms = 0, part = 0, weight = 0;
+  for (int i = 0; i < runs; ++i) {
+    const int b = adc2::rns_terms_byte(n[i], 1.0f / (float)K);
+    terms |= b;
+    part += b ? b - 1 : 0;
+    weight += adc2::rns_weight_byte(s[i], 1.0f / (float)K);
+  }
+  return adc2::rns_spread_serves(terms, part, weight);
 }
 extern "C" void moduli(int* p) { for (int q = 0; q < adc2::RNS_NM; ++q) p[q] = adc2::RNS_P[q]; }
 extern "C" void join(const int* u, double* out) {   // u[2 q], u[2 q + 1]: sums of c+, c- of modulus q
@@ -141,17 +150,17 @@ def test_largest_low_parts(lib):
     assert past > 0
 
 
-# ---- which entries the integers serve: sum |a| |b| >= 0.1 ||a|| ||b|| (csrc/rns.h) ----
+# ---- which entries the integers serve: N sum |a|^2 |b|^2 >= ||a||^2 ||b||^2 / 64, or N = 0 (csrc/rnsconst.h) ----
 def rule(lib):
-    r = (ctypes.c_double * 5)()
+    r = (ctypes.c_double * 4)()
     lib.rule(r)
     return list(r)
 
 
-def codes(a, qrms):
+def codes(a, qmean):
     import numpy as np
-    q = np.floor(qrms * np.sqrt(len(a)) * np.abs(a) / np.sqrt((np.abs(a) ** 2).sum()))
-    return np.where(a == 0, 0, np.clip(q, 1, 127))
+    q = np.floor(qmean * len(a) * np.abs(a) ** 2 / (np.abs(a) ** 2).sum())
+    return np.where(a == 0, 0, 1 + np.clip(q, 0, 126)).astype(int)
 
 
 def rows(K):
@@ -168,35 +177,83 @@ def rows(K):
 
 
 @pytest.mark.parametrize("K", [37, 150, 1500])
-def test_rows_that_the_integers_serve(lib, K):
+@pytest.mark.parametrize("runs", [1, 8, 32])
+def test_rows_that_the_integers_serve(lib, K, runs):
     import numpy as np
-    qrms, spread, *flat = rule(lib)
+    qmean, *flat = rule(lib)
     rs = rows(K)
-    qs = [codes(r, qrms) for r in rs]
-    fl = [all((q >= 4 * (i + 1)).sum() >= np.ceil(f * K) for i, f in enumerate(flat)) for q in qs]
+    qs = [codes(r, qmean) for r in rs]
+    fl = [all((q > i).sum() >= np.ceil(f * K) for i, f in enumerate(flat)) for q in qs]
+    cut = [K * i // runs for i in range(runs + 1)]
     served = refused = 0
     for a, qa, fa in zip(rs, qs, fl):
         for b, qb, fb in zip(rs, qs, fl):
-            cos = (np.abs(a) * np.abs(b)).sum() / np.sqrt((np.abs(a) ** 2).sum() * (np.abs(b) ** 2).sum())
-            if (qa * qb).sum() >= spread * K or (fa and fb):
+            n = (qa > 0) & (qb > 0)
+            s = np.maximum(qa - 1, 0) * np.maximum(qb - 1, 0)
+            sums = [(ctypes.c_int * runs)(*(int(v[i:j].sum()) for i, j in zip(cut, cut[1:]))) for v in (n, s)]
+            if lib.serves(runs, *sums, K) or (fa and fb):
                 served += 1
-                assert cos >= 0.099
+                d = n.sum() * (np.abs(a * b) ** 2).sum() / ((np.abs(a) ** 2).sum() * (np.abs(b) ** 2).sum())
+                assert n.sum() == 0 or d >= 0.999 / 64
             else:
                 refused += 1
     assert served and refused
+    # like entries are flat, entries over decades are not, and their products are served by their codes as well
     if K == 1500:
-        assert fl[0] and not any(fl[4:7])   # normal complex entries are flat, entries over decades are not
+        assert fl[0] and not any(fl[4:7])
+        n, s = np.ones(K, int), (qs[0] - 1) * np.roll(qs[0] - 1, 1)
+        sums = [(ctypes.c_int * runs)(*(int(v[i:j].sum()) for i, j in zip(cut, cut[1:]))) for v in (n, s)]
+        assert lib.serves(runs, *sums, K)
+
+
+def test_errors_where_the_integers_serve(lib):
+    """Rounded to the fixed point of the rows against FP64 sums term by term: over the products of 200 pairs
+    of each two kinds of rows that are served, the rms error is no larger than the FP64 sums'."""
+    import numpy as np
+    K = 400
+    qmean, *flat = rule(lib)
+
+    def fixed(a):   # whole numbers of a row scaled to a norm in (2^57.33, 2^58.33]
+        e = int(np.floor(58.33 - np.log2(np.sqrt((np.abs(a) ** 2).sum()))))
+        return [(int(round(float(np.ldexp(z.real, e)))), int(round(float(np.ldexp(z.imag, e))))) for z in a], e
+
+    rng = np.random.default_rng(11)
+    kinds = {"even": lambda: 1.0, "third": lambda: 10.0 ** (0.33 * rng.standard_normal(K)),
+             "half": lambda: 10.0 ** (0.5 * rng.standard_normal(K)), "few": lambda: np.where(np.arange(K) < 20, 1.0, 1e-3)}
+    seen = 0
+    for ka in kinds:
+        for kb in kinds:
+            ei, ef, served = 0.0, 0.0, 0
+            for _ in range(12):
+                a, b = ((rng.standard_normal(K) + 1j * rng.standard_normal(K)) * kinds[k]() for k in (ka, kb))
+                qa, qb = codes(a, qmean), codes(b, qmean)
+                n, s = int(((qa > 0) & (qb > 0)).sum()), int(((qa - 1) * (qb - 1)).sum())
+                if not lib.serves(1, (ctypes.c_int * 1)(n), (ctypes.c_int * 1)(s), K):
+                    continue
+                served += 1
+                (fa, xa), (fb, xb) = fixed(a), fixed(b)
+                got = sum(x[0] * y[0] - x[1] * y[1] for x, y in zip(fa, fb))
+                exact = sum(Fraction(x.real) * Fraction(y.real) - Fraction(x.imag) * Fraction(y.imag) for x, y in zip(a, b))
+                f64 = 0.0
+                for x, y in zip(a, b):
+                    f64 += x.real * y.real
+                    f64 -= x.imag * y.imag
+                scale = np.sqrt((np.abs(a) ** 2).sum() * (np.abs(b) ** 2).sum())
+                ei += (float(Fraction(got) / Fraction(2) ** (xa + xb) - exact) / scale) ** 2
+                ef += (float(Fraction(f64) - exact) / scale) ** 2
+            if served >= 6:
+                seen += 1
+                assert ei <= ef, (ka, kb, ei, ef, served)
+    assert seen >= 8
 
 
 def test_bounds_of_the_rule(lib):
-    """The worst rows: code products of flat rows in opposite order; codes rounded up to 1."""
-    qrms, spread, f4, f8, f12 = rule(lib)
+    """The worst flat rows: their codes in opposite order."""
+    qmean, f1, f2, f3 = rule(lib)
     N = 10000
-    q = [0.0] * N                      # a flat row at its limits, smallest first
-    for f, c in ((f4, 4), (f8, 8), (f12, 12)):
+    q = [0] * N                      # codes less one of a flat row at its limits, smallest first
+    for f, c in ((f2, 1), (f3, 2)):
         for i in range(round((1 - f) * N), N):
             q[i] = c
-    worst = sum(x * y for x, y in zip(q, reversed(q))) / N
-    assert worst >= 0.1 * qrms ** 2
-    # codes are at most the scaled magnitudes but where these are below 1: at most sqrt(K sum max(q, 1)^2) on each side
-    assert spread - 2 * (qrms ** 2 + 1) ** 0.5 >= 0.0995 * qrms ** 2
+    S = sum(x * y for x, y in zip(q, reversed(q))) / N
+    assert (2 * f1 - 1) * S >= qmean ** 2 / 64

@@ -378,11 +378,14 @@ struct RnsRows {
   const int* e;      // exponents, then code scales and counts
   int padded, n1, n2, n3;
 };
-// A flat row (RNS_FLAT), or a zero one
-__device__ __forceinline__ bool rns_flat(const RnsRows& r, int row) {
+// What is known of a row by the counts of its codes
+enum RnsClass { ROW_OTHER, ROW_FULL, ROW_FLAT, ROW_ZERO };   // (full: at least RNS_FLAT[0] of it not zero)
+__device__ __forceinline__ int rns_class(const RnsRows& r, int row) {
   const float w = ((const float*)(r.e + r.padded))[row];
   const unsigned long long n = ((const unsigned long long*)(r.e + 2 * r.padded))[row];
-  return w < 0.0f || (w > 0.0f && (int)(n & 0x1fffff) >= r.n1 && (int)(n >> 21 & 0x1fffff) >= r.n2 && (int)(n >> 42) >= r.n3);
+  if (w < 0.0f) return ROW_ZERO;
+  if (!(w > 0.0f) || (int)(n & 0x1fffff) < r.n1) return ROW_OTHER;
+  return (int)(n >> 21 & 0x1fffff) >= r.n2 && (int)(n >> 42) >= r.n3 ? ROW_FLAT : ROW_FULL;
 }
 static RnsRows rns_rows_of(const RnsMat& m) {
   return RnsRows{m.e, m.nrt * RNS_RT, (int)std::ceil(RNS_FLAT[0] * m.K), (int)std::ceil(RNS_FLAT[1] * m.K),
@@ -397,8 +400,14 @@ struct RnsSpread {
     part += n ? n - 1 : 0;
     weight += s;
   }
-  __device__ __forceinline__ bool serves() const { return rns_spread_serves(terms, part, weight); }
 };
+__device__ __forceinline__ bool rns_serves(const RnsSpread& s, int a, int b) {
+  if (a == ROW_ZERO || b == ROW_ZERO || (a == ROW_FLAT && b == ROW_FLAT)) return true;
+  if (a >= ROW_FULL && b >= ROW_FULL) return rns_spread_serves(1, RNS_FULL_PART, s.weight);
+  return rns_spread_serves(s.terms, s.part, s.weight);
+}
+// Of a tile: no code products needed, no count of the common terms needed
+constexpr int TILE_FLAT = 1, TILE_FULL = 2;
 
 // ---------------------------------------------------------------------------
 // the product of one plane:  C[i][j] = sum_k A[i][k] B[j][k] mod p
@@ -435,17 +444,17 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm
   const int per = 8 * nbn, grp = t0 / per, gm = min(8, nbm - grp * 8), r = t0 - grp * per;
   const int bm = grp * 8 + r % gm, bn = r / gm;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  if (codes) {   // none needed where all rows are flat (every wave looks: an LDS reduction beside the ring
-                 // would have the compiler wait for all loads before each fragment read)
-    bool uneven = false;
+  if (codes) {   // (every wave looks: an LDS reduction beside the ring would have the compiler wait for all
+                 // loads before each fragment read)
+    int least = ROW_ZERO;
     for (int r = lane; r < BM + BN; r += 64) {
       const bool isa = r < BM;
       const int row = isa ? bm * BM + r : brt0 * RNS_RT + bn * BN + r - BM;
-      if (row < (isa ? ra.padded : rb_.padded)) uneven = uneven || !rns_flat(isa ? ra : rb_, row);
+      if (row < (isa ? ra.padded : rb_.padded)) least = min(least, rns_class(isa ? ra : rb_, row));
     }
-    const bool flat = __ballot(uneven) == 0;
-    if (tid == 0) C[(long)(gridDim.x / nt) * nrb * ncb * 1024 + 2L * nrb * ncb + bm * nbn + bn] = flat;
-    if (flat) return;
+    const int of = (__ballot(least < ROW_FLAT) == 0 ? TILE_FLAT : 0) | (__ballot(least < ROW_FULL) == 0 ? TILE_FULL : 0);
+    if (tid == 0) C[(long)(gridDim.x / nt) * nrb * ncb * 1024 + 2L * nrb * ncb + bm * nbn + bn] = of;
+    if (of & (po == RNS_PL ? TILE_FULL : TILE_FLAT)) return;
   }
   // global address of each of this thread's NL pieces of a stage (chunk 0)
   const int8_t* src[NL];
@@ -602,22 +611,24 @@ __global__ __launch_bounds__(256) void k_rns_join(int8_t* __restrict__ R, int nr
   if (col >= cols) return;
   // which entries the integers serve: all of them in a tile of flat rows (tiles of 2^tr x 2^tc blocks)
   const int8_t* fl = R + (long)nsplit * RNS_OP * ps;
+  const int of = fl[2L * nrb * ncb + (rb >> tr) * nbn + (cb >> tc)];
   unsigned serve = 255;
-  if (!fl[2L * nrb * ncb + (rb >> tr) * nbn + (cb >> tc)]) {
+  if (!(of & TILE_FLAT)) {
     serve = 0;
     RnsSpread spread[8];
     for (int s = 0; s < nsplit; ++s) {
-      const int2 n = *(const int2*)(src + ((long)s * RNS_OP + RNS_PL) * ps);
+      int2 n = make_int2(0, 0);
+      if (!(of & TILE_FULL)) n = *(const int2*)(src + ((long)s * RNS_OP + RNS_PL) * ps);
       const int2 v = *(const int2*)(src + ((long)s * RNS_OP + RNS_PL + 1) * ps);
 #pragma unroll
       for (int x = 0; x < 8; ++x)
         spread[x].add(((x < 4 ? n.x : n.y) >> (8 * (x & 3))) & 255, ((x < 4 ? v.x : v.y) >> (8 * (x & 3))) & 255);
     }
-    const bool cflat = rns_flat(rb_, col0 + col);
+    const int cclass = rns_class(rb_, col0 + col);
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
       const int row = row0 + (x >> 2) * 16 + (x & 3);
-      serve |= (unsigned)(row >= rows || spread[x].serves() || (cflat && rns_flat(ra, row))) << x;
+      serve |= (unsigned)(row >= rows || rns_serves(spread[x], rns_class(ra, row), cclass)) << x;
     }
   }
   // (lane 0 has the block's first column, which is there)
@@ -703,12 +714,16 @@ struct SrcRns {
   }
 };
 
+constexpr int FSEG = 4096;   // chunks looked at together
 template <int MAPA, int MAPB>
 __global__ __launch_bounds__(256) void k_rns_fp64(const RnsSrc A, const RnsSrc B, int col0, int rows, int cols, int K,
                                                    const int8_t* __restrict__ R, int nrb, int ncb, int nsplit,
-                                                   const RnsRows ra, const RnsRows rb_, const RnsDst dst) {
+                                                   const RnsRows ra, const RnsRows rb_, const int8_t* __restrict__ qa,
+                                                   const int8_t* __restrict__ qb, int nkc, int tr, int tc, int nbn,
+                                                   const RnsDst dst) {
   __shared__ TileSmem s;
   __shared__ unsigned char own[64][64];
+  __shared__ unsigned long long need[FSEG / 64];   // chunks of 16 terms in which both operands have some
   __shared__ unsigned long long todo[4];   // the tiles that have such entries
   const int nct = (ncb + 1) >> 1, ntile = ((nrb + 1) >> 1) * nct;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -729,23 +744,83 @@ __global__ __launch_bounds__(256) void k_rns_fp64(const RnsSrc A, const RnsSrc B
         const int tile = t0 + (w * 64 + __builtin_ctzll(t)) * gridDim.x;
         const int i0 = (tile / nct) * 64, j0 = (tile % nct) * 64, rb = i0 / 32 + br, cb = j0 / 32 + bc;
         RnsSpread spread[16];
-        if (rb < nrb && cb < ncb)
+        if (rb < nrb && cb < ncb) {
+          const bool full = (((const int8_t*)left)[2L * nrb * ncb + (rb >> tr) * nbn + (cb >> tc)] & TILE_FULL) != 0;
           for (int q = 0; q < nsplit; ++q) {
             const int8_t* c = R + ((((long)q * RNS_OP + RNS_PL) * nrb + rb) * ncb + cb) * 1024 + lane * 16;
-            const i4v n = *(const i4v*)c, v = *(const i4v*)(c + (long)nrb * ncb * 1024);
+            const i4v n = full ? i4v{0, 0, 0, 0} : *(const i4v*)c, v = *(const i4v*)(c + (long)nrb * ncb * 1024);
 #pragma unroll
             for (int x = 0; x < 16; ++x) spread[x].add((n[x >> 2] >> (8 * (x & 3))) & 255, (v[x >> 2] >> (8 * (x & 3))) & 255);
           }
+        }
 #pragma unroll
         for (int x = 0; x < 16; ++x) {   // register order of the 16 x 16 blocks of k_rns_gemm
           const int q = x >> 2, r = 32 * br + 16 * (q & 1) + 4 * (lane >> 4) + (x & 3);
           const int c = 32 * bc + 16 * (q >> 1) + (lane & 15);
-          own[r][c] = (unsigned char)(i0 + r < rows && j0 + c < cols && !spread[x].serves() &&
-                                      !(rns_flat(ra, i0 + r) && rns_flat(rb_, col0 + j0 + c)));
+          own[r][c] = (unsigned char)(i0 + r < rows && j0 + c < cols &&
+                                      !rns_serves(spread[x], rns_class(ra, i0 + r), rns_class(rb_, col0 + j0 + c)));
         }
+        // Chunks in which one operand has no term of the tile are left out: they add exact zeros, unless a row is
+        // not finite (nc=6 no=60 nv=300, a folded solve from singles guesses: 121 -> 81 ms of 2.5 s, its first
+        // products being of rows with 60 terms in 18000).
+        const int ja = i0 + tid, jb = col0 + j0 + tid - 64;
+        const bool bad = tid < 64 ? ja < rows && ra.e[ja] == RNS_NAN : tid < 128 && jb < col0 + cols && rb_.e[jb] == RNS_NAN;
+        const bool all = __syncthreads_or(bad) != 0;
+        const SrcRns<MAPA> sa{A, i0, rows, K};
+        const SrcRns<MAPB> sb{B, col0 + j0, col0 + cols, K};
         Acc acc;
         acc.zero();
-        mainloop(s, SrcRns<MAPA>{A, i0, rows, K}, SrcRns<MAPB>{B, col0 + j0, col0 + cols, K}, 0, (K + TK - 1) / TK, acc);
+        const int nch = (K + TK - 1) / TK;
+        for (int h0 = 0; h0 < nch; h0 += FSEG) {
+          const int nh = min(FSEG, nch - h0);
+          for (int h = (tid >> 6) * 64; h < nh; h += 256) {   // a wave per 64 chunks
+            unsigned long long bits = 0;
+            if (all) bits = ~0ull;
+            else
+#pragma unroll 4
+              for (int c = 0; c < 64; ++c) {
+                const int ch = min(h0 + h + c, 4 * nkc - 1);
+                const long o = (long)(ch >> 2) * RNS_BLK + (lane >> 4) * 1024 + (ch & 3) * 256 + (lane & 15) * 16;
+                const i4v x = *(const i4v*)(qa + ((long)(i0 >> 7) * nkc) * RNS_BLK + ((i0 >> 6) & 1) * 4096 + o);
+                const i4v y = *(const i4v*)(qb + ((long)((col0 + j0) >> 7) * nkc) * RNS_BLK + (((col0 + j0) >> 6) & 1) * 4096 + o);
+                const bool both = __ballot((x[0] | x[1] | x[2] | x[3]) != 0) && __ballot((y[0] | y[1] | y[2] | y[3]) != 0);
+                bits |= (unsigned long long)both << c;
+              }
+            if (nh - h < 64) bits &= (1ull << (nh - h)) - 1;
+            if (lane == 0) need[h >> 6] = bits;
+          }
+          __syncthreads();
+          int wd = 0;
+          unsigned long long bits = need[0];
+          auto next = [&]() {   // the next such chunk, or -1 (the same in every thread)
+            while (bits == 0) {
+              if (++wd >= (nh + 63) >> 6) return -1;
+              bits = need[wd];
+            }
+            const int c = __builtin_ctzll(bits);
+            bits &= bits - 1;
+            return h0 + wd * 64 + c;
+          };
+          Regs va, vb;
+          int ch = next();
+          if (ch >= 0) {
+            fetch(sa, ch * TK, va, tid);
+            fetch(sb, ch * TK, vb, tid);
+          }
+          while (ch >= 0) {
+            __syncthreads();
+            stash<MAPA>(s.a_re, s.a_im, va, tid);
+            stash<MAPB>(s.b_re, s.b_im, vb, tid);
+            __syncthreads();
+            ch = next();
+            if (ch >= 0) {
+              fetch(sa, ch * TK, va, tid);
+              fetch(sb, ch * TK, vb, tid);
+            }
+            mma_chunk(s, acc, Acc::row0(tid >> 6), Acc::col0(tid >> 6), lane);
+          }
+          __syncthreads();   // need is free
+        }
         for_each_acc(acc, [&](int r, int c, double2 v) {
           if (!own[r][c]) return;
           const int i = dst.i0 + i0 + r, rg = i / dst.ii, j = dst.j0 + j0 + c, cg = j / dst.ji;
@@ -774,9 +849,10 @@ adc2_status rns_join(const RnsMat& A, const RnsMat& B, int col0, int ncols, int 
     k_rns_join<false><<<nblk, 256, 0, st>>>(out, nrb, ncb, A.rows, ncols, 1, ra, rb, col0, tr, tc, nbn, dst);
   ADC2_CHECK_LAUNCH();
   const unsigned ntile = (unsigned)std::min<long>(512, (long)((nrb + 1) / 2) * ((ncb + 1) / 2));
-#define RNS_FP64(MA_, MB_)                                                                                \
-  k_rns_fp64<MA_, MB_><<<ntile, 256, 0, st>>>(A.src, B.src, col0, A.rows, ncols, A.K, out, nrb, ncb, nsplit, ra, \
-                                              rb, dst)
+  const int8_t *qa = A.p + (long)RNS_PL * A.nrt * A.nkc * RNS_BLK, *qb = B.p + (long)RNS_PL * B.nrt * B.nkc * RNS_BLK;
+#define RNS_FP64(MA_, MB_)                                                                                        \
+  k_rns_fp64<MA_, MB_><<<ntile, 256, 0, st>>>(A.src, B.src, col0, A.rows, ncols, A.K, out, nrb, ncb, nsplit, ra, rb, qa, \
+                                              qb, A.nkc, tr, tc, nbn, dst)
   const bool ak = A.src.rx == 1, bk = B.src.rx == 1;   // contiguous along the rows
   if (ak && bk) RNS_FP64(KMAJOR, KMAJOR);
   else if (ak) RNS_FP64(KMAJOR, RMAJOR);

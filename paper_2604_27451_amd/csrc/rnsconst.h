@@ -105,7 +105,8 @@ constexpr double RNS_FLAT[3] = {0.90, 0.60, 0.46};
 // The two sums of a run of terms as bytes (rk = 1 / K): N in units of K / 254, 0 for none, and S in units of K / 8
 constexpr int rns_terms_byte(int n, float rk) { return n == 0 ? 0 : 1 + (int)((float)n * (254.0f * rk) < 254.0f ? (float)n * (254.0f * rk) : 254.0f); }
 constexpr int rns_weight_byte(int s, float rk) { return (int)((float)s * (8.0f * rk) < 255.0f ? (float)s * (8.0f * rk) : 255.0f); }
-// ... and the rule on their sums over the runs
+// ... N of two rows of which at least RNS_FLAT[0] is not zero, and the rule on the sums over the runs
+constexpr int RNS_FULL_PART = 203;   // 254 (2 * 0.90 - 1), rounded down
 constexpr bool rns_spread_serves(int terms, int part, int weight) { return terms == 0 || part * weight >= 254 * 8 / 4; }
 
 // hi + lo modulo 1, in [-1/2, 1/2]; |hi| < 2^50.  hi comes as an exact sum, so its whole part goes

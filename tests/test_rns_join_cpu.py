@@ -31,6 +31,12 @@ extern "C" int serves(int runs, const int* n, const int* s, int K) {   // of an 
   }
   return adc2::rns_spread_serves(terms, part, weight);
 }
+extern "C" int serves_full(int runs, const int* s, int K) {   // ... of two rows that are known to be full
+  int weight = 0;
+  for (int i = 0; i < runs; ++i) weight += adc2::rns_weight_byte(s[i], 1.0f / (float)K);
+  return adc2::rns_spread_serves(1, adc2::RNS_FULL_PART, weight);
+}
+extern "C" int full_part() { return adc2::RNS_FULL_PART; }
 extern "C" void moduli(int* p) { for (int q = 0; q < adc2::RNS_NM; ++q) p[q] = adc2::RNS_P[q]; }
 extern "C" void join(const int* u, double* out) {   // u[2 q], u[2 q + 1]: sums of c+, c- of modulus q
   double fr = 0, fi = 0, gr = 0, gi = 0;
@@ -184,14 +190,16 @@ def test_rows_that_the_integers_serve(lib, K, runs):
     rs = rows(K)
     qs = [codes(r, qmean) for r in rs]
     fl = [all((q > i).sum() >= np.ceil(f * K) for i, f in enumerate(flat)) for q in qs]
+    full = [(q > 0).sum() >= np.ceil(flat[0] * K) for q in qs]
     cut = [K * i // runs for i in range(runs + 1)]
     served = refused = 0
-    for a, qa, fa in zip(rs, qs, fl):
-        for b, qb, fb in zip(rs, qs, fl):
+    for a, qa, fa, ga in zip(rs, qs, fl, full):
+        for b, qb, fb, gb in zip(rs, qs, fl, full):
             n = (qa > 0) & (qb > 0)
             s = np.maximum(qa - 1, 0) * np.maximum(qb - 1, 0)
             sums = [(ctypes.c_int * runs)(*(int(v[i:j].sum()) for i, j in zip(cut, cut[1:]))) for v in (n, s)]
-            if lib.serves(runs, *sums, K) or (fa and fb):
+            assert not (ga and gb) or n.sum() >= lib.full_part() * K / 254.0
+            if (fa and fb) or (lib.serves_full(runs, sums[1], K) if ga and gb else lib.serves(runs, *sums, K)):
                 served += 1
                 d = n.sum() * (np.abs(a * b) ** 2).sum() / ((np.abs(a) ** 2).sum() * (np.abs(b) ** 2).sum())
                 assert n.sum() == 0 or d >= 0.999 / 64

@@ -65,8 +65,8 @@ TRAFFIC_FILES = {"c3": os.path.join(ROOT, "profiles", "traffic_c3.json")}
 CSRC = "paper_2604_27451_amd/csrc"
 # sources that define each heavy sigma kernel: its GEMM engine header(s) and its own definition
 # (FP64: the residue products of the whole step)
-KERNEL_DEFS = {("fp64", "ybuild"): (["rns.h", "rns.hip"], "rns_doubles_in("),
-               ("fp64", "sigma2"): (["rns.h", "rns.hip"], "rns_singles_in("),
+KERNEL_DEFS = {("fp64", "ybuild"): (["rns.h", "rnsconst.h", "rns.hip"], "rns_doubles_in("),
+               ("fp64", "sigma2"): (["rns.h", "rnsconst.h", "rns.hip"], "rns_singles_in("),
                ("c64", "ybuild"): (["zgemm32.h", "zgemm.h"], "k_ygemm_c64("),
                ("c64", "sigma2"): (["zgemm32.h", "zgemm.h"], "k_zsig2_c64("),
                ("bf16x3", "ybuild"): (["zgemmb.h", "zgemm.h"], "k_ygemm_b3("),

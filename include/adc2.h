@@ -59,18 +59,28 @@ typedef enum {
 typedef enum {
   ADC2_FP64 = 0,               /* complex FP64 contractions: the large ones as exact
                                   integer products on the INT8 MFMA, operands
-                                  rounded at 2^-58.3 of the norm of their row, where
-                                  that is no more than a FP64 sum would be off
-                                  (every entry is looked at: sum |a_k| |b_k| at
-                                  least a tenth of ||a|| ||b||, or no common
-                                  terms); the other entries, the smallest
-                                  products and those without the memory for it
-                                  on the FP64 MFMA                               */
+                                  rounded at 2^-58.3 of the norm of their row.  A
+                                  product is then off by about 2^-59 ||a|| ||b||,
+                                  whatever its terms; every entry for which a FP64
+                                  sum of its terms would be nearer (judged by the
+                                  squares of the terms) is formed as that sum on the
+                                  FP64 MFMA, as are the smallest products and those
+                                  without the memory for it.  Systems whose
+                                  entries mostly need that (spread over decades
+                                  without order) take up to 2.4 times as long as on the
+                                  FP64 MFMA alone; environment ADC2_ZGEMM=wide at
+                                  the setup keeps a handle there                 */
   ADC2_C64 = 1                 /* precision form: the two heavy sigma
                                   contractions on complex64 operands with the
                                   FP32 MFMA and FP32 accumulation; setup,
                                   denominators, packing, Davidson and subspace
-                                  eigensolver stay FP64                          */
+                                  eigensolver stay FP64.  Less memory for the
+                                  operands than FP64 (16 bytes against 66 for each
+                                  valence Cholesky entry), but not faster, as FP64
+                                  runs on the INT8 MFMA: ten vectors at nc=6 no=20
+                                  nv=100 1.24 ms either way, at no=60 nv=300 66 ms
+                                  against 46 (split BF16 24), at no=120 nv=600 991 ms
+                                  against 621 (split BF16 314)                   */
   ,
   ADC2_BF16X3 = 2              /* precision form, split-BF16 variant: the same
                                   two contractions on the BF16 MFMA with each
@@ -363,7 +373,9 @@ ADC2_API adc2_status adc2_sigma_batch(int nmol, const adc2_handle* hs, const int
  *        on its own stream and the GPU overlaps the streams (and one system's
  *        host work with the others' kernels).
  * In both modes each system's iterates, and so its roots, equal those of a
- * separate adc2_davidson call.
+ * separate adc2_davidson call.  Systems that fill the GPU by themselves gain nothing:
+ * eight of nc=6, no=20..80, nv=100..400, complex64, 16 roots: ROUNDS 24.7 s, STREAMS
+ * 28.0 s, adc2_davidson one after another 24.2 s.
  *   omega  host float64 [nmol][nroots];  X host [nmol] of dev pointers
  *   (complex128 [nroots][dim_i]) or NULL;  info host [nmol] or NULL.
  * Returns the first non-OK status in system order (every system's results

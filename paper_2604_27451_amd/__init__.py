@@ -480,7 +480,8 @@ def adc2_davidson_batch(hs, nroots, tol=1e-8, max_iter=0, max_subspace=0, nguess
     Xs = [torch.empty((nroots, h.dim), dtype=torch.complex128, device="cuda") for h in hs] if want_vectors else None
     hp = (ctypes.c_void_p * n)(*[h.ptr.value if isinstance(h.ptr, ctypes.c_void_p) else h.ptr for h in hs])
     xp = (ctypes.c_void_p * n)(*[X.data_ptr() for X in Xs]) if want_vectors else None
-    if mode is None:   # the faster of the two on the eight-system batch workload
+    if mode is None:   # the faster of the two on the eight-system batch workload (complex64: 24.7 s against 28.0 s;
+                       # adc2_davidson system by system takes 24.2 s)
         mode = ADC2_BATCH_ROUNDS
     st = load().adc2_davidson_batch(n, hp, nroots, ctypes.byref(opts), mode, omega, xp, infos, _stream_ptr(stream))
     _check(st, "adc2_davidson_batch")

@@ -30,19 +30,22 @@
 // rows that are not finite, are formed in FP64 by k_rns_fp64 (which ends at once
 // where there are none); which they are depends on the two rows
 // and the K-splits alone, not on tiles or chunks.  Rows of like entries are known for that by the
-// counts of their codes (rns_flat), and tiles of such rows need no product of codes.  What the
-// codes cost there: nc=6 no=60 nv=300 naux=1500, ten vectors, 46.6 -> 47.2 ms; the smallest sigma
-// 111 -> 113 us.
+// counts of their codes (rns_class), and tiles of such rows need no product of codes.  What the
+// codes cost there: nc=6 no=60 nv=300 naux=1500, ten vectors, 46.1 -> 46.7 ms; the smallest sigma
+// 98 -> 108 us.  Cholesky entries spread by a log-normal of half a decade at nc=6 no=45 nv=310 naux=1240,
+// seven vectors: 31 ms (even ones 24, the FP64 MFMA engine 59); of a whole decade, where most entries of the product
+// need the FP64 sum: 143.
 //
 // Measured against long double (nc=6 no=60 nv=300 naux=1500, a unit vector on a
 // singles entry, so that every doubles entry is one K = 1500 product): rms error
 // 1.2e-16 of the rms entry, 2.1e-15 on the FP64 MFMA engine; singles from random
 // doubles at nc=6 no=20 nv=100 naux=400: 8.8e-16 against 1.2e-15.
 //
-// What bounds it.  The INT8 products draw the card to its power limit: a loop of
-// v_mfma_i32_16x16x64_i8 on random bytes alone runs at 4085 TOPS (4850 on zeros), the
-// product of M=3072, N=9000, K=18000 at 2338, as 292 TFLOP/s of complex products; the
-// FP64 MFMA engine reaches 67.
+// What bounds it.  The product of M=3072, N=9000, K=18000 runs at 2338 TOPS, as 292 TFLOP/s of
+// complex products (the FP64 MFMA engine reaches 67); a loop of v_mfma_i32_16x16x64_i8 alone on
+// random bytes at 4085, at the power limit (4850 on zeros).  The matrix cores are 60% busy at the clock
+// that the limit leaves; what idles them in the rest is not shown.  LDS is the first suspect: four waves
+// read 12 KB of fragments each per 32 instructions.
 //
 // Rows with NaN or Inf give what the FP64 sum gives (NaN against rows of zeros);
 // rows of zeros give exact zeros.
@@ -136,7 +139,8 @@ adc2_status rns_pack(const RnsSrc& src, int rows, int K, int8_t* buf, int* ebuf,
 // (((s * RNS_OP + q) * nrb + rb) * ncb + cb) * 1024, in MFMA register order.
 adc2_status rns_gemm(const RnsMat& A, const RnsMat& B, int col0, int ncols, int nsplit, int8_t* out, hipStream_t st);
 // The products themselves out of those residues, and in FP64 from A.src and B.src
-// those entries that the integers do not hold well enough.
+// those entries that the integers do not hold well enough, after the others: dst must not overlap
+// what A.src and B.src read.
 adc2_status rns_join(const RnsMat& A, const RnsMat& B, int col0, int ncols, int nsplit, int8_t* out, const RnsDst& dst,
                      hipStream_t st);
 

@@ -204,7 +204,9 @@ template <bool KLANE>
 __global__ __launch_bounds__(256, KLANE ? 3 : 5) void k_rns_pack(const RnsSrc src, int rows, int K,
                                                                  int* __restrict__ e, int nrt, int nkc,
                                                                  int8_t* __restrict__ dst) {
-  __shared__ unsigned cnt[4][64];   // codes of at least 1, 2 and 3, a byte each
+  // codes of at least 1, 2 and 3, a byte each here and 21 bits in the row's count (the first to run over,
+  // by rows of more than 2^21 terms, is then below its RNS_FLAT: such rows are looked at by their codes)
+  __shared__ unsigned cnt[4][64];
   const int lane = threadIdx.x & 63, kg = threadIdx.x >> 6;
   const int rb = blockIdx.x % (2 * nrt), kc = blockIdx.x / (2 * nrt);
   const int row = rb * 64 + lane;
@@ -416,11 +418,10 @@ constexpr int TILE_FLAT = 1, TILE_FULL = 2;
 // 8 x 4 blocks, 128 accumulators a lane).  Chunks of 64 k go from global
 // memory straight into an LDS ring of NB stages (the operand layout is the
 // LDS image, and a fragment is 1 KB of it in lane order), NB - 1 chunks ahead;
-// one barrier a chunk.  The card's power limit sets the rate: on random bytes a
-// loop of this instruction alone runs at 4085 TOPS, of 32x32x32 at 3498 (both about 4850
-// on zeros), and the whole product at 2240 to 2340 against 1950 to 2050 at K = 18000,
-// 1960 to 1990 against 1710 to 1840 at K = 1500.  Two workgroups a CU, so that one's
-// reduction runs under the other's products.
+// one barrier a chunk.  On random bytes a loop of this instruction alone runs at 4085 TOPS, of
+// 32x32x32 at 3498 (both about 4850 on zeros: there the power limit sets the rate), and the whole product
+// at 2240 to 2340 against 1950 to 2050 at K = 18000, 1960 to 1990 against 1710 to 1840 at K = 1500
+// (rns.h: what bounds it).  Two workgroups a CU, so that one's reduction runs under the other's products.
 template <int WM, int WN, int NB>
 __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void k_rns_gemm(
     const int8_t* __restrict__ A, const int8_t* __restrict__ B, int nrtA, int nrtB, int brt0, int nkca, int nkcs, int nbm,
@@ -761,7 +762,7 @@ __global__ __launch_bounds__(256) void k_rns_fp64(const RnsSrc A, const RnsSrc B
                                       !rns_serves(spread[x], rns_class(ra, i0 + r), rns_class(rb_, col0 + j0 + c)));
         }
         // Chunks in which one operand has no term of the tile are left out: they add exact zeros, unless a row is
-        // not finite (nc=6 no=60 nv=300, a folded solve from singles guesses: 121 -> 81 ms of 2.5 s, its first
+        // not finite (nc=6 no=60 nv=300, a folded solve from singles guesses: 128 -> 81 ms of 2.6 s, its first
         // products being of rows with 60 terms in 18000).
         const int ja = i0 + tid, jb = col0 + j0 + tid - 64;
         const bool bad = tid < 64 ? ja < rows && ra.e[ja] == RNS_NAN : tid < 128 && jb < col0 + cols && rb_.e[jb] == RNS_NAN;

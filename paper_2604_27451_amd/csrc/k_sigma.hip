@@ -1527,8 +1527,17 @@ static bool rns_wanted(adc2_handle h, int m, bool noalloc = false) {
   return !noalloc || (h->rns_lvo && h->rns_lvt);
 }
 
+// (on the device of the handle's blocks: adc2_set_precision has no other use for it, so that another one may be current)
 adc2_status rns_enter_fp64(adc2_handle h, hipStream_t st) {
-  return h->prec == ADC2_FP64 && rns_system(h) ? rns_build_static(h, st) : ADC2_OK;
+  if (h->prec != ADC2_FP64 || !rns_system(h) || (h->rns_lvo && h->rns_lvt)) return ADC2_OK;
+  int cur = 0;
+  hipPointerAttribute_t at{};
+  ADC2_HIP(hipGetDevice(&cur));
+  ADC2_HIP(hipPointerGetAttributes(&at, h->Lvo));
+  if (at.device != cur) ADC2_HIP(hipSetDevice(at.device));
+  const adc2_status rc = rns_build_static(h, st);
+  if (at.device != cur) ADC2_HIP(hipSetDevice(cur));
+  return rc;
 }
 
 adc2_status rns_build_static(adc2_handle h, hipStream_t st) {

@@ -197,3 +197,26 @@ def test_not_finite_as_the_fp64_sum(monkeypatch, bad):
         got[engine] = (torch.isnan(S).cpu(), (torch.isinf(S) * torch.sign(S)).nan_to_num().cpu())
         h.close()
     assert all(torch.equal(a, b) for a, b in zip(got["wide"], got["rns"]))
+
+
+def test_more_terms_than_are_looked_at_together(monkeypatch):
+    """The pair density of the transition moments, K = 903 pairs x 75 virtuals = 67725 terms: k_rns_fp64 takes
+    a sixth of its entries, in runs of 65536 terms, and leaves out the pairs of a spinor without Cholesky
+    vectors.  Both engines are held to 1e-12 of the oracle above, so to 2e-12 of each other."""
+    from synth import dipole_integrals, random_vectors
+    nc, no, nv, naux = 2, 41, 75, 60
+    s = make_system(nc, no, nv, naux, seed=990)
+    g = 10.0 ** (1.5 * np.random.default_rng(7).standard_normal((naux, s.n, s.n)))
+    g[:, nc + 3, :] = 0.0
+    g[:, :, nc + 3] = 0.0
+    L = scaled(s, np.triu(g) + np.transpose(np.triu(g, 1), (0, 2, 1)))
+    L *= 0.05 / np.sqrt((np.abs(L) ** 2).mean())
+    T = {}
+    for engine in ("wide", "rns"):
+        monkeypatch.setenv("ADC2_ZGEMM", engine)
+        print(f"[case] graded transition of many pairs, {engine}", flush=True)
+        h = A.adc2_setup(dev(L), dev(s.eps), nc, no, nv, naux)
+        x = random_vectors(7, 2, h.dim)
+        T[engine], _ = A.adc2_transition(h, dev(dipole_integrals(3, nc + no + nv)), dev(x), [9.0, 9.5], order=2)
+        h.close()
+    assert np.abs(T["rns"] - T["wide"]).max() < 2e-12 * np.abs(T["wide"]).max()
